@@ -122,13 +122,18 @@ static int decode_target_wgs() {
 }
 #define FEDRAG_DEC_WGS decode_target_wgs()
 #endif
-#ifndef FEDRAG_DEC_MIN_STEPS
-#define FEDRAG_DEC_MIN_STEPS 4
-#endif
+// Shortest run of the decode kernel, in 128-key steps of a workgroup.  A run costs the launch a partial to fold, so
+// 512 keys (a decoded token's layer over two Context Owners of 4096 keys: 30.4 us, against 31.0 with 256 and 35.2 with
+// 1024), and a context of no more than that is one run and no fold (300 keys: 25.7 us a layer against 27.8 in two runs).
+// In between a context would be two to four runs, which leaves the chip idle: 400 + 700 keys take 23.1 us a layer in
+// 256-key runs against 24.9.
+constexpr int kDecMinSteps = 4;
+constexpr int kDecMinStepsShort = 2;
+constexpr int64_t kDecShortContext = 2048;  // keys of all shards of a unit up to which the shorter run is taken
 static bool use_decode_kernel(int Hq, int Hkv, int64_t Lq) { return (int64_t)(Hq / Hkv) * Lq <= 16; }
 
 // Decode kernel: about one workgroup per compute unit over the whole launch; a run is a whole number of 128-key
-// workgroup steps, at least 4 of them, and stays below 2^31 bytes (32-bit buffer offsets).
+// workgroup steps, at least kDecMinSteps (kDecMinStepsShort) of them, and stays below 2^31 bytes (32-bit buffer offsets).
 // Prefill kernel: one workgroup per (sequence, query head, 256 query rows) walks a run, about 2 us per 64-key tile.
 // When those workgroups cover less than half of the compute units, the keys are cut into runs of at least
 // kPreMinTilesPerSplit tiles (so that a workgroup's fixed cost stays small beside its tiles) for one round of
@@ -136,13 +141,13 @@ static bool use_decode_kernel(int Hq, int Hkv, int64_t Lq) { return (int64_t)(Hq
 KeyRuns attn_plan_runs(int B, int Hq, int Hkv, int dtype, int64_t Lq, int n, const int64_t* Ls, bool codes4) {
     KeyRuns r;
     for (int i = 0; i < kMaxShards; ++i) {
-        r.K[i] = r.V[i] = nullptr;
-        r.L[i] = 0;
-        r.per[i] = 1;
+        r.s[i] = KeyShard{nullptr, nullptr, 0, 1};
         r.first[i] = INT_MAX;
     }
     r.first[kMaxShards] = INT_MAX;
     r.n_runs = 0;
+    r.n_shards = n;
+    r.by_runs = FastDiv(1);
     if (n < 1 || n > kMaxShards) return r;
     int64_t total = 0;
     for (int i = 0; i < n; ++i) total += Ls[i] > 0 ? Ls[i] : 0;
@@ -157,7 +162,9 @@ KeyRuns attn_plan_runs(int B, int Hq, int Hkv, int dtype, int64_t Lq, int n, con
             quantum = kDecStride;
             per = (total + want - 1) / want;
             per = ((per + quantum - 1) / quantum) * quantum;
-            if (per < FEDRAG_DEC_MIN_STEPS * quantum) per = FEDRAG_DEC_MIN_STEPS * quantum;
+            const int64_t least = (total <= kDecShortContext && total > kDecMinSteps * quantum ? kDecMinStepsShort
+                                                                                          : kDecMinSteps) * quantum;
+            if (per < least) per = least;
             if (per > (int64_t)1 << 22) per = (int64_t)1 << 22;
         } else {
             // the query heads of a KV head form one run of G * Lq rows (see launch_prefill_t)
@@ -175,37 +182,39 @@ KeyRuns attn_plan_runs(int B, int Hq, int Hkv, int dtype, int64_t Lq, int n, con
     int at = 0;
     for (int i = 0; i < n; ++i) {
         const int64_t L = Ls[i] > 0 ? Ls[i] : 0;
-        r.L[i] = L;
+        r.s[i].L = L;
         r.first[i] = at;
         if (L == 0) continue;  // no runs: first[i] == first[i + 1]
         const int64_t runs = per == INT64_MAX ? 1 : (L + per - 1) / per;
         int64_t mine = (L + runs - 1) / runs;  // rebalanced inside the shard
         mine = ((mine + quantum - 1) / quantum) * quantum;
-        r.per[i] = mine;
+        r.s[i].per = mine;
         at += (int)((L + mine - 1) / mine);
     }
     for (int i = n; i <= kMaxShards; ++i) r.first[i] = i == n ? at : INT_MAX;
     r.n_runs = at;
+    r.by_runs = FastDiv(at > 0 ? at : 1);
     return r;
 }
 
 KeyRuns attn_runs_of(const AttnProblem& p) {
     if (p.n_shards <= 1) {
         KeyRuns r = attn_plan_runs(p.B, p.Hq, p.Hkv, p.dtype, p.Lq, 1, &p.Lkv, p.quant_bits == 4 && p.D == 128);
-        r.K[0] = p.K;
-        r.V[0] = p.V;
+        r.s[0].K = p.K;
+        r.s[0].V = p.V;
         if (p.single_run && r.n_runs > 1) {  // all keys of the shard in one run (a whole number of key tiles)
             const int64_t q = use_decode_kernel(p.Hq, p.Hkv, p.Lq) ? kDecStride : kPreK;
-            r.per[0] = ((r.L[0] + q - 1) / q) * q;
+            r.s[0].per = ((r.s[0].L + q - 1) / q) * q;
             r.first[1] = 1;
             r.n_runs = 1;
+            r.by_runs = FastDiv(1);
         }
         return r;
     }
     KeyRuns r = attn_plan_runs(p.B, p.Hq, p.Hkv, p.dtype, p.Lq, p.n_shards, p.Ls);
     for (int i = 0; i < p.n_shards && i < kMaxShards; ++i) {
-        r.K[i] = p.Ks[i];
-        r.V[i] = p.Vs[i];
+        r.s[i].K = p.Ks[i];
+        r.s[i].V = p.Vs[i];
     }
     return r;
 }

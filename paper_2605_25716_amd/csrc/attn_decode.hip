@@ -102,6 +102,11 @@ __device__ __forceinline__ typename T::vec8 dequant8(uint32_t w, u32x2_t prm) { 
 #ifndef FEDRAG_DEC_NBUF
 #define FEDRAG_DEC_NBUF 2   // register tile sets per wave
 #endif
+// SHORT: no run is longer than this, so a wave has at most 8 tiles.  A ring of two then spends its time in the code
+// around its steady state (every copy of a step fetched cold): with one tile set 768-key runs take 20.6 us instead of
+// 21.1 (4 sequences of 6000 keys) and a decoded token's layer 30.4 instead of 31.2; runs of 32768 keys are 1.8 % slower
+// with one.
+constexpr int64_t kDecShortRun = 1024;
 #ifndef FEDRAG_DEC_OCC
 #define FEDRAG_DEC_OCC 1    // workgroups per CU the register budget is sized for
 #endif
@@ -109,7 +114,7 @@ __device__ __forceinline__ typename T::vec8 dequant8(uint32_t w, u32x2_t prm) { 
 #define FEDRAG_DEC_AUX 2    // cache-policy bits of the streaming loads: non-temporal (K'/V' are read once)
 #endif
 
-template <class T, int D, int QB>
+template <class T, int D, int QB, bool SHORT>
 __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OCC) void decode_attn_kernel(const typename T::elem* __restrict__ Q,
                                                                      const KeyRuns runs,
                                                                      const float* __restrict__ Kprm,
@@ -128,42 +133,32 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
     constexpr int NW = DCH / 2;  // 32-bit words of that
     constexpr int ROWB = QB ? D * QB / 8 : D * 2;  // bytes per row of K' / V' as stored (values, or codes)
     constexpr int TILEB = kDecTile * ROWB;
-    constexpr int NBUF = QB == 0 ? FEDRAG_DEC_NBUF : (QB == 8 ? FEDRAG_DEC_NBUF_Q8 : FEDRAG_DEC_NBUF_Q4);
+    constexpr int NBUF = SHORT ? 1 : QB == 0 ? FEDRAG_DEC_NBUF : (QB == 8 ? FEDRAG_DEC_NBUF_Q8 : FEDRAG_DEC_NBUF_Q4);
     constexpr int AUX = FEDRAG_DEC_AUX;
 
     __shared__ float sm_m[kDecWaves][16];
     __shared__ float sm_l[kDecWaves][16];
-    __shared__ float sm_o[kDecWaves][16][D + 4];
+    __shared__ __attribute__((aligned(16))) float sm_o[kDecWaves][16][D + 4];
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // wave-uniform: keeps the tile loop scalar
     const int lane = tid % kWave;
     const int lr = lane % 16;
     const int lq = lane / 16;
-    const int64_t unit = blockIdx.x / runs.n_runs;
-    const int run = blockIdx.x % runs.n_runs;  // index of this workgroup's partial
-    // the shard this run belongs to (scalar compares against the table; first[] is INT_MAX past the last shard)
-    const void* K = runs.K[0];
-    const void* V = runs.V[0];
-    int64_t L = runs.L[0];
-    int64_t keys_per_split = runs.per[0];
-    int split = run;
-#pragma unroll
-    for (int i = 1; i < kMaxShards; ++i) {
-        if (run >= runs.first[i]) {
-            K = runs.K[i];
-            V = runs.V[i];
-            L = runs.L[i];
-            keys_per_split = runs.per[i];
-            split = run - runs.first[i];
-        }
-    }
+    const int64_t unit = runs.by_runs.div(blockIdx.x);
+    const int run = (int)runs.by_runs.mod(blockIdx.x);  // index of this workgroup's partial
+    int split;
+    const KeyShard shard = runs.shard_of(run, &split);
+    const void* K = shard.K;
+    const void* V = shard.V;
+    const int64_t L = shard.L;
+    const int64_t keys_per_split = shard.per;
     const int64_t k_begin = (int64_t)split * keys_per_split;
     // keys of this unit's sequence: all L rows, or the first kv_lens[b] of them (padded batch of unequal sequences);
     // a split that starts past them is empty and returns O = 0, lse = -inf like an empty shard
     int64_t L_seq = L;
     if (kv_lens) {
-        const int64_t v = kv_lens[unit / Hkv];
+        const int64_t v = kv_lens[(int)unit / Hkv];
         L_seq = v < 0 ? 0 : (v < L ? v : L);
     }
     int64_t k_end = k_begin + keys_per_split;
@@ -174,7 +169,8 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
     const char* Kb = (const char*)K + unit * L * ROWB;
     const char* Vb = (const char*)V + unit * L * ROWB;
 
-    // Q'^T operands: column lr (query), contraction slice 32 ks + 8 lq; padding queries are zero
+    // Q'^T operands: column lr (query), contraction slice 32 ks + 8 lq; padding queries lie past the end of the
+    // buffer and arrive as zeros
     // Which 8 channels lane group lq contracts in step ks is free as long as Q' and K' agree.  16-bit K': 32 ks + 8 lq
     // (a step's 32 channels are contiguous: 64 bytes per row and load).  Codes: every lane fetches 16 bytes of its
     // row at once - 16 codes = steps 2h, 2h+1 (8 bits) or 32 codes = all four steps (4 bits) - so that a load still
@@ -184,9 +180,10 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
         return QB == 0 ? ks * 32 + lq * 8 : (QB == 8 ? 16 * lq + 64 * (ks / 2) + 8 * (ks % 2) : 32 * lq + 8 * ks);
     };
     vec8 qop[KS];
+    const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc((void*)Qu, 0, R * D * 2, 0x00020000);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-        qop[ks] = (lr < R) ? *(const vec8*)(Qu + lr * D + chan0(ks)) : zero_vec<vec8>();
+        qop[ks] = __builtin_bit_cast(vec8, __builtin_amdgcn_raw_buffer_load_b128(rq, (lr * D + chan0(ks)) * 2, 0, 0));
 
     f32x4_t acc_o[DCH];
 #pragma unroll
@@ -326,8 +323,7 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
             p[e] = v;
             mx = fmaxf(mx, v);
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        mx = xor32_max(xor16_max(mx));
         const float m_new = fmaxf(m_run, mx);  // finite: the tile's first key exists
         const float alpha = exp2_diff(m_run, m_new);
         float psum = 0.f;
@@ -403,18 +399,23 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
         }
     }
 
-    // fold the four waves (Section 4.1 aggregation, in base 2)
-    float l_tot = l_run + __shfl_xor(l_run, 16);
-    l_tot += __shfl_xor(l_tot, 32);
+    // fold the four waves (Section 4.1 aggregation, in base 2); a thread finishes 4 columns of a row, so that the
+    // fold of a short launch is one pass of 16-byte LDS reads
+    const float l_tot = xor32_sum(xor16_sum(l_run));
     if (lq == 0) {
         sm_m[wave][lr] = m_run;
         sm_l[wave][lr] = l_tot;
     }
     if (lr < R) {
 #pragma unroll
-        for (int i = 0; i < DCH; ++i)
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) sm_o[wave][lr][DCH * (4 * lq + r) + i] = acc_o[i][r];
+            for (int i = 0; i < DCH; i += 4) {
+                f32x4_t o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = acc_o[i + e][r];
+                *(f32x4_t*)&sm_o[wave][lr][DCH * (4 * lq + r) + i] = o;
+            }
     }
     __syncthreads();
     float* Oout = O + ((int64_t)run * total_rows + unit * R) * D;
@@ -423,25 +424,30 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
     // sequence's count are padding and are not written
     int q_rows = Lq;
     if (q_lens) {
-        const int v = q_lens[unit / Hkv];
+        const int v = q_lens[(int)unit / Hkv];
         q_rows = v < 0 ? 0 : (v < Lq ? v : Lq);
     }
-    for (int idx = tid; idx < R * D; idx += kDecThreads) {
-        const int n = idx / D;
-        const int d = idx % D;
-        if (n % Lq >= q_rows) continue;
+    for (int idx = tid; idx < R * (D / 4); idx += kDecThreads) {
+        const int n = idx / (D / 4);
+        const int d = idx % (D / 4) * 4;
+        if (q_lens && n % Lq >= q_rows) continue;
         float M = sm_m[0][n];
 #pragma unroll
         for (int w = 1; w < kDecWaves; ++w) M = fmaxf(M, sm_m[w][n]);
-        float num = 0.f, den = 0.f;
+        f32x4_t num = zero_vec<f32x4_t>();
+        float den = 0.f;
 #pragma unroll
         for (int w = 0; w < kDecWaves; ++w) {
             const float a = exp2_diff(sm_m[w][n], M);
-            num = __builtin_fmaf(a, sm_o[w][n][d], num);
+            const f32x4_t o = *(const f32x4_t*)&sm_o[w][n][d];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) num[e] = __builtin_fmaf(a, o[e], num[e]);
             den = __builtin_fmaf(a, sm_l[w][n], den);
         }
         const bool any = den > 0.f;
-        Oout[n * D + d] = any ? num / den : 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) num[e] = any ? num[e] / den : 0.f;
+        *(f32x4_t*)(Oout + n * D + d) = num;
         if (d == 0) Lout[n] = any ? (M + fast_log2(den)) * kLn2 : -INFINITY;
     }
 }
@@ -456,7 +462,7 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
     if (splits < 1) return hipErrorInvalidValue;
     if (QB != 0 && p.n_shards > 1) return hipErrorInvalidValue;
     for (int i = 0; i < kMaxShards; ++i)  // a run is addressed with 32-bit byte offsets
-        if (runs.L[i] > 0 && runs.per[i] * (int64_t)(QB ? D * QB / 8 : D * 2) > 0x7fffffffLL) return hipErrorInvalidValue;
+        if (runs.s[i].L > 0 && runs.s[i].per * (int64_t)(QB ? D * QB / 8 : D * 2) > 0x7fffffffLL) return hipErrorInvalidValue;
     const int R = (int)((p.Hq / p.Hkv) * p.Lq);
     const int64_t units = (int64_t)p.B * p.Hkv;
     float* Odst = p.O;
@@ -467,9 +473,12 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
         Ldst = Odst + (size_t)splits * rows * D;
     }
     if (!grid_fits(units * splits)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((decode_attn_kernel<T, D, QB>), dim3((unsigned)(units * splits)), dim3(kDecThreads), 0, stream,
-                       (const elem*)p.Q, runs, p.K_params, p.V_params, R, scale_log2, Odst, Ldst, rows, p.kv_lens,
-                       p.q_lens, (int)p.Lq, p.Hkv);
+    bool is_short = QB == 0;  // on codes the rings above serve every run
+    for (int i = 0; i < runs.n_shards; ++i)
+        if (runs.s[i].L > kDecShortRun && runs.s[i].per > kDecShortRun) is_short = false;
+    const auto kernel = is_short ? decode_attn_kernel<T, D, QB, QB == 0> : decode_attn_kernel<T, D, QB, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(units * splits)), dim3(kDecThreads), 0, stream, (const elem*)p.Q, runs,
+                       p.K_params, p.V_params, R, scale_log2, Odst, Ldst, rows, p.kv_lens, p.q_lens, (int)p.Lq, p.Hkv);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
     return launch_lse_merge(Odst, Ldst, splits, rows, D, p.O, p.lse, stream, p.q_lens, p.Lq, (int64_t)p.Hq * p.Lq);

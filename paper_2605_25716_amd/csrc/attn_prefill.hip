@@ -51,11 +51,12 @@ template <class T, int D, bool CAUSAL, int QB>
 __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const typename T::elem* __restrict__ Q,
                                                                       const KeyRuns runs,
                                                                       const float* __restrict__ Kprm,
-                                                                      const float* __restrict__ Vprm, int Hq, int Hkv,
-                                                                      int64_t Lq,
+                                                                      const float* __restrict__ Vprm, int Hq,
+                                                                      FastDiv by_heads, FastDiv by_group,
+                                                                      FastDiv by_tiles, FastDiv by_unit, int64_t Lq,
                                                                       const int32_t* __restrict__ kv_lens,
-                                                                      const int32_t* __restrict__ q_lens, int q_tiles,
-                                                                      int n_units, float scale_log2,
+                                                                      const int32_t* __restrict__ q_lens, int n_units,
+                                                                      float scale_log2,
                                                                       float* __restrict__ O, float* __restrict__ lse) {
     typedef typename T::elem elem;
     typedef typename T::vec8 vec8;
@@ -77,38 +78,29 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
     // give every XCD whole (sequence, KV head) units so that the workgroups sharing K'/V' share an L2.
     // With more than one run (several shards, or few query tiles and many keys; not CAUSAL) there is one workgroup
     // per (query tile, run) and O / lse are [n_runs][rows] partials that the Section 4.1 aggregation folds afterwards.
-    const int G = Hq / Hkv;
+    const int G = (int)by_group.d;
     const int n_runs = runs.n_runs;
-    const int per_unit = G * q_tiles * n_runs;
     const int xcd = blockIdx.x % 8;
     const int slot = blockIdx.x / 8;
-    const int unit = xcd + 8 * (slot / per_unit);
+    const int unit_slot = (int)by_unit.div(slot);  // by_unit: G * q_tiles * n_runs
+    const int unit = xcd + 8 * unit_slot;
     if (unit >= n_units) return;
-    const int run = (slot % per_unit) % n_runs;
-    const int w_in_unit = (slot % per_unit) / n_runs;
-    // the shard this run belongs to (scalar compares against the table; first[] is INT_MAX past the last shard)
-    const elem* K = (const elem*)runs.K[0];
-    const elem* V = (const elem*)runs.V[0];
-    int64_t L_stride = runs.L[0];
-    int64_t keys_per_run = runs.per[0];
-    int split = run;
-#pragma unroll
-    for (int i = 1; i < kMaxShards; ++i) {
-        if (run >= runs.first[i]) {
-            K = (const elem*)runs.K[i];
-            V = (const elem*)runs.V[i];
-            L_stride = runs.L[i];
-            keys_per_run = runs.per[i];
-            split = run - runs.first[i];
-        }
-    }
+    const int in_unit = slot - unit_slot * (int)by_unit.d;
+    const int w_in_unit = (int)runs.by_runs.div(in_unit);
+    const int run = in_unit - w_in_unit * n_runs;
+    int split;
+    const KeyShard shard = runs.shard_of(run, &split);
+    const elem* K = (const elem*)shard.K;
+    const elem* V = (const elem*)shard.V;
+    const int64_t L_stride = shard.L;
+    const int64_t keys_per_run = shard.per;
     // CAUSAL: later query tiles visit more keys.  Hand out the last tile of every head of the group first, then the
     // one before it, and so on: workgroups are started in index order as compute units free up, so every compute
     // unit ends up with a long tile followed by short ones and the launch does not wait on a late long tile.
-    const int hg = CAUSAL ? w_in_unit % G : w_in_unit / q_tiles;
-    const int qt = CAUSAL ? q_tiles - 1 - w_in_unit / G : w_in_unit % q_tiles;
-    const int b = unit / Hkv;
-    const int g = unit % Hkv;
+    const int hg = CAUSAL ? (int)by_group.mod(w_in_unit) : (int)by_tiles.div(w_in_unit);
+    const int qt = CAUSAL ? (int)(by_tiles.d - 1 - by_group.div(w_in_unit)) : (int)by_tiles.mod(w_in_unit);
+    const int b = (int)by_heads.div(unit);
+    const int g = (int)by_heads.mod(unit);
     const int h = g * G + hg;
 
     const int tid = threadIdx.x;
@@ -118,10 +110,10 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
     const int lh = lane / 32;
 
     const elem* Qh = Q + ((int64_t)b * Hq + h) * Lq * D;
-    const char* Kg = (const char*)K + ((int64_t)b * Hkv + g) * L_stride * CROWB;
-    const char* Vg = (const char*)V + ((int64_t)b * Hkv + g) * L_stride * CROWB;
-    const float* Kpg = QB ? Kprm + ((int64_t)b * Hkv + g) * L_stride * 2 : nullptr;  // (scale, lo) per key row
-    const float* Vpg = QB ? Vprm + ((int64_t)b * Hkv + g) * L_stride * 2 : nullptr;
+    const char* Kg = (const char*)K + (int64_t)unit * L_stride * CROWB;
+    const char* Vg = (const char*)V + (int64_t)unit * L_stride * CROWB;
+    const float* Kpg = QB ? Kprm + (int64_t)unit * L_stride * 2 : nullptr;  // (scale, lo) per key row
+    const float* Vpg = QB ? Vprm + (int64_t)unit * L_stride * 2 : nullptr;
     // keys of this sequence: all L_stride rows, or the first kv_lens[b] of them (padded batch of unequal sequences)
     int64_t L = L_stride;
     if (kv_lens) {
@@ -539,9 +531,10 @@ static hipError_t launch_prefill_t(const AttnProblem& p, hipStream_t stream) {
     const bool one_run_only = CAUSAL || p.kv_lens || p.q_lens;
     if (one_run_only) {
         if (p.n_shards > 1) return hipErrorInvalidValue;
-        runs.per[0] = runs.L[0] > 0 ? ((runs.L[0] + kPreK - 1) / kPreK) * kPreK : kPreK;
+        runs.s[0].per = runs.s[0].L > 0 ? ((runs.s[0].L + kPreK - 1) / kPreK) * kPreK : kPreK;
         runs.first[1] = 1;
         runs.n_runs = 1;
+        runs.by_runs = FastDiv(1);
     }
     const int splits = runs.n_runs;
     if (splits < 1) return hipErrorInvalidValue;
@@ -558,8 +551,8 @@ static hipError_t launch_prefill_t(const AttnProblem& p, hipStream_t stream) {
     if (!grid_fits(grid)) return hipErrorInvalidValue;
     if (QB != 0 && (p.n_shards > 1 || !p.K_params || !p.V_params)) return hipErrorInvalidValue;
     hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB>), dim3((unsigned)grid), dim3(kPreThreads), 0, stream,
-                       (const elem*)p.Q, runs, p.K_params, p.V_params, Hq_k, p.Hkv, Lq_k, p.kv_lens, p.q_lens,
-                       q_tiles, n_units, scale_log2, Odst, Ldst);
+                       (const elem*)p.Q, runs, p.K_params, p.V_params, Hq_k, FastDiv(p.Hkv), FastDiv(Hq_k / p.Hkv),
+                       FastDiv(q_tiles), FastDiv(per_unit), Lq_k, p.kv_lens, p.q_lens, n_units, scale_log2, Odst, Ldst);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
     return launch_lse_merge(Odst, Ldst, splits, rows, D, p.O, p.lse, stream);

@@ -69,9 +69,28 @@ __device__ __forceinline__ void wave_lds_fence() {
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
-// Max / sum over the lane pair (l, l ^ 32).
-__device__ __forceinline__ float xor32_max(float x) { return fmaxf(x, __shfl_xor(x, 32)); }
-__device__ __forceinline__ float xor32_sum(float x) { return x + __shfl_xor(x, 32); }
+// Max / sum over the lane pairs (l, l ^ 32) and (l, l ^ 16).  The lane-swap instructions exchange half waves (rows of
+// 16) between two registers: given the same value twice they leave one register with the lower partner's value in
+// both lanes and one with the upper's, without the trip through the LDS crossbar that a shuffle takes.
+struct LanePair {
+    float lower, upper;
+};
+__device__ __forceinline__ LanePair lane_pair32(float x) {
+    const uint32_t v = __builtin_bit_cast(uint32_t, x);
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    const uint32_t a = r[0], b = r[1];
+    return LanePair{__builtin_bit_cast(float, a), __builtin_bit_cast(float, b)};
+}
+__device__ __forceinline__ LanePair lane_pair16(float x) {
+    const uint32_t v = __builtin_bit_cast(uint32_t, x);
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    const uint32_t a = r[0], b = r[1];
+    return LanePair{__builtin_bit_cast(float, a), __builtin_bit_cast(float, b)};
+}
+__device__ __forceinline__ float xor32_max(float x) { const LanePair p = lane_pair32(x); return fmaxf(p.lower, p.upper); }
+__device__ __forceinline__ float xor32_sum(float x) { const LanePair p = lane_pair32(x); return p.lower + p.upper; }
+__device__ __forceinline__ float xor16_max(float x) { const LanePair p = lane_pair16(x); return fmaxf(p.lower, p.upper); }
+__device__ __forceinline__ float xor16_sum(float x) { const LanePair p = lane_pair16(x); return p.lower + p.upper; }
 
 // min / max over aligned groups of N = 8 or 16 consecutive lanes, result in every lane of the group, with data-parallel
 // primitives only (no LDS crossbar): exchange inside quads, then mirror the half row (lane k <-> 7 - k: the other

@@ -78,18 +78,54 @@ struct AttnProblem {
     void* workspace;
     size_t workspace_bytes;
 };
+// Division of an index below 2^31 by a number the host knows: n / d = (n * m) >> s, exact because m = ceil(2^s / d) with
+// s = 31 + ceil(log2 d) leaves an error n * (m d - 2^s) < 2^31 * 2^ceil(log2 d) = 2^s.  Three scalar instructions in a
+// kernel's first lines instead of some twenty-five with a reciprocal estimate in them.
+struct FastDiv {
+    uint32_t m, s, d;
+    FastDiv() = default;
+    explicit FastDiv(int64_t div) : d((uint32_t)div) {
+        s = 31;
+        while (((int64_t)1 << (s - 31)) < div) ++s;
+        m = (uint32_t)((((unsigned __int128)1 << s) + (uint64_t)div - 1) / (uint64_t)div);
+    }
+    __host__ __device__ uint32_t div(uint32_t n) const { return (uint32_t)(((uint64_t)n * m) >> s); }
+    __host__ __device__ uint32_t mod(uint32_t n) const { return n - div(n) * d; }
+};
+
 // How a launch cuts the keys into runs, one workgroup per (unit of queries, run): what both attention kernels
-// receive by value.  Shard i contributes runs first[i] .. first[i+1]-1 of per[i] keys each (the last one shorter);
+// receive by value.  Shard i contributes runs first[i] .. first[i+1]-1 of s[i].per keys each (the last one shorter);
 // first[i] = INT_MAX past the last shard, so a kernel finds its shard with compares only.  With more than one run
 // the kernels write one normalised partial per run into the workspace, [n_runs][rows][D] then [n_runs][rows], and
 // the Section 4.1 aggregation folds them.
+struct KeyShard {
+    const void* K;
+    const void* V;
+    int64_t L;
+    int64_t per;
+};
 struct KeyRuns {
-    const void* K[kMaxShards];
-    const void* V[kMaxShards];
-    int64_t L[kMaxShards];
-    int64_t per[kMaxShards];
-    int first[kMaxShards + 1];
     int n_runs;
+    int n_shards;
+    FastDiv by_runs;  // n_runs (1 when there is none)
+    int first[kMaxShards + 1];
+    KeyShard s[kMaxShards];
+    // The shard that run `run` (0 <= run < n_runs) belongs to; *split = index of the run inside it.  All of first[] is
+    // read at once and counted (one compare after the other, each waiting for its own scalar load, kept a short
+    // kernel from starting for 1.5 us); a single shard needs none of it.
+    __device__ __forceinline__ KeyShard shard_of(int run, int* split) const {
+        *split = run;
+        if (n_shards == 1) return s[0];
+        int i = 0, begin = 0;
+#pragma unroll
+        for (int j = 1; j < kMaxShards; ++j) {
+            const bool past = run >= first[j];
+            i += past ? 1 : 0;
+            begin = past ? first[j] : begin;
+        }
+        *split = run - begin;
+        return s[i];
+    }
 };
 // Plans the runs for n shards of lengths Ls (n >= 1); pointers are left unset.  codes4: the streaming kernel will
 // read 4-bit transport codes (d = 128 decode shapes), where it wants kDecCodesOcc workgroups per compute unit.
