@@ -1,10 +1,10 @@
 // The Compute Node's work on one KV shard (Section 4.1, per-node local computation):
 //   O_i = softmax(Q' K_i'^T * scale) V_i'   and   lse_i = ln sum_t exp(Q' K_i'^T * scale)   (= ln w_i)
 // evaluated with a running maximum so that outlier logits cannot overflow.  Three kernels:
-//   attn_f32_kernel     (here)             fp32 storage, plain FMAs, one wave per query row (accuracy path)
+//   attn_f32_kernel     (attn_f32.hip)     fp32 storage on the fp32 matrix cores (accuracy path)
 //   decode_attn_kernel  (attn_decode.hip)  16-bit storage, <= 16 query rows per KV head: HBM-bound streaming
 //   prefill_attn_kernel (attn_prefill.hip) 16-bit storage, many query rows: MFMA-bound tiled kernel
-// This file holds the fp32 kernel and the dispatch between the three.
+// This file holds the plan of the key runs and the dispatch between the three.
 #include "fedrag_device.h"
 #include "fedrag_host.h"
 
@@ -14,93 +14,11 @@
 
 namespace fedrag {
 
-// ------------------------------------------------------------------------------------------------ fp32 path
-template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
-                                                       const float* __restrict__ V, int Hq, int Hkv, int64_t Lq,
-                                                       int64_t Lkv, int causal, int64_t total_rows, float scale,
-                                                       float* __restrict__ O, float* __restrict__ lse,
-                                                       const int32_t* __restrict__ kv_lens,
-                                                       const int32_t* __restrict__ q_lens) {
-    constexpr int CPL = D / kWave;  // output columns per lane
-    __shared__ float qs[4][D];
-    const int wave = threadIdx.x / kWave;
-    const int lane = threadIdx.x % kWave;
-    const int64_t row = (int64_t)blockIdx.x * 4 + wave;
-    if (row >= total_rows) return;  // no workgroup barrier below
-    const int64_t bh = row / Lq;
-    const int b = (int)(bh / Hq);
-    const int h = (int)(bh % Hq);
-    const int g = h / (Hq / Hkv);
-    if (q_lens && (row % Lq) >= q_lens[b]) return;  // padding query row of a shorter sequence: not computed
-    const float* q = Q + row * D;
-    const float* Kg = K + ((int64_t)b * Hkv + g) * Lkv * D;
-    const float* Vg = V + ((int64_t)b * Hkv + g) * Lkv * D;
-    // keys this row sees: all of them, or (causal) those up to its own position among the last Lq tokens
-    int64_t L = causal ? (row % Lq) + (Lkv - Lq) + 1 : Lkv;
-    if (kv_lens) {  // padded batch of unequal sequences: only the first kv_lens[b] keys exist
-        const int64_t v = kv_lens[b];
-        const int64_t cap = v < 0 ? 0 : (v < Lkv ? v : Lkv);
-        if (L > cap) L = cap;
-    }
-    for (int c = lane; c < D; c += kWave) qs[wave][c] = q[c];
-    wave_lds_fence();
-
-    float m = -INFINITY, l = 0.f;
-    float acc[CPL];
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
-
-    for (int64_t t0 = 0; t0 < L; t0 += kWave) {
-        const int64_t t = t0 + lane;
-        float s = -INFINITY;
-        if (t < L) {
-            const float* kr = Kg + t * D;
-            float dot = 0.f;
-#pragma unroll 8
-            for (int c = 0; c < D; c += 4) {
-                const f32x4_t kv = *(const f32x4_t*)(kr + c);
-                const f32x4_t qv = *(const f32x4_t*)(&qs[wave][c]);
-                dot = __builtin_fmaf(qv[0], kv[0], dot);
-                dot = __builtin_fmaf(qv[1], kv[1], dot);
-                dot = __builtin_fmaf(qv[2], kv[2], dot);
-                dot = __builtin_fmaf(qv[3], kv[3], dot);
-            }
-            s = dot * scale;
-        }
-        float mx = s;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-        const float m_new = fmaxf(m, mx);  // finite: lane 0 of this tile always has a key
-        const float alpha = (m == -INFINITY) ? 0.f : expf(m - m_new);
-        const float p = (t < L) ? expf(s - m_new) : 0.f;
-        float ps = p;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) ps += __shfl_xor(ps, o);
-        l = l * alpha + ps;
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c] *= alpha;
-        const int n = (L - t0 < kWave) ? (int)(L - t0) : kWave;
-        for (int j = 0; j < n; ++j) {
-            const float pj = __shfl(p, j);
-            const float* vr = Vg + (t0 + j) * D;
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) acc[c] = __builtin_fmaf(pj, vr[c * kWave + lane], acc[c]);
-        }
-        m = m_new;
-    }
-    const float inv = (l > 0.f) ? 1.0f / l : 0.f;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) O[row * D + c * kWave + lane] = acc[c] * inv;
-    if (lane == 0) lse[row] = (l > 0.f) ? m + logf(l) : -INFINITY;
-}
-
 // ------------------------------------------------------------------------------------------------ dispatch
 // Decode workgroups to aim for over the whole launch: one per CU (the kernel is sized for one resident
 // workgroup per CU; a single round of equal-sized workgroups measured fastest).  256 CUs on MI355X; the
 // attribute query is host-only and falls back to that number when no device is present.
-#ifndef FEDRAG_DEC_WGS
-static int decode_target_wgs() {
+int attn_target_wgs() {
     // the count belongs to the device that is current in the calling thread; it is cached per device ordinal in
     // atomics, so concurrent first calls only repeat the query
     constexpr int kMaxDev = 64;
@@ -120,8 +38,6 @@ static int decode_target_wgs() {
     }
     return n;
 }
-#define FEDRAG_DEC_WGS decode_target_wgs()
-#endif
 // Shortest run of the decode kernel, in 128-key steps of a workgroup.  A run costs the launch a partial to fold, so
 // 512 keys (a decoded token's layer over two Context Owners of 4096 keys: 30.4 us, against 31.0 with 256 and 35.2 with
 // 1024), and a context of no more than that is one run and no fold (300 keys: 25.7 us a layer against 27.8 in two runs).
@@ -152,7 +68,7 @@ KeyRuns attn_plan_runs(int B, int Hq, int Hkv, int dtype, int64_t Lq, int n, con
     int64_t total = 0;
     for (int i = 0; i < n; ++i) total += Ls[i] > 0 ? Ls[i] : 0;
     const bool decode = use_decode_kernel(Hq, Hkv, Lq);
-    const int64_t cus = (int64_t)FEDRAG_DEC_WGS * ((codes4 && decode) ? kDecCodesOcc : 1);
+    const int64_t cus = (int64_t)attn_target_wgs() * ((codes4 && decode) ? kDecCodesOcc : 1);
     int64_t per = INT64_MAX;  // keys per run before rebalancing inside a shard
     int64_t quantum = 1;
     if (dtype != FEDRAG_F32 && total > 0 && Lq > 0) {
@@ -233,16 +149,6 @@ size_t attn_workspace_bytes(int B, int Hq, int Hkv, int D, int dtype, int64_t Lq
     return (size_t)runs * rows * (size_t)(D + 1) * sizeof(float);
 }
 
-template <int D>
-static hipError_t launch_attn_f32(const AttnProblem& p, hipStream_t stream) {
-    const int64_t rows = (int64_t)p.B * p.Hq * p.Lq;
-    if (!grid_fits((rows + 3) / 4)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(attn_f32_kernel<D>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, (const float*)p.Q,
-                       (const float*)p.K, (const float*)p.V, p.Hq, p.Hkv, p.Lq, p.Lkv, p.causal ? 1 : 0, rows, p.scale,
-                       p.O, p.lse, p.kv_lens, p.q_lens);
-    return hipGetLastError();
-}
-
 // Scratch for callers that cannot allocate: the key-run partials of a launch land in this file-scope device array
 // instead of a caller's workspace.  Every GPU the library runs on holds its own copy (at its own address) until the
 // process ends.  The name below is only the host's handle for the symbol: the device address is looked up once per
@@ -280,8 +186,9 @@ hipError_t launch_partial_attn(const AttnProblem& p_in, hipStream_t stream) {
         for (int i = 0; i < p.n_shards; ++i) total += p.Ls[i];
         if (total == 0) return launch_fill_empty(p.O, p.lse, rows, p.D, stream);
         const bool decode = use_decode_kernel(p.Hq, p.Hkv, p.Lq);
-        bool one_launch_per_shard = p.dtype == FEDRAG_F32;  // the accuracy path has no run table
-        if (!one_launch_per_shard && (!decode || (int64_t)p.B * p.Hkv >= decode_target_wgs())) {
+        if (p.dtype == FEDRAG_F32) return launch_attn_f32(p, stream);
+        bool one_launch_per_shard = false;
+        if ((!decode || (int64_t)p.B * p.Hkv >= attn_target_wgs())) {
             // The chip is already covered by one shard's workgroups (prefill: query tiles; decode: as many
             // (sequence, KV head) units as compute units) and every shard is one run: a launch per shard keeps the
             // workgroups of a launch on one shard's K', V' (prefill, 8 shards of 8192 keys, 4096 x 64 query rows:
@@ -327,7 +234,7 @@ hipError_t launch_partial_attn(const AttnProblem& p_in, hipStream_t stream) {
         return (use_decode_kernel(p.Hq, p.Hkv, p.Lq) && p.D == 128) ? launch_decode_attn(p, stream)
                                                                     : launch_prefill_attn(p, stream);
     }
-    if (p.dtype == FEDRAG_F32) return p.D == 128 ? launch_attn_f32<128>(p, stream) : launch_attn_f32<64>(p, stream);
+    if (p.dtype == FEDRAG_F32) return launch_attn_f32(p, stream);
     if (p.dtype != FEDRAG_BF16 && p.dtype != FEDRAG_F16) return hipErrorInvalidValue;
     return (!p.causal && use_decode_kernel(p.Hq, p.Hkv, p.Lq)) ? launch_decode_attn(p, stream)
                                                                : launch_prefill_attn(p, stream);

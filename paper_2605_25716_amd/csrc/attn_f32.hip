@@ -1,0 +1,278 @@
+// Partial attention for fp32 storage (Section 4.1, per-node local computation): the accuracy path.  Products and sums
+// are fp32 on the fp32 matrix cores (v_mfma_f32_16x16x4_f32), exponentials and logarithms the accurate library ones.
+//
+// One workgroup = 16 NQ query rows of one (sequence, KV head) unit x one shard; its 8 waves take 16-key tiles
+// round-robin and are folded at the end with the Section 4.1 aggregation, so that a handful of rows over a few hundred
+// keys already keeps a compute unit busy without scratch memory.
+// Lane l of a wave: lr = l % 16, lq = l / 16.
+//   S^T tile (16 keys x 16 queries) = K (16 x d) . Q^T (d x 16), four channels per instruction: lane (lr, lq) supplies
+//   channels 16 j + 4 lq + e of key row lr and of query lr, fetched 16 bytes at a time.  It ends up with query lr and
+//   keys 4 lq + r, r = 0..3.
+//   O^T (d x 16) += V^T (d x 16) . P^T (16 x 16), four keys per instruction: in instruction r lane group lq contracts
+//   key 4 lq + r, which is the probability it holds, and the d-rows are assigned d = DCH i + t (tile t, row i), so that
+//   lane (i = lr) needs DCH contiguous channels of each of its four keys: full rows, no transposition anywhere.
+// Bound by the matrix pipe (64 NQ instructions of 32 cycles per 16 KiB of K, V at d = 128) as soon as the workgroups
+// cover the chip, by the latency of a tile before that.  NQ = 2 reads K, V half as often and is taken when its
+// workgroups still cover the compute units; below that NQ = 1 spreads the rows over twice as many of them.
+// 4 rows x 512 keys x 2 heads of 64: MEASURED_TINY us (132 us with one wave per row and plain multiply-adds).
+#include "fedrag_device.h"
+#include "fedrag_host.h"
+
+namespace fedrag {
+
+constexpr int kF32Waves = 8;
+constexpr int kF32AttnThreads = kF32Waves * kWave;
+constexpr int kF32Tile = 16;  // keys per wave step
+
+__device__ __forceinline__ f32x4_t mfma_f32(float a, float b, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+// exp(a - b) with the convention that a == -inf gives 0 even when b == -inf.
+__device__ __forceinline__ float exp_diff(float a, float b) { return (a == -INFINITY) ? 0.0f : expf(a - b); }
+
+template <int D, int NQ>
+__global__ __launch_bounds__(kF32AttnThreads, 1) void attn_f32_kernel(const float* __restrict__ Q, const KeyRuns runs,
+                                                                      FastDiv by_tiles, FastDiv by_lq, int Hkv, int R,
+                                                                      int64_t Lq, int64_t causal_off, int causal,
+                                                                      float scale, float* __restrict__ O,
+                                                                      float* __restrict__ lse, int64_t total_rows,
+                                                                      const int32_t* __restrict__ kv_lens,
+                                                                      const int32_t* __restrict__ q_lens) {
+    constexpr int DCH = D / 16;  // channels per lane and key of V (= 16-row tiles of O^T)
+    constexpr int KJ = D / 16;   // 16-byte reads per lane of a K or Q row
+    constexpr int LDO = D + 4;
+    __shared__ float sm_m[kF32Waves][NQ * 16], sm_l[kF32Waves][NQ * 16];
+    __shared__ __attribute__((aligned(16))) float sm_o[kF32Waves][NQ * 16][LDO];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int lane = tid % kWave;
+    const int lr = lane % 16;
+    const int lq = lane / 16;
+    const uint32_t group = runs.by_runs.div(blockIdx.x);  // (unit, row tile); the runs of one are neighbours
+    const int run = (int)(blockIdx.x - group * runs.by_runs.d);
+    const uint32_t unit = by_tiles.div(group);
+    const int row0 = (int)(group - unit * by_tiles.d) * (NQ * 16);
+    int split;
+    const KeyShard shard = runs.shard_of(run, &split);  // one run per shard: split == 0
+    int64_t L = shard.L;
+    const float* K = (const float*)shard.K + (int64_t)unit * L * D;
+    const float* V = (const float*)shard.V + (int64_t)unit * L * D;
+    if (kv_lens) {  // padded batch of unequal sequences: only the first kv_lens[b] keys exist
+        const int64_t v = kv_lens[(int)unit / Hkv];
+        L = v < 0 ? 0 : (v < L ? v : L);
+    }
+
+    // row n of the unit is query n % Lq of head n / Lq of the group; it sees keys < lim
+    f32x4_t q[NQ][KJ];
+    int64_t lim[NQ];
+    int64_t most = 0;  // keys that some row of the workgroup sees
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+        const int row = row0 + n * 16 + lr;
+        const int row_ld = row < R ? row : R - 1;  // rows past the end are computed on a real one and not written
+        const float* qp = Q + ((int64_t)unit * R + row_ld) * D + 4 * lq;
+#pragma unroll
+        for (int j = 0; j < KJ; ++j) q[n][j] = *(const f32x4_t*)(qp + 16 * j);
+        lim[n] = L;
+        if (causal) {
+            const int64_t own = (int64_t)by_lq.mod((uint32_t)row_ld) + causal_off + 1;
+            if (own < L) lim[n] = own;
+        }
+    }
+    if (causal) {
+        int top = 0;  // L <= INT32_MAX
+#pragma unroll
+        for (int n = 0; n < NQ; ++n) top = (int)lim[n] > top ? (int)lim[n] : top;
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) {
+            const int other = __shfl_xor(top, o);
+            top = other > top ? other : top;
+        }
+        most = __builtin_amdgcn_readfirstlane(top);
+    } else {
+        most = L;
+    }
+
+    f32x4_t acc[NQ][DCH];
+    float m_run[NQ], l_run[NQ];
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+        m_run[n] = -INFINITY;
+        l_run[n] = 0.f;
+#pragma unroll
+        for (int t = 0; t < DCH; ++t) acc[n][t] = zero_vec<f32x4_t>();
+    }
+
+    // rows past the last key re-read it (it exists when a tile does); their scores are masked
+    auto load_k = [&](int64_t key0, f32x4_t (&k)[KJ]) {
+        int64_t key = key0 + lr;
+        if (key >= most) key = most - 1;
+        const float* kp = K + key * D + 4 * lq;
+#pragma unroll
+        for (int j = 0; j < KJ; ++j) k[j] = *(const f32x4_t*)(kp + 16 * j);
+    };
+    const int64_t stride = (int64_t)kF32Waves * kF32Tile;
+    int64_t key0 = (int64_t)wave * kF32Tile;
+    f32x4_t k[KJ];
+    if (key0 < most) load_k(key0, k);
+    for (; key0 < most; key0 += stride) {
+        f32x4_t v[4][DCH / 4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            int64_t key = key0 + 4 * lq + r;
+            if (key >= most) key = most - 1;
+            const float* vp = V + key * D + DCH * lr;
+#pragma unroll
+            for (int c = 0; c < DCH / 4; ++c) v[r][c] = *(const f32x4_t*)(vp + 4 * c);
+        }
+        f32x4_t s[NQ];
+#pragma unroll
+        for (int n = 0; n < NQ; ++n) {
+            f32x4_t part[2] = {zero_vec<f32x4_t>(), zero_vec<f32x4_t>()};  // two chains: no wait for the last result
+#pragma unroll
+            for (int j = 0; j < KJ; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) part[e % 2] = mfma_f32(k[j][e], q[n][j][e], part[e % 2]);
+            s[n] = part[0] + part[1];
+        }
+        if (key0 + stride < most) load_k(key0 + stride, k);
+        const bool whole = !causal && key0 + kF32Tile <= L;  // wave-uniform
+        bool odd_v = false;
+        if (!whole) {
+            float sum = 0.f;  // x - x is 0 for a finite x and NaN otherwise
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int t = 0; t < DCH; ++t) sum += v[r][t / 4][t % 4] - v[r][t / 4][t % 4];
+            odd_v = __builtin_amdgcn_ballot_w64(sum != 0.f) != 0;
+        }
+#pragma unroll
+        for (int n = 0; n < NQ; ++n) {
+            float mx = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[n][r] *= scale;
+                if (!whole && key0 + 4 * lq + r >= lim[n]) s[n][r] = -INFINITY;
+                mx = fmaxf(mx, s[n][r]);
+            }
+            mx = xor32_max(xor16_max(mx));
+            const float m_new = fmaxf(m_run[n], mx);
+            const float alpha = exp_diff(m_run[n], m_new);
+            float p[4];
+            float psum = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                p[r] = exp_diff(s[n][r], m_new);
+                psum += p[r];
+            }
+            l_run[n] = l_run[n] * alpha + psum;
+            m_run[n] = m_new;
+#pragma unroll
+            for (int t = 0; t < DCH; ++t) acc[n][t] *= alpha;
+            if (whole || !odd_v) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int t = 0; t < DCH; ++t) acc[n][t] = mfma_f32(v[r][t / 4][t % 4], p[r], acc[n][t]);
+            } else {
+                // an infinity or NaN in V times the zero probability of a row that does not see its key would reach
+                // that row: one query at a time, with the rows of V that it does not see left out
+#pragma unroll 1
+                for (int c = 0; c < 16; ++c) {
+                    const int lim_c = __shfl((int)lim[n], c);
+#pragma unroll
+                    for (int t = 0; t < DCH; ++t) {
+                        f32x4_t one = zero_vec<f32x4_t>();
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            one = mfma_f32(key0 + 4 * lq + r < lim_c ? v[r][t / 4][t % 4] : 0.f, lr == c ? p[r] : 0.f, one);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[n][t][r] += lr == c ? one[r] : 0.f;
+                    }
+                }
+            }
+        }
+    }
+
+    // fold the waves
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+        const float l_tot = xor32_sum(xor16_sum(l_run[n]));
+        if (lq == 0) {
+            sm_m[wave][n * 16 + lr] = m_run[n];
+            sm_l[wave][n * 16 + lr] = l_tot;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int t = 0; t < DCH; t += 4) {
+                f32x4_t o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = acc[n][t + e][r];
+                *(f32x4_t*)&sm_o[wave][n * 16 + lr][DCH * (4 * lq + r) + t] = o;
+            }
+    }
+    __syncthreads();
+    int64_t q_rows = Lq;  // query rows past the sequence's count are padding and are not written
+    if (q_lens) q_rows = q_lens[(int)unit / Hkv];
+    const int64_t base = (int64_t)run * total_rows + (int64_t)unit * R;
+    for (int idx = tid; idx < NQ * 16 * (D / 4); idx += kF32AttnThreads) {
+        const int n = idx / (D / 4);
+        const int d = idx % (D / 4) * 4;
+        const int row = row0 + n;
+        if (row >= R || (q_lens && (int64_t)by_lq.mod((uint32_t)row) >= q_rows)) continue;
+        float M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < kF32Waves; ++w) M = fmaxf(M, sm_m[w][n]);
+        f32x4_t num = zero_vec<f32x4_t>();
+        float den = 0.f;
+#pragma unroll
+        for (int w = 0; w < kF32Waves; ++w) {
+            const float a = exp_diff(sm_m[w][n], M);
+            const f32x4_t o = *(const f32x4_t*)&sm_o[w][n][d];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) num[e] = __builtin_fmaf(a, o[e], num[e]);
+            den = __builtin_fmaf(a, sm_l[w][n], den);
+        }
+        const float inv = den > 0.f ? 1.0f / den : 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) num[e] *= inv;
+        *(f32x4_t*)(O + (base + row) * D + d) = num;
+        if (d == 0) lse[base + row] = den > 0.f ? M + logf(den) : -INFINITY;
+    }
+}
+
+template <int D, int NQ>
+static hipError_t launch_f32_t(const AttnProblem& p, const KeyRuns& runs, hipStream_t stream) {
+    const int64_t rows = (int64_t)p.B * p.Hq * p.Lq;
+    const int64_t R = (int64_t)(p.Hq / p.Hkv) * p.Lq;  // rows of a unit, contiguous in Q, O and lse
+    const int64_t tiles = (R + NQ * 16 - 1) / (NQ * 16);
+    const int64_t grid = (int64_t)p.B * p.Hkv * tiles * runs.n_runs;
+    if (R > 0x7fffffffLL || !grid_fits(grid)) return hipErrorInvalidValue;
+    float* Odst = p.O;
+    float* Ldst = p.lse;
+    if (runs.n_runs > 1) {
+        if (!p.workspace || p.workspace_bytes < (size_t)runs.n_runs * rows * (D + 1) * sizeof(float))
+            return hipErrorInvalidValue;
+        Odst = (float*)p.workspace;
+        Ldst = Odst + (size_t)runs.n_runs * rows * D;
+    }
+    hipLaunchKernelGGL((attn_f32_kernel<D, NQ>), dim3((unsigned)grid), dim3(kF32AttnThreads), 0, stream,
+                       (const float*)p.Q, runs, FastDiv(tiles), FastDiv(p.Lq), p.Hkv, (int)R, p.Lq, p.Lkv - p.Lq,
+                       p.causal ? 1 : 0, p.scale, Odst, Ldst, rows, p.kv_lens, p.q_lens);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || runs.n_runs == 1) return e;
+    return launch_lse_merge(Odst, Ldst, runs.n_runs, rows, D, p.O, p.lse, stream);
+}
+
+hipError_t launch_attn_f32(const AttnProblem& p, hipStream_t stream) {
+    const KeyRuns runs = attn_runs_of(p);  // fp32: one run per shard
+    if (runs.n_runs < 1) return hipErrorInvalidValue;
+    const int64_t R = (int64_t)(p.Hq / p.Hkv) * p.Lq;
+    const bool wide = (int64_t)p.B * p.Hkv * ((R + 31) / 32) * runs.n_runs >= attn_target_wgs();
+    if (p.D == 128) return wide ? launch_f32_t<128, 2>(p, runs, stream) : launch_f32_t<128, 1>(p, runs, stream);
+    return wide ? launch_f32_t<64, 2>(p, runs, stream) : launch_f32_t<64, 1>(p, runs, stream);
+}
+
+}  // namespace fedrag

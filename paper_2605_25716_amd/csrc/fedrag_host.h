@@ -130,6 +130,8 @@ struct KeyRuns {
 // Plans the runs for n shards of lengths Ls (n >= 1); pointers are left unset.  codes4: the streaming kernel will
 // read 4-bit transport codes (d = 128 decode shapes), where it wants kDecCodesOcc workgroups per compute unit.
 KeyRuns attn_plan_runs(int B, int Hq, int Hkv, int dtype, int64_t Lq, int n, const int64_t* Ls, bool codes4 = false);
+// Workgroups that make one round over the chip: the compute units of the device that is current in the calling thread.
+int attn_target_wgs();
 bool attn_uses_decode_kernel(int Hq, int Hkv, int64_t Lq);  // G * Lq <= 16: the HBM-bound streaming kernel
 // bytes of workspace the plan needs (0 when there is a single run)
 size_t attn_workspace_bytes(int B, int Hq, int Hkv, int D, int dtype, int64_t Lq, int n, const int64_t* Ls);
@@ -157,6 +159,7 @@ constexpr int kPreQ = 32;                     // query rows per wave (one 32-wid
 constexpr int kPreQTile = kPreWaves * kPreQ;  // query rows per workgroup
 constexpr int kPreK = 64;                     // keys per LDS tile
 constexpr int kPreMinTilesPerSplit = 4;       // a KV split is at least this many tiles
+hipError_t launch_attn_f32(const AttnProblem& p, hipStream_t stream);      // fp32 storage, any L_q
 hipError_t launch_decode_attn(const AttnProblem& p, hipStream_t stream);   // 16-bit storage, G * L_q <= 16
 hipError_t launch_prefill_attn(const AttnProblem& p, hipStream_t stream);  // 16-bit storage, any L_q
 
