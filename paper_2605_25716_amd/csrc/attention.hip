@@ -84,7 +84,7 @@ KeyRuns attn_plan_runs(int B, int Hq, int Hkv, int dtype, int64_t Lq, int n, con
             if (per > (int64_t)1 << 22) per = (int64_t)1 << 22;
         } else {
             // the query heads of a KV head form one run of G * Lq rows (see launch_prefill_t)
-            const int64_t wgs = (int64_t)B * Hkv * (((int64_t)(Hq / Hkv) * Lq + kPreQTile - 1) / kPreQTile);
+            const int64_t wgs = (int64_t)B * Hkv * (((int64_t)(Hq / Hkv) * Lq + kPrePlanRows - 1) / kPrePlanRows);
             quantum = kPreK;
             if (wgs > 0 && wgs * 2 <= cus) {
                 const int64_t want = cus / wgs;

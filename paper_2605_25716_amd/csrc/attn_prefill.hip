@@ -4,8 +4,8 @@
 // best inside one wave (in the shadow of that wave's own MFMAs), so each wave software-pipelines across key tiles:
 // in iteration t it computes S^T(t) = K'(t) Q'^T and then issues the MFMAs of O^T += V'(t-1)^T P(t-1)^T together with
 // the online softmax of tile t.
-//   * one workgroup = 8 waves x 32 query rows = 256 query rows of one (sequence, query head);
-//   * K'/V' tiles of 64 keys are shared by the 8 waves through LDS (two slots each), filled by LDS-direct global
+//   * one workgroup = 8 or 4 waves x 32 query rows of one (sequence, query head); the launch chooses (see below);
+//   * K'/V' tiles of 64 keys are shared by the waves through LDS (two slots each), filled by LDS-direct global
 //     loads one iteration ahead (no staging registers), one workgroup barrier per iteration;
 //   * LDS tiles are unpadded (LDS-direct loads write 64 consecutive 16-byte slots per wave); bank conflicts are
 //     avoided by XOR-swizzling the 16-byte chunk index with the row;
@@ -25,7 +25,6 @@
 
 namespace fedrag {
 
-constexpr int kPreThreads = kPreWaves * kWave;
 #ifndef FEDRAG_PRE_PD
 #define FEDRAG_PRE_PD 4
 #endif
@@ -47,25 +46,27 @@ __device__ __forceinline__ u32x2_t lds_read_tr16(const char* p) {
 // storage type (relative error 2^-9 in bf16) would move an output by more than the 16-bit output tolerance.  The
 // CAUSAL instantiation therefore feeds the second product P = P_hi + P_lo, two storage-type terms (about 16
 // significant bits), at the price of twice the MFMAs of that product.
-template <class T, int D, bool CAUSAL, int QB>
-__global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const typename T::elem* __restrict__ Q,
+template <class T, int D, bool CAUSAL, int QB, int NW>
+__global__ __launch_bounds__(NW * kWave, 2) void prefill_attn_kernel(const typename T::elem* __restrict__ Q,
                                                                       const KeyRuns runs,
                                                                       const float* __restrict__ Kprm,
                                                                       const float* __restrict__ Vprm, int Hq,
                                                                       FastDiv by_heads, FastDiv by_group,
                                                                       FastDiv by_tiles, FastDiv by_unit, int64_t Lq,
                                                                       const int32_t* __restrict__ kv_lens,
-                                                                      const int32_t* __restrict__ q_lens, int n_units,
+                                                                      const int32_t* __restrict__ q_lens, int n_units, int fold,
                                                                       float scale_log2,
                                                                       float* __restrict__ O, float* __restrict__ lse) {
     typedef typename T::elem elem;
     typedef typename T::vec8 vec8;
+    constexpr int kThreads = NW * kWave;
+    constexpr int kQTile = NW * kPreQ;   // query rows per workgroup
     constexpr int ROWB = D * 2;             // bytes per tile row in LDS (no padding)
     constexpr int SLOT = kPreK * ROWB;      // bytes per tile slot
     constexpr int KS = D / 16;              // contraction steps of S^T
     constexpr int MT = D / 32;              // 32-row tiles of O^T
     constexpr int CH = D / 8;               // 16-byte chunks per row
-    constexpr int LPT = (kPreK * CH) / kPreThreads;  // LDS-direct loads (QB: 8-element chunks) per thread per tile
+    constexpr int LPT = (kPreK * CH) / kThreads;  // LDS-direct loads (QB: 8-element chunks) per thread per tile
     static_assert(QB == 0 || QB == 8 || QB == 4, "16-bit values, or 8- / 4-bit codes");
     static_assert(QB == 0 || !CAUSAL, "codes are what travels to the Compute Node; the Inquirer's own K, V are plain");
     constexpr int CROWB = QB ? D * QB / 8 : ROWB;  // bytes per row of K' / V' as stored (values, or codes)
@@ -98,7 +99,12 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
     // one before it, and so on: workgroups are started in index order as compute units free up, so every compute
     // unit ends up with a long tile followed by short ones and the launch does not wait on a late long tile.
     const int hg = CAUSAL ? (int)by_group.mod(w_in_unit) : (int)by_tiles.div(w_in_unit);
-    const int qt = CAUSAL ? (int)(by_tiles.d - 1 - by_group.div(w_in_unit)) : (int)by_tiles.mod(w_in_unit);
+    int qt = (int)by_tiles.mod(w_in_unit);
+    if (CAUSAL) {
+        const int pos = (int)by_group.div(w_in_unit);
+        const int folded = fold ? (int)(by_tiles.d + 1) / 2 : (int)by_tiles.d;  // first part: last tile first
+        qt = pos < folded ? (int)by_tiles.d - 1 - pos : pos - folded;
+    }
     const int b = (int)by_heads.div(unit);
     const int g = (int)by_heads.mod(unit);
     const int h = g * G + hg;
@@ -126,7 +132,7 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
         const int64_t v = q_lens[b];
         Lq_rows = v < 0 ? 0 : (v < Lq ? v : Lq);
     }
-    if ((int64_t)qt * kPreQTile >= Lq_rows) return;  // workgroup-uniform, before any barrier
+    if ((int64_t)qt * kQTile >= Lq_rows) return;  // workgroup-uniform, before any barrier
     const int64_t part_row0 = (int64_t)run * n_units * G * Lq;  // n_units * G * Lq = rows of one partial
     float* Oh = O + (part_row0 + ((int64_t)b * Hq + h) * Lq) * D;
     float* Lh = lse + part_row0 + ((int64_t)b * Hq + h) * Lq;
@@ -142,7 +148,7 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
         }
     }
 
-    const int64_t q_row = (int64_t)qt * kPreQTile + wave * kPreQ + li;  // this lane's query row
+    const int64_t q_row = (int64_t)qt * kQTile + wave * kPreQ + li;  // this lane's query row
     if (L == 0) {  // no keys (workgroup-uniform, before any barrier): O = 0, lse = -inf
         if (q_row < Lq_rows) {
             for (int c = lh * (D / 2); c < (lh + 1) * (D / 2); c += 4) *(f32x4_t*)(Oh + q_row * D + c) = zero_vec<f32x4_t>();
@@ -158,32 +164,35 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
     f32x16_t acc_o[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i) acc_o[i] = zero_vec<f32x16_t>();
-    float m_run = -INFINITY, l_run = 0.f;
+    // The running maximum starts at the lowest finite value: a row may see no key of the first tiles that its workgroup
+    // visits, and -inf - m_run has to be -inf then.
+    float m_run = -__FLT_MAX__, l_run = 0.f;
 
     // ---- global -> LDS (direct buffer loads).  One wave-wide load fills 64 consecutive 16-byte slots = 64 / CH
     // tile rows.  LDS slot p of row r holds global chunk p ^ swz(r): K' swz(r) = r % CH, V' swz(r) = (4 (r % 4)) % CH;
     // both depend on r only through r % 16, which is the same for every load of a thread.  The buffer resource
-    // starts at the tile and covers the rest of the shard, so rows past the end of the shard arrive as zeros.
+    // starts at the tile and covers the rest of the shard, so rows past the end of the shard arrive as zeros; tile -1, which
+    // the steady loop asks for behind its last one, reads nothing.
     constexpr int RPW = kWave / CH;  // rows per wave-wide load
-    const int ld_r = wave * RPW + lane / CH;  // row within a group of kPreWaves * RPW rows
+    const int ld_r = wave * RPW + lane / CH;  // row within a group of NW * RPW rows
     const int ld_p = lane % CH;               // slot within the row
     const int ld_voff_k = ld_r * ROWB + ((ld_p ^ (ld_r % CH)) << 4);
     const int ld_voff_v = ld_r * ROWB + ((ld_p ^ ((4 * (ld_r % 4)) % CH)) << 4);
-    static_assert((kPreWaves * RPW) % 16 == 0, "swizzle must not depend on the load index");
+    static_assert((NW * RPW) % 16 == 0, "swizzle must not depend on the load index");
     auto load_tile = [&](const char* G_, char* slot_base, int tile, bool is_k) {
         const int64_t byte0 = (int64_t)tile * SLOT;
         const int64_t left = L * ROWB - byte0;
-        const int n_rec = (int)(left < 0x7fffffff ? left : 0x7fffffff);
+        const int n_rec = tile < 0 ? 0 : (int)(left < 0x7fffffff ? left : 0x7fffffff);
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(G_ + byte0), 0, n_rec, 0x00020000);
 #pragma unroll
         for (int j = 0; j < LPT; ++j) {
-            char* lp = slot_base + (j * kPreWaves + wave) * (RPW * ROWB);  // wave-uniform LDS base
+            char* lp = slot_base + (j * NW + wave) * (RPW * ROWB);  // wave-uniform LDS base
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (void __attribute__((address_space(3)))*)lp, 16,
-                                                     is_k ? ld_voff_k : ld_voff_v, j * (kPreWaves * RPW * ROWB), 0, 0);
+                                                     is_k ? ld_voff_k : ld_voff_v, j * (NW * RPW * ROWB), 0, 0);
         }
     };
 
-    // ---- QB: codes -> registers one iteration ahead, then -> LDS.  Chunk j of a thread is row (j * kPreThreads + tid)
+    // ---- QB: codes -> registers one iteration ahead, then -> LDS.  Chunk j of a thread is row (j * kThreads + tid)
     // / CH of the tile, 8 channels from 8 (tid % CH); reads past the end of the shard return zeros (code 0, scale 0,
     // lo 0: the row dequantises to zeros, as rows past the end arrive in the 16-bit path).
     struct CodeChunk {
@@ -194,7 +203,7 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
     const int cq_row = tid / CH, cq_c = tid % CH;
     auto fetch_codes = [&](const char* G_, const float* Pg_, int tile, CodeChunk (&st)[QB ? LPT : 1]) {
         const int64_t row0 = (int64_t)tile * kPreK;
-        const int64_t left_rows = L - row0 > 0 ? L - row0 : 0;
+        const int64_t left_rows = tile >= 0 && L - row0 > 0 ? L - row0 : 0;
         const int64_t lc = left_rows * CROWB, lp = left_rows * 8;
         const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
             (void*)(G_ + row0 * CROWB), 0, (int)(lc < 0x7fffffff ? lc : 0x7fffffff), 0x00020000);
@@ -202,7 +211,7 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
             (void*)(Pg_ + row0 * 2), 0, (int)(lp < 0x7fffffff ? lp : 0x7fffffff), 0x00020000);
 #pragma unroll
         for (int j = 0; j < LPT; ++j) {
-            const int r = j * (kPreThreads / CH) + cq_row;
+            const int r = j * (kThreads / CH) + cq_row;
             if constexpr (QB == 8) {
                 const u32x2_t w = __builtin_amdgcn_raw_buffer_load_b64(rc, r * CROWB + cq_c * 8, 0, 0);
                 st[j].c[0] = w[0];
@@ -216,7 +225,7 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
     auto store_codes = [&](char* slot_base, const CodeChunk (&st)[QB ? LPT : 1], bool is_k) {
 #pragma unroll
         for (int j = 0; j < LPT; ++j) {
-            const int r = j * (kPreThreads / CH) + cq_row;
+            const int r = j * (kThreads / CH) + cq_row;
             const uint32_t sb = st[j].prm[0], lb = st[j].prm[1];
             const float scale = __builtin_bit_cast(float, sb), lo = __builtin_bit_cast(float, lb);
             vec8 out;
@@ -253,8 +262,8 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
     // keys this workgroup has to visit, and the first tile in which some key is hidden from some row of the
     // workgroup (past the end of the shard, or - CAUSAL - after the row's own position)
     const int64_t off = L - Lq;
-    const int64_t q_first = (int64_t)qt * kPreQTile;
-    const int64_t q_last = (q_first + kPreQTile < Lq ? q_first + kPreQTile : Lq) - 1;
+    const int64_t q_first = (int64_t)qt * kQTile;
+    const int64_t q_last = (q_first + kQTile < Lq ? q_first + kQTile : Lq) - 1;
     const int64_t wg_keys = CAUSAL ? (q_last + off + 1 < L ? q_last + off + 1 : L) : L;
     const int n_tiles = (int)((wg_keys + kPreK - 1) / kPreK);
     const int t_mask0 = (int)((CAUSAL ? (q_first + off + 1 < L ? q_first + off + 1 : L) : L) / kPreK);
@@ -289,25 +298,34 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
     // Splitting the softmax of a tile over two phases gives both MFMA phases about the same vector load.
     // `par` carries t % 2 as a compile-time constant so that the double-buffered register sets are addressed
     // statically.  m_run is the running maximum after tile t-1 until B1(t) replaces it.
-    auto iteration = [&](int t, auto par, bool doC, bool doAB, bool ldK, bool may_mask) {
+    // Tiles are visited from the last one down (tile n_tiles - 1 - visit), so that those with keys that some row must not
+    // see come first: the ragged end of the shard, or the tiles on the diagonal.  t counts the visits of the pipelined
+    // part: t = 0 is its first tile and has no C, t = n is nothing but B2 and C of tile n - 1, all between run both
+    // phases on tiles that every row sees whole.  Only the kFirst form masks.  (A tail of masked tiles behind the steady
+    // loop, its stages switched by runtime flags, spilled its registers: 9000 cycles per tile against 1300 to 2600,
+    // most of the time of a segment of a few hundred tokens; masking in the steady loop made that loop 15 % slower.)
+    enum { kFirst, kSteady, kLast };
+    auto iteration = [&](int tile, auto par, auto stage, bool ldK) {
         constexpr int p = decltype(par)::value;  // t & 1
         constexpr int q = 1 - p;                 // (t - 1) & 1 == (t + 1) & 1
+        constexpr int kind = decltype(stage)::value;
+        constexpr bool doC = kind != kFirst;
+        constexpr bool doAB = kind != kLast;
         constexpr int NM = 4 * MT;
         static_assert(NM == 16 || NM == 8, "slice plans assume d = 128 or 64");
         if constexpr (QB == 0) {
-            if (ldK) load_tile(Kg, q ? ks1 : ks0, t + 1, true);    // K'(t+1) -> slot (t+1) & 1 (last read by A(t-1))
-            if (doAB) load_tile(Vg, p ? vs1 : vs0, t, false);      // V'(t)   -> slot t & 1     (last read by C(t-2))
+            if (ldK) load_tile(Kg, q ? ks1 : ks0, tile - 1, true);  // K'(t+1) -> slot (t+1) & 1 (last read by A(t-1))
+            if constexpr (doAB) load_tile(Vg, p ? vs1 : vs0, tile, false);  // V'(t) -> slot t & 1 (last read by C(t-2))
         } else {  // the codes of the same two tiles into registers; they reach their (free) slots between the phases
-            if (ldK) fetch_codes(Kg, Kpg, t + 1, kst);
-            if (doAB) fetch_codes(Vg, Vpg, t, vst);
+            if (ldK) fetch_codes(Kg, Kpg, tile - 1, kst);
+            if constexpr (doAB) fetch_codes(Vg, Vpg, tile, vst);
         }
-        const bool steady = doC && doAB && !may_mask;
 
         // --- A(t) and B2(t-1).  Lane gets query li and, per 32-key half, keys 8 (r / 4) + 4 lh + r % 4, r = 0..15.
         // Contraction element e of step kk of the second product <-> key 16 kk + 8 (e / 4) + 4 lh + e % 4, so
         // register r of half 1 goes to step 2 + r / 8, element r % 8.
         const char* kt = p ? ks1 : ks0;
-        if (steady) {
+        if constexpr (doAB) {
             constexpr int NA = 2 * KS;  // MFMAs of A: slice j -> half j % 2, contraction step j / 2
             vec8 kop[NA];
 #pragma unroll
@@ -321,37 +339,37 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
                 if (j + kPrePD < NA) kop[j + kPrePD] = *(const vec8*)(kt + ((j + kPrePD) % 2) * 32 * ROWB + k_off[(j + kPrePD) / 2]);
                 if (j % 2 == 0) S0 = T::mfma32(kop[j], qop[j / 2], S0);
                 else S1[p] = T::mfma32(kop[j], qop[j / 2], S1[p]);
-                const int r0 = (j * 16) / NA, r1 = ((j + 1) * 16) / NA;  // registers of half 1 handled here
+                if constexpr (doC) {
+                    const int r0 = (j * 16) / NA, r1 = ((j + 1) * 16) / NA;  // registers of half 1 handled here
 #pragma unroll
-                for (int r = r0; r < r1; ++r) {
-                    const float pe = fast_exp2(__builtin_fmaf(S1[q][r], scale_log2, -m_run));
-                    psum += pe;
-                    put_p(q, 2 + r / 8, r % 8, pe);
+                    for (int r = r0; r < r1; ++r) {
+                        const float pe = fast_exp2(__builtin_fmaf(S1[q][r], scale_log2, -m_run));
+                        psum += pe;
+                        put_p(q, 2 + r / 8, r % 8, pe);
+                    }
+                    pin_here(psum);  // the slice's vector work stays in the slice
                 }
-                pin_here(psum);  // the slice's vector work stays in the slice
                 __builtin_amdgcn_sched_barrier(0);
             }
             l_run += psum;
-        } else {
-            if (doC) {  // B2(t-1)
-                float psum = 0.f;
+            if (kind == kFirst && tile >= t_mask0) {  // the ragged end, or a tile that reaches past a row's own position
+                const int key0 = tile * kPreK + 4 * lh;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const float pe = fast_exp2(__builtin_fmaf(S1[q][r], scale_log2, -m_run));
-                    psum += pe;
-                    put_p(q, 2 + r / 8, r % 8, pe);
+                    const int key = key0 + 8 * (r / 4) + (r % 4);
+                    if (key >= key_lim) S0[r] = -INFINITY;
+                    if (key + 32 >= key_lim) S1[p][r] = -INFINITY;  // also seen by B2(t) later
                 }
-                l_run += psum;
             }
-            if (doAB) {
-                S0 = zero_vec<f32x16_t>();
-                S1[p] = zero_vec<f32x16_t>();
+        } else {  // B2(t-1)
+            float psum = 0.f;
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    S0 = T::mfma32(*(const vec8*)(kt + k_off[ks]), qop[ks], S0);
-                    S1[p] = T::mfma32(*(const vec8*)(kt + 32 * ROWB + k_off[ks]), qop[ks], S1[p]);
-                }
+            for (int r = 0; r < 16; ++r) {
+                const float pe = fast_exp2(__builtin_fmaf(S1[q][r], scale_log2, -m_run));
+                psum += pe;
+                put_p(q, 2 + r / 8, r % 8, pe);
             }
+            l_run += psum;
         }
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (QB != 0) {
@@ -359,7 +377,7 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
             __builtin_amdgcn_sched_barrier(0);
         }
         const char* vt = q ? vs1 : vs0;
-        if (doC) {
+        if constexpr (doC) {
             if (__builtin_amdgcn_ballot_w64(alph[q] != 1.0f) != 0) {  // wave-uniform: skip when no maximum moved
 #pragma unroll
                 for (int i = 0; i < MT; ++i) acc_o[i] *= alph[q];
@@ -367,135 +385,113 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
         }
         __builtin_amdgcn_sched_barrier(0);
         // --- C(t-1) and B1(t)
-        if (steady) {
+        {
             // 4 MT slices of one MFMA each, with scheduling fences between slices: a slice holds the MFMA, its
             // share of B1 and the transposing reads of the operand four MFMAs ahead.  Shares: slices 0-1 the row
             // maximum, slice 2 the new running maximum and the rescale factor, slices 2.. the 16 probabilities.
             constexpr int FIRST = 2;  // first slice that produces probabilities
             vec8 vop[NM];
+            if constexpr (doC) {
 #pragma unroll
-            for (int j = 0; j < kPrePD; ++j) vop[j] = read_vop(vt, j / MT, j % MT);
+                for (int j = 0; j < kPrePD; ++j) vop[j] = read_vop(vt, j / MT, j % MT);
+            }
             float mx = S0[0];
             float m_new = 0.f, psum = 0.f;
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < NM; ++j) {
-                if (j + kPrePD < NM) vop[j + kPrePD] = read_vop(vt, (j + kPrePD) / MT, (j + kPrePD) % MT);
-                acc_o[j % MT] = T::mfma32(vop[j], P[q][j / MT], acc_o[j % MT]);
-                if constexpr (SPLIT) acc_o[j % MT] = T::mfma32(vop[j], Plo[q][j / MT], acc_o[j % MT]);
-                if (j == 0) {
-#pragma unroll
-                    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, S0[r]);
+                if constexpr (doC) {
+                    if (j + kPrePD < NM) vop[j + kPrePD] = read_vop(vt, (j + kPrePD) / MT, (j + kPrePD) % MT);
+                    acc_o[j % MT] = T::mfma32(vop[j], P[q][j / MT], acc_o[j % MT]);
+                    if constexpr (SPLIT) acc_o[j % MT] = T::mfma32(vop[j], Plo[q][j / MT], acc_o[j % MT]);
                 }
-                if (j == 1) {
+                if constexpr (doAB) {
+                    if (j == 0) {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, S1[p][r]);
-                }
-                if (j == FIRST) {
-                    mx = xor32_max(mx);
-                    m_new = fmaxf(m_run, mx * scale_log2);  // scale > 0: max commutes with the scaling
-                    alph[p] = exp2_diff(m_run, m_new);
-                }
-                if (j >= FIRST) {
-                    constexpr int NS = NM - FIRST;
-                    const int r0 = ((j - FIRST) * 16) / NS, r1 = ((j - FIRST + 1) * 16) / NS;
+                        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, S0[r]);
+                    }
+                    if (j == 1) {
 #pragma unroll
-                    for (int r = r0; r < r1; ++r) {
-                        const float pe = fast_exp2(__builtin_fmaf(S0[r], scale_log2, -m_new));
-                        psum += pe;
-                        put_p(p, r / 8, r % 8, pe);
+                        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, S1[p][r]);
+                    }
+                    if (j == FIRST) {
+                        mx = xor32_max(mx);
+                        m_new = fmaxf(m_run, mx * scale_log2);  // scale > 0: max commutes with the scaling
+                        alph[p] = exp2_diff(m_run, m_new);
+                    }
+                    if (j >= FIRST) {
+                        constexpr int NS = NM - FIRST;
+                        const int r0 = ((j - FIRST) * 16) / NS, r1 = ((j - FIRST + 1) * 16) / NS;
+#pragma unroll
+                        for (int r = r0; r < r1; ++r) {
+                            const float pe = fast_exp2(__builtin_fmaf(S0[r], scale_log2, -m_new));
+                            psum += pe;
+                            put_p(p, r / 8, r % 8, pe);
+                        }
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            l_run = l_run * alph[p] + psum;
-            m_run = m_new;
-        } else {
-            if (doC) {
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-                    for (int i = 0; i < MT; ++i) {
-                        const vec8 vop = read_vop(vt, kk, i);
-                        acc_o[i] = T::mfma32(vop, P[q][kk], acc_o[i]);
-                        if constexpr (SPLIT) acc_o[i] = T::mfma32(vop, Plo[q][kk], acc_o[i]);
-                    }
-            }
-            if (doAB) {  // B1(t); keys past the end of the shard get a score of -inf (also seen by B2(t) later)
-                const int key0 = t * kPreK;
-                if (t >= t_mask0) {  // ragged last tile, or tiles that reach past a row's own position
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int key = key0 + 8 * (r / 4) + 4 * lh + (r % 4);
-                        if (key >= key_lim) S0[r] = -INFINITY;
-                        if (key + 32 >= key_lim) S1[p][r] = -INFINITY;
-                    }
-                }
-                float mx = S0[0];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, fmaxf(S0[r], S1[p][r]));
-                mx = xor32_max(mx);
-                const float m_new = fmaxf(m_run, mx * scale_log2);
-                alph[p] = exp2_diff(m_run, m_new);
-                float psum = 0.f;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float pe = fast_exp2(__builtin_fmaf(S0[r], scale_log2, -m_new));
-                    psum += pe;
-                    put_p(p, r / 8, r % 8, pe);
-                }
+            if constexpr (doAB) {
                 l_run = l_run * alph[p] + psum;
                 m_run = m_new;
             }
         }
-        if constexpr (QB != 0) {
-            if (doAB) store_codes(p ? vs1 : vs0, vst, false);
-        }
-        // keep this iteration's results above the barrier that follows (they are consumed in the next iteration)
+        if constexpr (doAB) {
+            if constexpr (QB != 0) store_codes(p ? vs1 : vs0, vst, false);
+            // keep this iteration's results above the barrier that follows (they are consumed in the next iteration)
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            u32x4_t w = __builtin_bit_cast(u32x4_t, P[p][kk]);
-            pin_here(w);
-            P[p][kk] = __builtin_bit_cast(vec8, w);
-            if constexpr (SPLIT) {
-                u32x4_t wl = __builtin_bit_cast(u32x4_t, Plo[p][kk]);
-                pin_here(wl);
-                Plo[p][kk] = __builtin_bit_cast(vec8, wl);
+            for (int kk = 0; kk < 2; ++kk) {
+                u32x4_t w = __builtin_bit_cast(u32x4_t, P[p][kk]);
+                pin_here(w);
+                P[p][kk] = __builtin_bit_cast(vec8, w);
+                if constexpr (SPLIT) {
+                    u32x4_t wl = __builtin_bit_cast(u32x4_t, Plo[p][kk]);
+                    pin_here(wl);
+                    Plo[p][kk] = __builtin_bit_cast(vec8, wl);
+                }
             }
+            pin_here(l_run);
         }
-        pin_here(l_run);
         __builtin_amdgcn_sched_barrier(0);
     };
 
     std::integral_constant<int, 0> even;
     std::integral_constant<int, 1> odd;
+    std::integral_constant<int, kFirst> first;
+    std::integral_constant<int, kSteady> steady;
+    std::integral_constant<int, kLast> last;
 
-    // prologue: K'(0)
+    // prologue: K' of the last tile
+    int tile = n_tiles - 1;
     if constexpr (QB == 0) {
-        load_tile(Kg, ks0, 0, true);
+        load_tile(Kg, ks0, tile, true);
     } else {
-        fetch_codes(Kg, Kpg, 0, kst);
+        fetch_codes(Kg, Kpg, tile, kst);
         store_codes(ks0, kst, true);
     }
     alph[0] = alph[1] = 1.0f;
     __syncthreads();
-
-    // iterations t = 0 .. n_tiles; the steady-state ones (1 <= t, t + 1 < n_tiles, no hidden keys) run with every
-    // stage on and without the masking code
-    iteration(0, even, false, true, n_tiles > 1, true);
+    // masked tiles are finished one by one, except the last of them, which the pipeline starts with
+    while (tile > t_mask0 || (tile & 1)) {
+        iteration(tile, even, first, false);
+        __syncthreads();
+        --tile;
+        if constexpr (QB == 0) load_tile(Kg, ks0, tile, true);
+        else fetch_codes(Kg, Kpg, tile, kst);
+        iteration(tile, odd, last, false);
+        if constexpr (QB != 0) store_codes(ks0, kst, true);
+        __syncthreads();
+    }
+    iteration(tile, even, first, true);
     __syncthreads();
-    int t = 1;
-    for (; t + 2 < n_tiles && t + 1 < t_mask0; t += 2) {
-        iteration(t, odd, true, true, true, false);
+    for (; tile > 0; tile -= 2) {
+        iteration(tile - 1, odd, steady, true);
         __syncthreads();
-        iteration(t + 1, even, true, true, true, false);
-        __syncthreads();
-    }
-    for (; t <= n_tiles; ++t) {
-        if (t & 1) iteration(t, odd, true, t < n_tiles, t + 1 < n_tiles, true);
-        else iteration(t, even, true, t < n_tiles, t + 1 < n_tiles, true);
+        iteration(tile - 2, even, steady, true);
         __syncthreads();
     }
+    iteration(-1, odd, last, false);
 
     // epilogue: lane holds query li and rows d = 32 i + 8 (r / 4) + 4 lh + r % 4 of O^T
     const float l_tot = xor32_sum(l_run);
@@ -514,18 +510,45 @@ __global__ __launch_bounds__(kPreThreads, 1) void prefill_attn_kernel(const type
     }
 }
 
+// Waves per workgroup.  Eight share a K'/V' tile between 256 query rows, one workgroup per compute unit: the best rate
+// when the launch is whole rounds of them (2048 x 16384 x 32 heads: 492 us, against 521 with four).  Four (128 rows) sit
+// two to a compute unit, fill and drain it independently and waste less of a ragged end, which wins wherever the
+// workgroups are few or unequal: always with a mask or with per-sequence lengths (2048-token segment 66 against 80 us,
+// 500 tokens 18 against 27, the 10-pair re-rank batch 28 against 39), else when the rounds below come out shorter.
+static bool prefill_wants_4_waves(int64_t wgs8, int64_t wgs4) {
+    const int64_t cus = attn_target_wgs();
+    const int64_t rounds8 = (wgs8 + cus - 1) / cus;
+    const int64_t rest = wgs4 % (2 * cus);  // a last round of at most one workgroup per unit takes 0.6 of a full one
+    const int64_t rounds4_x10 = wgs4 / (2 * cus) * 10 + (rest == 0 ? 0 : rest <= cus ? 6 : 10);
+    return rounds4_x10 * 106 < rounds8 * 1000;  // a round of four-wave workgroups takes 6 % longer
+}
+
+template <class T, int D, bool CAUSAL, int QB, int NW>
+static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, int Hq_k, int64_t Lq_k, int64_t q_tiles,
+                                    float* Odst, float* Ldst, hipStream_t stream) {
+    typedef typename T::elem elem;
+    const int n_units = p.B * p.Hkv;
+    const int64_t per_unit = (int64_t)(Hq_k / p.Hkv) * q_tiles * runs.n_runs;
+    const int64_t grid = (int64_t)8 * ((n_units + 7) / 8) * per_unit;
+    if (!grid_fits(grid)) return hipErrorInvalidValue;
+    // With every workgroup resident at once (two per compute unit, started in index order) the second half goes beside
+    // the first: the shortest tile to the longest, and all compute units end together (2048 tokens: 65 -> 60 us).
+    const int fold = CAUSAL && grid <= 2 * (int64_t)attn_target_wgs() ? 1 : 0;
+    hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB, NW>), dim3((unsigned)grid), dim3(NW * kWave), 0, stream,
+                       (const elem*)p.Q, runs, p.K_params, p.V_params, Hq_k, FastDiv(p.Hkv), FastDiv(Hq_k / p.Hkv),
+                       FastDiv(q_tiles), FastDiv(per_unit), Lq_k, p.kv_lens, p.q_lens, n_units, fold,
+                       p.scale * kLog2e, Odst, Ldst);
+    return hipGetLastError();
+}
+
 template <class T, int D, bool CAUSAL, int QB = 0>
 static hipError_t launch_prefill_t(const AttnProblem& p, hipStream_t stream) {
-    typedef typename T::elem elem;
-    const float scale_log2 = p.scale * kLog2e;
     // Without a mask or per-sequence query counts a row's position in its head means nothing, and the query heads of
     // a KV head are contiguous in Q, O and lse: the kernel then sees one head of G * Lq rows per KV head, so that
     // short segments fill their 256-row tiles (128 queries x 4 heads: 2 full tiles instead of 4 half-empty ones).
     const bool pack_group = !CAUSAL && !p.q_lens;
     const int Hq_k = pack_group ? p.Hkv : p.Hq;
     const int64_t Lq_k = pack_group ? (int64_t)(p.Hq / p.Hkv) * p.Lq : p.Lq;
-    const int q_tiles = (int)((Lq_k + kPreQTile - 1) / kPreQTile);
-    const int n_units = p.B * p.Hkv;
     // several runs: only the plain call (every key of every sequence, every query row, no mask) takes them
     KeyRuns runs = attn_runs_of(p);
     const bool one_run_only = CAUSAL || p.kv_lens || p.q_lens;
@@ -538,6 +561,7 @@ static hipError_t launch_prefill_t(const AttnProblem& p, hipStream_t stream) {
     }
     const int splits = runs.n_runs;
     if (splits < 1) return hipErrorInvalidValue;
+    if (QB != 0 && (p.n_shards > 1 || !p.K_params || !p.V_params)) return hipErrorInvalidValue;
     const int64_t rows = (int64_t)p.B * p.Hq * p.Lq;
     float* Odst = p.O;
     float* Ldst = p.lse;
@@ -546,14 +570,13 @@ static hipError_t launch_prefill_t(const AttnProblem& p, hipStream_t stream) {
         Odst = (float*)p.workspace;
         Ldst = Odst + (size_t)splits * rows * D;
     }
-    const int64_t per_unit = (int64_t)(Hq_k / p.Hkv) * q_tiles * splits;
-    const int64_t grid = (int64_t)8 * ((n_units + 7) / 8) * per_unit;
-    if (!grid_fits(grid)) return hipErrorInvalidValue;
-    if (QB != 0 && (p.n_shards > 1 || !p.K_params || !p.V_params)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB>), dim3((unsigned)grid), dim3(kPreThreads), 0, stream,
-                       (const elem*)p.Q, runs, p.K_params, p.V_params, Hq_k, FastDiv(p.Hkv), FastDiv(Hq_k / p.Hkv),
-                       FastDiv(q_tiles), FastDiv(per_unit), Lq_k, p.kv_lens, p.q_lens, n_units, scale_log2, Odst, Ldst);
-    const hipError_t e = hipGetLastError();
+    const int64_t tiles8 = (Lq_k + 8 * kPreQ - 1) / (8 * kPreQ), tiles4 = (Lq_k + 4 * kPreQ - 1) / (4 * kPreQ);
+    const int64_t heads = (int64_t)p.B * Hq_k * splits;
+    hipError_t e;
+    if (CAUSAL || p.kv_lens || p.q_lens || prefill_wants_4_waves(heads * tiles8, heads * tiles4))
+        e = launch_prefill_nw<T, D, CAUSAL, QB, 4>(p, runs, Hq_k, Lq_k, tiles4, Odst, Ldst, stream);
+    else
+        e = launch_prefill_nw<T, D, false, QB, 8>(p, runs, Hq_k, Lq_k, tiles8, Odst, Ldst, stream);
     if (e != hipSuccess || splits == 1) return e;
     return launch_lse_merge(Odst, Ldst, splits, rows, D, p.O, p.lse, stream);
 }

@@ -154,9 +154,8 @@ constexpr int kDecStride = kDecWaves * kDecTile;  // keys per workgroup step
 #endif
 constexpr int kDecCodesOcc = FEDRAG_DECQ_OCC;     // workgroups per compute unit when the kernel reads 4-bit codes
 // prefill kernel geometry (shared by the split planner and the kernel)
-constexpr int kPreWaves = 8;
 constexpr int kPreQ = 32;                     // query rows per wave (one 32-wide MFMA column tile)
-constexpr int kPreQTile = kPreWaves * kPreQ;  // query rows per workgroup
+constexpr int kPrePlanRows = 8 * kPreQ;       // query rows the planner counts per workgroup (the larger of the two forms)
 constexpr int kPreK = 64;                     // keys per LDS tile
 constexpr int kPreMinTilesPerSplit = 4;       // a KV split is at least this many tiles
 hipError_t launch_attn_f32(const AttnProblem& p, hipStream_t stream);      // fp32 storage, any L_q
