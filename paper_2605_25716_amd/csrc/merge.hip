@@ -7,14 +7,25 @@
 
 namespace fedrag {
 
-// What bounds it: for a handful of rows (a decoding step has 32 of them over 16 key runs) the chain of dependent
-// loads, not bytes.  So the loads of a batch of partials are issued together, weights first, and the workgroups are
-// small so that few rows still spread over the chip; sums are formed in shard order whatever the batch.
-// 32 rows of 128 over 16 partials in a chain of calls: 12.6 -> 4.6 us (one partial after the other before).
-constexpr int kMergeLse = 16;  // log-sum-exps in flight
-constexpr int kMergeO = 8;     // partial outputs in flight (4 registers each)
+// What bounds it: for a handful of rows (a decoding step has 32 of them over 16 key runs) the chain of dependent loads,
+// for many rows over many runs the instructions around them.  So the lanes of a row share the weights out - each loads
+// one log-sum-exp and evaluates one exponential, and a weight reaches the others by a lane shuffle - the first batch of
+// partials is in flight before the weights are known, and the workgroups are one wave while rows are few.  Sums are
+// formed in shard order whatever the batch.
+// 32 rows of 128 over 16 partials in a chain of calls: 4.6 us (12.6 with one partial after the other); 3744 rows over 15:
+// MERGE_AFTER us (11.5 with every thread evaluating every weight).
 
-template <int D>
+// max over the TPR = 16 or 32 consecutive lanes that hold a row
+template <int TPR>
+__device__ __forceinline__ float row_max(float x) {
+    x = group_max<16>(x);
+    return TPR == 32 ? xor16_max(x) : x;
+}
+
+// NB: partial outputs in flight (4 registers each).  16 for few rows over many partials, where a second batch is another
+// trip to memory (a decoded token over 32 layers: 941 us against 949 with 8); 8 otherwise, where more waves per SIMD
+// are worth more (the 117-token segment 2243 against 2276 with 16).
+template <int D, int NB>
 __global__ __launch_bounds__(256) void lse_merge_kernel(const float* __restrict__ O_parts,
                                                         const float* __restrict__ lses, int S, int64_t rows,
                                                         float* __restrict__ O, float* __restrict__ lse,
@@ -23,54 +34,54 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const float* __restrict_
     constexpr int TPR = D / 4;  // threads per row
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t r = gid / TPR;
-    const int c4 = (int)(gid % TPR) * 4;
+    const int c = (int)(gid % TPR);
+    const int c4 = c * 4;
     if (r >= rows) return;
     // padded batch with per-sequence query counts: padding rows hold no partials and are not written
     if (q_lens && (r % Lq) >= q_lens[r / rows_per_seq]) return;
     const float* lp = lses + r;
     const float* op = O_parts + r * D + c4;
     // a batch reads past the last partial by re-reading it, and leaves those values out
-    auto load_o = [&](int i0, f32x4_t (&o)[kMergeO]) {
+    auto load_o = [&](int i0, f32x4_t (&o)[NB]) {
 #pragma unroll
-        for (int u = 0; u < kMergeO; ++u) {
+        for (int u = 0; u < NB; ++u) {
             const int i = i0 + u < S ? i0 + u : S - 1;
             o[u] = *(const f32x4_t*)(op + (int64_t)i * rows * D);
         }
     };
-    f32x4_t o[kMergeO];
+    auto load_l = [&](int i0) { return i0 + c < S ? lp[(int64_t)(i0 + c) * rows] : -INFINITY; };  // this lane's partial
+    f32x4_t o[NB];
     load_o(0, o);  // in flight together with the log-sum-exps
-    float M = -INFINITY;
-    for (int i0 = 0; i0 < S; i0 += kMergeLse) {
-        float l[kMergeLse];
-#pragma unroll
-        for (int u = 0; u < kMergeLse; ++u) l[u] = lp[(int64_t)(i0 + u < S ? i0 + u : S - 1) * rows];
-#pragma unroll
-        for (int u = 0; u < kMergeLse; ++u) M = fmaxf(M, l[u]);
-    }
+    float l = load_l(0);
+    float M = l;
+    for (int i0 = TPR; i0 < S; i0 += TPR) M = fmaxf(M, load_l(i0));
+    M = row_max<TPR>(M);
     f32x4_t acc = zero_vec<f32x4_t>();
     float den = 0.f;
     if (M != -INFINITY) {
-        for (int i0 = 0; i0 < S; i0 += kMergeO) {
-            if (i0) load_o(i0, o);
-            float l[kMergeO];
+        for (int i0 = 0; i0 < S; i0 += TPR) {
+            if (i0) l = load_l(i0);
+            const float mine = l == -INFINITY ? -1.0f : expf(l - M);  // below 0: weight zero, its O takes no part
+#pragma unroll 1
+            for (int j0 = 0; j0 < TPR && i0 + j0 < S; j0 += NB) {
+                if (i0 + j0) load_o(i0 + j0, o);
 #pragma unroll
-            for (int u = 0; u < kMergeO; ++u) l[u] = lp[(int64_t)(i0 + u < S ? i0 + u : S - 1) * rows];
-#pragma unroll
-            for (int u = 0; u < kMergeO; ++u) {
-                if (i0 + u >= S || l[u] == -INFINITY) continue;  // weight zero: its O takes no part
-                const float a = expf(l[u] - M);
-                den += a;
-                acc[0] = __builtin_fmaf(a, o[u][0], acc[0]);
-                acc[1] = __builtin_fmaf(a, o[u][1], acc[1]);
-                acc[2] = __builtin_fmaf(a, o[u][2], acc[2]);
-                acc[3] = __builtin_fmaf(a, o[u][3], acc[3]);
+                for (int u = 0; u < NB; ++u) {
+                    const float a = __shfl(mine, j0 + u, TPR);
+                    if (a == -1.0f) continue;
+                    den += a;
+                    acc[0] = __builtin_fmaf(a, o[u][0], acc[0]);
+                    acc[1] = __builtin_fmaf(a, o[u][1], acc[1]);
+                    acc[2] = __builtin_fmaf(a, o[u][2], acc[2]);
+                    acc[3] = __builtin_fmaf(a, o[u][3], acc[3]);
+                }
             }
         }
         const float inv = 1.0f / den;
         acc[0] *= inv; acc[1] *= inv; acc[2] *= inv; acc[3] *= inv;
     }
     *(f32x4_t*)(O + r * D + c4) = acc;
-    if (c4 == 0) lse[r] = (M == -INFINITY) ? -INFINITY : M + logf(den);
+    if (c == 0) lse[r] = (M == -INFINITY) ? -INFINITY : M + logf(den);
 }
 
 template <int D>
@@ -93,12 +104,10 @@ hipError_t launch_lse_merge(const float* O_parts, const float* lses, int S, int6
     const int wg = threads <= 256 * 256 ? 64 : 256;  // one wave per workgroup until every compute unit has four
     if (!grid_fits((threads + wg - 1) / wg)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((threads + wg - 1) / wg));
-    if (D == 128)
-        hipLaunchKernelGGL(lse_merge_kernel<128>, grid, dim3(wg), 0, stream, O_parts, lses, S, rows, O, lse,
-                           q_lens, Lq, rows_per_seq);
-    else
-        hipLaunchKernelGGL(lse_merge_kernel<64>, grid, dim3(wg), 0, stream, O_parts, lses, S, rows, O, lse,
-                           q_lens, Lq, rows_per_seq);
+    const bool deep = S > 8 && threads <= 256 * 256;
+    const auto kernel = D == 128 ? (deep ? lse_merge_kernel<128, 16> : lse_merge_kernel<128, 8>)
+                                 : (deep ? lse_merge_kernel<64, 16> : lse_merge_kernel<64, 8>);
+    hipLaunchKernelGGL(kernel, grid, dim3(wg), 0, stream, O_parts, lses, S, rows, O, lse, q_lens, Lq, rows_per_seq);
     return hipGetLastError();
 }
 
@@ -116,22 +125,25 @@ hipError_t launch_fill_empty(float* O, float* lse, int64_t rows, int D, hipStrea
 
 // out[bh, perm[i]] = in[bh, i]: the log-sum-exps of permuted query rows put back in the rows' own order (the
 // token-permutation part of Dec, Section 4.2, for the per-row scalar that travels with the output).
-__global__ void scatter_rows_f32_kernel(const float* __restrict__ in, const int32_t* __restrict__ perm, int64_t L,
-                                        int64_t total, float* __restrict__ out) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total) return;
-    const int64_t bh = e / L, i = e % L;
+// One thread per value, a row of workgroups per (sequence, head) row: no division.
+__global__ __launch_bounds__(256) void scatter_rows_f32_kernel(const float* __restrict__ in,
+                                                               const int32_t* __restrict__ perm, int64_t L,
+                                                               FastDiv by_chunks, float* __restrict__ out) {
+    const int64_t bh = by_chunks.div(blockIdx.x);
+    const int64_t i = (int64_t)by_chunks.mod(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= L) return;
     const int64_t dst = perm ? (int64_t)perm[i] : i;
-    out[bh * L + dst] = in[e];
+    out[bh * L + dst] = in[bh * L + i];
 }
 
 hipError_t launch_scatter_rows_f32(const float* in, const int32_t* perm, int64_t n_bh, int64_t L, float* out,
                                    hipStream_t stream) {
-    const int64_t total = n_bh * L;
-    if (total == 0) return hipSuccess;
-    if (!grid_fits((total + 255) / 256)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(scatter_rows_f32_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, in, perm,
-                       L, total, out);
+    if (n_bh * L == 0) return hipSuccess;
+    const int64_t wg = L <= 64 ? 64 : 256;
+    const int64_t chunks = (L + wg - 1) / wg;
+    if (!grid_fits(n_bh * chunks)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(scatter_rows_f32_kernel, dim3((unsigned)(n_bh * chunks)), dim3((unsigned)wg), 0, stream, in,
+                       perm, L, FastDiv(chunks), out);
     return hipGetLastError();
 }
 
