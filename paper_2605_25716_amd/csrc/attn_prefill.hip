@@ -30,16 +30,6 @@ namespace fedrag {
 #endif
 constexpr int kPrePD = FEDRAG_PRE_PD;         // MFMA operands are read from LDS this many MFMAs ahead
 
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-
-// Transposing LDS read: within each group of 16 lanes, lane j receives element (j % 4) of the 8 bytes addressed
-// by lane 4 e + j / 4, for e = 0..3.  With lane s of the group pointing at row (s / 4), columns 4 (s % 4)..+4 of
-// a row-major 4 x 16 block, lane j gets column j of the block, rows 0..3.
-__device__ __forceinline__ u32x2_t lds_read_tr16(const char* p) {
-    const s16x4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)p);
-    return __builtin_bit_cast(u32x2_t, v);
-}
-
 // CAUSAL: the queries are the last Lq of the L tokens whose K'/V' are given, and query i sees keys 0 .. i + (L - Lq)
 // (Section 5.3: the Inquirer's own part of a decoder layer's attention).  That call works on plaintext V, whose
 // outlier channels are not spread by a scrambling matrix (|v| of several tens), so a probability rounded once to the

@@ -124,6 +124,15 @@ __device__ __forceinline__ void pin_here(V& v) {
     asm volatile("" : "+v"(v));
 }
 
+// Transposing LDS read: within each group of 16 lanes, lane j receives element (j % 4) of the 8 bytes addressed
+// by lane 4 e + j / 4, for e = 0..3.  With lane s of the group pointing at row (s / 4), columns 4 (s % 4)..+4 of
+// a row-major 4 x 16 block, lane j gets column j of the block, rows 0..3.
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x2_t lds_read_tr16(const char* p) {
+    const s16x4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)p);
+    return __builtin_bit_cast(u32x2_t, v);
+}
+
 // exp2(a - b) with the convention that a == -inf gives 0 even when b == -inf.
 __device__ __forceinline__ float exp2_diff(float a, float b) {
     return (a == -INFINITY) ? 0.0f : fast_exp2(a - b);

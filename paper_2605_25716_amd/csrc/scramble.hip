@@ -86,8 +86,8 @@ __global__ __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_kernel
     constexpr int kTileElems = kScrWaves * kScrRows * LDP;
     constexpr int kLdsElems = kScrPhiLds ? kPhiElems + kTileElems : (kPhiElems > kTileElems ? kPhiElems : kTileElems);
 
-    // Phi^T staging and the per-wave row tiles share one buffer when the operands are copied into registers (Phi^T
-    // is then only needed until every wave has done so); with kScrPhiLds Phi^T stays and the row tiles follow it.
+    // The staged matrix and the per-wave row tiles share one buffer when the operands are copied into registers (it is
+    // then only needed until every wave has done so); with kScrPhiLds Phi^T stays and the row tiles follow it.
     __shared__ __attribute__((aligned(16))) elem lds[kLdsElems];
 
     const ScrambleJob job = blockIdx.y == 0 ? job0 : job1;
@@ -98,8 +98,24 @@ __global__ __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_kernel
     const int member = (blockIdx.x / b_groups) % members;
     const int bg = blockIdx.x % b_groups;  // this workgroup takes sequences bg, bg + b_groups, ...
 
-    // ---- stage Phi^T[n][k] = Phi[k][n] in LDS (once per workgroup) ----
-    __shared__ int32_t p_in_inv[ST ? D : 1];
+    // ---- Phi^T operands (once per workgroup): phi operand (mt, ks) of a lane is Phi^T[16 mt + lane%16][32 ks + 8 (lane/16)
+    // .. +8].  A structured key is multiplied out as Phi^T; a dense Phi goes to LDS row by row as it is stored and the
+    // transposing LDS read hands out the operands.  (Transposed on the way in, two bytes at a time, this took longer than a
+    // short slab's rows: a 117-token segment of 32 heads 12.2 -> 7.9 us, Enc of a 4096-token shard 13.2 -> 10.6 us.)
+    const int lr = lane % 16;
+    const int lq = lane / 16;
+    // codec shape: Phi^T stays in front, a dense Phi is staged in the row tiles' place behind it
+    elem* stage = lds + (kScrPhiLds && !ST ? kPhiElems : 0);
+    auto phi_operand = [&](int mt, int ks) -> vec8 {
+        if constexpr (ST) return *(const vec8*)(&lds[(mt * 16 + lr) * LDP + ks * 32 + lq * 8]);
+        // two 4 x 16 blocks of Phi
+        const char* p = (const char*)&stage[(ks * 32 + lq * 8 + lr / 4) * LDP + mt * 16 + (lr % 4) * 4];
+        const u32x2_t lo = lds_read_tr16(p), hi = lds_read_tr16(p + 4 * LDP * (int)sizeof(elem));
+        u32x4_t w;
+        w[0] = lo[0]; w[1] = lo[1]; w[2] = hi[0]; w[3] = hi[1];
+        return __builtin_bit_cast(vec8, w);
+    };
+    __shared__ __attribute__((aligned(16))) int32_t p_in_inv[ST ? D : 4];
     if (ST) {
         // structured form: the matrix is S1 P1 Hs P2, generated here from the key (entries +-s_in[k], which the
         // storage type holds exactly by the caller's contract); indices are masked into range
@@ -108,34 +124,46 @@ __global__ __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_kernel
         __syncthreads();
         const float* a = job.s_in + (int64_t)(h / G) * D;
         const int32_t* g2 = job.p_out + (int64_t)(h / G) * D;
-        for (int c = tid; c < D * D; c += kScrThreads) {
-            const int n = c / D;
-            const int k = c % D;
-            lds[n * LDP + k] = T::from_float(structured_entry(a[k], p_in_inv[k], g2[n] & (D - 1)));
+        // a thread keeps its 8 rows k0 .. k0+7 of Phi and walks the columns
+        static_assert(kScrThreads % CH == 0, "k0 is the same in every pass");
+        const int k0 = (tid % CH) * 8;
+        float ak[8];
+        int inv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            ak[e] = a[k0 + e];
+            inv[e] = p_in_inv[k0 + e];
+        }
+#pragma unroll
+        for (int n = tid / CH; n < D; n += kScrThreads / CH) {
+            const int m = g2[n] & (D - 1);
+            vec8 v;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = T::from_float(structured_entry(ak[e], inv[e], m));
+            *(vec8*)&lds[n * LDP + k0] = v;
         }
     } else {
         const elem* P = (const elem*)job.Phi + (int64_t)(h / G) * D * D;
-        for (int c = tid; c < D * CH; c += kScrThreads) {
-            const int k = c / CH;
-            const int n0 = (c % CH) * 8;
-            const vec8 v = *(const vec8*)(P + k * D + n0);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) lds[(n0 + e) * LDP + k] = v[e];
-        }
+        for (int c = tid; c < D * CH; c += kScrThreads)
+            *(vec8*)&stage[c / CH * LDP + (c % CH) * 8] = *(const vec8*)(P + (int64_t)c * 8);
     }
     __syncthreads();
-
-    // Phi^T operands for the whole kernel: phi[mt][ks] = Phi^T[16 mt + lane%16][32 ks + 8 (lane/16) .. +8]
-    const int lr = lane % 16;
-    const int lq = lane / 16;
     vec8 phi[kScrPhiLds ? 1 : MT][kScrPhiLds ? 1 : KS];
-    if constexpr (!kScrPhiLds) {
+    if constexpr (!kScrPhiLds) {  // in registers for the whole kernel
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                phi[mt][ks] = *(const vec8*)(&lds[(mt * 16 + lr) * LDP + ks * 32 + lq * 8]);
-        __syncthreads();  // Phi^T is dead from here on; the buffer becomes the row tiles
+            for (int ks = 0; ks < KS; ++ks) phi[mt][ks] = phi_operand(mt, ks);
+        __syncthreads();  // the matrix in LDS is dead from here on; the buffer becomes the row tiles
+    } else if constexpr (!ST) {  // to LDS, so that an operand is one 16-byte read from here on
+        static_assert(MT * KS % kScrWaves == 0, "the operands divide evenly over the waves");
+#pragma unroll
+        for (int u = 0; u < MT * KS / kScrWaves; ++u) {
+            const int op = wave + u * kScrWaves;
+            *(vec8*)&lds[(op / KS * 16 + lr) * LDP + op % KS * 32 + lq * 8] = phi_operand(op / KS, op % KS);
+        }
+        __syncthreads();
     }
     const elem* phi_lds = &lds[lr * LDP + lq * 8];  // kScrPhiLds: operand (mt, ks) at + mt * 16 * LDP + ks * 32
     // structured form: S2 and the Hadamard normalisation, for this lane's output columns 16 mt + 4 lq + r
