@@ -37,7 +37,7 @@ constexpr int kPrePD = FEDRAG_PRE_PD;         // MFMA operands are read from LDS
 // CAUSAL instantiation therefore feeds the second product P = P_hi + P_lo, two storage-type terms (about 16
 // significant bits), at the price of twice the MFMAs of that product.
 template <class T, int D, bool CAUSAL, int QB, int NW>
-__global__ __launch_bounds__(NW * kWave, 2) void prefill_attn_kernel(const typename T::elem* __restrict__ Q,
+__global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefill_attn_kernel(const typename T::elem* __restrict__ Q,
                                                                       const KeyRuns runs,
                                                                       const float* __restrict__ Kprm,
                                                                       const float* __restrict__ Vprm, int Hq,
@@ -146,11 +146,6 @@ __global__ __launch_bounds__(NW * kWave, 2) void prefill_attn_kernel(const typen
         }
         return;
     }
-    const int64_t q_ld = q_row < Lq ? q_row : Lq - 1;
-    vec8 qop[KS];  // Q'^T operands: column li, contraction slice 16 ks + 8 lh
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qop[ks] = *(const vec8*)(Qh + q_ld * D + ks * 16 + lh * 8);
-
     f32x16_t acc_o[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i) acc_o[i] = zero_vec<f32x16_t>();
@@ -257,6 +252,15 @@ __global__ __launch_bounds__(NW * kWave, 2) void prefill_attn_kernel(const typen
     const int64_t wg_keys = CAUSAL ? (q_last + off + 1 < L ? q_last + off + 1 : L) : L;
     const int n_tiles = (int)((wg_keys + kPreK - 1) / kPreK);
     const int t_mask0 = (int)((CAUSAL ? (q_first + off + 1 < L ? q_first + off + 1 : L) : L) / kPreK);
+    // prologue: K' of the last tile is fetched first, Q' behind it
+    int tile = n_tiles - 1;
+    if constexpr (QB == 0) load_tile(Kg, ks0, tile, true);
+    else fetch_codes(Kg, Kpg, tile, kst);
+    const int64_t q_ld = q_row < Lq ? q_row : Lq - 1;
+    vec8 qop[KS];  // Q'^T operands: column li, contraction slice 16 ks + 8 lh
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qop[ks] = *(const vec8*)(Qh + q_ld * D + ks * 16 + lh * 8);
+
     const int key_lim = (int)(CAUSAL ? (q_row + off + 1 < L ? q_row + off + 1 : L) : L);  // this lane's row sees keys < key_lim
     f32x16_t S0;      // S^T of the current tile, keys 0..31
     f32x16_t S1[2];   // S1[t & 1]: S^T of tile t, keys 32..63 (kept one iteration longer, see below)
@@ -452,14 +456,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void prefill_attn_kernel(const typen
     std::integral_constant<int, kSteady> steady;
     std::integral_constant<int, kLast> last;
 
-    // prologue: K' of the last tile
-    int tile = n_tiles - 1;
-    if constexpr (QB == 0) {
-        load_tile(Kg, ks0, tile, true);
-    } else {
-        fetch_codes(Kg, Kpg, tile, kst);
-        store_codes(ks0, kst, true);
-    }
+    if constexpr (QB != 0) store_codes(ks0, kst, true);
     alph[0] = alph[1] = 1.0f;
     __syncthreads();
     // masked tiles are finished one by one, except the last of them, which the pipeline starts with
@@ -483,21 +480,43 @@ __global__ __launch_bounds__(NW * kWave, 2) void prefill_attn_kernel(const typen
     }
     iteration(-1, odd, last, false);
 
-    // epilogue: lane holds query li and rows d = 32 i + 8 (r / 4) + 4 lh + r % 4 of O^T
+    // epilogue: lane holds query li and rows d = 32 i + 8 (r / 4) + 4 lh + r % 4 of O^T.  The rows go out through LDS
+    // (the tiles are dead; every wave has its share of them), so that a store covers whole 128-byte lines: straight from
+    // the accumulators it would cover 32 bytes of each of 32 rows, 4 us for a 256-row workgroup.  The 16-byte chunk
+    // index is XORed with the row against bank conflicts.
     const float l_tot = xor32_sum(l_run);
     const float inv = (l_tot > 0.f) ? 1.0f / l_tot : 0.f;
-    if (q_row < Lq_rows) {
+    __syncthreads();
+    constexpr int WB = 4 * SLOT / NW;          // bytes per wave
+    constexpr int PC = WB / (kPreQ * 4);       // columns per pass
+    constexpr int PCH = PC / 4;                // 16-byte chunks per row and pass
+    static_assert(PC % 32 == 0 && D % PC == 0, "a pass is whole 32-column tiles");
+    const int slot_w = wave * 4 / NW;
+    char* mine = (slot_w == 0 ? ks0 : slot_w == 1 ? ks1 : slot_w == 2 ? vs0 : vs1) + (wave % (NW / 4)) * WB;
+    const int64_t row0 = (int64_t)qt * kQTile + wave * kPreQ;
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+    for (int c0 = 0; c0 < D; c0 += PC) {
+#pragma unroll
+        for (int i = c0 / 32; i < (c0 + PC) / 32; ++i)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
                 f32x4_t o;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) o[r] = acc_o[i][4 * r4 + r] * inv;
-                *(f32x4_t*)(Oh + q_row * D + 32 * i + 8 * r4 + 4 * lh) = o;
+                const int chunk = 8 * (i - c0 / 32) + 2 * r4 + lh;
+                *(f32x4_t*)(mine + li * (PC * 4) + ((chunk ^ (li % PCH)) << 4)) = o;
             }
-        if (lh == 0) Lh[q_row] = (l_tot > 0.f) ? (m_run + fast_log2(l_tot)) * kLn2 : -INFINITY;
+        wave_lds_fence();
+#pragma unroll
+        for (int u = 0; u < kPreQ * PCH / kWave; ++u) {
+            const int e = u * kWave + lane;
+            const int row = e / PCH, chunk = e % PCH;
+            const f32x4_t o = *(const f32x4_t*)(mine + row * (PC * 4) + ((chunk ^ (row % PCH)) << 4));
+            if (row0 + row < Lq_rows) *(f32x4_t*)(Oh + (row0 + row) * D + c0 + chunk * 4) = o;
+        }
+        wave_lds_fence();
     }
+    if (lh == 0 && q_row < Lq_rows) Lh[q_row] = (l_tot > 0.f) ? (m_run + fast_log2(l_tot)) * kLn2 : -INFINITY;
 }
 
 // Waves per workgroup.  Eight share a K'/V' tile between 256 query rows, one workgroup per compute unit: the best rate
