@@ -14,6 +14,8 @@
 // ~16 significant bits; the matrix pipe is idle most of the time anyway.
 // Splits are normalised partials (O, lse) in the caller's workspace and are folded by the Section 4.1
 // aggregation kernel (merge.hip).
+#include <type_traits>
+
 #include "fedrag_device.h"
 #include "fedrag_host.h"
 
@@ -58,35 +60,73 @@ struct DecTile<T, D, 4> {
 
 // 8 codes -> 8 storage-type values, exactly as dequantize_rows_kernel produces them: fma(code, scale, lo) in fp32,
 // narrowed once.  (The fp32 value is pinned so that the two roundings are not folded into one.)
-template <class T>
-__device__ __forceinline__ typename T::vec8 dequant_codes(const uint32_t (&q)[8], u32x2_t prm) {
+//
+// The kernel is bound by these instructions, so a 4-bit code is not converted to a float first: its bits, masked in place,
+// are read as an fp16 subnormal - code * 2^-24, or code * 2^-20 four bits further up - by an fma that takes an fp16 operand
+// from either half of a register, and the row's scale carries the power of two.  Both scalings are exact, so the product
+// the fma rounds is the same.  A scale from 2^100 up (rows whose range is beyond any activation) would overflow and takes
+// the plain conversions: a wave-uniform branch before each operand's part of a step, so that the check of the V' scales does
+// not wait for them before the first product.
+struct RowScale {
+    float scale, lo, scale24, scale20;
+};
+__device__ __forceinline__ RowScale row_scale(u32x2_t prm) {
     const uint32_t scale_bits = prm[0], lo_bits = prm[1];  // (bit-casting a vector element in place picks element 0)
     const float scale = __builtin_bit_cast(float, scale_bits), lo = __builtin_bit_cast(float, lo_bits);
+    return RowScale{scale, lo, scale * 16777216.0f, scale * 1048576.0f};
+}
+constexpr float kPlainScale = 1.2676506e30f;  // 2^100
+template <int N>
+__device__ __forceinline__ bool any_plain_scale(const u32x2_t (&prm)[N]) {
+    float top = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) top = fmaxf(top, fabsf(row_scale(prm[i]).scale));
+    return __builtin_amdgcn_ballot_w64(!(top < kPlainScale)) != 0;
+}
+typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float fma_half(uint32_t w, int half, float scale, float lo) {
+    const f16x2_t h = __builtin_bit_cast(f16x2_t, w);
+    float x = __builtin_fmaf((float)h[half], scale, lo);
+    pin_here(x);
+    return x;
+}
+template <class T>
+__device__ __forceinline__ typename T::vec8 dequant8(u32x2_t w, const RowScale& r, std::true_type) {  // 8-bit codes
+    // a byte converts with one instruction wherever it sits, which leaves the masks nothing to save (56 us per shard of
+    // the decode workload against 64 by way of the subnormals)
     typename T::vec8 out;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        float x = __builtin_fmaf((float)q[e], scale, lo);
+        float x = __builtin_fmaf((float)((w[e / 4] >> (8 * (e % 4))) & 255u), r.scale, r.lo);
         pin_here(x);
         out[e] = T::from_float(x);
     }
     return out;
 }
-template <class T>
-__device__ __forceinline__ typename T::vec8 dequant8(u32x2_t w, u32x2_t prm) {  // 8-bit codes
-    uint32_t q[8];
+template <class T, bool PLAIN>
+__device__ __forceinline__ typename T::vec8 dequant8(uint32_t w, const RowScale& r, std::bool_constant<PLAIN>) {  // 4-bit
+    typename T::vec8 out;
+    if constexpr (PLAIN) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) q[e] = (w[e / 4] >> (8 * (e % 4))) & 255u;
-    return dequant_codes<T>(q, prm);
-}
-template <class T>
-__device__ __forceinline__ typename T::vec8 dequant8(uint32_t w, u32x2_t prm) {  // 4-bit codes
-    // even and odd nibbles spread to bytes first (3 instructions for 8 codes), so that each code then converts with
-    // one byte-to-float instruction
-    const uint32_t ev = w & 0x0f0f0f0fu, od = (w >> 4) & 0x0f0f0f0fu;
-    uint32_t q[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) q[e] = ((e % 2 ? od : ev) >> (8 * (e / 2))) & 255u;
-    return dequant_codes<T>(q, prm);
+        for (int e = 0; e < 8; ++e) {
+            float x = __builtin_fmaf((float)((w >> (4 * e)) & 15u), r.scale, r.lo);
+            pin_here(x);
+            out[e] = T::from_float(x);
+        }
+        return out;
+    }
+    const uint32_t up = w >> 8;
+    const uint32_t a = w & 0x000f000fu, b = w & 0x00f000f0u;    // codes 0, 4 and (times 16) 1, 5
+    const uint32_t c = up & 0x000f000fu, d = up & 0x00f000f0u;  // codes 2, 6 and (times 16) 3, 7
+    out[0] = T::from_float(fma_half(a, 0, r.scale24, r.lo));
+    out[1] = T::from_float(fma_half(b, 0, r.scale20, r.lo));
+    out[2] = T::from_float(fma_half(c, 0, r.scale24, r.lo));
+    out[3] = T::from_float(fma_half(d, 0, r.scale20, r.lo));
+    out[4] = T::from_float(fma_half(a, 1, r.scale24, r.lo));
+    out[5] = T::from_float(fma_half(b, 1, r.scale20, r.lo));
+    out[6] = T::from_float(fma_half(c, 1, r.scale24, r.lo));
+    out[7] = T::from_float(fma_half(d, 1, r.scale20, r.lo));
+    return out;
 }
 
 // On codes the kernel is bound by its own instruction stream (rebuilding every element costs more than fetching
@@ -289,26 +329,39 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
     // softmax, the second product and the other tile set's step.
     auto step = [&](Tile& t, int64_t key0, bool masked, bool reload, int next_tile) {
         f32x4_t s[2];
+        auto score = [&](auto plain) {
+            RowScale krow[2];
+            if constexpr (QB != 0) {
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            s[mt] = zero_vec<f32x4_t>();
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                vec8 kop;
-                if constexpr (QB == 0) kop = t.k[mt][ks];
-                else if constexpr (QB == 8) {
-                    const u32x4_t w = t.kc[mt][ks / 2];
-                    u32x2_t c;  // (vector elements are copied out one by one before use)
-                    const uint32_t c0 = w[2 * (ks % 2)], c1 = w[2 * (ks % 2) + 1];
-                    c[0] = c0;
-                    c[1] = c1;
-                    kop = dequant8<T>(c, t.kp[mt]);
-                } else {
-                    const uint32_t c = t.kc[mt][ks];
-                    kop = dequant8<T>(c, t.kp[mt]);
-                }
-                s[mt] = T::mfma16(kop, qop[ks], s[mt]);
+                for (int mt = 0; mt < 2; ++mt) krow[mt] = row_scale(t.kp[mt]);
             }
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) {
+                s[mt] = zero_vec<f32x4_t>();
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    vec8 kop;
+                    if constexpr (QB == 0) kop = t.k[mt][ks];
+                    else if constexpr (QB == 8) {
+                        const u32x4_t w = t.kc[mt][ks / 2];
+                        u32x2_t c;  // (vector elements are copied out one by one before use)
+                        const uint32_t c0 = w[2 * (ks % 2)], c1 = w[2 * (ks % 2) + 1];
+                        c[0] = c0;
+                        c[1] = c1;
+                        kop = dequant8<T>(c, krow[mt], plain);
+                    } else {
+                        const uint32_t c = t.kc[mt][ks];
+                        kop = dequant8<T>(c, krow[mt], plain);
+                    }
+                    s[mt] = T::mfma16(kop, qop[ks], s[mt]);
+                }
+            }
+        };
+        if constexpr (QB == 4) {
+            if (any_plain_scale(t.kp)) score(std::true_type{});
+            else score(std::false_type{});
+        } else {
+            score(std::true_type{});
         }
         if (reload) load_k(next_tile, t);
         float p[8];
@@ -343,11 +396,19 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
             transpose_keys_b16<DCH>(t.v, vt);
         } else {
             uint32_t v16[8][DCH / 2];  // the eight keys' rows in the storage type, as the unquantised path loads them
+            auto rebuild = [&](auto plain) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const u32x4_t w = __builtin_bit_cast(u32x4_t, dequant8<T>(t.vc[e], t.vp[e]));
+                for (int e = 0; e < 8; ++e) {
+                    const u32x4_t w = __builtin_bit_cast(u32x4_t, dequant8<T>(t.vc[e], row_scale(t.vp[e]), plain));
 #pragma unroll
-                for (int c = 0; c < DCH / 2; ++c) v16[e][c] = w[c];
+                    for (int c = 0; c < DCH / 2; ++c) v16[e][c] = w[c];
+                }
+            };
+            if constexpr (QB == 4) {
+                if (any_plain_scale(t.vp)) rebuild(std::true_type{});
+                else rebuild(std::false_type{});
+            } else {
+                rebuild(std::true_type{});
             }
             transpose_keys_b16<DCH>(v16, vt);
         }
