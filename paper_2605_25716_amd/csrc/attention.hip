@@ -38,15 +38,18 @@ int attn_target_wgs() {
     }
     return n;
 }
-// Shortest run of the decode kernel, in 128-key steps of a workgroup: 256 keys, two tiles per wave, both in flight at
-// once (a decoded token's layer over two Context Owners of 4096 keys: 28.2 us, 29.3 with 512, 35 with 1024).  A context of
-// at most 512 keys is one run all the same, which needs no fold (300 keys: 25.7 us a layer against 27.8 in two runs).
-constexpr int kDecMinSteps = 2;
-constexpr int kDecOneRunSteps = 4;
+// Shortest run of the decode kernel, in 128-key steps of a workgroup.  A run costs the launch a partial to fold, so
+// 512 keys (a decoded token's layer over two Context Owners of 4096 keys: 30.4 us, against 31.0 with 256 and 35.2 with
+// 1024), and a context of no more than that is one run and no fold (300 keys: 25.7 us a layer against 27.8 in two runs).
+// In between a context would be two to four runs, which leaves the chip idle: 400 + 700 keys take 23.1 us a layer in
+// 256-key runs against 24.9.
+constexpr int kDecMinSteps = 4;
+constexpr int kDecMinStepsShort = 2;
+constexpr int64_t kDecShortContext = 2048;  // keys of all shards of a unit up to which the shorter run is taken
 static bool use_decode_kernel(int Hq, int Hkv, int64_t Lq) { return (int64_t)(Hq / Hkv) * Lq <= 16; }
 
 // Decode kernel: about one workgroup per compute unit over the whole launch; a run is a whole number of 128-key
-// workgroup steps, at least kDecMinSteps of them, and stays below 2^31 bytes (32-bit buffer offsets).
+// workgroup steps, at least kDecMinSteps (kDecMinStepsShort) of them, and stays below 2^31 bytes (32-bit buffer offsets).
 // Prefill kernel: one workgroup per (sequence, query head, 256 query rows) walks a run, about 2 us per 64-key tile.
 // When those workgroups cover less than half of the compute units, the keys are cut into runs of at least
 // kPreMinTilesPerSplit tiles (so that a workgroup's fixed cost stays small beside its tiles) for one round of
@@ -75,7 +78,8 @@ KeyRuns attn_plan_runs(int B, int Hq, int Hkv, int dtype, int64_t Lq, int n, con
             quantum = kDecStride;
             per = (total + want - 1) / want;
             per = ((per + quantum - 1) / quantum) * quantum;
-            const int64_t least = (total > kDecOneRunSteps * quantum ? kDecMinSteps : kDecOneRunSteps) * quantum;
+            const int64_t least = (total <= kDecShortContext && total > kDecMinSteps * quantum ? kDecMinStepsShort
+                                                                                          : kDecMinSteps) * quantum;
             if (per < least) per = least;
             if (per > (int64_t)1 << 22) per = (int64_t)1 << 22;
         } else {
