@@ -7,6 +7,7 @@ library has not been built, loading raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional
 
@@ -131,22 +132,32 @@ def _check(status: int, where: str) -> None:
 
 
 def _ptr(t: Optional[torch.Tensor]):
+    """A tensor's device address (ctypes makes a pointer of the integer itself)."""
     if t is None:
         return None
     if not t.is_cuda:
         raise ValueError("the library works on device memory: pass CUDA tensors")
     if not t.is_contiguous():
         raise ValueError("tensors must be dense row-major (contiguous)")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream of the current device, as its handle: torch.cuda.current_stream() builds a Stream object by way
+    # of a device lookup, which took 2 us of a 9 us call
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def make_shape(batch: int, n_q_heads: int, n_kv_heads: int, d_head: int, dtype) -> Shape:
     code = _DTYPES[dtype] if isinstance(dtype, torch.dtype) else int(dtype)
     return Shape(batch, n_q_heads, n_kv_heads, d_head, code)
+
+
+@functools.lru_cache(maxsize=256)
+def _shape_ref(batch: int, n_q_heads: int, n_kv_heads: int, d_head: int, dtype):
+    """A reference to the shape struct of these numbers, for the calls' `const fedrag_shape*` (read during the call
+    only): small calls spend as long on building ctypes objects as on the device."""
+    return ctypes.byref(make_shape(batch, n_q_heads, n_kv_heads, d_head, dtype))
 
 
 def _shape_of(q_like: torch.Tensor, n_kv_heads: int, dtype=None) -> Shape:
@@ -159,48 +170,55 @@ def fedrag_scramble_kv(K, V, phi_k, phi_v, perm_kv=None, n_q_heads: Optional[int
                        K_out=None, V_out=None):
     """K' = P_KV K Phi_KQ^{-T}, V' = P_KV V Phi_V for one shard.  K, V [B,Hkv,L,d]; perm_kv [n_perm,L] or [L]."""
     B, Hkv, L, d = K.shape
-    shape = make_shape(B, n_q_heads or Hkv, Hkv, d, K.dtype)
+    shape = _shape_ref(B, n_q_heads or Hkv, Hkv, d, K.dtype)
     K_out = torch.empty_like(K) if K_out is None else K_out
     V_out = torch.empty_like(V) if V_out is None else V_out
     n_perm = 0
     if perm_kv is not None:
         n_perm = 1 if perm_kv.dim() == 1 else perm_kv.shape[0]
-    st = load().fedrag_scramble_kv(ctypes.byref(shape), L, _ptr(K), _ptr(V), _ptr(phi_k), _ptr(phi_v),
+    st = load().fedrag_scramble_kv(shape, L, _ptr(K), _ptr(V), _ptr(phi_k), _ptr(phi_v),
                                    _ptr(perm_kv), n_perm, _ptr(K_out), _ptr(V_out), _stream())
     _check(st, "fedrag_scramble_kv")
     return K_out, V_out
 
 
+def _workspace(workspace, like, query: str, *sizes):
+    """(tensor or None, its bytes): the caller's, whose size the call itself checks, or one of the size that it asks for."""
+    if workspace is None:
+        need = int(getattr(load(), query)(*sizes))
+        if need == 0:
+            return None, 0
+        workspace = torch.empty(need, dtype=torch.uint8, device=like.device)
+    return workspace, workspace.numel() * workspace.element_size()
+
+
 def fedrag_scramble_q(Q, phi_q, perm_q=None, Q_out=None):
     """Q' = P_Q Q Phi_KQ.  Q [B,Hq,Lq,d]; phi_q [Hkv,d,d]."""
     B, Hq, Lq, d = Q.shape
-    shape = make_shape(B, Hq, phi_q.shape[0], d, Q.dtype)
+    shape = _shape_ref(B, Hq, phi_q.shape[0], d, Q.dtype)
     Q_out = torch.empty_like(Q) if Q_out is None else Q_out
-    st = load().fedrag_scramble_q(ctypes.byref(shape), Lq, _ptr(Q), _ptr(phi_q), _ptr(perm_q), _ptr(Q_out), _stream())
+    st = load().fedrag_scramble_q(shape, Lq, _ptr(Q), _ptr(phi_q), _ptr(perm_q), _ptr(Q_out), _stream())
     _check(st, "fedrag_scramble_q")
     return Q_out
 
 
 def fedrag_partial_attn_workspace_bytes(batch, n_q_heads, n_kv_heads, d_head, dtype, L_q, L_kv) -> int:
-    shape = make_shape(batch, n_q_heads, n_kv_heads, d_head, dtype)
-    return int(load().fedrag_partial_attn_workspace_bytes(ctypes.byref(shape), L_q, L_kv))
+    shape = _shape_ref(batch, n_q_heads, n_kv_heads, d_head, dtype)
+    return int(load().fedrag_partial_attn_workspace_bytes(shape, L_q, L_kv))
 
 
 def fedrag_partial_attn(Qs, Ks, Vs, softmax_scale: Optional[float] = None, O_part=None, lse=None, workspace=None):
     """One shard's (O_i, lse_i).  Qs [B,Hq,Lq,d], Ks/Vs [B,Hkv,L,d] -> fp32 [B,Hq,Lq,d], fp32 [B,Hq,Lq]."""
     B, Hq, Lq, d = Qs.shape
     Hkv, L = Ks.shape[1], Ks.shape[2]
-    shape = make_shape(B, Hq, Hkv, d, Qs.dtype)
+    shape = _shape_ref(B, Hq, Hkv, d, Qs.dtype)
     if softmax_scale is None:
         softmax_scale = float(d) ** -0.5
     O_part = torch.empty((B, Hq, Lq, d), dtype=torch.float32, device=Qs.device) if O_part is None else O_part
     lse = torch.empty((B, Hq, Lq), dtype=torch.float32, device=Qs.device) if lse is None else lse
-    need = int(load().fedrag_partial_attn_workspace_bytes(ctypes.byref(shape), Lq, L))
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=Qs.device)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = load().fedrag_partial_attn(ctypes.byref(shape), Lq, L, _ptr(Qs), _ptr(Ks) if L > 0 else None,
-                                    _ptr(Vs) if L > 0 else None, ctypes.c_float(softmax_scale), _ptr(O_part),
+    workspace, ws_bytes = _workspace(workspace, Qs, "fedrag_partial_attn_workspace_bytes", shape, Lq, L)
+    st = load().fedrag_partial_attn(shape, Lq, L, _ptr(Qs), _ptr(Ks) if L > 0 else None,
+                                    _ptr(Vs) if L > 0 else None, softmax_scale, _ptr(O_part),
                                     _ptr(lse), _ptr(workspace), ws_bytes, _stream())
     _check(st, "fedrag_partial_attn")
     return O_part, lse
@@ -211,21 +229,21 @@ def fedrag_partial_attn_static(Qs, Ks, Vs, O_part, lse, softmax_scale: Optional[
     outputs, so that the call allocates nothing."""
     B, Hq, Lq, d = Qs.shape
     Hkv, L = Ks.shape[1], Ks.shape[2]
-    shape = make_shape(B, Hq, Hkv, d, Qs.dtype)
+    shape = _shape_ref(B, Hq, Hkv, d, Qs.dtype)
     if softmax_scale is None:
         softmax_scale = float(d) ** -0.5
-    st = load().fedrag_partial_attn_static(ctypes.byref(shape), Lq, L, _ptr(Qs), _ptr(Ks) if L > 0 else None,
-                                           _ptr(Vs) if L > 0 else None, ctypes.c_float(softmax_scale), _ptr(O_part),
+    st = load().fedrag_partial_attn_static(shape, Lq, L, _ptr(Qs), _ptr(Ks) if L > 0 else None,
+                                           _ptr(Vs) if L > 0 else None, softmax_scale, _ptr(O_part),
                                            _ptr(lse), _stream())
     _check(st, "fedrag_partial_attn_static")
     return O_part, lse
 
 
 def fedrag_partial_attn_shards_workspace_bytes(batch, n_q_heads, n_kv_heads, d_head, dtype, L_q, L_kv_list) -> int:
-    shape = make_shape(batch, n_q_heads, n_kv_heads, d_head, dtype)
+    shape = _shape_ref(batch, n_q_heads, n_kv_heads, d_head, dtype)
     n = len(L_kv_list)
     Ls = (ctypes.c_int64 * n)(*[int(x) for x in L_kv_list])
-    return int(load().fedrag_partial_attn_shards_workspace_bytes(ctypes.byref(shape), L_q, n, Ls))
+    return int(load().fedrag_partial_attn_shards_workspace_bytes(shape, L_q, n, Ls))
 
 
 def fedrag_partial_attn_shards(Qs, Ks_list, Vs_list, softmax_scale: Optional[float] = None, O=None, lse=None,
@@ -235,7 +253,7 @@ def fedrag_partial_attn_shards(Qs, Ks_list, Vs_list, softmax_scale: Optional[flo
     B, Hq, Lq, d = Qs.shape
     n = len(Ks_list)
     Hkv = Ks_list[0].shape[1]
-    shape = make_shape(B, Hq, Hkv, d, Qs.dtype)
+    shape = _shape_ref(B, Hq, Hkv, d, Qs.dtype)
     if softmax_scale is None:
         softmax_scale = float(d) ** -0.5
     O = torch.empty((B, Hq, Lq, d), dtype=torch.float32, device=Qs.device) if O is None else O
@@ -243,12 +261,9 @@ def fedrag_partial_attn_shards(Qs, Ks_list, Vs_list, softmax_scale: Optional[flo
     Ls = (ctypes.c_int64 * n)(*[int(k.shape[2]) for k in Ks_list])
     Kp = (ctypes.c_void_p * n)(*[_ptr(k) if k.shape[2] > 0 else None for k in Ks_list])
     Vp = (ctypes.c_void_p * n)(*[_ptr(v) if v.shape[2] > 0 else None for v in Vs_list])
-    need = int(load().fedrag_partial_attn_shards_workspace_bytes(ctypes.byref(shape), Lq, n, Ls))
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=Qs.device)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = load().fedrag_partial_attn_shards(ctypes.byref(shape), Lq, n, Ls, Kp, Vp, _ptr(Qs),
-                                           ctypes.c_float(softmax_scale), _ptr(O), _ptr(lse), _ptr(workspace),
+    workspace, ws_bytes = _workspace(workspace, Qs, "fedrag_partial_attn_shards_workspace_bytes", shape, Lq, n, Ls)
+    st = load().fedrag_partial_attn_shards(shape, Lq, n, Ls, Kp, Vp, _ptr(Qs),
+                                           softmax_scale, _ptr(O), _ptr(lse), _ptr(workspace),
                                            ws_bytes, _stream())
     _check(st, "fedrag_partial_attn_shards")
     return O, lse
@@ -261,18 +276,15 @@ def fedrag_partial_attn_varlen(Qs, Ks, Vs, kv_lens, softmax_scale: Optional[floa
     Hkv, L = Ks.shape[1], Ks.shape[2]
     if kv_lens.dtype != torch.int32 or kv_lens.shape != (B,):
         raise ValueError("kv_lens: int32 [B]")
-    shape = make_shape(B, Hq, Hkv, d, Qs.dtype)
+    shape = _shape_ref(B, Hq, Hkv, d, Qs.dtype)
     if softmax_scale is None:
         softmax_scale = float(d) ** -0.5
     O_part = torch.empty((B, Hq, Lq, d), dtype=torch.float32, device=Qs.device) if O_part is None else O_part
     lse = torch.empty((B, Hq, Lq), dtype=torch.float32, device=Qs.device) if lse is None else lse
-    need = int(load().fedrag_partial_attn_workspace_bytes(ctypes.byref(shape), Lq, L))
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=Qs.device)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = load().fedrag_partial_attn_varlen(ctypes.byref(shape), Lq, L, _ptr(Qs), _ptr(Ks) if L > 0 else None,
+    workspace, ws_bytes = _workspace(workspace, Qs, "fedrag_partial_attn_workspace_bytes", shape, Lq, L)
+    st = load().fedrag_partial_attn_varlen(shape, Lq, L, _ptr(Qs), _ptr(Ks) if L > 0 else None,
                                            _ptr(Vs) if L > 0 else None, _ptr(kv_lens), _ptr(q_lens),
-                                           ctypes.c_float(softmax_scale),
+                                           softmax_scale,
                                            _ptr(O_part), _ptr(lse), _ptr(workspace), ws_bytes, _stream())
     _check(st, "fedrag_partial_attn_varlen")
     return O_part, lse
@@ -283,19 +295,16 @@ def fedrag_partial_attn_quantized(Qs, K_codes, K_params, V_codes, V_params, bits
     """fedrag_partial_attn reading K', V' as transport-codec codes (any query count; 16-bit storage)."""
     B, Hq, Lq, d = Qs.shape
     Hkv, L = K_codes.shape[1], K_codes.shape[2]
-    shape = make_shape(B, Hq, Hkv, d, Qs.dtype)
+    shape = _shape_ref(B, Hq, Hkv, d, Qs.dtype)
     if softmax_scale is None:
         softmax_scale = float(d) ** -0.5
     O_part = torch.empty((B, Hq, Lq, d), dtype=torch.float32, device=Qs.device) if O_part is None else O_part
     lse = torch.empty((B, Hq, Lq), dtype=torch.float32, device=Qs.device) if lse is None else lse
-    need = int(load().fedrag_partial_attn_workspace_bytes(ctypes.byref(shape), Lq, L))
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=Qs.device)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    workspace, ws_bytes = _workspace(workspace, Qs, "fedrag_partial_attn_workspace_bytes", shape, Lq, L)
     nz = L > 0
-    st = load().fedrag_partial_attn_quantized(ctypes.byref(shape), Lq, L, _ptr(Qs), _ptr(K_codes) if nz else None,
+    st = load().fedrag_partial_attn_quantized(shape, Lq, L, _ptr(Qs), _ptr(K_codes) if nz else None,
                                               _ptr(K_params) if nz else None, _ptr(V_codes) if nz else None,
-                                              _ptr(V_params) if nz else None, bits, ctypes.c_float(softmax_scale),
+                                              _ptr(V_params) if nz else None, bits, softmax_scale,
                                               _ptr(O_part), _ptr(lse), _ptr(workspace), ws_bytes, _stream())
     _check(st, "fedrag_partial_attn_quantized")
     return O_part, lse
@@ -310,20 +319,17 @@ def fedrag_partial_attn_varlen_quantized(Qs, K_codes, K_params, V_codes, V_param
     Hkv, L = K_codes.shape[1], K_codes.shape[2]
     if kv_lens.dtype != torch.int32 or kv_lens.shape != (B,):
         raise ValueError("kv_lens: int32 [B]")
-    shape = make_shape(B, Hq, Hkv, d, Qs.dtype)
+    shape = _shape_ref(B, Hq, Hkv, d, Qs.dtype)
     if softmax_scale is None:
         softmax_scale = float(d) ** -0.5
     O_part = torch.empty((B, Hq, Lq, d), dtype=torch.float32, device=Qs.device) if O_part is None else O_part
     lse = torch.empty((B, Hq, Lq), dtype=torch.float32, device=Qs.device) if lse is None else lse
-    need = int(load().fedrag_partial_attn_workspace_bytes(ctypes.byref(shape), Lq, L))
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=Qs.device)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    workspace, ws_bytes = _workspace(workspace, Qs, "fedrag_partial_attn_workspace_bytes", shape, Lq, L)
     nz = L > 0
     st = load().fedrag_partial_attn_varlen_quantized(
-        ctypes.byref(shape), Lq, L, _ptr(Qs), _ptr(K_codes) if nz else None, _ptr(K_params) if nz else None,
+        shape, Lq, L, _ptr(Qs), _ptr(K_codes) if nz else None, _ptr(K_params) if nz else None,
         _ptr(V_codes) if nz else None, _ptr(V_params) if nz else None, bits, _ptr(kv_lens), _ptr(q_lens),
-        ctypes.c_float(softmax_scale), _ptr(O_part), _ptr(lse), _ptr(workspace), ws_bytes, _stream())
+        softmax_scale, _ptr(O_part), _ptr(lse), _ptr(workspace), ws_bytes, _stream())
     _check(st, "fedrag_partial_attn_varlen_quantized")
     return O_part, lse
 
@@ -333,17 +339,16 @@ def fedrag_local_attn(Q, K, V, softmax_scale: Optional[float] = None, O_part=Non
     and what comes before.  Q [B,Hq,Lq,d], K/V [B,Hkv,L,d] plaintext -> fp32 [B,Hq,Lq,d], fp32 [B,Hq,Lq]."""
     B, Hq, Lq, d = Q.shape
     Hkv, L = K.shape[1], K.shape[2]
-    shape = make_shape(B, Hq, Hkv, d, Q.dtype)
+    shape = _shape_ref(B, Hq, Hkv, d, Q.dtype)
     if softmax_scale is None:
         softmax_scale = float(d) ** -0.5
     O_part = torch.empty((B, Hq, Lq, d), dtype=torch.float32, device=Q.device) if O_part is None else O_part
     lse = torch.empty((B, Hq, Lq), dtype=torch.float32, device=Q.device) if lse is None else lse
-    need = int(load().fedrag_partial_attn_workspace_bytes(ctypes.byref(shape), Lq, L)) if Lq == 1 else 0
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=Q.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = load().fedrag_local_attn(ctypes.byref(shape), Lq, L, _ptr(Q), _ptr(K) if L > 0 else None,
-                                  _ptr(V) if L > 0 else None, ctypes.c_float(softmax_scale), _ptr(O_part), _ptr(lse),
+    if Lq == 1:
+        workspace, ws_bytes = _workspace(workspace, Q, "fedrag_partial_attn_workspace_bytes", shape, Lq, L)
+    st = load().fedrag_local_attn(shape, Lq, L, _ptr(Q), _ptr(K) if L > 0 else None,
+                                  _ptr(V) if L > 0 else None, softmax_scale, _ptr(O_part), _ptr(lse),
                                   _ptr(workspace), ws_bytes, _stream())
     _check(st, "fedrag_local_attn")
     return O_part, lse
@@ -353,10 +358,10 @@ def fedrag_unscramble_merge(O_scr, lse_scr, phi_v_inv, perm_q, O_local, lse_loca
                             n_kv_heads: Optional[int] = None):
     """Dec of the remote result and its aggregation with the Inquirer's own partial, in one call."""
     B, Hq, Lq, d = O_scr.shape
-    shape = make_shape(B, Hq, n_kv_heads or phi_v_inv.shape[0], d, F32)
+    shape = _shape_ref(B, Hq, n_kv_heads or phi_v_inv.shape[0], d, F32)
     O_out = torch.empty_like(O_scr) if O_out is None else O_out
     lse_out = torch.empty_like(lse_scr) if lse_out is None else lse_out
-    st = load().fedrag_unscramble_merge(ctypes.byref(shape), Lq, _ptr(O_scr), _ptr(lse_scr), _ptr(phi_v_inv),
+    st = load().fedrag_unscramble_merge(shape, Lq, _ptr(O_scr), _ptr(lse_scr), _ptr(phi_v_inv),
                                         _ptr(perm_q), _ptr(O_local), _ptr(lse_local), _ptr(O_out), _ptr(lse_out),
                                         _stream())
     _check(st, "fedrag_unscramble_merge")
@@ -366,9 +371,9 @@ def fedrag_unscramble_merge(O_scr, lse_scr, phi_v_inv, perm_q, O_local, lse_loca
 def fedrag_unpermute_lse(lse_scr, perm_q=None, lse_out=None):
     """lse_out[b,h,perm_q[i]] = lse_scr[b,h,i]: the log-sum-exps back in the query rows' own order."""
     B, Hq, Lq = lse_scr.shape
-    shape = make_shape(B, Hq, Hq, 128, F32)
+    shape = _shape_ref(B, Hq, Hq, 128, F32)
     lse_out = torch.empty_like(lse_scr) if lse_out is None else lse_out
-    st = load().fedrag_unpermute_lse(ctypes.byref(shape), Lq, _ptr(lse_scr), _ptr(perm_q), _ptr(lse_out), _stream())
+    st = load().fedrag_unpermute_lse(shape, Lq, _ptr(lse_scr), _ptr(perm_q), _ptr(lse_out), _stream())
     _check(st, "fedrag_unpermute_lse")
     return lse_out
 
@@ -376,10 +381,10 @@ def fedrag_unpermute_lse(lse_scr, perm_q=None, lse_out=None):
 def fedrag_lse_merge(O_parts, lses, n_kv_heads: Optional[int] = None, O_out=None, lse_out=None):
     """Aggregation over shards.  O_parts fp32 [S,B,Hq,Lq,d], lses fp32 [S,B,Hq,Lq]."""
     S, B, Hq, Lq, d = O_parts.shape
-    shape = make_shape(B, Hq, n_kv_heads or Hq, d, F32)
+    shape = _shape_ref(B, Hq, n_kv_heads or Hq, d, F32)
     O_out = torch.empty((B, Hq, Lq, d), dtype=torch.float32, device=O_parts.device) if O_out is None else O_out
     lse_out = torch.empty((B, Hq, Lq), dtype=torch.float32, device=O_parts.device) if lse_out is None else lse_out
-    st = load().fedrag_lse_merge(ctypes.byref(shape), Lq, S, _ptr(O_parts), _ptr(lses), _ptr(O_out), _ptr(lse_out),
+    st = load().fedrag_lse_merge(shape, Lq, S, _ptr(O_parts), _ptr(lses), _ptr(O_out), _ptr(lse_out),
                                  _stream())
     _check(st, "fedrag_lse_merge")
     return O_out, lse_out
@@ -388,9 +393,9 @@ def fedrag_lse_merge(O_parts, lses, n_kv_heads: Optional[int] = None, O_out=None
 def fedrag_unscramble(O_scr, phi_v_inv, perm_q=None, O_out=None):
     """Dec: out[b,h,perm_q[i]] = O_scr[b,h,i] @ phi_v_inv[h // G].  O_scr fp32 [B,Hq,Lq,d]; phi_v_inv fp32 [Hkv,d,d]."""
     B, Hq, Lq, d = O_scr.shape
-    shape = make_shape(B, Hq, phi_v_inv.shape[0], d, F32)
+    shape = _shape_ref(B, Hq, phi_v_inv.shape[0], d, F32)
     O_out = torch.empty_like(O_scr) if O_out is None else O_out
-    st = load().fedrag_unscramble(ctypes.byref(shape), Lq, _ptr(O_scr), _ptr(phi_v_inv), _ptr(perm_q), _ptr(O_out),
+    st = load().fedrag_unscramble(shape, Lq, _ptr(O_scr), _ptr(phi_v_inv), _ptr(perm_q), _ptr(O_out),
                                   _stream())
     _check(st, "fedrag_unscramble")
     return O_out
@@ -412,14 +417,14 @@ def fedrag_scramble_kv_structured(K, V, key_k, key_v, perm_kv=None, n_q_heads: O
     B, Hkv, L, d = K.shape
     if key_k[0].shape != (Hkv, d) or key_v[0].shape != (Hkv, d):
         raise ValueError("structured key does not match [Hkv, d]")
-    shape = make_shape(B, n_q_heads or Hkv, Hkv, d, K.dtype)
+    shape = _shape_ref(B, n_q_heads or Hkv, Hkv, d, K.dtype)
     K_out = torch.empty_like(K) if K_out is None else K_out
     V_out = torch.empty_like(V) if V_out is None else V_out
     n_perm = 0
     if perm_kv is not None:
         n_perm = 1 if perm_kv.dim() == 1 else perm_kv.shape[0]
     kk, kv = _key(key_k), _key(key_v)
-    st = load().fedrag_scramble_kv_structured(ctypes.byref(shape), L, _ptr(K), _ptr(V), ctypes.byref(kk),
+    st = load().fedrag_scramble_kv_structured(shape, L, _ptr(K), _ptr(V), ctypes.byref(kk),
                                               ctypes.byref(kv), _ptr(perm_kv), n_perm, _ptr(K_out), _ptr(V_out),
                                               _stream())
     _check(st, "fedrag_scramble_kv_structured")
@@ -430,10 +435,10 @@ def fedrag_scramble_q_structured(Q, key_q, perm_q=None, Q_out=None):
     B, Hq, Lq, d = Q.shape
     if key_q[0].dim() != 2 or key_q[0].shape[1] != d:
         raise ValueError("structured key does not match [Hkv, d]")
-    shape = make_shape(B, Hq, key_q[0].shape[0], d, Q.dtype)
+    shape = _shape_ref(B, Hq, key_q[0].shape[0], d, Q.dtype)
     Q_out = torch.empty_like(Q) if Q_out is None else Q_out
     kq = _key(key_q)
-    st = load().fedrag_scramble_q_structured(ctypes.byref(shape), Lq, _ptr(Q), ctypes.byref(kq), _ptr(perm_q),
+    st = load().fedrag_scramble_q_structured(shape, Lq, _ptr(Q), ctypes.byref(kq), _ptr(perm_q),
                                              _ptr(Q_out), _stream())
     _check(st, "fedrag_scramble_q_structured")
     return Q_out
@@ -443,10 +448,10 @@ def fedrag_unscramble_structured(O_scr, key_v_inv, perm_q=None, O_out=None):
     B, Hq, Lq, d = O_scr.shape
     if key_v_inv[0].dim() != 2 or key_v_inv[0].shape[1] != d:
         raise ValueError("structured key does not match [Hkv, d]")
-    shape = make_shape(B, Hq, key_v_inv[0].shape[0], d, F32)
+    shape = _shape_ref(B, Hq, key_v_inv[0].shape[0], d, F32)
     O_out = torch.empty_like(O_scr) if O_out is None else O_out
     kv = _key(key_v_inv)
-    st = load().fedrag_unscramble_structured(ctypes.byref(shape), Lq, _ptr(O_scr), ctypes.byref(kv), _ptr(perm_q),
+    st = load().fedrag_unscramble_structured(shape, Lq, _ptr(O_scr), ctypes.byref(kv), _ptr(perm_q),
                                              _ptr(O_out), _stream())
     _check(st, "fedrag_unscramble_structured")
     return O_out
@@ -479,7 +484,7 @@ def fedrag_scramble_kv_quantized(K, V, phi_k, phi_v, perm_kv, bits: int, n_q_hea
     """Enc of a KV shard with the transport codec as epilogue.  phi_k / phi_v: dense matrices, or structured keys
     with structured=True.  Returns (K_codes, K_params, V_codes, V_params)."""
     B, Hkv, L, d = K.shape
-    shape = make_shape(B, n_q_heads or Hkv, Hkv, d, K.dtype)
+    shape = _shape_ref(B, n_q_heads or Hkv, Hkv, d, K.dtype)
     mk_c = lambda: torch.empty((B, Hkv, L, d * bits // 8), dtype=torch.uint8, device=K.device)
     mk_p = lambda: torch.empty((B, Hkv, L, 2), dtype=torch.float32, device=K.device)
     Kc, Kp, Vc, Vp = (mk_c(), mk_p(), mk_c(), mk_p()) if out is None else out
@@ -488,11 +493,11 @@ def fedrag_scramble_kv_quantized(K, V, phi_k, phi_v, perm_kv, bits: int, n_q_hea
         n_perm = 1 if perm_kv.dim() == 1 else perm_kv.shape[0]
     if structured:
         kk, kv = _key(phi_k), _key(phi_v)
-        st = load().fedrag_scramble_kv_structured_quantized(ctypes.byref(shape), L, _ptr(K), _ptr(V), ctypes.byref(kk),
+        st = load().fedrag_scramble_kv_structured_quantized(shape, L, _ptr(K), _ptr(V), ctypes.byref(kk),
                                                             ctypes.byref(kv), _ptr(perm_kv), n_perm, bits, _ptr(Kc),
                                                             _ptr(Kp), _ptr(Vc), _ptr(Vp), _stream())
     else:
-        st = load().fedrag_scramble_kv_quantized(ctypes.byref(shape), L, _ptr(K), _ptr(V), _ptr(phi_k), _ptr(phi_v),
+        st = load().fedrag_scramble_kv_quantized(shape, L, _ptr(K), _ptr(V), _ptr(phi_k), _ptr(phi_v),
                                                  _ptr(perm_kv), n_perm, bits, _ptr(Kc), _ptr(Kp), _ptr(Vc), _ptr(Vp),
                                                  _stream())
     _check(st, "fedrag_scramble_kv_quantized")
