@@ -187,15 +187,14 @@ hipError_t launch_partial_attn(const AttnProblem& p_in, hipStream_t stream) {
         if (total == 0) return launch_fill_empty(p.O, p.lse, rows, p.D, stream);
         const bool decode = use_decode_kernel(p.Hq, p.Hkv, p.Lq);
         if (p.dtype == FEDRAG_F32) return launch_attn_f32(p, stream);
-        bool one_launch_per_shard = false;
-        if ((!decode || (int64_t)p.B * p.Hkv >= attn_target_wgs())) {
-            // The chip is already covered by one shard's workgroups (prefill: query tiles; decode: as many
-            // (sequence, KV head) units as compute units) and every shard is one run: a launch per shard keeps the
-            // workgroups of a launch on one shard's K', V' (prefill, 8 shards of 8192 keys, 4096 x 64 query rows:
-            // 8.2 ms against 8.9 ms with all shards in one launch; decode, 8 shards of 8 GiB: 9.55 against 10.05 ms);
-            // the partials and their aggregation are the same
+        if (p.dtype != FEDRAG_BF16 && p.dtype != FEDRAG_F16) return hipErrorInvalidValue;
+        if (!decode) return launch_prefill_attn(p, stream);
+        bool one_launch_per_shard = (int64_t)p.B * p.Hkv >= attn_target_wgs();
+        if (one_launch_per_shard) {
+            // The chip is already covered by one shard's workgroups (as many (sequence, KV head) units as compute units)
+            // and every shard is one run: a launch per shard keeps the workgroups of a launch on one shard's K', V'
+            // (8 shards of 8 GiB: 9.55 against 10.05 ms); the partials and their aggregation are the same
             const KeyRuns plan = attn_runs_of(p);
-            one_launch_per_shard = true;
             for (int i = 0; i < p.n_shards; ++i)
                 if (plan.first[i + 1] - plan.first[i] > 1) one_launch_per_shard = false;
         }
@@ -224,8 +223,7 @@ hipError_t launch_partial_attn(const AttnProblem& p_in, hipStream_t stream) {
             }
             return n > 1 ? launch_lse_merge(Ow, Lw, n, rows, p.D, p.O, p.lse, stream) : hipSuccess;
         }
-        if (p.dtype != FEDRAG_BF16 && p.dtype != FEDRAG_F16) return hipErrorInvalidValue;
-        return decode ? launch_decode_attn(p, stream) : launch_prefill_attn(p, stream);
+        return launch_decode_attn(p, stream);
     }
     if (p.Lkv == 0) return launch_fill_empty(p.O, p.lse, rows, p.D, stream);
     if (p.quant_bits != 0) {  // K', V' as transport codes: 16-bit storage, no mask

