@@ -1,0 +1,147 @@
+"""The launch forms of the attention and aggregation kernels at the sizes where they change over or end raggedly:
+tiles of query rows and of keys, key runs, shards visited in one launch, partials per batch.  Against the oracle, with the
+bounds of parity.py; what a form must not touch is poisoned."""
+import numpy as np
+import pytest
+import torch
+
+import parity as PT
+from paper_2605_25716_amd import binding as fb
+from paper_2605_25716_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def rnd(B, H, L, d, dt, tid, seed=5):
+    return W.activations(B, H, L, d, seed=seed, tensor_id=tid, outliers=False, dtype=W.torch_dtype(dt))
+
+
+# query tiles cover the chip (8 units of 4132 rows): every shard is one run and a workgroup visits them one after the other
+@pytest.mark.parametrize("d,dt,Ls", [(64, "bf16", [64, 1, 65]), (128, "bf16", [63, 0, 128, 40, 129]), (128, "f16", [1]),
+                                     (64, "f16", [192, 191, 0])])
+def test_shards_visited_in_one_launch(oracle, d, dt, Ls):
+    Q = rnd(1, 32, 1033, d, dt, W.TID_Q)
+    Ks = [rnd(1, 8, L, d, dt, W.TID_K + 16 * (i + 1)) for i, L in enumerate(Ls)]
+    Vs = [rnd(1, 8, L, d, dt, W.TID_V + 16 * (i + 1)) for i, L in enumerate(Ls)]
+    print(f"walk {d} {dt} {Ls}", flush=True)
+    O, lse = fb.fedrag_partial_attn_shards(Q.to(DEV), [k.to(DEV) for k in Ks], [v.to(DEV) for v in Vs])
+    torch.cuda.synchronize()
+    Or, lr = oracle.partial_attn(Q, torch.cat(Ks, dim=2), torch.cat(Vs, dim=2))
+    PT.check_attn(O, lse, Or, lr, Q.dtype, f"{d} {dt} {Ls}")
+
+
+def test_every_shard_boundary_keeps_its_keys():
+    """One key tile of one shard holds all the weight of a query row: a tile lost or read twice where a workgroup passes from
+    shard to shard moves that row's log-sum-exp by ln 2 or more."""
+    d, L, S, Lq = 128, 256, 3, 1024
+    tile = torch.arange(L) // 64
+    Q = torch.nn.functional.one_hot(torch.arange(Lq) % 4, d).to(torch.bfloat16).expand(1, 32, Lq, d).contiguous().to(DEV)
+    hot = (torch.nn.functional.one_hot(tile, d) * 226.0).to(torch.bfloat16).expand(1, 8, L, d).contiguous().to(DEV)
+    zero = torch.zeros_like(hot)
+    expect = np.log(64 * np.exp(226.0 / np.sqrt(d)) + (S * L - 64))
+    for which in range(S):
+        _, lse = fb.fedrag_partial_attn_shards(Q, [hot if s == which else zero for s in range(S)], [zero] * S)
+        torch.cuda.synchronize()
+        assert float((lse.double() - expect).abs().max()) <= PT.TOL_16_LSE_ABS, which
+
+
+# 128-row tiles and 64-key tiles of the masked form; the last two launches are one past the fold of the tile order
+@pytest.mark.parametrize("B,Hq,d,Lq,L,dt", [(1, 4, 128, 128, 128, "bf16"), (1, 4, 128, 129, 129, "bf16"),
+                                            (1, 2, 128, 127, 191, "f16"), (1, 4, 64, 65, 130, "bf16"),
+                                            (2, 4, 64, 257, 300, "f16"), (1, 4, 128, 2, 64, "bf16"),
+                                            (1, 4, 128, 640, 640, "bf16"), (4, 32, 64, 515, 515, "bf16"),
+                                            (4, 32, 128, 520, 583, "bf16")])
+def test_masked_tiles(oracle, B, Hq, d, Lq, L, dt):
+    Hkv = max(2, Hq // 4)
+    Q, K, V = rnd(B, Hq, Lq, d, dt, W.TID_Q), rnd(B, Hkv, L, d, dt, W.TID_K), rnd(B, Hkv, L, d, dt, W.TID_V)
+    print(f"local {B} {Hq} {d} {Lq} {L} {dt}", flush=True)
+    O, lse = fb.fedrag_local_attn(Q.to(DEV), K.to(DEV), V.to(DEV))
+    torch.cuda.synchronize()
+    Or, lr = oracle.local_causal_attn(Q, K, V)
+    PT.check_attn(O, lse, Or, lr, Q.dtype, f"local {Lq} of {L}")
+
+
+# fp32: 16 query rows per workgroup, 32 once those cover the chip (last case); 16-key tiles over 8 waves
+@pytest.mark.parametrize("B,Hq,Hkv,d,Lq,L", [(1, 2, 2, 64, 16, 1), (1, 2, 2, 128, 17, 15), (1, 4, 2, 128, 8, 16),
+                                             (2, 4, 1, 64, 5, 127), (1, 2, 1, 128, 3, 128), (1, 2, 2, 64, 33, 129),
+                                             (1, 8, 2, 128, 1, 513), (4, 8, 8, 64, 250, 70), (4, 8, 8, 128, 256, 33)])
+def test_fp32_tiles(oracle, B, Hq, Hkv, d, Lq, L):
+    Q, K, V = (rnd(B, h, n, d, "f32", t) for h, n, t in ((Hq, Lq, W.TID_Q), (Hkv, L, W.TID_K), (Hkv, L, W.TID_V)))
+    print(f"f32 {B} {Hq} {Hkv} {d} {Lq} {L}", flush=True)
+    O, lse = fb.fedrag_partial_attn(Q.to(DEV), K.to(DEV), V.to(DEV))
+    O2, lse2 = fb.fedrag_partial_attn_shards(Q.to(DEV), [K[:, :, :L // 2].contiguous().to(DEV), K[:, :, L // 2:].contiguous().to(DEV)],
+                                             [V[:, :, :L // 2].contiguous().to(DEV), V[:, :, L // 2:].contiguous().to(DEV)])
+    torch.cuda.synchronize()
+    Or, lr = oracle.partial_attn(Q, K, V)
+    PT.check_attn(O, lse, Or, lr, torch.float32, "plain")
+    PT.check_attn(O2, lse2, Or, lr, torch.float32, "two shards")
+    if L >= Lq:
+        O, lse = fb.fedrag_local_attn(Q.to(DEV), K.to(DEV), V.to(DEV))
+        torch.cuda.synchronize()
+        Or, lr = oracle.local_causal_attn(Q, K, V)
+        PT.check_attn(O, lse, Or, lr, torch.float32, "masked")
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_fp32_rows_do_not_see_a_later_token(oracle, bad):
+    """A token whose K, V are not finite leaves the rows before it as they are (0 x inf must not reach them)."""
+    Q, K, V = (rnd(1, h, 40, 64, "f32", t) for h, t in ((4, W.TID_Q), (2, W.TID_K), (2, W.TID_V)))
+    Or, lr = oracle.local_causal_attn(Q, K, V)
+    K[:, :, 21], V[:, :, 21] = bad, bad
+    O, lse = fb.fedrag_local_attn(Q.to(DEV), K.to(DEV), V.to(DEV))
+    torch.cuda.synchronize()
+    PT.check_attn(O[:, :, :21], lse[:, :, :21], Or[:, :, :21], lr[:, :, :21], torch.float32, "rows before the token")
+
+
+@pytest.mark.parametrize("S", [1, 2, 8, 9, 16, 17, 33])
+@pytest.mark.parametrize("rows,d", [(3, 128), (5, 64), (2500, 128)])  # many rows: the form with fewer partials in flight
+def test_aggregation_of_many_partials(oracle, S, rows, d):
+    g = torch.Generator().manual_seed(S * 100 + rows)
+    O, lse = torch.randn((S, 1, 1, rows, d), generator=g), torch.randn((S, 1, 1, rows), generator=g) * 30
+    lse[S // 2, 0, 0, ::3] = float("-inf")
+    lse[:, 0, 0, 1] = float("-inf")
+    Or, lr = oracle.lse_merge(O, lse)
+    O[lse == float("-inf")] = float("nan")  # a partial without weight takes no part, whatever it holds
+    got, got_l = fb.fedrag_lse_merge(O.to(DEV), lse.to(DEV))
+    torch.cuda.synchronize()
+    assert PT.max_abs(got, Or) <= 1e-4 and PT.max_abs(got_l, lr) <= 1e-4
+
+
+# one run up to 512 keys, 256-key runs up to 2048 in all, 512-key runs behind; one tile set up to 1024 keys per run
+@pytest.mark.parametrize("Ls", [[31], [512], [513], [2047], [2049], [400, 700], [300, 0, 213], [9000]])
+@pytest.mark.parametrize("d", [64, 128])
+def test_decode_key_runs(oracle, Ls, d):
+    Q = rnd(1, 8, 1, d, "bf16", W.TID_Q)
+    Ks = [rnd(1, 2, L, d, "bf16", W.TID_K + 16 * (i + 1)) for i, L in enumerate(Ls)]
+    Vs = [rnd(1, 2, L, d, "bf16", W.TID_V + 16 * (i + 1)) for i, L in enumerate(Ls)]
+    O, lse = fb.fedrag_partial_attn_shards(Q.to(DEV), [k.to(DEV) for k in Ks], [v.to(DEV) for v in Vs])
+    torch.cuda.synchronize()
+    Or, lr = oracle.partial_attn(Q, torch.cat(Ks, dim=2), torch.cat(Vs, dim=2))
+    PT.check_attn(O, lse, Or, lr, Q.dtype, str(Ls))
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+def test_decode_on_4bit_codes_of_every_scale(dt):
+    """Rows of every magnitude, tiny, ordinary and (bf16) beyond 2^100, rebuild to what fedrag_dequantize_rows gives: with one
+    key per sequence the output is that row of V' itself."""
+    B, d = 24, 128
+    V = rnd(B, 1, 1, d, "f32", W.TID_V)
+    e = torch.linspace(-14.0, 14.0, B) if dt == "f16" else torch.linspace(-120.0, 124.0, B)
+    V = (V.clamp(-3, 3) * torch.exp2(e).view(B, 1, 1, 1)).to(W.torch_dtype(dt)).to(DEV)
+    K = rnd(B, 1, 1, d, dt, W.TID_K).to(DEV)
+    Kc, Kp = fb.fedrag_quantize_rows(K, 4)
+    Vc, Vp = fb.fedrag_quantize_rows(V, 4)
+    ref = fb.fedrag_dequantize_rows(Vc, Vp, 4, V.dtype).float()
+    O, _ = fb.fedrag_partial_attn_quantized(rnd(B, 2, 1, d, dt, W.TID_Q).to(DEV), Kc, Kp, Vc, Vp, 4)
+    torch.cuda.synchronize()
+    # the probability is 1, exactly representable; fp32 division by a denominator of 1
+    assert torch.equal(O, ref.expand(B, 2, 1, d))
+
+
+@pytest.mark.parametrize("L", [1, 64, 65, 256, 300])
+def test_lse_scatter(L):
+    lse = torch.randn((2, 3, L))
+    perm = torch.randperm(L, generator=torch.Generator().manual_seed(L)).to(torch.int32)
+    out = fb.fedrag_unpermute_lse(lse.to(DEV), perm.to(DEV)).cpu()
+    assert torch.equal(out[:, :, perm.long()], lse)
