@@ -117,6 +117,49 @@ __device__ __forceinline__ float group_max(float x) {
     return group_reduce<N>(x, [](float a, float b) { return fmaxf(a, b); });
 }
 
+// The same reduction of a minimum and a maximum at once, one instruction per step and value: the data-parallel move is
+// folded into the minimum / maximum (the compiler emits a move, a canonicalising maximum and the operation itself).  A
+// register has to be two instructions old before a data-parallel read, which the other value's step and a nop give it.
+template <int N>
+__device__ __forceinline__ void group_min_max(float& lo, float& hi) {
+    static_assert(N == 8 || N == 16, "groups of 8 or 16 lanes");
+    asm("s_nop 1\n\t"
+        "v_min_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_min_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_min_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1"
+        : "+v"(lo), "+v"(hi));
+    if (N == 16)
+        asm("v_min_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "v_max_f32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "s_nop 1"
+            : "+v"(lo), "+v"(hi));
+}
+
+// Eight values in [0, 256) truncated to bytes, value e in byte e % 4 of word e / 4, each conversion writing its byte.  The
+// two words alternate because a partly written register must not be written again by the next instruction.
+__device__ __forceinline__ void bytes_of(const float (&t)[8], uint32_t& w0, uint32_t& w1) {
+    asm("v_cvt_u32_f32_sdwa %0, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %1, %6 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:DWORD\n\t"
+        "s_nop 0\n\t"
+        "v_cvt_u32_f32_sdwa %0, %3 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %1, %7 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "s_nop 0\n\t"
+        "v_cvt_u32_f32_sdwa %0, %4 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %1, %8 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "s_nop 0\n\t"
+        "v_cvt_u32_f32_sdwa %0, %5 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %1, %9 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "s_nop 1"
+        : "=&v"(w0), "=&v"(w1)
+        : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]));
+}
+
 // Keep a value's computation above this point: the compiler may otherwise sink pure register arithmetic towards
 // its first use (past a barrier, into the next loop iteration), out of the scheduling region it was written for.
 template <class V>

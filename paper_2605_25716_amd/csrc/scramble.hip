@@ -15,7 +15,9 @@ namespace fedrag {
 
 // Two shapes of the tiled kernel.  Plain rows (QB = 0): 4 waves per workgroup, one per SIMD, Phi^T in 128 registers
 // per wave for the whole kernel - the wave does little besides moving rows, and memory time hides it.  Rows that
-// leave through the transport codec (QB = 8, 4): the codec's ~110 vector instructions per 8-element chunk need a
+// leave through the transport codec (QB = 8, 4): the codec's ~90 vector instructions per 8-element chunk (~125 before the
+// range reduction took one instruction a step and the bytes were written in place: 16 x 8192 tokens to 8 bits 200 -> 182
+// us, to 4 bits 105 -> 97 for half of them) need a
 // second wave per SIMD to hide behind the other wave's memory time, and two waves only fit when Phi^T stays in LDS
 // and its operands are read per tile (32 KiB of LDS reads per 8 KiB of rows: a few per cent of the LDS rate).
 constexpr int scr_waves(int qb) { return qb ? 8 : 4; }
@@ -68,7 +70,7 @@ __global__ __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_kernel
                                                                        const int32_t* __restrict__ perm,
                                                                        int64_t perm_batch_stride,  // 0 or L
                                                                        int B, int H, int G, int64_t L, int members,
-                                                                       int tiles_per_slab, int b_groups) {
+                                                                       FastDiv by_slab, int b_groups) {
     typedef typename T::elem elem;
     typedef typename T::vec8 vec8;
     typedef typename T::vec4 vec4;
@@ -182,11 +184,11 @@ __global__ __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_kernel
     const int ld_row = lane / CH;        // row within one wave-wide load
     const int ld_col = (lane % CH) * 8;  // element offset of this lane's 16 bytes
 
-    // tile i of this wave: sequence b = i / tiles_per_slab, k-th tile of the wave inside this member's part
-    const int n_mine = ((B - bg + b_groups - 1) / b_groups) * tiles_per_slab;
-    auto tile_b = [&](int i) { return bg + (i / tiles_per_slab) * b_groups; };
+    // tile i of this wave: sequence b = i / tiles per slab, k-th tile of the wave inside this member's part
+    const int n_mine = ((B - bg + b_groups - 1) / b_groups) * (int)by_slab.d;
+    auto tile_b = [&](int i) { return bg + (int)by_slab.div((uint32_t)i) * b_groups; };
     auto tile_row0 = [&](int i) {
-        const int k = i % tiles_per_slab;
+        const int k = (int)by_slab.mod((uint32_t)i);
         return ((int64_t)(k * members + member) * kScrWaves + wave) * kScrRows;
     };
     auto slab_off = [&](int i) { return ((int64_t)tile_b(i) * H + h) * L * D; };
@@ -212,7 +214,8 @@ __global__ __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_kernel
 
     auto step = [&](vec8 (&buf)[NI], int i, bool reload, int32_t& idx_next) {
         const int64_t row0 = tile_row0(i);
-        elem* Y = Yj + slab_off(i);
+        const int64_t slab_row0 = ((int64_t)tile_b(i) * H + h) * L;
+        elem* Y = Yj + slab_row0 * D;
         // rows -> LDS tile
 #pragma unroll
         for (int k = 0; k < NI; ++k) *(vec8*)(&my[(k * RPI + ld_row) * LDP + ld_col]) = buf[k];
@@ -273,33 +276,33 @@ __global__ __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_kernel
                 float lo = x[0], hi = x[0];
 #pragma unroll
                 for (int e = 1; e < 8; ++e) { lo = fminf(lo, x[e]); hi = fmaxf(hi, x[e]); }
-                lo = group_min<CH>(lo);
-                hi = group_max<CH>(hi);
+                group_min_max<CH>(lo, hi);
                 const float range = hi - lo;
                 const float scale = range / (float)LEVELS;
                 // x - lo >= 0, so the sum is >= 1/2: converting to unsigned truncates = floors, and only the upper
                 // clamp can act; a constant row (range 0) gets steps 0, hence code 0
                 const float steps = range > 0.0f ? (float)LEVELS / range : 0.0f;
-                // 8 bits: floor, then the conversion to a byte, which saturates at 255 (the upper clamp of the
-                // definition; the argument is >= 1/2, so there is no lower one) and packs the code into its place
+                // 8 bits: the sum is below 256 (x - lo <= range, and range * steps rounds to 255 or one unit above it), so
+                // the truncated byte is the code; an infinite sum (a range too small for 255 / range) truncates to 255,
+                // the upper clamp of the definition, and a NaN (0 times that) to 0
                 uint32_t q[8];
                 u32x2_t w8;
                 w8[0] = w8[1] = 0u;
                 if (QB == 8) {
+                    float t[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const uint32_t old = e < 4 ? w8[0] : w8[1];
-                        const uint32_t nw = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_floorf(__builtin_fmaf(x[e] - lo, steps, 0.5f)), e % 4, old);
-                        if (e < 4) w8[0] = nw;
-                        else w8[1] = nw;
-                    }
+                    for (int e = 0; e < 8; ++e) t[e] = __builtin_fmaf(x[e] - lo, steps, 0.5f);
+                    uint32_t b0, b1;
+                    bytes_of(t, b0, b1);
+                    w8[0] = b0;
+                    w8[1] = b1;
                 } else {
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
                         q[e] = (uint32_t)fminf(__builtin_fmaf(x[e] - lo, steps, 0.5f), (float)LEVELS);
                 }
                 if (j < L) {
-                    const int64_t row = slab_off(i) / D + j;  // row index over the whole tensor
+                    const int64_t row = slab_row0 + j;  // row index over the whole tensor
                     uint8_t* out = (uint8_t*)job.Y + row * (D * QB / 8);
                     if (QB == 8) {
                         __builtin_nontemporal_store(w8, (u32x2_t*)(out + (lane % CH) * 8));
@@ -716,7 +719,7 @@ static hipError_t launch_scramble16(const RowsJob& j, hipStream_t stream) {
     const ScrambleJob a = device_job(j, 0), b = device_job(j, 1);
 #define FEDRAG_SCR_LAUNCH(ST_, QB_)                                                                              \
     hipLaunchKernelGGL((scramble_rows_kernel<T, D, ST_, QB_>), grid, dim3(waves * kWave), 0, stream, a, b, j.perm, \
-                       j.perm_batch_stride, B, j.H, j.G, j.L, members, tiles_per_slab, b_groups)
+                       j.perm_batch_stride, B, j.H, j.G, j.L, members, FastDiv(tiles_per_slab), b_groups)
     if (j.structured) {
         if (j.quant_bits == 8) FEDRAG_SCR_LAUNCH(true, 8);
         else if (j.quant_bits == 4) FEDRAG_SCR_LAUNCH(true, 4);
