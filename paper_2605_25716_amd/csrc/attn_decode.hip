@@ -438,7 +438,12 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
         int i = 0;
         for (; i + 2 * NBUF <= n_mine; i += NBUF) {
 #pragma unroll
-            for (int j = 0; j < NBUF; ++j) step(t[j], tile_key(i + j), false, true, tile_of(i + j + NBUF));
+            for (int j = 0; j < NBUF; ++j) {
+                step(t[j], tile_key(i + j), false, true, tile_of(i + j + NBUF));
+                // d = 64: without a fence the steps of both sets are scheduled into one another, and the loop waits for
+                // every load in flight at its top (8 shards of 25479 keys, 32 units: 283 us, 255 with the fence)
+                if (D == 64) __builtin_amdgcn_sched_barrier(0);
+            }
         }
         // fewer than 2*NBUF tiles left: refills become conditional, then the ring drains
 #pragma unroll
