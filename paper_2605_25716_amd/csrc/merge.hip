@@ -12,8 +12,8 @@ namespace fedrag {
 // one log-sum-exp and evaluates one exponential, and a weight reaches the others by a lane shuffle - the first batch of
 // partials is in flight before the weights are known, and the workgroups are one wave while rows are few.  Sums are
 // formed in shard order whatever the batch.
-// 32 rows of 128 over 16 partials in a chain of calls: 4.6 us (12.6 with one partial after the other); 3744 rows over 15:
-// about 9.5 us (11 with every thread evaluating every weight).
+// 32 rows of 128 over 16 partials in a chain of calls: 4.1 us (12.6 with one partial after the other); 3744 rows over 15:
+// 6.7 us (8.0 with every thread evaluating every weight).
 
 // max over the TPR = 16 or 32 consecutive lanes that hold a row
 template <int TPR>
