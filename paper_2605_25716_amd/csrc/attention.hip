@@ -118,13 +118,6 @@ KeyRuns attn_runs_of(const AttnProblem& p) {
         KeyRuns r = attn_plan_runs(p.B, p.Hq, p.Hkv, p.dtype, p.Lq, 1, &p.Lkv, p.quant_bits == 4 && p.D == 128);
         r.s[0].K = p.K;
         r.s[0].V = p.V;
-        if (p.single_run && r.n_runs > 1) {  // all keys of the shard in one run (a whole number of key tiles)
-            const int64_t q = use_decode_kernel(p.Hq, p.Hkv, p.Lq) ? kDecStride : kPreK;
-            r.s[0].per = ((r.s[0].L + q - 1) / q) * q;
-            r.first[1] = 1;
-            r.n_runs = 1;
-            r.by_runs = FastDiv(1);
-        }
         return r;
     }
     KeyRuns r = attn_plan_runs(p.B, p.Hq, p.Hkv, p.dtype, p.Lq, p.n_shards, p.Ls);
@@ -188,6 +181,9 @@ hipError_t launch_partial_attn(const AttnProblem& p_in, hipStream_t stream) {
         const bool decode = use_decode_kernel(p.Hq, p.Hkv, p.Lq);
         if (p.dtype == FEDRAG_F32) return launch_attn_f32(p, stream);
         if (p.dtype != FEDRAG_BF16 && p.dtype != FEDRAG_F16) return hipErrorInvalidValue;
+        // Prefill shapes: one launch, a partial per run and never less than one per shard (a workgroup that visited all
+        // shards with its state took 7.42 ms against 7.97 for 8 shards of 8192 keys, 4096 x 64 query rows, but held the
+        // weights between the shards in the 16 bits of the probabilities).
         if (!decode) return launch_prefill_attn(p, stream);
         bool one_launch_per_shard = (int64_t)p.B * p.Hkv >= attn_target_wgs();
         if (one_launch_per_shard) {
@@ -199,7 +195,8 @@ hipError_t launch_partial_attn(const AttnProblem& p_in, hipStream_t stream) {
                 if (plan.first[i + 1] - plan.first[i] > 1) one_launch_per_shard = false;
         }
         if (one_launch_per_shard) {
-            // one launch per non-empty shard into the workspace ([n][rows][D] then [n][rows]), then the aggregation
+            // one launch per non-empty shard into the workspace ([n][rows][D] then [n][rows]), then the aggregation.  A shard
+            // alone is planned as one run too (units >= compute units), so its launch needs no workspace of its own.
             int idx[kMaxShards], n = 0;
             for (int i = 0; i < p.n_shards; ++i)
                 if (p.Ls[i] > 0) idx[n++] = i;
@@ -213,7 +210,6 @@ hipError_t launch_partial_attn(const AttnProblem& p_in, hipStream_t stream) {
                 one.K = p.Ks[idx[j]];
                 one.V = p.Vs[idx[j]];
                 one.Lkv = p.Ls[idx[j]];
-                one.single_run = true;  // the workspace holds the per-shard partials: no runs inside a shard
                 one.workspace = nullptr;
                 one.workspace_bytes = 0;
                 one.O = Ow + (size_t)j * rows * p.D;

@@ -36,17 +36,14 @@ constexpr int kPrePD = FEDRAG_PRE_PD;         // MFMA operands are read from LDS
 // storage type (relative error 2^-9 in bf16) would move an output by more than the 16-bit output tolerance.  The
 // CAUSAL instantiation therefore feeds the second product P = P_hi + P_lo, two storage-type terms (about 16
 // significant bits), at the price of twice the MFMAs of that product.
-// WALK: the launch has several shards and its query tiles alone cover the chip, so a workgroup visits all of them, one after
-// the other, and carries its running maximum, sum and output from shard to shard: no partials and no aggregation (eight
-// shards of 8192 keys, 4096 x 64 query rows: 7.72 ms against 8.22 with a launch per shard and 1.2 GB of partials
-// written and folded).  Only in the plain form; the host leaves empty shards out of the table.
-template <class T, int D, bool CAUSAL, int QB, int NW, bool WALK>
+template <class T, int D, bool CAUSAL, int QB, int NW>
 __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefill_attn_kernel(const typename T::elem* __restrict__ Q,
                                                                       const KeyRuns runs,
                                                                       const float* __restrict__ Kprm,
                                                                       const float* __restrict__ Vprm, int Hq,
                                                                       FastDiv by_heads, FastDiv by_group,
-                                                                      FastDiv by_tiles, FastDiv by_unit, int64_t Lq,
+                                                                      FastDiv by_tiles, FastDiv by_unit,
+                                                                      FastDiv by_inner, int run_by_run, int64_t Lq,
                                                                       const int32_t* __restrict__ kv_lens,
                                                                       const int32_t* __restrict__ q_lens, int n_units, int fold,
                                                                       float scale_log2,
@@ -61,7 +58,6 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     constexpr int MT = D / 32;              // 32-row tiles of O^T
     constexpr int CH = D / 8;               // 16-byte chunks per row
     constexpr int LPT = (kPreK * CH) / kThreads;  // LDS-direct loads (QB: 8-element chunks) per thread per tile
-    static_assert(!WALK || (!CAUSAL && QB == 0), "several shards: the plain form");
     static_assert(QB == 0 || QB == 8 || QB == 4, "16-bit values, or 8- / 4-bit codes");
     static_assert(QB == 0 || !CAUSAL, "codes are what travels to the Compute Node; the Inquirer's own K, V are plain");
     constexpr int CROWB = QB ? D * QB / 8 : ROWB;  // bytes per row of K' / V' as stored (values, or codes)
@@ -74,6 +70,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     // give every XCD whole (sequence, KV head) units so that the workgroups sharing K'/V' share an L2.
     // With more than one run (several shards, or few query tiles and many keys; not CAUSAL) there is one workgroup
     // per (query tile, run) and O / lse are [n_runs][rows] partials that the Section 4.1 aggregation folds afterwards.
+    // The launch chooses which of the two varies faster inside a unit (by_inner: the number of runs, or of query tiles).
     const int G = (int)by_group.d;
     const int n_runs = runs.n_runs;
     const int xcd = blockIdx.x % 8;
@@ -82,10 +79,11 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     const int unit = xcd + 8 * unit_slot;
     if (unit >= n_units) return;
     const int in_unit = slot - unit_slot * (int)by_unit.d;
-    const int w_in_unit = (int)runs.by_runs.div(in_unit);
-    const int run = in_unit - w_in_unit * n_runs;
+    const int outer = (int)by_inner.div(in_unit), inner = in_unit - outer * (int)by_inner.d;
+    const int w_in_unit = run_by_run ? inner : outer;
+    const int run = run_by_run ? outer : inner;
     int split = 0;
-    const KeyShard shard = WALK ? runs.s[0] : runs.shard_of(run, &split);
+    const KeyShard shard = runs.shard_of(run, &split);
     const elem* K = (const elem*)shard.K;
     const elem* V = (const elem*)shard.V;
     const int64_t L_stride = shard.L;
@@ -131,7 +129,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     const int64_t part_row0 = (int64_t)run * n_units * G * Lq;  // n_units * G * Lq = rows of one partial
     float* Oh = O + (part_row0 + ((int64_t)b * Hq + h) * Lq) * D;
     float* Lh = lse + part_row0 + ((int64_t)b * Hq + h) * Lq;
-    if (!CAUSAL && !WALK && n_runs > 1) {  // this workgroup's run of keys; a run past the end is empty
+    if (!CAUSAL && n_runs > 1) {  // this workgroup's run of keys; a run past the end is empty
         const int64_t k_begin = (int64_t)split * keys_per_run;
         const int64_t k_end = k_begin + keys_per_run < L ? k_begin + keys_per_run : L;
         L = k_end > k_begin ? k_end - k_begin : 0;
@@ -256,7 +254,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     const int64_t q_last = (q_first + kQTile < Lq ? q_first + kQTile : Lq) - 1;
     const int64_t wg_keys = CAUSAL ? (q_last + off + 1 < L ? q_last + off + 1 : L) : L;
     const int n_tiles = (int)((wg_keys + kPreK - 1) / kPreK);
-    int t_mask0 = (int)((CAUSAL ? (q_first + off + 1 < L ? q_first + off + 1 : L) : L) / kPreK);
+    const int t_mask0 = (int)((CAUSAL ? (q_first + off + 1 < L ? q_first + off + 1 : L) : L) / kPreK);
     // prologue: K' of the last tile is fetched first, Q' behind it
     int tile = n_tiles - 1;
     if constexpr (QB == 0) load_tile(Kg, ks0, tile, true);
@@ -266,7 +264,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qop[ks] = *(const vec8*)(Qh + q_ld * D + ks * 16 + lh * 8);
 
-    int key_lim = (int)(CAUSAL ? (q_row + off + 1 < L ? q_row + off + 1 : L) : L);  // this lane's row sees keys < key_lim
+    const int key_lim = (int)(CAUSAL ? (q_row + off + 1 < L ? q_row + off + 1 : L) : L);  // this lane's row sees keys < key_lim
     f32x16_t S0;      // S^T of the current tile, keys 0..31
     f32x16_t S1[2];   // S1[t & 1]: S^T of tile t, keys 32..63 (kept one iteration longer, see below)
     vec8 P[2][4];     // P[t & 1]: P^T operands of tile t, one per 16-key step
@@ -467,44 +465,29 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
         __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), the other counters untouched
         __syncthreads();
     };
-    for (int sh = 0;;) {
+    if constexpr (QB != 0) store_codes(ks0, kst, true);
+    alph[0] = alph[1] = 1.0f;
+    tile_barrier();
+    // masked tiles are finished one by one, except the last of them, which the pipeline starts with
+    while (tile > t_mask0 || (tile & 1)) {
+        iteration(tile, even, first, false);
+        tile_barrier();
+        --tile;
+        if constexpr (QB == 0) load_tile(Kg, ks0, tile, true);
+        else fetch_codes(Kg, Kpg, tile, kst);
+        iteration(tile, odd, last, false);
         if constexpr (QB != 0) store_codes(ks0, kst, true);
-        alph[0] = alph[1] = 1.0f;
         tile_barrier();
-        // masked tiles are finished one by one, except the last of them, which the pipeline starts with
-        while (tile > t_mask0 || (tile & 1)) {
-            iteration(tile, even, first, false);
-            tile_barrier();
-            --tile;
-            if constexpr (QB == 0) load_tile(Kg, ks0, tile, true);
-            else fetch_codes(Kg, Kpg, tile, kst);
-            iteration(tile, odd, last, false);
-            if constexpr (QB != 0) store_codes(ks0, kst, true);
-            tile_barrier();
-        }
-        iteration(tile, even, first, true);
-        tile_barrier();
-        for (; tile > 0; tile -= 2) {
-            iteration(tile - 1, odd, steady, true);
-            tile_barrier();
-            iteration(tile - 2, even, steady, true);
-            tile_barrier();
-        }
-        iteration(-1, odd, last, false);
-        if constexpr (!WALK) {
-            break;
-        } else {
-            if (++sh == runs.n_shards) break;
-            const KeyShard next = runs.s[sh];
-            L = next.L;
-            Kg = (const char*)next.K + (int64_t)unit * L * CROWB;
-            Vg = (const char*)next.V + (int64_t)unit * L * CROWB;
-            tile = (int)((L + kPreK - 1) / kPreK) - 1;
-            t_mask0 = (int)(L / kPreK);
-            key_lim = (int)L;
-            load_tile(Kg, ks0, tile, true);  // ks0 was last read before the barrier ahead of the iteration above
-        }
     }
+    iteration(tile, even, first, true);
+    tile_barrier();
+    for (; tile > 0; tile -= 2) {
+        iteration(tile - 1, odd, steady, true);
+        tile_barrier();
+        iteration(tile - 2, even, steady, true);
+        tile_barrier();
+    }
+    iteration(-1, odd, last, false);
 
     // epilogue: lane holds query li and rows d = 32 i + 8 (r / 4) + 4 lh + r % 4 of O^T.  The rows go out through LDS
     // (the tiles are dead; every wave has its share of them), so that a store covers whole 128-byte lines: straight from
@@ -558,20 +541,31 @@ static bool prefill_wants_4_waves(int64_t wgs8, int64_t wgs4) {
     return rounds4_x10 * 106 < rounds8 * 1000;  // a round of four-wave workgroups takes 6 % longer
 }
 
-template <class T, int D, bool CAUSAL, int QB, int NW, bool WALK>
+// Order of a unit's workgroups when there are several runs.  The runs of a query tile side by side, unless one run's
+// workgroups fill the chip by themselves and a unit's keys are several times an XCD's 4 MiB of L2: then run by run, so that
+// the workgroups at work share the keys of one shard (8 shards of 8192 keys, 4096 x 64 query rows: 7.97 ms, 8.24 side by
+// side, 8.02 with a launch per shard; at 8 MB of keys both orders take the same time, at 3 MB run by run is 5 % slower).
+constexpr int64_t kPreRunByRunBytes = 16 << 20;
+
+template <class T, int D, bool CAUSAL, int QB, int NW>
 static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, int Hq_k, int64_t Lq_k, int64_t q_tiles,
                                     float* Odst, float* Ldst, hipStream_t stream) {
     typedef typename T::elem elem;
     const int n_units = p.B * p.Hkv;
-    const int64_t per_unit = (int64_t)(Hq_k / p.Hkv) * q_tiles * runs.n_runs;
+    const int64_t tiles_of_unit = (int64_t)(Hq_k / p.Hkv) * q_tiles;
+    const int64_t per_unit = tiles_of_unit * runs.n_runs;
     const int64_t grid = (int64_t)8 * ((n_units + 7) / 8) * per_unit;
     if (!grid_fits(grid)) return hipErrorInvalidValue;
+    int64_t keys = 0;
+    for (int i = 0; i < runs.n_shards; ++i) keys += runs.s[i].L;
+    const bool run_by_run = n_units * tiles_of_unit >= attn_target_wgs() && keys * (4 * D) > kPreRunByRunBytes;
     // With every workgroup resident at once (two per compute unit, started in index order) the second half goes beside
     // the first: the shortest tile to the longest, and all compute units end together (2048 tokens: 65 -> 60 us).
     const int fold = CAUSAL && grid <= 2 * (int64_t)attn_target_wgs() ? 1 : 0;
-    hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB, NW, WALK>), dim3((unsigned)grid), dim3(NW * kWave), 0, stream,
+    hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB, NW>), dim3((unsigned)grid), dim3(NW * kWave), 0, stream,
                        (const elem*)p.Q, runs, p.K_params, p.V_params, Hq_k, FastDiv(p.Hkv), FastDiv(Hq_k / p.Hkv),
-                       FastDiv(q_tiles), FastDiv(per_unit), Lq_k, p.kv_lens, p.q_lens, n_units, fold,
+                       FastDiv(q_tiles), FastDiv(per_unit), FastDiv(run_by_run ? tiles_of_unit : runs.n_runs),
+                       run_by_run ? 1 : 0, Lq_k, p.kv_lens, p.q_lens, n_units, fold,
                        p.scale * kLog2e, Odst, Ldst);
     return hipGetLastError();
 }
@@ -595,20 +589,6 @@ static hipError_t launch_prefill_t(const AttnProblem& p, hipStream_t stream) {
         runs.by_runs = FastDiv(1);
     }
     if (runs.n_runs < 1) return hipErrorInvalidValue;
-    bool walk = false;  // several shards, each of them one run: a workgroup visits them all
-    if (p.n_shards > 1) {
-        int n = 0;
-        for (int i = 0; i < p.n_shards; ++i)
-            if (runs.s[i].L > 0) runs.s[n++] = runs.s[i];
-        walk = runs.n_runs == n;
-        if (walk) {
-            runs.n_shards = n;
-            runs.n_runs = 1;
-            runs.by_runs = FastDiv(1);
-        } else {
-            runs = attn_runs_of(p);
-        }
-    }
     const int splits = runs.n_runs;
     if (QB != 0 && (p.n_shards > 1 || !p.K_params || !p.V_params)) return hipErrorInvalidValue;
     const int64_t rows = (int64_t)p.B * p.Hq * p.Lq;
@@ -623,12 +603,8 @@ static hipError_t launch_prefill_t(const AttnProblem& p, hipStream_t stream) {
     const int64_t heads = (int64_t)p.B * Hq_k * splits;
     const bool four = CAUSAL || p.kv_lens || p.q_lens || prefill_wants_4_waves(heads * tiles8, heads * tiles4);
     hipError_t e = hipErrorInvalidValue;
-    if constexpr (!CAUSAL && QB == 0) {
-        if (walk && !four) e = launch_prefill_nw<T, D, false, 0, 8, true>(p, runs, Hq_k, Lq_k, tiles8, Odst, Ldst, stream);
-        if (walk && four) e = launch_prefill_nw<T, D, false, 0, 4, true>(p, runs, Hq_k, Lq_k, tiles4, Odst, Ldst, stream);
-    }
-    if (!walk && !four) e = launch_prefill_nw<T, D, false, QB, 8, false>(p, runs, Hq_k, Lq_k, tiles8, Odst, Ldst, stream);
-    if (!walk && four) e = launch_prefill_nw<T, D, CAUSAL, QB, 4, false>(p, runs, Hq_k, Lq_k, tiles4, Odst, Ldst, stream);
+    if (four) e = launch_prefill_nw<T, D, CAUSAL, QB, 4>(p, runs, Hq_k, Lq_k, tiles4, Odst, Ldst, stream);
+    else if constexpr (!CAUSAL) e = launch_prefill_nw<T, D, false, QB, 8>(p, runs, Hq_k, Lq_k, tiles8, Odst, Ldst, stream);
     if (e != hipSuccess || splits == 1) return e;
     return launch_lse_merge(Odst, Ldst, splits, rows, D, p.O, p.lse, stream);
 }

@@ -62,7 +62,7 @@ struct AttnProblem {
     int quant_bits;          // 0, or 8 / 4: K, V hold the transport codec's codes and K_params, V_params their
     const float* K_params;   //   per-row (scale, lo), [B,Hkv,Lkv,2] (decode shapes, 16-bit dtype, D = 128 only)
     const float* V_params;
-    int n_shards;            // 0 or 1: K, V, Lkv above; else Ks, Vs, Ls below (16-bit dtype, no codes, no lengths, no mask)
+    int n_shards;            // 0 or 1: K, V, Lkv above; else Ks, Vs, Ls below (no codes, no lengths, no mask)
     const void* Ks[kMaxShards];
     const void* Vs[kMaxShards];
     int64_t Ls[kMaxShards];
@@ -70,9 +70,6 @@ struct AttnProblem {
     const int32_t* q_lens;   // NULL, or [B] device array: only the first q_lens[b] query rows of sequence b are computed
                              //   and written (prefill and fp32 kernels; the decode kernel computes all its <= 16 rows)
     bool causal;  // the Lq queries are the last Lq of the Lkv tokens and see nothing after themselves
-    bool single_run;  // one shard only: its keys are one run whatever the planner would choose, so the launch writes
-                      //   (O, lse) directly and touches no workspace (the per-shard launches of a multi-shard call,
-                      //   whose workspace already holds the per-shard partials)
     float* O;     // [B,Hq,Lq,D]
     float* lse;   // [B,Hq,Lq]
     void* workspace;

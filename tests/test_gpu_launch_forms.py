@@ -1,5 +1,5 @@
 """The launch forms of the attention and aggregation kernels at the sizes where they change over or end raggedly:
-tiles of query rows and of keys, key runs, shards visited in one launch, partials per batch.  Against the oracle, with the
+tiles of query rows and of keys, key runs, shards of one run each, partials per batch.  Against the oracle, with the
 bounds of parity.py; what a form must not touch is poisoned."""
 import numpy as np
 import pytest
@@ -17,23 +17,37 @@ def rnd(B, H, L, d, dt, tid, seed=5):
     return W.activations(B, H, L, d, seed=seed, tensor_id=tid, outliers=False, dtype=W.torch_dtype(dt))
 
 
-# query tiles cover the chip (8 units of 4132 rows): every shard is one run and a workgroup visits them one after the other
+# query tiles cover the chip (8 units of 4132 rows): every shard is one run, with a partial of its own
 @pytest.mark.parametrize("d,dt,Ls", [(64, "bf16", [64, 1, 65]), (128, "bf16", [63, 0, 128, 40, 129]), (128, "f16", [1]),
                                      (64, "f16", [192, 191, 0])])
-def test_shards_visited_in_one_launch(oracle, d, dt, Ls):
+def test_shards_of_one_run_each(oracle, d, dt, Ls):
     Q = rnd(1, 32, 1033, d, dt, W.TID_Q)
     Ks = [rnd(1, 8, L, d, dt, W.TID_K + 16 * (i + 1)) for i, L in enumerate(Ls)]
     Vs = [rnd(1, 8, L, d, dt, W.TID_V + 16 * (i + 1)) for i, L in enumerate(Ls)]
-    print(f"walk {d} {dt} {Ls}", flush=True)
+    print(f"shards {d} {dt} {Ls}", flush=True)
     O, lse = fb.fedrag_partial_attn_shards(Q.to(DEV), [k.to(DEV) for k in Ks], [v.to(DEV) for v in Vs])
     torch.cuda.synchronize()
     Or, lr = oracle.partial_attn(Q, torch.cat(Ks, dim=2), torch.cat(Vs, dim=2))
     PT.check_attn(O, lse, Or, lr, Q.dtype, f"{d} {dt} {Ls}")
 
 
+@pytest.mark.parametrize("d,dt,Ls", [(128, "bf16", [192, 63, 300]), (64, "f16", [128, 0, 65, 512])])
+def test_weights_between_shards_are_fp32(d, dt, Ls):
+    """The weight of a shard's partial is an fp32 number whatever the storage type: the call equals the shards one by one and
+    the aggregation of their partials, bit for bit."""
+    Q = rnd(1, 32, 1033, d, dt, W.TID_Q).to(DEV)
+    Ks = [rnd(1, 8, L, d, dt, W.TID_K + 16 * (i + 1)).to(DEV) for i, L in enumerate(Ls)]
+    Vs = [rnd(1, 8, L, d, dt, W.TID_V + 16 * (i + 1)).to(DEV) for i, L in enumerate(Ls)]
+    O, lse = fb.fedrag_partial_attn_shards(Q, Ks, Vs)
+    parts = [fb.fedrag_partial_attn(Q, k, v) for k, v in zip(Ks, Vs)]
+    Om, lm = fb.fedrag_lse_merge(torch.stack([p[0] for p in parts]), torch.stack([p[1] for p in parts]), n_kv_heads=8)
+    torch.cuda.synchronize()
+    assert torch.equal(O, Om) and torch.equal(lse, lm)
+
+
 def test_every_shard_boundary_keeps_its_keys():
-    """One key tile of one shard holds all the weight of a query row: a tile lost or read twice where a workgroup passes from
-    shard to shard moves that row's log-sum-exp by ln 2 or more."""
+    """One key tile of one shard holds all the weight of a query row: a tile lost or read twice at a shard's end moves that
+    row's log-sum-exp by ln 2 or more."""
     d, L, S, Lq = 128, 256, 3, 1024
     tile = torch.arange(L) // 64
     Q = torch.nn.functional.one_hot(torch.arange(Lq) % 4, d).to(torch.bfloat16).expand(1, 32, Lq, d).contiguous().to(DEV)

@@ -23,10 +23,10 @@ CASES = [
     ("pre_bf16_d64", 2, 2, 2, 64, 300, [1111, 129], "bf16"),
     ("pre_f16", 1, 2, 1, 128, 40, [100, 777], "f16"),
     # enough query tiles to cover the chip: one run per shard
-    ("pre_bf16_walk", 4, 8, 2, 128, 1100, [200, 0, 333], "bf16"),
+    ("pre_bf16_covering", 4, 8, 2, 128, 1100, [200, 0, 333], "bf16"),
     ("f32", 2, 4, 2, 128, 3, [197, 0, 50], "f32"),
-    # prefill shapes where all shards together plan one run per shard (so the call launches shard by shard) while a
-    # shard alone would be cut into runs: the per-shard launches must not cut, the workspace holds the shards' partials
+    # prefill shapes where all shards together plan one run per shard (one partial each, all in one launch) while a
+    # shard alone would be cut into runs
     ("pre_bf16_two_shards_one_run_each", 1, 32, 8, 64, 1024, [1024, 1024], "bf16"),
     ("pre_bf16_16_shards_one_run_each", 2, 32, 8, 64, 64, [512] * 16, "bf16"),
     ("pre_f16_4_shards_one_run_each", 1, 32, 8, 128, 512, [1024] * 4, "f16"),
@@ -57,7 +57,7 @@ def test_shards_equal_per_shard_then_merge_and_concatenation(oracle, case):
     PT.check_attn(O, lse, Oc, lc, dtype, name + " vs concatenated keys")
 
 
-def test_planner_geometries_launch_shard_by_shard():
+def test_planner_geometries_have_one_run_per_shard():
     """The three cases above exist for one geometry: more than one run for a shard on its own, one run per shard for
     all of them together.  The workspace sizes say which plan the library made."""
     for (B, Hq, Hkv, d, Lq, Ls) in [(1, 32, 8, 64, 1024, [1024, 1024]), (2, 32, 8, 64, 64, [512] * 16),
