@@ -152,15 +152,15 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     f32x16_t acc_o[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i) acc_o[i] = zero_vec<f32x16_t>();
-    // The running maximum starts at the lowest finite value: a row may see no key of the first tiles that its workgroup
-    // visits, and -inf - m_run has to be -inf then.
-    float m_run = -__FLT_MAX__, l_run = 0.f;
+    // CAUSAL: the running maximum starts at the lowest finite value: a row may see no key of the first tiles that its
+    // workgroup visits, and -inf - m_run has to be -inf then.
+    float m_run = CAUSAL ? -__FLT_MAX__ : -INFINITY, l_run = 0.f;
 
     // ---- global -> LDS (direct buffer loads).  One wave-wide load fills 64 consecutive 16-byte slots = 64 / CH
     // tile rows.  LDS slot p of row r holds global chunk p ^ swz(r): K' swz(r) = r % CH, V' swz(r) = (4 (r % 4)) % CH;
     // both depend on r only through r % 16, which is the same for every load of a thread.  The buffer resource
-    // starts at the tile and covers the rest of the shard, so rows past the end of the shard arrive as zeros; tile -1, which
-    // the steady loop asks for behind its last one, reads nothing.
+    // starts at the tile and covers the rest of the shard, so rows past the end of the shard arrive as zeros; tile -1 and
+    // tiles past the end, which the loops ask for behind their last one, read nothing.
     constexpr int RPW = kWave / CH;  // rows per wave-wide load
     const int ld_r = wave * RPW + lane / CH;  // row within a group of NW * RPW rows
     const int ld_p = lane % CH;               // slot within the row
@@ -170,7 +170,8 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     auto load_tile = [&](const char* G_, char* slot_base, int tile, bool is_k) {
         const int64_t byte0 = (int64_t)tile * SLOT;
         const int64_t left = L * ROWB - byte0;
-        const int n_rec = tile < 0 ? 0 : (int)(left < 0x7fffffff ? left : 0x7fffffff);
+        const bool none = CAUSAL ? tile < 0 : left < 0;
+        const int n_rec = none ? 0 : (int)(left < 0x7fffffff ? left : 0x7fffffff);
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(G_ + byte0), 0, n_rec, 0x00020000);
 #pragma unroll
         for (int j = 0; j < LPT; ++j) {
@@ -191,7 +192,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     const int cq_row = tid / CH, cq_c = tid % CH;
     auto fetch_codes = [&](const char* G_, const float* Pg_, int tile, CodeChunk (&st)[QB ? LPT : 1]) {
         const int64_t row0 = (int64_t)tile * kPreK;
-        const int64_t left_rows = tile >= 0 && L - row0 > 0 ? L - row0 : 0;
+        const int64_t left_rows = L - row0 > 0 ? L - row0 : 0;
         const int64_t lc = left_rows * CROWB, lp = left_rows * 8;
         const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
             (void*)(G_ + row0 * CROWB), 0, (int)(lc < 0x7fffffff ? lc : 0x7fffffff), 0x00020000);
@@ -255,8 +256,8 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     const int64_t wg_keys = CAUSAL ? (q_last + off + 1 < L ? q_last + off + 1 : L) : L;
     const int n_tiles = (int)((wg_keys + kPreK - 1) / kPreK);
     const int t_mask0 = (int)((CAUSAL ? (q_first + off + 1 < L ? q_first + off + 1 : L) : L) / kPreK);
-    // prologue: K' of the last tile is fetched first, Q' behind it
-    int tile = n_tiles - 1;
+    // prologue: K' of the first tile to visit is fetched first, Q' behind it
+    int tile = CAUSAL ? n_tiles - 1 : 0;
     if constexpr (QB == 0) load_tile(Kg, ks0, tile, true);
     else fetch_codes(Kg, Kpg, tile, kst);
     const int64_t q_ld = q_row < Lq ? q_row : Lq - 1;
@@ -295,14 +296,17 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     // Splitting the softmax of a tile over two phases gives both MFMA phases about the same vector load.
     // `par` carries t % 2 as a compile-time constant so that the double-buffered register sets are addressed
     // statically.  m_run is the running maximum after tile t-1 until B1(t) replaces it.
-    // Tiles are visited from the last one down (tile n_tiles - 1 - visit), so that those with keys that some row must not
-    // see come first: the ragged end of the shard, or the tiles on the diagonal.  t counts the visits of the pipelined
-    // part: t = 0 is its first tile and has no C, t = n is nothing but B2 and C of tile n - 1, all between run both
-    // phases on tiles that every row sees whole.  Only the kFirst form masks.  (A tail of masked tiles behind the steady
-    // loop, its stages switched by runtime flags, spilled its registers: 9000 cycles per tile against 1300 to 2600,
-    // most of the time of a segment of a few hundred tokens; masking in the steady loop made that loop 15 % slower.)
+    // t counts the visits of the pipelined part: t = 0 is its first tile and has no C, t = n is nothing but B2 and C of
+    // tile n - 1, all between run both phases on tiles that every row sees whole.  Only the kFirst form masks; a masked
+    // tile is one kFirst and one kLast by itself, outside the pipeline.  (A tail of masked tiles behind the steady loop, its
+    // stages switched by runtime flags, spilled its registers: 9000 cycles per tile against 1300 to 2600, most of the time
+    // of a segment of a few hundred tokens; masking in the steady loop made that loop 15 % slower.)
+    // The order of the tiles decides which probabilities are exact (those of the keys that raise the maximum) and so the
+    // bits of the result.  Plain: first to last, the one ragged tile at the end.  CAUSAL, whose two terms of P leave no such
+    // error: last to first, so that the pipeline starts with the last of the tiles on the diagonal.
+    // `next` is the tile after this one, whose K' is fetched meanwhile (ldK).
     enum { kFirst, kSteady, kLast };
-    auto iteration = [&](int tile, auto par, auto stage, bool ldK) {
+    auto iteration = [&](int tile, int next, auto par, auto stage, bool ldK) {
         constexpr int p = decltype(par)::value;  // t & 1
         constexpr int q = 1 - p;                 // (t - 1) & 1 == (t + 1) & 1
         constexpr int kind = decltype(stage)::value;
@@ -311,10 +315,10 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
         constexpr int NM = 4 * MT;
         static_assert(NM == 16 || NM == 8, "slice plans assume d = 128 or 64");
         if constexpr (QB == 0) {
-            if (ldK) load_tile(Kg, q ? ks1 : ks0, tile - 1, true);  // K'(t+1) -> slot (t+1) & 1 (last read by A(t-1))
+            if (ldK) load_tile(Kg, q ? ks1 : ks0, next, true);  // K'(t+1) -> slot (t+1) & 1 (last read by A(t-1))
             if constexpr (doAB) load_tile(Vg, p ? vs1 : vs0, tile, false);  // V'(t) -> slot t & 1 (last read by C(t-2))
         } else {  // the codes of the same two tiles into registers; they reach their (free) slots between the phases
-            if (ldK) fetch_codes(Kg, Kpg, tile - 1, kst);
+            if (ldK) fetch_codes(Kg, Kpg, next, kst);
             if constexpr (doAB) fetch_codes(Vg, Vpg, tile, vst);
         }
 
@@ -468,26 +472,54 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     if constexpr (QB != 0) store_codes(ks0, kst, true);
     alph[0] = alph[1] = 1.0f;
     tile_barrier();
-    // masked tiles are finished one by one, except the last of them, which the pipeline starts with
-    while (tile > t_mask0 || (tile & 1)) {
-        iteration(tile, even, first, false);
+    if constexpr (CAUSAL) {
+        // masked tiles are finished one by one, except the last of them, which the pipeline starts with; it takes an odd
+        // number of tiles
+        while (tile > t_mask0 || (tile & 1)) {
+            iteration(tile, 0, even, first, false);
+            tile_barrier();
+            --tile;
+            load_tile(Kg, ks0, tile, true);
+            iteration(0, 0, odd, last, false);
+            tile_barrier();
+        }
+        iteration(tile, tile - 1, even, first, true);
         tile_barrier();
-        --tile;
-        if constexpr (QB == 0) load_tile(Kg, ks0, tile, true);
-        else fetch_codes(Kg, Kpg, tile, kst);
-        iteration(tile, odd, last, false);
-        if constexpr (QB != 0) store_codes(ks0, kst, true);
+        for (; tile > 0; tile -= 2) {
+            iteration(tile - 1, tile - 2, odd, steady, true);
+            tile_barrier();
+            iteration(tile - 2, tile - 3, even, steady, true);
+            tile_barrier();
+        }
+        iteration(0, 0, odd, last, false);
+    } else {
+        // the pipeline takes the largest odd number of whole tiles (tile 0 in any case); what is left, a whole tile, the
+        // ragged one or both, is finished one by one behind it.  Their K' arrives in the slot of odd tiles, where the
+        // pipeline's last iteration has put the next one.
+        const int n_pipe = t_mask0 <= 2 ? 1 : t_mask0 - 1 + (t_mask0 & 1);
+        iteration(0, 1, even, first, true);
         tile_barrier();
+        for (tile = 1; tile < n_pipe; tile += 2) {
+            iteration(tile, tile + 1, odd, steady, true);
+            tile_barrier();
+            iteration(tile + 1, tile + 2, even, steady, true);
+            tile_barrier();
+        }
+        iteration(0, 0, odd, last, false);
+        for (tile = n_pipe; tile < n_tiles;) {
+            iteration(tile, 0, odd, first, false);
+            tile_barrier();
+            const bool more = ++tile < n_tiles;
+            if (more) {
+                if constexpr (QB == 0) load_tile(Kg, ks1, tile, true);
+                else fetch_codes(Kg, Kpg, tile, kst);
+            }
+            iteration(0, 0, even, last, false);
+            if (!more) break;
+            if constexpr (QB != 0) store_codes(ks1, kst, true);
+            tile_barrier();
+        }
     }
-    iteration(tile, even, first, true);
-    tile_barrier();
-    for (; tile > 0; tile -= 2) {
-        iteration(tile - 1, odd, steady, true);
-        tile_barrier();
-        iteration(tile - 2, even, steady, true);
-        tile_barrier();
-    }
-    iteration(-1, odd, last, false);
 
     // epilogue: lane holds query li and rows d = 32 i + 8 (r / 4) + 4 lh + r % 4 of O^T.  The rows go out through LDS
     // (the tiles are dead; every wave has its share of them), so that a store covers whole 128-byte lines: straight from

@@ -60,6 +60,34 @@ def test_every_shard_boundary_keeps_its_keys():
         assert float((lse.double() - expect).abs().max()) <= PT.TOL_16_LSE_ABS, which
 
 
+# key tiles are visited first to last: odd and even counts, with and without a ragged one; 8- and 4-wave workgroups
+@pytest.mark.parametrize("d,dt,Lq,tiles,tail", [(128, "bf16", 512, 5, 0), (128, "bf16", 40, 6, 1), (64, "bf16", 300, 3, 63),
+                                                (64, "f16", 512, 4, 30), (128, "f16", 100, 2, 0), (64, "bf16", 512, 8, 2)])
+@pytest.mark.parametrize("form", ["plain", "lengths"])
+def test_keys_that_raise_the_maximum_are_exact(d, dt, Lq, tiles, tail, form):
+    """One key per tile carries the weight and each has a higher score than the one before: it is the row's maximum when
+    its tile is visited, so its probability is exactly 1 and what is left are fp32 rescales.  In another order the lower
+    ones would be rounded to the storage type (2^-9 or 2^-12 of their weight)."""
+    L = 64 * tiles + tail
+    Q = torch.zeros(1, 32, Lq, d)
+    Q[..., 0] = 16.0
+    K = torch.zeros(1, 8, L, d)
+    K[..., 0] = -300.0
+    hot = [min(64 * t + (37 * t) % 64, L - 1) for t in range((L + 63) // 64)]
+    K[:, :, hot, 0] = torch.arange(len(hot)) * 0.3
+    K, V = K.to(W.torch_dtype(dt)), rnd(1, 8, L, d, dt, W.TID_V)
+    Qd, Kd, Vd = Q.to(W.torch_dtype(dt)).to(DEV), K.to(DEV), V.to(DEV)
+    if form == "plain":
+        O, _ = fb.fedrag_partial_attn(Qd, Kd, Vd, 1.0 / 16.0)
+    else:
+        O, _ = fb.fedrag_partial_attn_varlen(Qd, Kd, Vd, torch.tensor([L], dtype=torch.int32, device=DEV), 1.0 / 16.0)
+    torch.cuda.synchronize()
+    p = torch.softmax(K[..., 0].double(), -1)  # [1, 8, L]
+    want = (p[..., None] * V.double()).sum(2)  # [1, 8, d]
+    # one fp32 exponential (2^-22) and rescale per tile of a weighted mean of |v| <= 5
+    assert float((O.cpu().double() - want.repeat_interleave(4, 1)[:, :, None]).abs().max()) <= 1e-5
+
+
 # 128-row tiles and 64-key tiles of the masked form; the last two launches are one past the fold of the tile order
 @pytest.mark.parametrize("B,Hq,d,Lq,L,dt", [(1, 4, 128, 128, 128, "bf16"), (1, 4, 128, 129, 129, "bf16"),
                                             (1, 2, 128, 127, 191, "f16"), (1, 4, 64, 65, 130, "bf16"),
