@@ -383,7 +383,8 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
         vec8 ph, pl;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float pe = fast_exp2(p[e] - m_new);
+            // one rounding of the exponent's argument: scores of some hundreds leave 2^-15 in a product rounded first
+            const float pe = fast_exp2(masked ? p[e] - m_new : __builtin_fmaf(s[e / 4][e % 4], scale_log2, -m_new));
             psum += pe;
             ph[e] = T::from_float(pe);
             pl[e] = T::from_float(pe - T::to_float(ph[e]));

@@ -181,6 +181,31 @@ def test_decode_on_4bit_codes_of_every_scale(dt):
     assert torch.equal(O, ref.expand(B, 2, 1, d))
 
 
+@pytest.mark.parametrize("bits", [8, 4, 0])
+def test_decode_rounds_the_exponent_once(bits):
+    """Scores around 960, exact in fp32: rounding score x scale before the maximum is taken off would leave up to 2^-14 in the
+    exponent, 4e-5 of a probability, the same for all keys of a score.  What is left otherwise, times a mean |v| of 0.8: the
+    exponential (2^-22) and two fp16 terms of probabilities >= e^-3.75 (2^-25 absolute from subnormals)."""
+    L, d = 1024, 128
+    K = torch.zeros(1, 1, L, d)
+    K[..., 0], K[..., 1] = 60.0, 4.0 * (torch.arange(L) * 7 % 16)  # rows of range 60: 4- (8-) bit codes are exact
+    Q = torch.zeros(1, 4, 1, d)
+    Q[..., 0], Q[..., 1] = 16.0, 0.0625
+    V = rnd(1, 1, 16, d, "f16", W.TID_V)[:, :, torch.arange(L) * 7 % 16]  # one value per score
+    Q, K, V = Q.half().to(DEV), K.half().to(DEV), V.contiguous().to(DEV)
+    if bits:
+        Vc, Vp = fb.fedrag_quantize_rows(V, bits)
+        V = fb.fedrag_dequantize_rows(Vc, Vp, bits, V.dtype)
+        O, _ = fb.fedrag_partial_attn_quantized(Q, *fb.fedrag_quantize_rows(K, bits), Vc, Vp, bits, 1.0)
+    else:
+        O, _ = fb.fedrag_partial_attn(Q, K, V, 1.0)
+    torch.cuda.synchronize()
+    p = torch.softmax(960.0 + K[0, 0, :, 1].double() / 16.0, 0)
+    err = float((O[0].double() - (p[:, None] * V[0, 0].double()).sum(0)).abs().max())
+    print(f"bits {bits}: {err:.2e}")
+    assert err <= 1e-6
+
+
 @pytest.mark.parametrize("L", [1, 64, 65, 256, 300])
 def test_lse_scatter(L):
     lse = torch.randn((2, 3, L))
