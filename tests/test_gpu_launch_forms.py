@@ -104,10 +104,14 @@ def test_masked_tiles(oracle, B, Hq, d, Lq, L, dt):
     PT.check_attn(O, lse, Or, lr, Q.dtype, f"local {Lq} of {L}")
 
 
-# fp32: 16 query rows per workgroup, 32 once those cover the chip (last case); 16-key tiles over 8 waves
+# fp32: 16 query rows per workgroup, 32 where there are more and those cover the chip (last three cases); 16-key tiles over
+# 8, 4, 2 or 1 waves, by the number of workgroups and of tiles
 @pytest.mark.parametrize("B,Hq,Hkv,d,Lq,L", [(1, 2, 2, 64, 16, 1), (1, 2, 2, 128, 17, 15), (1, 4, 2, 128, 8, 16),
                                              (2, 4, 1, 64, 5, 127), (1, 2, 1, 128, 3, 128), (1, 2, 2, 64, 33, 129),
-                                             (1, 8, 2, 128, 1, 513), (4, 8, 8, 64, 250, 70), (4, 8, 8, 128, 256, 33)])
+                                             (1, 8, 2, 128, 1, 513), (1, 2, 2, 64, 5, 20), (1, 4, 2, 128, 3, 50),
+                                             (1, 2, 2, 64, 3, 65), (128, 8, 8, 64, 1, 40), (64, 8, 8, 128, 1, 90),
+                                             (257, 8, 8, 64, 2, 5), (256, 8, 8, 128, 1, 4), (256, 8, 8, 128, 1, 21),
+                                             (33, 8, 8, 128, 40, 60), (4, 8, 8, 64, 250, 70), (4, 8, 8, 128, 256, 33)])
 def test_fp32_tiles(oracle, B, Hq, Hkv, d, Lq, L):
     Q, K, V = (rnd(B, h, n, d, "f32", t) for h, n, t in ((Hq, Lq, W.TID_Q), (Hkv, L, W.TID_K), (Hkv, L, W.TID_V)))
     print(f"f32 {B} {Hq} {Hkv} {d} {Lq} {L}", flush=True)
@@ -123,6 +127,27 @@ def test_fp32_tiles(oracle, B, Hq, Hkv, d, Lq, L):
         torch.cuda.synchronize()
         Or, lr = oracle.local_causal_attn(Q, K, V)
         PT.check_attn(O, lse, Or, lr, torch.float32, "masked")
+
+
+@pytest.mark.parametrize("B,H,d,Lq,L", [(3, 2, 64, 70, 90), (128, 16, 128, 40, 17), (64, 8, 64, 33, 50)])
+def test_fp32_padding_rows(oracle, B, H, d, Lq, L):
+    """Per-sequence counts in fp32: whole tiles of padding rows, partly filled ones and sequences without rows or keys; what is
+    padding is neither read nor written."""
+    Q, K, V = (rnd(B, H, n, d, "f32", t) for n, t in ((Lq, W.TID_Q), (L, W.TID_K), (L, W.TID_V)))
+    ql = torch.tensor([(7 * b + 1) % (Lq + 1) for b in range(B)], dtype=torch.int32)
+    kl = torch.tensor([(5 * b + L) % (L + 1) for b in range(B)], dtype=torch.int32)
+    O, lse = torch.full((B, H, Lq, d), -7.0, device=DEV), torch.full((B, H, Lq), -7.0, device=DEV)
+    Kp, Vp = K.clone(), V.clone()
+    for b in range(B):
+        Kp[b, :, kl[b]:], Vp[b, :, kl[b]:] = float("nan"), float("inf")
+    fb.fedrag_partial_attn_varlen(Q.to(DEV), Kp.to(DEV), Vp.to(DEV), kl.to(DEV), None, O_part=O, lse=lse, q_lens=ql.to(DEV))
+    torch.cuda.synchronize()
+    for b in sorted({0, 1, 2, B // 2, B - 1}):
+        q, k = int(ql[b]), int(kl[b])
+        assert bool((O[b, :, q:] == -7.0).all()) and bool((lse[b, :, q:] == -7.0).all())
+        if q:
+            Or, lr = oracle.partial_attn(Q[b:b + 1, :, :q].contiguous(), K[b:b + 1, :, :k].contiguous(), V[b:b + 1, :, :k].contiguous())
+            PT.check_attn(O[b:b + 1, :, :q], lse[b:b + 1, :, :q], Or, lr, torch.float32, f"sequence {b}: {q} of {k}")
 
 
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
