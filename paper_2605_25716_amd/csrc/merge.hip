@@ -125,25 +125,29 @@ hipError_t launch_fill_empty(float* O, float* lse, int64_t rows, int D, hipStrea
 
 // out[bh, perm[i]] = in[bh, i]: the log-sum-exps of permuted query rows put back in the rows' own order (the
 // token-permutation part of Dec, Section 4.2, for the per-row scalar that travels with the output).
-// One thread per value, a row of workgroups per (sequence, head) row: no division.
+// One thread per value over the whole tensor, whatever its rows: decoding steps have rows of one value by the thousand (262144
+// of them take 2.3 us; 59 with a workgroup of its own for every row).  Below 2^31 values the row is found without a division.
 __global__ __launch_bounds__(256) void scatter_rows_f32_kernel(const float* __restrict__ in,
                                                                const int32_t* __restrict__ perm, int64_t L,
-                                                               FastDiv by_chunks, float* __restrict__ out) {
-    const int64_t bh = by_chunks.div(blockIdx.x);
-    const int64_t i = (int64_t)by_chunks.mod(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= L) return;
-    const int64_t dst = perm ? (int64_t)perm[i] : i;
-    out[bh * L + dst] = in[bh * L + i];
+                                                               FastDiv by_l, int small, int64_t total,
+                                                               float* __restrict__ out) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= total) return;
+    if (!perm) {
+        out[e] = in[e];
+        return;
+    }
+    const int64_t bh = small ? (int64_t)by_l.div((uint32_t)e) : e / L;
+    out[bh * L + perm[e - bh * L]] = in[e];
 }
 
 hipError_t launch_scatter_rows_f32(const float* in, const int32_t* perm, int64_t n_bh, int64_t L, float* out,
                                    hipStream_t stream) {
-    if (n_bh * L == 0) return hipSuccess;
-    const int64_t wg = L <= 64 ? 64 : 256;
-    const int64_t chunks = (L + wg - 1) / wg;
-    if (!grid_fits(n_bh * chunks)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(scatter_rows_f32_kernel, dim3((unsigned)(n_bh * chunks)), dim3((unsigned)wg), 0, stream, in,
-                       perm, L, FastDiv(chunks), out);
+    const int64_t total = n_bh * L;
+    if (total == 0) return hipSuccess;
+    if (!grid_fits((total + 255) / 256)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(scatter_rows_f32_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, in, perm,
+                       L, FastDiv(L), total <= 0x7fffffffLL ? 1 : 0, total, out);
     return hipGetLastError();
 }
 

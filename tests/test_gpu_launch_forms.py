@@ -231,9 +231,17 @@ def test_decode_rounds_the_exponent_once(bits):
     assert err <= 1e-6
 
 
-@pytest.mark.parametrize("L", [1, 64, 65, 256, 300])
-def test_lse_scatter(L):
-    lse = torch.randn((2, 3, L))
+@pytest.mark.parametrize("B,H,L", [(2, 3, 1), (2, 3, 64), (2, 3, 65), (2, 3, 256), (2, 3, 300), (700, 5, 3), (4097, 3, 1)])
+def test_lse_scatter(B, H, L):
+    lse = torch.randn((B, H, L))
     perm = torch.randperm(L, generator=torch.Generator().manual_seed(L)).to(torch.int32)
     out = fb.fedrag_unpermute_lse(lse.to(DEV), perm.to(DEV)).cpu()
     assert torch.equal(out[:, :, perm.long()], lse)
+
+
+def test_lse_scatter_of_many_rows():
+    """2^26 rows and more of one value each, which a workgroup per row could not launch."""
+    lse = torch.randn((1 << 21, 33, 1), device=DEV)
+    out = fb.fedrag_unpermute_lse(lse, torch.zeros(1, dtype=torch.int32, device=DEV))
+    torch.cuda.synchronize()
+    assert torch.equal(out, lse)
