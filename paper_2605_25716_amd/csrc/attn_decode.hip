@@ -539,7 +539,7 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
         Odst = (float*)p.workspace;
         Ldst = Odst + (size_t)splits * rows * D;
     }
-    if (!grid_fits(units * splits)) return hipErrorInvalidValue;
+    if (!grid_fits(units * splits, kDecThreads)) return hipErrorInvalidValue;
     bool is_short = QB == 0;  // on codes the rings above serve every run
     for (int i = 0; i < runs.n_shards; ++i)
         if (runs.s[i].L > kDecShortRun && runs.s[i].per > kDecShortRun) is_short = false;

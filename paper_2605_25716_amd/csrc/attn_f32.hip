@@ -286,7 +286,7 @@ static hipError_t launch_f32_t(const AttnProblem& p, const KeyRuns& runs, hipStr
     const int64_t R = (int64_t)(p.Hq / p.Hkv) * p.Lq;  // rows of a unit, contiguous in Q, O and lse
     const int64_t tiles = (R + NQ * 16 - 1) / (NQ * 16);
     const int64_t grid = (int64_t)p.B * p.Hkv * tiles * runs.n_runs;
-    if (R > 0x7fffffffLL || !grid_fits(grid)) return hipErrorInvalidValue;
+    if (R > 0x7fffffffLL || !grid_fits(grid, W * kWave)) return hipErrorInvalidValue;
     float* Odst = p.O;
     float* Ldst = p.lse;
     if (runs.n_runs > 1) {

@@ -587,7 +587,7 @@ static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, i
     const int64_t tiles_of_unit = (int64_t)(Hq_k / p.Hkv) * q_tiles;
     const int64_t per_unit = tiles_of_unit * runs.n_runs;
     const int64_t grid = (int64_t)8 * ((n_units + 7) / 8) * per_unit;
-    if (!grid_fits(grid)) return hipErrorInvalidValue;
+    if (!grid_fits(grid, NW * kWave)) return hipErrorInvalidValue;
     int64_t keys = 0;
     for (int i = 0; i < runs.n_shards; ++i) keys += runs.s[i].L;
     const bool run_by_run = n_units * tiles_of_unit >= attn_target_wgs() && keys * (4 * D) > kPreRunByRunBytes;

@@ -8,8 +8,10 @@
 
 namespace fedrag {
 
-// A launch grid's x dimension: the launchers refuse (hipErrorInvalidValue) what would not fit instead of truncating.
-inline bool grid_fits(int64_t n) { return n >= 1 && n <= 0x7fffffffLL; }
+// A launch grid's x dimension of n workgroups: the launchers refuse (hipErrorInvalidValue) what would not fit instead of
+// truncating.  A dispatch counts its threads in 32 bits, and the runtime starts fewer of them without an error beyond that.
+constexpr bool grid_fits(int64_t n, int64_t threads) { return n >= 1 && n <= 0xffffffffLL / threads; }
+static_assert(grid_fits((1 << 24) - 1, 256) && !grid_fits(1 << 24, 256) && !grid_fits(0, 64), "32 bits of threads");
 
 // Second partial for the scatter form (Dec followed by the Section 4.1 aggregation of two partials): row i of X has
 // log-sum-exp lse_in[bh, i]; (O_other, lse_other) is the other partial, already in destination row order.

@@ -691,7 +691,7 @@ static ScrambleJob device_job(const RowsJob& j, int i) {
 template <class T, int D>
 static hipError_t launch_scramble16(const RowsJob& j, hipStream_t stream) {
     if (j.L <= kFewRows && j.quant_bits == 0) {
-        if (!grid_fits(j.BH)) return hipErrorInvalidValue;
+        if (!grid_fits(j.BH, kF32Threads)) return hipErrorInvalidValue;
         dim3 grid((unsigned)j.BH, (unsigned)j.n_jobs);
         const ScrambleJob a = device_job(j, 0), b = device_job(j, 1);
         if (j.structured)
@@ -743,7 +743,7 @@ static hipError_t launch_rows_mfma_f32(const RowsJob& j, hipStream_t stream) {
     if (spw < 1) spw = 1;
     if (spw > 64) spw = 64;
     const int chunks = ceil_div_i64(steps, spw);
-    if (!grid_fits(j.BH * chunks)) return hipErrorInvalidValue;
+    if (!grid_fits(j.BH * chunks, kF32Threads)) return hipErrorInvalidValue;
     dim3 grid((unsigned)(j.BH * chunks), (unsigned)j.n_jobs);
     const ScrambleJob a = device_job(j, 0), b = device_job(j, 1);
     if (j.structured)
@@ -765,7 +765,7 @@ static hipError_t launch_rows_f32(const RowsJob& j, hipStream_t stream) {
     if (tpw < 1) tpw = 1;
     if (tpw > 64) tpw = 64;
     const int chunks = ceil_div_i64(tiles, tpw);
-    if (!grid_fits(j.BH * chunks)) return hipErrorInvalidValue;
+    if (!grid_fits(j.BH * chunks, kF32Threads)) return hipErrorInvalidValue;
     dim3 grid((unsigned)(j.BH * chunks), (unsigned)j.n_jobs);
     const ScrambleJob a = device_job(j, 0), b = device_job(j, 1);
     if (j.structured)
@@ -802,7 +802,7 @@ hipError_t launch_invert_perm(const int32_t* perm, int64_t L, int32_t* inv, hipS
 hipError_t launch_validate_perm(const int32_t* perm, int n_perm, int64_t L, int32_t* marks, int32_t* flag,
                                 hipStream_t stream) {
     const int64_t total = (int64_t)n_perm * L;
-    if (!grid_fits((total > 0 ? total + 255 : 256) / 256)) return hipErrorInvalidValue;
+    if (!grid_fits((total > 0 ? total + 255 : 256) / 256, 256)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((total > 0 ? total + 255 : 256) / 256));
     hipLaunchKernelGGL(validate_perm_clear_kernel, grid, dim3(256), 0, stream, marks, total, flag);
     hipError_t e = hipGetLastError();
