@@ -1,7 +1,7 @@
 // Global aggregation of Section 4.1 in the log domain:
 //   M = max_i lse_i, a_i = exp(lse_i - M), O = sum_i a_i O_i / sum_i a_i, lse = M + ln sum_i a_i
 // which equals sum_i w_i (.) O_i / sum_i w_i with w_i = exp(lse_i).  Also used to fold the intra-shard KV
-// splits of the decode kernel.  Pure streaming: one thread per (row, 4 output columns).
+// splits of the decode kernel.  Pure streaming: one thread per (row, 4 output columns).  Two forms, up to four partials and more.
 #include "fedrag_device.h"
 #include "fedrag_host.h"
 
@@ -12,8 +12,8 @@ namespace fedrag {
 // one log-sum-exp and evaluates one exponential, and a weight reaches the others by a lane shuffle - the first batch of
 // partials is in flight before the weights are known, and the workgroups are one wave while rows are few.  Sums are
 // formed in shard order whatever the batch.
-// 32 rows of 128 over 16 partials in a chain of calls: 4.1 us (12.6 with one partial after the other); 3744 rows over 15:
-// 6.7 us (8.0 with every thread evaluating every weight).
+// 32 rows of 128 over 16 partials, calls back to back: 3.5 us (6.7 with one partial after the other); 3744 rows over 16: 5.0
+// (11.9).  In a chain of other launches add what a launch costs there.
 
 // max over the TPR = 16 or 32 consecutive lanes that hold a row
 template <int TPR>
@@ -22,9 +22,10 @@ __device__ __forceinline__ float row_max(float x) {
     return TPR == 32 ? xor16_max(x) : x;
 }
 
-// NB: partial outputs in flight (4 registers each).  16 for few rows over many partials, where a second batch is another
-// trip to memory (a decoded token over 32 layers: 941 us against 949 with 8); 8 otherwise, where more waves per SIMD
-// are worth more (the 117-token segment 2243 against 2276 with 16).
+// NB: partial outputs in flight (4 registers each).  16 for few rows over many partials, where a second batch is another trip
+// to memory (a decoded token over 32 layers: 941 us against 949 with 8); 8 up to twice as many threads (8192 rows of 64 over 16:
+// 5.2 us, 6.5 with two); beyond that memory is the bound and the waves that fewer registers leave room for are worth more than
+// loads in flight: two (16384 rows of 128 over 8: 13.1 us, 15.2 with eight, 14.2 one after the other).
 template <int D, int NB>
 __global__ __launch_bounds__(256) void lse_merge_kernel(const float* __restrict__ O_parts,
                                                         const float* __restrict__ lses, int S, int64_t rows,
@@ -84,6 +85,50 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const float* __restrict_
     if (c == 0) lse[r] = (M == -INFINITY) ? -INFINITY : M + logf(den);
 }
 
+// One to four partials, the usual number: every thread reads the row's log-sum-exps itself, and all that it reads is in flight
+// at once.  65536 rows of 128 over 2: 16.6 us (18.7 one after the other, 18.2 in the form above, whose batch reads the last
+// partial again); 32 rows: 2.3 (2.5, 2.9).
+template <int D, int S>
+__global__ __launch_bounds__(256) void lse_merge_few_kernel(const float* __restrict__ O_parts,
+                                                            const float* __restrict__ lses, int64_t rows,
+                                                            float* __restrict__ O, float* __restrict__ lse,
+                                                            const int32_t* __restrict__ q_lens, int64_t Lq,
+                                                            int64_t rows_per_seq) {
+    constexpr int TPR = D / 4;
+    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t r = gid / TPR;
+    const int c4 = (int)(gid % TPR) * 4;
+    if (r >= rows) return;
+    if (q_lens && (r % Lq) >= q_lens[r / rows_per_seq]) return;
+    float l[S];
+    f32x4_t o[S];
+#pragma unroll
+    for (int i = 0; i < S; ++i) l[i] = lses[i * rows + r];
+#pragma unroll
+    for (int i = 0; i < S; ++i) o[i] = *(const f32x4_t*)(O_parts + (i * rows + r) * D + c4);
+    float M = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < S; ++i) M = fmaxf(M, l[i]);
+    f32x4_t acc = zero_vec<f32x4_t>();
+    float den = 0.f;
+    if (M != -INFINITY) {
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+            if (l[i] == -INFINITY) continue;  // weight zero: its O takes no part
+            const float a = expf(l[i] - M);
+            den += a;
+            acc[0] = __builtin_fmaf(a, o[i][0], acc[0]);
+            acc[1] = __builtin_fmaf(a, o[i][1], acc[1]);
+            acc[2] = __builtin_fmaf(a, o[i][2], acc[2]);
+            acc[3] = __builtin_fmaf(a, o[i][3], acc[3]);
+        }
+        const float inv = 1.0f / den;
+        acc[0] *= inv; acc[1] *= inv; acc[2] *= inv; acc[3] *= inv;
+    }
+    *(f32x4_t*)(O + r * D + c4) = acc;
+    if (c4 == 0) lse[r] = (M == -INFINITY) ? -INFINITY : M + logf(den);
+}
+
 template <int D>
 __global__ __launch_bounds__(256) void fill_empty_kernel(float* __restrict__ O, float* __restrict__ lse,
                                                          int64_t rows) {
@@ -104,9 +149,17 @@ hipError_t launch_lse_merge(const float* O_parts, const float* lses, int S, int6
     const int wg = threads <= 256 * 256 ? 64 : 256;  // one wave per workgroup until every compute unit has four
     if (!grid_fits((threads + wg - 1) / wg, wg)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((threads + wg - 1) / wg));
-    const bool deep = S > 8 && threads <= 256 * 256;
-    const auto kernel = D == 128 ? (deep ? lse_merge_kernel<128, 16> : lse_merge_kernel<128, 8>)
-                                 : (deep ? lse_merge_kernel<64, 16> : lse_merge_kernel<64, 8>);
+    if (S <= 4) {
+#define FEDRAG_FEW(S_) (D == 128 ? lse_merge_few_kernel<128, S_> : lse_merge_few_kernel<64, S_>)
+        const auto few = S == 1 ? FEDRAG_FEW(1) : S == 2 ? FEDRAG_FEW(2) : S == 3 ? FEDRAG_FEW(3) : FEDRAG_FEW(4);
+#undef FEDRAG_FEW
+        hipLaunchKernelGGL(few, grid, dim3(wg), 0, stream, O_parts, lses, rows, O, lse, q_lens, Lq, rows_per_seq);
+        return hipGetLastError();
+    }
+    const int nb = threads <= 256 * 256 && S > 8 ? 16 : threads <= 256 * 512 ? 8 : 2;
+#define FEDRAG_MANY(NB_) (D == 128 ? lse_merge_kernel<128, NB_> : lse_merge_kernel<64, NB_>)
+    const auto kernel = nb == 16 ? FEDRAG_MANY(16) : nb == 8 ? FEDRAG_MANY(8) : FEDRAG_MANY(2);
+#undef FEDRAG_MANY
     hipLaunchKernelGGL(kernel, grid, dim3(wg), 0, stream, O_parts, lses, S, rows, O, lse, q_lens, Lq, rows_per_seq);
     return hipGetLastError();
 }

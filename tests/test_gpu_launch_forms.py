@@ -161,8 +161,8 @@ def test_fp32_rows_do_not_see_a_later_token(oracle, bad):
     PT.check_attn(O[:, :, :21], lse[:, :, :21], Or[:, :, :21], lr[:, :, :21], torch.float32, "rows before the token")
 
 
-@pytest.mark.parametrize("S", [1, 2, 8, 9, 16, 17, 33])
-@pytest.mark.parametrize("rows,d", [(3, 128), (5, 64), (2500, 128)])  # many rows: the form with fewer partials in flight
+@pytest.mark.parametrize("S", [1, 2, 3, 4, 5, 8, 9, 16, 17, 33])
+@pytest.mark.parametrize("rows,d", [(3, 128), (5, 64), (2500, 128), (8300, 64)])  # the more rows the fewer partials in flight
 def test_aggregation_of_many_partials(oracle, S, rows, d):
     g = torch.Generator().manual_seed(S * 100 + rows)
     O, lse = torch.randn((S, 1, 1, rows, d), generator=g), torch.randn((S, 1, 1, rows), generator=g) * 30
