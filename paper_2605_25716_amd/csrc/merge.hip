@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const float* __restrict_
     f32x4_t o[NB];
     load_o(0, o);  // in flight together with the log-sum-exps
     float l = load_l(0);
-    float M = l;
+    float M = fmaxf(l, -INFINITY);  // (a NaN does not count as a maximum, also where every lane holds one)
     for (int i0 = TPR; i0 < S; i0 += TPR) M = fmaxf(M, load_l(i0));
     M = row_max<TPR>(M);
     f32x4_t acc = zero_vec<f32x4_t>();

@@ -175,6 +175,17 @@ def test_aggregation_of_many_partials(oracle, S, rows, d):
     assert PT.max_abs(got, Or) <= 1e-4 and PT.max_abs(got_l, lr) <= 1e-4
 
 
+@pytest.mark.parametrize("S", [2, 16, 33])
+def test_aggregation_of_partials_without_a_number(S):
+    """A row whose log-sum-exps are all NaN has no weight, like one where all are -inf, whatever the number of partials."""
+    O, lse = torch.ones((S, 1, 1, 3, 64)), torch.zeros((S, 1, 1, 3))
+    lse[:, 0, 0, 1] = float("nan")
+    got, got_l = fb.fedrag_lse_merge(O.to(DEV), lse.to(DEV))
+    torch.cuda.synchronize()
+    assert bool((got[0, 0, 1] == 0).all()) and float(got_l[0, 0, 1]) == float("-inf")
+    assert bool((got[0, 0, ::2] == 1).all())
+
+
 # one run up to 512 keys, 256-key runs up to 2048 in all, 512-key runs behind; one tile set up to 1024 keys per run
 @pytest.mark.parametrize("Ls", [[31], [512], [513], [2047], [2049], [400, 700], [300, 0, 213], [9000]])
 @pytest.mark.parametrize("d", [64, 128])
