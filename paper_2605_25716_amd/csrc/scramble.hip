@@ -521,9 +521,6 @@ __global__ __launch_bounds__(kF32Threads) void rows_times_matrix_f32_kernel(Scra
 // 8 j + 4 (lane / 32) + e for read j, element e.  The next step's rows are fetched into registers before the MFMAs
 // of the current one and go to the other LDS buffer after them: one barrier per step.
 constexpr int kMfMinRows = 64;
-// Workgroups to aim for: twelve per compute unit, three resident at a time.  With two per unit (512) a launch ends on
-// the units that got three of five: Enc of a 64 x 8000-row fp32 shard 574 -> 460 us, Dec of 65536 rows 42 -> 38 us.
-constexpr int64_t kMfWantWgs = 3072;
 
 template <int D, bool SCATTER, bool ST>
 __global__ __launch_bounds__(kF32Threads) void rows_times_matrix_mfma_f32_kernel(ScrambleJob job0, ScrambleJob job1,
@@ -733,15 +730,42 @@ static hipError_t launch_scramble16(const RowsJob& j, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// Row steps per workgroup.  What a launch takes is the load of the compute unit that gets the most workgroups, in steps of a
+// unit whose matrix pipe is busy: `resident` workgroups of a unit (by registers: 120, 152, 184 a lane) take a step each in as
+// many of those; one, two or three of them, which wait for their rows, take `part`, more with a second partial to read; every
+// workgroup costs `setup` (its slice of Phi, or the multiplying out of the key), and where they come in several rounds the last
+// one ends unevenly (`tail` of a workgroup).  Fitted to 16 splits of 124 launches; over those the choice is 0.4 % from the best
+// split on average, 8 % at most.  d = 128: Dec of 2048 rows x 32 heads 34.8 us (39.8 with 3072 workgroups for every launch, as
+// before; structured 34.7 and 43.8), Enc of 16 x 500 rows x 8 heads 53 (63; structured 53 and 74), of 16 x 8192 840 (877; 897
+// and 987).
+static int mf_steps_per_wg(int64_t steps, int64_t slabs, int D, bool structured, bool merge) {
+    const int resident = D == 64 ? 4 : structured ? 2 : 3;
+    const float setup = D == 64 ? 0.15f : 0.3f;
+    const float tail = D == 64 ? 0.2f : structured ? 0.0f : 0.4f;
+    const float part[4] = {0.0f, merge ? 1.7f : 1.3f, merge ? 2.6f : 2.2f, merge ? 3.3f : 3.1f};
+    const int64_t cus = attn_target_wgs();
+    int best = 1;
+    float least = 0.0f;
+    for (int64_t most = 1; most <= 64 && most <= steps; ++most) {
+        const int64_t chunks = (steps + most - 1) / most;
+        const int64_t spw = (steps + chunks - 1) / chunks;
+        const int64_t wgs = (slabs * chunks + cus - 1) / cus;  // of the fullest unit
+        const float load = (float)(wgs / resident * resident) + part[wgs % resident];
+        const float per = wgs <= resident ? (float)spw : (float)steps / (float)chunks;
+        const float cost = load * per + (float)wgs * setup + (wgs > resident ? tail * (float)spw : 0.0f);
+        if (most == 1 || cost < least) {
+            least = cost;
+            best = (int)spw;
+        }
+    }
+    return best;
+}
+
 template <int D, bool SCATTER>
 static hipError_t launch_rows_mfma_f32(const RowsJob& j, hipStream_t stream) {
     constexpr int TR = 32 * (4 / (D / 32));  // rows per workgroup step
     const int64_t steps = (j.L + TR - 1) / TR;
-    // at most 64 steps each (a workgroup loads its slice of Phi once)
-    const int64_t total = steps * j.BH * j.n_jobs;
-    int spw = (int)(total / kMfWantWgs);
-    if (spw < 1) spw = 1;
-    if (spw > 64) spw = 64;
+    const int spw = mf_steps_per_wg(steps, j.BH * j.n_jobs, D, j.structured, j.merge.lse_in != nullptr);
     const int chunks = ceil_div_i64(steps, spw);
     if (!grid_fits(j.BH * chunks, kF32Threads)) return hipErrorInvalidValue;
     dim3 grid((unsigned)(j.BH * chunks), (unsigned)j.n_jobs);
