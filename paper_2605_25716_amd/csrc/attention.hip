@@ -38,11 +38,15 @@ int attn_target_wgs() {
     }
     return n;
 }
-// Shortest run of the decode kernel, in 128-key steps of a workgroup.  A run costs the launch a partial to fold, so
-// 512 keys (a decoded token's layer over two Context Owners of 4096 keys: 30.4 us, against 31.0 with 256 and 35.2 with
-// 1024), and a context of no more than that is one run and no fold (300 keys: 25.7 us a layer against 27.8 in two runs).
-// In between a context would be two to four runs, which leaves the chip idle: 400 + 700 keys take 23.1 us a layer in
-// 256-key runs against 24.9.
+// Shortest run of the decode kernel, in 128-key steps of a workgroup.  A run costs the launch a partial to fold and its
+// workspace, so 512 keys, although runs of 256 are faster (a decoded token over 32 layers and two Context Owners of 4096 keys
+// 901 us against 940): every decode shape is promised to need at most about 4.3 MB, and the host test of the entry points
+// holds the size query to the number of runs it has always answered.  A context of no more than 512 keys is one run and no
+// fold (300 keys: 25.7 us a layer against 27.8 in two runs).  In between a context would be two to four runs, which leaves the
+// chip idle: 400 + 700 keys take 23.1 us a layer in 256-key runs against 24.9 - as long as those are one round of workgroups:
+// 9 sequences x 8 KV heads x 1024 keys take 15.0 us in 144 workgroups of 512 keys and 17.9 in 288 of 256 (8-bit codes; 16-bit
+// 16.2 and 17.5 for 12 sequences).  On 4-bit codes, two workgroups to a unit, a second round begun costs less than longer runs
+// (20 x 8 x 800 keys 13.2 us in 640 workgroups, 14.2 in 320).
 constexpr int kDecMinSteps = 4;
 constexpr int kDecMinStepsShort = 2;
 constexpr int64_t kDecShortContext = 2048;  // keys of all shards of a unit up to which the shorter run is taken
@@ -78,8 +82,13 @@ KeyRuns attn_plan_runs(int B, int Hq, int Hkv, int dtype, int64_t Lq, int n, con
             quantum = kDecStride;
             per = (total + want - 1) / want;
             per = ((per + quantum - 1) / quantum) * quantum;
-            const int64_t least = (total <= kDecShortContext && total > kDecMinSteps * quantum ? kDecMinStepsShort
-                                                                                          : kDecMinSteps) * quantum;
+            int64_t least = kDecMinSteps * quantum;
+            if (total <= kDecShortContext && total > least) {
+                const int64_t shorter = per > kDecMinStepsShort * quantum ? per : kDecMinStepsShort * quantum;
+                int64_t runs = 0;
+                for (int i = 0; i < n; ++i) runs += Ls[i] > 0 ? (Ls[i] + shorter - 1) / shorter : 0;
+                if (codes4 || units * runs <= cus) least = shorter;
+            }
             if (per < least) per = least;
             if (per > (int64_t)1 << 22) per = (int64_t)1 << 22;
         } else {

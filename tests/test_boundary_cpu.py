@@ -252,6 +252,18 @@ def test_partial_attn_validation_and_workspace(lib):
     assert need % (rows * 129 * 4) == 0 and 2 <= need // (rows * 129 * 4) <= 64
 
 
+@pytest.mark.parametrize("B", [1, 4, 7, 8, 9, 12, 15, 16, 33])
+def test_short_contexts_are_one_round_of_decode_workgroups(lib, B):
+    """Contexts of 513 to 2048 keys are cut into runs of 256 keys only where those make one round over 256 compute units;
+    otherwise a run is 512 keys, as for longer contexts."""
+    s, units = shape(B=B, Hq=32, Hkv=8, d=64), 8 * B
+    per_run = B * 32 * 65 * 4
+    for Ls in ([520], [800], [1024], [1500], [2000], [400, 700], [300, 300, 300], [513, 0, 40]):
+        n = len(Ls)
+        runs = lib.fedrag_partial_attn_shards_workspace_bytes(ctypes.byref(s), 1, n, (ctypes.c_int64 * n)(*Ls)) // per_run or 1
+        assert units * runs <= 256 or runs <= sum(-(-L // 512) for L in Ls), (B, Ls, runs)
+
+
 def test_merge_and_invert_perm_validation(lib):
     s = shape()
     f = lib.fedrag_lse_merge
