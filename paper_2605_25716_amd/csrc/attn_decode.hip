@@ -324,6 +324,24 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
         }
     };
 
+    // d = 64: without fences the steps of both tile sets are scheduled into one another, the refills go to other registers than
+    // the loop expects them in, and it waits at its top for every load in flight to copy them: 8 shards of 25479 keys, 32
+    // units, 279 us; 252 with a fence behind each step, 251 with one around every refill as well, which 512 units of 9000
+    // keys, two workgroups to a compute unit, need (227, 185 and 175 us).
+    auto fence = [&]() {
+        if (D == 64) __builtin_amdgcn_sched_barrier(0);
+    };
+    auto refill_k = [&](int tile, Tile& t) {
+        fence();
+        load_k(tile, t);
+        fence();
+    };
+    auto refill_v = [&](int tile, Tile& t) {
+        fence();
+        load_v(tile, t);
+        fence();
+    };
+
     // One 32-key tile.  `reload` refills the tile's registers for key `next0` as soon as each half has been
     // consumed (K' after the first product, V' after the in-register transpose), so the loads fly behind the
     // softmax, the second product and the other tile set's step.
@@ -363,7 +381,7 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
         } else {
             score(std::true_type{});
         }
-        if (reload) load_k(next_tile, t);
+        if (reload) refill_k(next_tile, t);
         float p[8];
         float mx = -INFINITY;
 #pragma unroll
@@ -413,7 +431,7 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
             }
             transpose_keys_b16<DCH>(v16, vt);
         }
-        if (reload) load_v(next_tile, t);
+        if (reload) refill_v(next_tile, t);
 #pragma unroll
         for (int i = 0; i < DCH; ++i) {
             acc_o[i] *= alpha;
@@ -441,9 +459,7 @@ __global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OC
 #pragma unroll
             for (int j = 0; j < NBUF; ++j) {
                 step(t[j], tile_key(i + j), false, true, tile_of(i + j + NBUF));
-                // d = 64: without a fence the steps of both sets are scheduled into one another, and the loop waits for
-                // every load in flight at its top (8 shards of 25479 keys, 32 units: 283 us, 255 with the fence)
-                if (D == 64) __builtin_amdgcn_sched_barrier(0);
+                fence();
             }
         }
         // fewer than 2*NBUF tiles left: refills become conditional, then the ring drains
