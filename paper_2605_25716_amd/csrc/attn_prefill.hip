@@ -561,16 +561,23 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
 }
 
 // Waves per workgroup.  Eight share a K'/V' tile between 256 query rows, one workgroup per compute unit: the best rate
-// when the launch is whole rounds of them (2048 x 16384 x 32 heads: 492 us, against 521 with four).  Four (128 rows) sit
-// two to a compute unit, fill and drain it independently and waste less of a ragged end, which wins wherever the
-// workgroups are few or unequal: always with a mask or with per-sequence lengths (2048-token segment 66 against 80 us,
-// 500 tokens 18 against 27, the 10-pair re-rank batch 28 against 39), else when the rounds below come out shorter.
-static bool prefill_wants_4_waves(int64_t wgs8, int64_t wgs4) {
+// when the launch is whole rounds of them (2048 x 16384 x 32 heads of 128: 478 us, against 508 with four).  Four (128 rows) sit
+// two to a compute unit, three at d = 64, fill and drain it independently and waste less of a ragged end.  q of them per unit
+// take a + b q rounds of the larger form, fitted to launches of 1 to 15 per unit: b is half a round at d = 128, less where three
+// overlap, more on codes, whose tiles are rebuilt for half the rows (2 x 1347 tokens x 16 heads on 8-bit codes of 64: 39 us with
+// four, 35 with eight; of 128 63 and 53; 2500 x 4 x 32 heads of 64 in 16 bits 258 and 290).  Where there are several rounds a
+// workgroup's start and end, some four tiles (two on codes), are half hidden behind its neighbours with four waves (4096 x 64
+// rows of 128 x 500 keys: 88 us, 101 with eight).
+// Always four with a mask, whose tiles are unequal (2048-token segment 62 against 79 us, 300 tokens 12 against 17), and for 16-bit
+// batches with query counts, whose workgroups are fewer than the padded shape says (the 10-pair re-rank batch 29 against 42;
+// where every sequence is as long as the padding, 2 to 6 % slower).  On codes such a batch goes by its padded shape.
+static bool prefill_wants_4_waves(int64_t wgs8, int64_t wgs4, int64_t tiles, int D, bool codes) {
     const int64_t cus = attn_target_wgs();
-    const int64_t rounds8 = (wgs8 + cus - 1) / cus;
-    const int64_t rest = wgs4 % (2 * cus);  // a last round of at most one workgroup per unit takes 0.6 of a full one
-    const int64_t rounds4_x10 = wgs4 / (2 * cus) * 10 + (rest == 0 ? 0 : rest <= cus ? 6 : 10);
-    return rounds4_x10 * 106 < rounds8 * 1000;  // a round of four-wave workgroups takes 6 % longer
+    const int64_t q8 = (wgs8 + cus - 1) / cus, q4 = (wgs4 + cus - 1) / cus;
+    const float a = D == 64 ? (codes ? 0.20f : 0.15f) : codes ? 0.08f : 0.05f;
+    const float b = D == 64 ? (codes ? 0.465f : 0.445f) : codes ? 0.55f : 0.51f;
+    const float ends = q8 == 1 ? 0.0f : codes ? 2.0f : 4.0f;
+    return (a + b * (float)q4) * ((float)tiles + 0.5f * ends) < (float)q8 * ((float)tiles + ends);
 }
 
 // Order of a unit's workgroups when there are several runs.  The runs of a query tile side by side, unless one run's
@@ -633,7 +640,13 @@ static hipError_t launch_prefill_t(const AttnProblem& p, hipStream_t stream) {
     }
     const int64_t tiles8 = (Lq_k + 8 * kPreQ - 1) / (8 * kPreQ), tiles4 = (Lq_k + 4 * kPreQ - 1) / (4 * kPreQ);
     const int64_t heads = (int64_t)p.B * Hq_k * splits;
-    const bool four = CAUSAL || p.kv_lens || p.q_lens || prefill_wants_4_waves(heads * tiles8, heads * tiles4);
+    int64_t key_tiles = 1;  // of the longest run
+    for (int i = 0; i < runs.n_shards; ++i) {
+        const int64_t keys = runs.s[i].L < runs.s[i].per ? runs.s[i].L : runs.s[i].per;
+        if ((keys + kPreK - 1) / kPreK > key_tiles) key_tiles = (keys + kPreK - 1) / kPreK;
+    }
+    const bool four = CAUSAL || (p.q_lens && QB == 0 && p.B > 1) ||
+                      prefill_wants_4_waves(heads * tiles8, heads * tiles4, key_tiles, D, QB != 0);
     hipError_t e = hipErrorInvalidValue;
     if (four) e = launch_prefill_nw<T, D, CAUSAL, QB, 4>(p, runs, Hq_k, Lq_k, tiles4, Odst, Ldst, stream);
     else if constexpr (!CAUSAL) e = launch_prefill_nw<T, D, false, QB, 8>(p, runs, Hq_k, Lq_k, tiles8, Odst, Ldst, stream);
