@@ -154,9 +154,16 @@ def make_shape(batch: int, n_q_heads: int, n_kv_heads: int, d_head: int, dtype) 
 
 
 @functools.lru_cache(maxsize=256)
+def _cached_shape_ref(batch: int, n_q_heads: int, n_kv_heads: int, d_head: int, dtype: torch.dtype):
+    return ctypes.byref(make_shape(batch, n_q_heads, n_kv_heads, d_head, dtype))
+
+
 def _shape_ref(batch: int, n_q_heads: int, n_kv_heads: int, d_head: int, dtype):
     """A reference to the shape struct of these numbers, for the calls' `const fedrag_shape*` (read during the call
-    only): small calls spend as long on building ctypes objects as on the device."""
+    only): small calls spend as long on building ctypes objects as on the device.  Only plain integers are looked up: a
+    cache takes 8.0 for 8, which the struct refuses, and an integer tensor for itself whatever it holds by now."""
+    if type(batch) is type(n_q_heads) is type(n_kv_heads) is type(d_head) is int and type(dtype) is torch.dtype:
+        return _cached_shape_ref(batch, n_q_heads, n_kv_heads, d_head, dtype)
     return ctypes.byref(make_shape(batch, n_q_heads, n_kv_heads, d_head, dtype))
 
 

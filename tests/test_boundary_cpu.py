@@ -6,7 +6,9 @@ import os
 import re
 import subprocess
 
+import numpy as np
 import pytest
+import torch
 
 from paper_2605_25716_amd import binding as fb
 from paper_2605_25716_amd import build as fbuild
@@ -308,6 +310,23 @@ def test_workspace_size_of_prefill_shapes(lib):
     # the prefill benchmark shape (256 workgroups) and fp32 storage: no runs
     assert need(1, 32, 8, 128, 2048, 16384) == 0
     assert need(1, 4, 2, 128, 70, 1500, fb.F32) == 0
+
+
+def test_shape_numbers_are_integers_also_when_the_shape_is_known(lib):
+    """A repeated shape is taken from a cache, which must refuse and read what building it anew would."""
+    query = fb.fedrag_partial_attn_workspace_bytes
+    sizes = (1, 32, 8, 128, torch.bfloat16, 1, 5003)
+    expect = query(*sizes)
+    assert expect > 0 and query(*sizes) == expect
+    for i in range(4):
+        with pytest.raises(TypeError):
+            query(*sizes[:i], float(sizes[i]), *sizes[i + 1:])
+    batch = torch.tensor(1)
+    assert query(batch, *sizes[1:]) == expect
+    batch.fill_(3)
+    assert query(batch, *sizes[1:]) == query(3, *sizes[1:]) != expect
+    heads = np.array(32)
+    assert query(1, heads, *sizes[2:]) == expect
 
 
 def test_partial_attn_shards_validation_and_workspace(lib):
