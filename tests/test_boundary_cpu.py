@@ -2,6 +2,7 @@
 header declares, and every argument error is reported before any HIP call is made (so fake, never
 dereferenced pointers are safe here: each call below must fail validation)."""
 import ctypes
+import glob
 import os
 import re
 import subprocess
@@ -327,6 +328,23 @@ def test_shape_numbers_are_integers_also_when_the_shape_is_known(lib):
     assert query(batch, *sizes[1:]) == query(3, *sizes[1:]) != expect
     heads = np.array(32)
     assert query(1, heads, *sizes[2:]) == expect
+
+
+def test_asm_with_data_parallel_reads_opens_with_a_wait():
+    """A vector register must be two instructions old before a data-parallel read, and the compiler, which may place a copy
+    right before an asm statement, does not look inside it.  The wait is therefore each such statement's own first
+    instruction.  The macros are expanded by the host's preprocessor: what counts is the text of the statement."""
+    for f in sorted(glob.glob(os.path.join(fbuild.CSRC, "*.h*"))):
+        body = "".join(l for l in open(f) if not l.startswith(("#include", "#pragma")))
+        if "_dpp" not in body:
+            continue
+        text = subprocess.run(["g++", "-E", "-P", "-x", "c++", "-"], input=body, capture_output=True, text=True,
+                              check=True).stdout
+        statements = [m.group(1) for m in re.finditer(r'\basm\s*(?:volatile)?\s*\(((?:\s*"(?:[^"\\]|\\.)*")+)', text)]
+        with_reads = [re.sub(r'"\s*"', "", s).strip() for s in statements if "_dpp" in s]
+        assert with_reads and sum(s.count("_dpp") for s in with_reads) == text.count("_dpp ")
+        for s in with_reads:
+            assert re.match(r'"s_nop [1-9]', s), (f, s[:60])
 
 
 def test_partial_attn_shards_validation_and_workspace(lib):
