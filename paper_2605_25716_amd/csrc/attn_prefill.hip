@@ -46,6 +46,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
                                                                       FastDiv by_inner, int run_by_run, int64_t Lq,
                                                                       const int32_t* __restrict__ kv_lens,
                                                                       const int32_t* __restrict__ q_lens, int n_units, int fold,
+                                                                      int together,
                                                                       float scale_log2,
                                                                       float* __restrict__ O, float* __restrict__ lse) {
     typedef typename T::elem elem;
@@ -75,10 +76,13 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     const int n_runs = runs.n_runs;
     const int xcd = blockIdx.x % 8;
     const int slot = blockIdx.x / 8;
-    const int unit_slot = (int)by_unit.div(slot);  // by_unit: G * q_tiles * n_runs
+    // by_unit: the workgroups of a unit, G * q_tiles * n_runs, or (CAUSAL only: together) the units of an XCD, which then
+    // advance side by side: the long tiles of all of them first, as below
+    const int outer_slot = (int)by_unit.div(slot), inner_slot = slot - outer_slot * (int)by_unit.d;
+    const int unit_slot = CAUSAL && together ? inner_slot : outer_slot;
     const int unit = xcd + 8 * unit_slot;
     if (unit >= n_units) return;
-    const int in_unit = slot - unit_slot * (int)by_unit.d;
+    const int in_unit = CAUSAL && together ? outer_slot : inner_slot;
     const int outer = (int)by_inner.div(in_unit), inner = in_unit - outer * (int)by_inner.d;
     const int w_in_unit = run_by_run ? inner : outer;
     const int run = run_by_run ? outer : inner;
@@ -585,6 +589,7 @@ static bool prefill_wants_4_waves(int64_t wgs8, int64_t wgs4, int64_t tiles, int
 // the workgroups at work share the keys of one shard (8 shards of 8192 keys, 4096 x 64 query rows: 7.97 ms, 8.24 side by
 // side, 8.02 with a launch per shard; at 8 MB of keys both orders take the same time, at 3 MB run by run is 5 % slower).
 constexpr int64_t kPreRunByRunBytes = 16 << 20;
+constexpr int64_t kPreTogetherBytes = 8 << 20;  // K and V of an XCD's units, whose L2 is 4 MiB
 
 template <class T, int D, bool CAUSAL, int QB, int NW>
 static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, int Hq_k, int64_t Lq_k, int64_t q_tiles,
@@ -601,10 +606,15 @@ static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, i
     // With every workgroup resident at once (two per compute unit, started in index order) the second half goes beside
     // the first: the shortest tile to the longest, and all compute units end together (2048 tokens: 65 -> 60 us).
     const int fold = CAUSAL && grid <= 2 * (int64_t)attn_target_wgs() ? 1 : 0;
+    // With a mask the units of an XCD advance together, unless their keys are many times its L2: 2 x 4096 tokens x 16 heads
+    // of 64 one unit after the other 143 us, together 126; 2 x 2048 of 128 83 and 62; 4 x 4096 of 128 (8 MiB) 415 and 386, but
+    // 8 x 4096 (16 MiB) 1524 and 1567.
+    const int64_t units_per_xcd = (n_units + 7) / 8;
+    const int together = CAUSAL && units_per_xcd * keys * (4 * D) <= kPreTogetherBytes ? 1 : 0;
     hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB, NW>), dim3((unsigned)grid), dim3(NW * kWave), 0, stream,
                        (const elem*)p.Q, runs, p.K_params, p.V_params, Hq_k, FastDiv(p.Hkv), FastDiv(Hq_k / p.Hkv),
-                       FastDiv(q_tiles), FastDiv(per_unit), FastDiv(run_by_run ? tiles_of_unit : runs.n_runs),
-                       run_by_run ? 1 : 0, Lq_k, p.kv_lens, p.q_lens, n_units, fold,
+                       FastDiv(q_tiles), FastDiv(together ? units_per_xcd : per_unit), FastDiv(run_by_run ? tiles_of_unit : runs.n_runs),
+                       run_by_run ? 1 : 0, Lq_k, p.kv_lens, p.q_lens, n_units, fold, together,
                        p.scale * kLog2e, Odst, Ldst);
     return hipGetLastError();
 }

@@ -257,3 +257,23 @@ def test_lse_scatter_of_many_rows():
     out = fb.fedrag_unpermute_lse(lse, torch.zeros(1, dtype=torch.int32, device=DEV))
     torch.cuda.synchronize()
     assert torch.equal(out, lse)
+
+
+@pytest.mark.parametrize("B,Hkv,G,Lq,L,d", [
+    (1, 8, 2, 300, 300, 128), (1, 9, 2, 300, 300, 128), (3, 3, 3, 129, 200, 64), (2, 8, 4, 1024, 1024, 64),  # together
+    (64, 64, 1, 64, 64, 64), (65, 64, 1, 64, 64, 64), (5, 821, 1, 40, 64, 64)])  # 8 MiB of keys an XCD, and beyond
+def test_masked_batches_reach_every_tile_of_every_unit(oracle, B, Hkv, G, Lq, L, d):
+    """The order in which the tiles of several units are handed out must not show: the outputs, filled with NaN before, are
+    those of the sequences one by one, and the last sequence matches the oracle."""
+    g = torch.Generator().manual_seed(B * Hkv + Lq)
+    Q, K, V = (torch.randn(s, generator=g).to(torch.bfloat16) for s in ((B, Hkv * G, Lq, d), (B, Hkv, L, d), (B, Hkv, L, d)))
+    O = torch.full((B, Hkv * G, Lq, d), float("nan"), device=DEV)
+    lse = torch.full((B, Hkv * G, Lq), float("nan"), device=DEV)
+    Qd, Kd, Vd = Q.to(DEV), K.to(DEV), V.to(DEV)
+    fb.fedrag_local_attn(Qd, Kd, Vd, O_part=O, lse=lse)
+    for b in range(B):
+        Ob, lb = fb.fedrag_local_attn(Qd[b:b + 1], Kd[b:b + 1], Vd[b:b + 1])
+        assert torch.equal(O[b:b + 1], Ob) and torch.equal(lse[b:b + 1], lb), b
+    heads = slice(0, min(Hkv, 16) * G)
+    Or, lr = oracle.local_causal_attn(Q[-1:, heads], K[-1:, :min(Hkv, 16)], V[-1:, :min(Hkv, 16)])
+    PT.check_attn(O[-1:, heads], lse[-1:, heads], Or, lr, torch.bfloat16, f"masked batch {B}x{Hkv}x{G} {Lq}/{L}", report=True)
