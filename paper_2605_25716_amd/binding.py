@@ -9,6 +9,7 @@ from __future__ import annotations
 import ctypes
 import functools
 import os
+from operator import index
 from typing import Optional
 
 import torch  # noqa: F401  (imported before the library so that both share one HIP runtime)
@@ -154,17 +155,17 @@ def make_shape(batch: int, n_q_heads: int, n_kv_heads: int, d_head: int, dtype) 
 
 
 @functools.lru_cache(maxsize=256)
-def _cached_shape_ref(batch: int, n_q_heads: int, n_kv_heads: int, d_head: int, dtype: torch.dtype):
-    return ctypes.byref(make_shape(batch, n_q_heads, n_kv_heads, d_head, dtype))
-
-
 def _shape_ref(batch: int, n_q_heads: int, n_kv_heads: int, d_head: int, dtype):
     """A reference to the shape struct of these numbers, for the calls' `const fedrag_shape*` (read during the call
-    only): small calls spend as long on building ctypes objects as on the device.  Only plain integers are looked up: a
-    cache takes 8.0 for 8, which the struct refuses, and an integer tensor for itself whatever it holds by now."""
-    if type(batch) is type(n_q_heads) is type(n_kv_heads) is type(d_head) is int and type(dtype) is torch.dtype:
-        return _cached_shape_ref(batch, n_q_heads, n_kv_heads, d_head, dtype)
+    only): small calls spend as long on building ctypes objects as on the device.  For sizes of tensors and numbers passed
+    through `index`: the cache would take 8.0 for 8, which the struct refuses, and an integer tensor for itself whatever it
+    holds by now."""
     return ctypes.byref(make_shape(batch, n_q_heads, n_kv_heads, d_head, dtype))
+
+
+def _shape_ref_of_numbers(batch, n_q_heads, n_kv_heads, d_head, dtype):
+    return _shape_ref(index(batch), index(n_q_heads), index(n_kv_heads), index(d_head),
+                      dtype if isinstance(dtype, torch.dtype) else int(dtype))
 
 
 def _shape_of(q_like: torch.Tensor, n_kv_heads: int, dtype=None) -> Shape:
@@ -177,7 +178,7 @@ def fedrag_scramble_kv(K, V, phi_k, phi_v, perm_kv=None, n_q_heads: Optional[int
                        K_out=None, V_out=None):
     """K' = P_KV K Phi_KQ^{-T}, V' = P_KV V Phi_V for one shard.  K, V [B,Hkv,L,d]; perm_kv [n_perm,L] or [L]."""
     B, Hkv, L, d = K.shape
-    shape = _shape_ref(B, n_q_heads or Hkv, Hkv, d, K.dtype)
+    shape = _shape_ref(B, index(n_q_heads or Hkv), Hkv, d, K.dtype)
     K_out = torch.empty_like(K) if K_out is None else K_out
     V_out = torch.empty_like(V) if V_out is None else V_out
     n_perm = 0
@@ -210,7 +211,7 @@ def fedrag_scramble_q(Q, phi_q, perm_q=None, Q_out=None):
 
 
 def fedrag_partial_attn_workspace_bytes(batch, n_q_heads, n_kv_heads, d_head, dtype, L_q, L_kv) -> int:
-    shape = _shape_ref(batch, n_q_heads, n_kv_heads, d_head, dtype)
+    shape = _shape_ref_of_numbers(batch, n_q_heads, n_kv_heads, d_head, dtype)
     return int(load().fedrag_partial_attn_workspace_bytes(shape, L_q, L_kv))
 
 
@@ -247,7 +248,7 @@ def fedrag_partial_attn_static(Qs, Ks, Vs, O_part, lse, softmax_scale: Optional[
 
 
 def fedrag_partial_attn_shards_workspace_bytes(batch, n_q_heads, n_kv_heads, d_head, dtype, L_q, L_kv_list) -> int:
-    shape = _shape_ref(batch, n_q_heads, n_kv_heads, d_head, dtype)
+    shape = _shape_ref_of_numbers(batch, n_q_heads, n_kv_heads, d_head, dtype)
     n = len(L_kv_list)
     Ls = (ctypes.c_int64 * n)(*[int(x) for x in L_kv_list])
     return int(load().fedrag_partial_attn_shards_workspace_bytes(shape, L_q, n, Ls))
@@ -365,7 +366,7 @@ def fedrag_unscramble_merge(O_scr, lse_scr, phi_v_inv, perm_q, O_local, lse_loca
                             n_kv_heads: Optional[int] = None):
     """Dec of the remote result and its aggregation with the Inquirer's own partial, in one call."""
     B, Hq, Lq, d = O_scr.shape
-    shape = _shape_ref(B, Hq, n_kv_heads or phi_v_inv.shape[0], d, F32)
+    shape = _shape_ref(B, Hq, index(n_kv_heads or phi_v_inv.shape[0]), d, F32)
     O_out = torch.empty_like(O_scr) if O_out is None else O_out
     lse_out = torch.empty_like(lse_scr) if lse_out is None else lse_out
     st = load().fedrag_unscramble_merge(shape, Lq, _ptr(O_scr), _ptr(lse_scr), _ptr(phi_v_inv),
@@ -388,7 +389,7 @@ def fedrag_unpermute_lse(lse_scr, perm_q=None, lse_out=None):
 def fedrag_lse_merge(O_parts, lses, n_kv_heads: Optional[int] = None, O_out=None, lse_out=None):
     """Aggregation over shards.  O_parts fp32 [S,B,Hq,Lq,d], lses fp32 [S,B,Hq,Lq]."""
     S, B, Hq, Lq, d = O_parts.shape
-    shape = _shape_ref(B, Hq, n_kv_heads or Hq, d, F32)
+    shape = _shape_ref(B, Hq, index(n_kv_heads or Hq), d, F32)
     O_out = torch.empty((B, Hq, Lq, d), dtype=torch.float32, device=O_parts.device) if O_out is None else O_out
     lse_out = torch.empty((B, Hq, Lq), dtype=torch.float32, device=O_parts.device) if lse_out is None else lse_out
     st = load().fedrag_lse_merge(shape, Lq, S, _ptr(O_parts), _ptr(lses), _ptr(O_out), _ptr(lse_out),
@@ -424,7 +425,7 @@ def fedrag_scramble_kv_structured(K, V, key_k, key_v, perm_kv=None, n_q_heads: O
     B, Hkv, L, d = K.shape
     if key_k[0].shape != (Hkv, d) or key_v[0].shape != (Hkv, d):
         raise ValueError("structured key does not match [Hkv, d]")
-    shape = _shape_ref(B, n_q_heads or Hkv, Hkv, d, K.dtype)
+    shape = _shape_ref(B, index(n_q_heads or Hkv), Hkv, d, K.dtype)
     K_out = torch.empty_like(K) if K_out is None else K_out
     V_out = torch.empty_like(V) if V_out is None else V_out
     n_perm = 0
@@ -491,7 +492,7 @@ def fedrag_scramble_kv_quantized(K, V, phi_k, phi_v, perm_kv, bits: int, n_q_hea
     """Enc of a KV shard with the transport codec as epilogue.  phi_k / phi_v: dense matrices, or structured keys
     with structured=True.  Returns (K_codes, K_params, V_codes, V_params)."""
     B, Hkv, L, d = K.shape
-    shape = _shape_ref(B, n_q_heads or Hkv, Hkv, d, K.dtype)
+    shape = _shape_ref(B, index(n_q_heads or Hkv), Hkv, d, K.dtype)
     mk_c = lambda: torch.empty((B, Hkv, L, d * bits // 8), dtype=torch.uint8, device=K.device)
     mk_p = lambda: torch.empty((B, Hkv, L, 2), dtype=torch.float32, device=K.device)
     Kc, Kp, Vc, Vp = (mk_c(), mk_p(), mk_c(), mk_p()) if out is None else out
