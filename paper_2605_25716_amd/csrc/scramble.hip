@@ -734,15 +734,16 @@ static hipError_t launch_scramble16(const RowsJob& j, hipStream_t stream) {
 // unit whose matrix pipe is busy: `resident` workgroups of a unit (by registers: 120, 152, 184 a lane) take a step each in as
 // many of those; one, two or three of them, which wait for their rows, take `part`, more with a second partial to read; every
 // workgroup costs `setup` (its slice of Phi, or the multiplying out of the key), and where they come in several rounds the last
-// one ends unevenly (`tail` of a workgroup).  Fitted to 16 splits of 124 launches; over those the choice is 0.4 % from the best
-// split on average, 8 % at most.  d = 128: Dec of 2048 rows x 32 heads 34.8 us (39.8 with 3072 workgroups for every launch, as
-// before; structured 34.7 and 43.8), Enc of 16 x 500 rows x 8 heads 53 (63; structured 53 and 74), of 16 x 8192 840 (877; 897
-// and 987).
+// one ends unevenly (`tail` of a workgroup).  Fitted to 16 splits of 172 launches; over those the choice is 0.5 % from the
+// best split on average, 14 % at most from 10 us on.  d = 128: Dec of 2048 rows x 32 heads 32 us (36 with 3072 workgroups for
+// every launch, as before; structured 33 and 40), Enc of 16 x 500 rows x 8 heads 51 (56; structured 51 and 68), of 16 x 8192
+// 851 (879; 903 and 993).
 static int mf_steps_per_wg(int64_t steps, int64_t slabs, int D, bool structured, bool merge) {
     const int resident = D == 64 ? 4 : structured ? 2 : 3;
-    const float setup = D == 64 ? 0.15f : 0.3f;
-    const float tail = D == 64 ? 0.2f : structured ? 0.0f : 0.4f;
-    const float part[4] = {0.0f, merge ? 1.7f : 1.3f, merge ? 2.6f : 2.2f, merge ? 3.3f : 3.1f};
+    const float setup = D == 64 ? 0.4f : structured ? 0.3f : 0.5f;
+    const float tail = structured && D != 64 ? 0.0f : 0.4f;
+    const float part[4] = {0.0f, merge ? 1.7f : resident == 2 ? 1.3f : 1.5f, merge ? 2.6f : D == 64 ? 2.5f : 2.3f,
+                           merge ? 3.3f : 3.1f};
     const int64_t cus = attn_target_wgs();
     int best = 1;
     float least = 0.0f;
