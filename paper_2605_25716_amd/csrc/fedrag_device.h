@@ -9,6 +9,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -90,6 +91,8 @@ __device__ __forceinline__ LanePair lane_pair16(float x) {
 __device__ __forceinline__ float xor32_max(float x) { const LanePair p = lane_pair32(x); return fmaxf(p.lower, p.upper); }
 __device__ __forceinline__ float xor32_sum(float x) { const LanePair p = lane_pair32(x); return p.lower + p.upper; }
 __device__ __forceinline__ float xor16_max(float x) { const LanePair p = lane_pair16(x); return fmaxf(p.lower, p.upper); }
+__device__ __forceinline__ float xor32_min(float x) { const LanePair p = lane_pair32(x); return fminf(p.lower, p.upper); }
+__device__ __forceinline__ float xor16_min(float x) { const LanePair p = lane_pair16(x); return fminf(p.lower, p.upper); }
 __device__ __forceinline__ float xor16_sum(float x) { const LanePair p = lane_pair16(x); return p.lower + p.upper; }
 
 // min / max over aligned groups of N = 8 or 16 consecutive lanes, result in every lane of the group, with data-parallel
@@ -117,46 +120,29 @@ __device__ __forceinline__ float group_max(float x) {
     return group_reduce<N>(x, [](float a, float b) { return fmaxf(a, b); });
 }
 
-// The same reduction of a minimum and a maximum at once, one instruction per step and value: the data-parallel move is
-// folded into the minimum / maximum (the compiler emits a move, a canonicalising maximum and the operation itself).  A
-// register has to be two instructions old before a data-parallel read, which the other value's step and a nop give it.
-// One statement from the first step to the last, opened by that wait: the compiler may put a copy of either value before a
-// statement and does not look inside it for the distance.
-#define FEDRAG_MIN_MAX_STEP(lanes)                                       \
-    "v_min_f32_dpp %0, %0, %0 " lanes " row_mask:0xf bank_mask:0xf\n\t" \
-    "v_max_f32_dpp %1, %1, %1 " lanes " row_mask:0xf bank_mask:0xf\n\t"
-#define FEDRAG_MIN_MAX_OF_8                                         \
-    "s_nop 1\n\t" FEDRAG_MIN_MAX_STEP("quad_perm:[1,0,3,2]")        \
-    "s_nop 0\n\t" FEDRAG_MIN_MAX_STEP("quad_perm:[2,3,0,1]")        \
-    "s_nop 0\n\t" FEDRAG_MIN_MAX_STEP("row_half_mirror")
-template <int N>
-__device__ __forceinline__ void group_min_max(float& lo, float& hi) {
-    static_assert(N == 8 || N == 16, "groups of 8 or 16 lanes");
-    if constexpr (N == 8)
-        asm(FEDRAG_MIN_MAX_OF_8 "s_nop 1" : "+v"(lo), "+v"(hi));
-    else
-        asm(FEDRAG_MIN_MAX_OF_8 "s_nop 0\n\t" FEDRAG_MIN_MAX_STEP("row_mirror") "s_nop 1" : "+v"(lo), "+v"(hi));
-}
-#undef FEDRAG_MIN_MAX_OF_8
-#undef FEDRAG_MIN_MAX_STEP
-
-// Eight values in [0, 256) truncated to bytes, value e in byte e % 4 of word e / 4, each conversion writing its byte.  The
-// two words alternate because a partly written register must not be written again by the next instruction.
-__device__ __forceinline__ void bytes_of(const float (&t)[8], uint32_t& w0, uint32_t& w1) {
-    asm("v_cvt_u32_f32_sdwa %0, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:DWORD\n\t"
-        "v_cvt_u32_f32_sdwa %1, %6 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:DWORD\n\t"
-        "s_nop 0\n\t"
-        "v_cvt_u32_f32_sdwa %0, %3 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
-        "v_cvt_u32_f32_sdwa %1, %7 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
-        "s_nop 0\n\t"
-        "v_cvt_u32_f32_sdwa %0, %4 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
-        "v_cvt_u32_f32_sdwa %1, %8 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
-        "s_nop 0\n\t"
-        "v_cvt_u32_f32_sdwa %0, %5 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
-        "v_cvt_u32_f32_sdwa %1, %9 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+// Sixteen values in [0, 256) truncated to bytes, value e in byte e % 4 of word e / 4, each conversion writing its byte.  The
+// words take turns because a partly written register must not be written again by the next instruction.
+__device__ __forceinline__ void bytes_of(const float (&t)[16], uint32_t (&w)[4]) {
+    asm("v_cvt_u32_f32_sdwa %0, %4 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %1, %8 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %2, %12 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %3, %16 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %0, %5 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %1, %9 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %2, %13 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %3, %17 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %0, %6 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %1, %10 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %2, %14 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %3, %18 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %0, %7 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %1, %11 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %2, %15 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
+        "v_cvt_u32_f32_sdwa %3, %19 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD\n\t"
         "s_nop 1"
-        : "=&v"(w0), "=&v"(w1)
-        : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]));
+        : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+        : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]), "v"(t[8]), "v"(t[9]),
+          "v"(t[10]), "v"(t[11]), "v"(t[12]), "v"(t[13]), "v"(t[14]), "v"(t[15]));
 }
 
 // Keep a value's computation above this point: the compiler may otherwise sink pure register arithmetic towards

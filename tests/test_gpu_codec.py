@@ -134,6 +134,55 @@ def test_scramble_with_codec_epilogue(oracle, bits, dt, d, structured):
     assert (np.abs(Kh - ref_h) <= 1.01 * step + 3 * PT.storage_ulp(ref_h, dtype)).all()
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("structured", [False, True])
+@pytest.mark.parametrize("dt,d", [("bf16", 128), ("f16", 128), ("bf16", 64), ("f16", 64)])
+def test_codec_epilogue_at_the_edges_of_its_tiles(bits, structured, dt, d):
+    """Rows coded from the sums are the codes and parameters of the rows as stored, whatever the number of rows
+    left for the last 32-row tile, with and without a permutation, rows of zeros among them, and nothing is written behind the
+    last row.  Of a row with infinities only the parameters are defined."""
+    dtype = W.torch_dtype(dt)
+    for B, H, L in ((1, 1, 1), (2, 3, 31), (1, 2, 32), (1, 2, 33), (2, 2, 257), (3, 1, 4100), (1, 1, 20001)):
+        g = torch.Generator().manual_seed(1000 * L + d)
+        K, V = (torch.randn((B, H, L, d), generator=g) * torch.exp2(torch.randint(-6, 7, (B, H, L, 1), generator=g)) for _ in "KV")
+        K[:, :, L // 2] = 0.0
+        V[:, :, L // 3, d // 2:] = 0.0
+        if L > 1:
+            V[:, :, L - 1] = 65000.0 if dt == "f16" else 3e38  # sums beyond the storage type
+        K, V = K.to(dtype).to(DEV), V.to(dtype).to(DEV)
+        perms = W.make_keys(H, d, 1, L, 1, seed=L, dtype=dtype).perm_kv[0].to(DEV), None
+        if structured:
+            ks = W.make_structured_keys(H, d, 1, L, 1, seed=L, dtype=dtype)
+            kk, kv = tuple(t.to(DEV) for t in ks.k), tuple(t.to(DEV) for t in ks.v)
+        else:
+            keys = W.make_keys(H, d, 1, L, 1, seed=L, dtype=dtype)
+            kk, kv = keys.phi_k.to(DEV), keys.phi_v.to(DEV)
+        for perm in perms:
+            print(f"codec epilogue {dt} {d} {bits} {structured} {B} {H} {L} {perm is None}", flush=True)
+            # one block of bytes, so that what lies behind each output is seen
+            nc, np_ = B * H * L * d * bits // 8, B * H * L * 8
+            room = torch.full((2 * (nc + np_ + 512),), 0xA5, dtype=torch.uint8, device=DEV)
+            cut = [0, nc + 128 - nc % 16, 0, 0]
+            cut[2] = cut[1] + np_ + 128 - np_ % 16
+            cut[3] = cut[2] + nc + 128 - nc % 16
+            ends = [cut[0] + nc, cut[1] + np_, cut[2] + nc, cut[3] + np_]
+            codes = lambda i: room[cut[i]:ends[i]].view(B, H, L, d * bits // 8)  # noqa: E731
+            prm = lambda i: room[cut[i]:ends[i]].view(torch.float32).view(B, H, L, 2)  # noqa: E731
+            out = fb.fedrag_scramble_kv_quantized(K, V, kk, kv, perm, bits, structured=structured,
+                                                  out=(codes(0), prm(1), codes(2), prm(3)))
+            f = fb.fedrag_scramble_kv_structured if structured else fb.fedrag_scramble_kv
+            ref = sum((fb.fedrag_quantize_rows(x, bits) for x in f(K, V, kk, kv, perm)), ())
+            torch.cuda.synchronize()
+            defined = torch.isfinite(ref[3]).all(-1)
+            for i, (a, b) in enumerate(zip(out, ref)):
+                if i == 2:
+                    a, b = a[defined], b[defined]
+                # (the sign of a zero minimum is that of either zero)
+                assert torch.equal(a, b) if i % 2 == 0 else torch.allclose(a, b, 0, 0, equal_nan=True), (i, L, perm is None)
+            for end, begin in zip(ends, cut[1:] + [room.numel()]):
+                assert (room[end:begin] == 0xA5).all()
+
+
 ATTN_Q_CASES = [
     # name, B, Hq, Hkv, Lq, L, dtype
     ("g4_L3000", 3, 8, 2, 1, 3000, "bf16"),        # several KV splits, ragged tail
