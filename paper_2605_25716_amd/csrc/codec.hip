@@ -82,8 +82,7 @@ __global__ __launch_bounds__(kCodecThreads) void quantize_rows_kernel(const char
             float lo = x[u][0], hi = x[u][0];
 #pragma unroll
             for (int e = 1; e < 8; ++e) { lo = fminf(lo, x[u][e]); hi = fmaxf(hi, x[u][e]); }
-            lo = group_min<LPR>(lo);
-            hi = group_max<LPR>(hi);
+            group_min_max<LPR>(lo, hi);
             const float range = hi - lo;
             const float scale = range / (float)LEVELS;
             // x - lo >= 0, so the sum is >= 1/2: converting to unsigned truncates = floors, and only the upper clamp

@@ -112,13 +112,32 @@ __device__ __forceinline__ float group_reduce(float x, Op op) {
     return x;
 }
 template <int N>
-__device__ __forceinline__ float group_min(float x) {
-    return group_reduce<N>(x, [](float a, float b) { return fminf(a, b); });
-}
-template <int N>
 __device__ __forceinline__ float group_max(float x) {
     return group_reduce<N>(x, [](float a, float b) { return fmaxf(a, b); });
 }
+
+// The same reduction of a minimum and a maximum at once, one instruction per step and value: the data-parallel move is
+// folded into the minimum / maximum (the compiler emits a move, a canonicalising maximum and the operation itself).  A
+// register has to be two instructions old before a data-parallel read, which the other value's step and a nop give it.
+// One statement from the first step to the last, opened by that wait: the compiler may put a copy of either value before a
+// statement and does not look inside it for the distance.
+#define FEDRAG_MIN_MAX_STEP(lanes)                                       \
+    "v_min_f32_dpp %0, %0, %0 " lanes " row_mask:0xf bank_mask:0xf\n\t" \
+    "v_max_f32_dpp %1, %1, %1 " lanes " row_mask:0xf bank_mask:0xf\n\t"
+#define FEDRAG_MIN_MAX_OF_8                                         \
+    "s_nop 1\n\t" FEDRAG_MIN_MAX_STEP("quad_perm:[1,0,3,2]")        \
+    "s_nop 0\n\t" FEDRAG_MIN_MAX_STEP("quad_perm:[2,3,0,1]")        \
+    "s_nop 0\n\t" FEDRAG_MIN_MAX_STEP("row_half_mirror")
+template <int N>
+__device__ __forceinline__ void group_min_max(float& lo, float& hi) {
+    static_assert(N == 8 || N == 16, "groups of 8 or 16 lanes");
+    if constexpr (N == 8)
+        asm(FEDRAG_MIN_MAX_OF_8 "s_nop 1" : "+v"(lo), "+v"(hi));
+    else
+        asm(FEDRAG_MIN_MAX_OF_8 "s_nop 0\n\t" FEDRAG_MIN_MAX_STEP("row_mirror") "s_nop 1" : "+v"(lo), "+v"(hi));
+}
+#undef FEDRAG_MIN_MAX_OF_8
+#undef FEDRAG_MIN_MAX_STEP
 
 // Sixteen values in [0, 256) truncated to bytes, value e in byte e % 4 of word e / 4, each conversion writing its byte.  The
 // words take turns because a partly written register must not be written again by the next instruction.
