@@ -135,8 +135,9 @@ fedrag_status fedrag_partial_attn_static(const fedrag_shape* shape, int64_t L_q,
  * fedrag_lse_merge over them, in one call.  Small problems take one attention launch over all shards' keys plus one
  * aggregation launch, instead of one of each per shard (what counts when a shard is a few thousand tokens and a
  * launch costs as much as its work); at decode shapes, when a single shard's sequences already cover the chip, the
- * attention is launched shard by shard and aggregated once.  Every shard has at least one fp32 partial of its own.  The
- * result equals attention over the concatenation of the shards' keys (eq. (1)).
+ * attention is launched shard by shard and aggregated once; at prefill shapes whose query tiles cover the chip, a
+ * workgroup may visit the shards in turn and use no workspace.  The weight between shards is an fp32 number in every form.
+ * The result equals attention over the concatenation of the shards' keys (eq. (1)).
  * n_shards : 1 .. FEDRAG_MAX_SHARDS.  L_kv, Ks, Vs : HOST arrays of n_shards entries - shard lengths (>= 0; an empty
  * shard contributes nothing and its pointers may be NULL) and DEVICE pointers to [B,Hkv,L_kv[i],d] tensors in
  * shape->dtype (16-byte aligned).  The arrays are read during the call only.

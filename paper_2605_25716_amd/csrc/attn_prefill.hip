@@ -36,7 +36,13 @@ constexpr int kPrePD = FEDRAG_PRE_PD;         // MFMA operands are read from LDS
 // storage type (relative error 2^-9 in bf16) would move an output by more than the 16-bit output tolerance.  The
 // CAUSAL instantiation therefore feeds the second product P = P_hi + P_lo, two storage-type terms (about 16
 // significant bits), at the price of twice the MFMAs of that product.
-template <class T, int D, bool CAUSAL, int QB, int NW>
+// WALK: several shards whose query tiles alone cover the chip.  A workgroup visits the shards one after the other and carries
+// its maximum, sum and output along: no partials and no aggregation.  The probabilities of a shard are rounded against the
+// shard's own running maximum, as they are in a launch of its own: its first tile starts the maximum anew, 2^63 below the
+// weight collected so far, and the output takes the fp32 factor between the two, which may be as large as that.  (What stays
+// below is nothing beside fp32 sums.  With the maximum carried along the weight between shards sat in the 16 bits of the
+// probabilities: an error of 3.6e-4 against 64 bits where this, like a partial per shard, has 3.3e-4.)
+template <class T, int D, bool CAUSAL, int QB, int NW, bool WALK>
 __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefill_attn_kernel(const typename T::elem* __restrict__ Q,
                                                                       const KeyRuns runs,
                                                                       const float* __restrict__ Kprm,
@@ -59,6 +65,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     constexpr int MT = D / 32;              // 32-row tiles of O^T
     constexpr int CH = D / 8;               // 16-byte chunks per row
     constexpr int LPT = (kPreK * CH) / kThreads;  // LDS-direct loads (QB: 8-element chunks) per thread per tile
+    static_assert(!WALK || (!CAUSAL && QB == 0), "several shards: the plain form");
     static_assert(QB == 0 || QB == 8 || QB == 4, "16-bit values, or 8- / 4-bit codes");
     static_assert(QB == 0 || !CAUSAL, "codes are what travels to the Compute Node; the Inquirer's own K, V are plain");
     constexpr int CROWB = QB ? D * QB / 8 : ROWB;  // bytes per row of K' / V' as stored (values, or codes)
@@ -87,7 +94,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     const int w_in_unit = run_by_run ? inner : outer;
     const int run = run_by_run ? outer : inner;
     int split = 0;
-    const KeyShard shard = runs.shard_of(run, &split);
+    const KeyShard shard = WALK ? runs.s[0] : runs.shard_of(run, &split);
     const elem* K = (const elem*)shard.K;
     const elem* V = (const elem*)shard.V;
     const int64_t L_stride = shard.L;
@@ -133,7 +140,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     const int64_t part_row0 = (int64_t)run * n_units * G * Lq;  // n_units * G * Lq = rows of one partial
     float* Oh = O + (part_row0 + ((int64_t)b * Hq + h) * Lq) * D;
     float* Lh = lse + part_row0 + ((int64_t)b * Hq + h) * Lq;
-    if (!CAUSAL && n_runs > 1) {  // this workgroup's run of keys; a run past the end is empty
+    if (!CAUSAL && !WALK && n_runs > 1) {  // this workgroup's run of keys; a run past the end is empty
         const int64_t k_begin = (int64_t)split * keys_per_run;
         const int64_t k_end = k_begin + keys_per_run < L ? k_begin + keys_per_run : L;
         L = k_end > k_begin ? k_end - k_begin : 0;
@@ -258,8 +265,8 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     const int64_t q_first = (int64_t)qt * kQTile;
     const int64_t q_last = (q_first + kQTile < Lq ? q_first + kQTile : Lq) - 1;
     const int64_t wg_keys = CAUSAL ? (q_last + off + 1 < L ? q_last + off + 1 : L) : L;
-    const int n_tiles = (int)((wg_keys + kPreK - 1) / kPreK);
-    const int t_mask0 = (int)((CAUSAL ? (q_first + off + 1 < L ? q_first + off + 1 : L) : L) / kPreK);
+    int n_tiles = (int)((wg_keys + kPreK - 1) / kPreK);
+    int t_mask0 = (int)((CAUSAL ? (q_first + off + 1 < L ? q_first + off + 1 : L) : L) / kPreK);
     // prologue: K' of the first tile to visit is fetched first, Q' behind it
     int tile = CAUSAL ? n_tiles - 1 : 0;
     if constexpr (QB == 0) load_tile(Kg, ks0, tile, true);
@@ -269,7 +276,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qop[ks] = *(const vec8*)(Qh + q_ld * D + ks * 16 + lh * 8);
 
-    const int key_lim = (int)(CAUSAL ? (q_row + off + 1 < L ? q_row + off + 1 : L) : L);  // this lane's row sees keys < key_lim
+    int key_lim = (int)(CAUSAL ? (q_row + off + 1 < L ? q_row + off + 1 : L) : L);  // this lane's row sees keys < key_lim
     f32x16_t S0;      // S^T of the current tile, keys 0..31
     f32x16_t S1[2];   // S1[t & 1]: S^T of tile t, keys 32..63 (kept one iteration longer, see below)
     vec8 P[2][4];     // P[t & 1]: P^T operands of tile t, one per 16-key step
@@ -281,6 +288,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
         if constexpr (SPLIT) Plo[par][kk][e] = T::from_float(pe - T::to_float(hi));
     };
     float alph[2];    // alph[t & 1]: rescale factor of the running output that goes with P(t)
+    float drop = 0.f;  // WALK: what the first tile of a shard takes off the maximum it finds
 
     auto read_vop = [&](const char* vt, int kk, int i) -> vec8 {
         const char* p = vt + kk * 16 * ROWB + v_off[i];
@@ -421,7 +429,8 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
                     }
                     if (j == FIRST) {
                         mx = xor32_max(mx);
-                        m_new = fmaxf(m_run, mx * scale_log2);  // scale > 0: max commutes with the scaling
+                        // scale > 0: max commutes with the scaling
+                        m_new = fmaxf(WALK && kind == kFirst ? m_run - drop : m_run, mx * scale_log2);
                         alph[p] = exp2_diff(m_run, m_new);
                     }
                     if (j >= FIRST) {
@@ -473,6 +482,18 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
         __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), the other counters untouched
         __syncthreads();
     };
+    // WALK: the next shard's first K' tile is fetched behind the last step of this one, which reads no K' (slot 0 was last read
+    // before the barrier ahead of it)
+    auto next_shard = [&](int sh) {
+        if constexpr (WALK) {
+            if (sh + 1 == runs.n_shards) return;
+            const KeyShard next = runs.s[sh + 1];
+            L = next.L;
+            Kg = (const char*)next.K + (int64_t)unit * L * CROWB;
+            Vg = (const char*)next.V + (int64_t)unit * L * CROWB;
+            load_tile(Kg, ks0, 0, true);
+        }
+    };
     if constexpr (QB != 0) store_codes(ks0, kst, true);
     alph[0] = alph[1] = 1.0f;
     tile_barrier();
@@ -496,12 +517,13 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
             tile_barrier();
         }
         iteration(0, 0, odd, last, false);
-    } else {
+    } else for (int sh = 0;;) {
         // the pipeline takes the largest odd number of whole tiles (tile 0 in any case); what is left, a whole tile, the
         // ragged one or both, is finished one by one behind it.  Their K' arrives in the slot of odd tiles, where the
         // pipeline's last iteration has put the next one.
         const int n_pipe = t_mask0 <= 2 ? 1 : t_mask0 - 1 + (t_mask0 & 1);
         iteration(0, 1, even, first, true);
+        drop = 0.f;
         tile_barrier();
         for (tile = 1; tile < n_pipe; tile += 2) {
             iteration(tile, tile + 1, odd, steady, true);
@@ -509,6 +531,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
             iteration(tile + 1, tile + 2, even, steady, true);
             tile_barrier();
         }
+        if (n_pipe == n_tiles) next_shard(sh);
         iteration(0, 0, odd, last, false);
         for (tile = n_pipe; tile < n_tiles;) {
             iteration(tile, 0, odd, first, false);
@@ -517,12 +540,21 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
             if (more) {
                 if constexpr (QB == 0) load_tile(Kg, ks1, tile, true);
                 else fetch_codes(Kg, Kpg, tile, kst);
+            } else {
+                next_shard(sh);
             }
             iteration(0, 0, even, last, false);
             if (!more) break;
             if constexpr (QB != 0) store_codes(ks1, kst, true);
             tile_barrier();
         }
+        if (!WALK || ++sh == runs.n_shards) break;
+        tile = 0;
+        n_tiles = (int)((L + kPreK - 1) / kPreK);
+        t_mask0 = (int)(L / kPreK);
+        key_lim = (int)L;
+        drop = 64.0f - (float)__builtin_amdgcn_frexp_expf(xor32_sum(l_run));
+        tile_barrier();
     }
 
     // epilogue: lane holds query li and rows d = 32 i + 8 (r / 4) + 4 lh + r % 4 of O^T.  The rows go out through LDS
@@ -575,13 +607,51 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
 // Always four with a mask, whose tiles are unequal (2048-token segment 62 against 79 us, 300 tokens 12 against 17), and for 16-bit
 // batches with query counts, whose workgroups are fewer than the padded shape says (the 10-pair re-rank batch 29 against 42;
 // where every sequence is as long as the padding, 2 to 6 % slower).  On codes such a batch goes by its padded shape.
-static bool prefill_wants_4_waves(int64_t wgs8, int64_t wgs4, int64_t tiles, int D, bool codes) {
+struct PrefillCost {
+    float c8, c4;  // in tiles of the larger form, for the launch with workgroups of eight and of four waves
+    bool four() const { return c4 < c8; }
+    float least() const { return c4 < c8 ? c4 : c8; }
+};
+static PrefillCost prefill_cost(int64_t wgs8, int64_t wgs4, float tiles, float ends, int D, bool codes) {
     const int64_t cus = attn_target_wgs();
     const int64_t q8 = (wgs8 + cus - 1) / cus, q4 = (wgs4 + cus - 1) / cus;
     const float a = D == 64 ? (codes ? 0.20f : 0.15f) : codes ? 0.08f : 0.05f;
     const float b = D == 64 ? (codes ? 0.465f : 0.445f) : codes ? 0.55f : 0.51f;
-    const float ends = q8 == 1 ? 0.0f : codes ? 2.0f : 4.0f;
-    return (a + b * (float)q4) * ((float)tiles + 0.5f * ends) < (float)q8 * ((float)tiles + ends);
+    return PrefillCost{(float)q8 * (tiles + ends), (a + b * (float)q4) * (tiles + 0.5f * ends)};
+}
+static bool prefill_wants_4_waves(int64_t wgs8, int64_t wgs4, int64_t tiles, int D, bool codes) {
+    const float ends = wgs8 <= attn_target_wgs() ? 0.0f : codes ? 2.0f : 4.0f;
+    return prefill_cost(wgs8, wgs4, (float)tiles, ends, D, codes).four();
+}
+
+// Several shards: whether a workgroup visits them all (WALK), by the same cost.  Either way a workgroup's start and end take
+// four tiles; a shard's end inside a walk takes one, runs of unequal length end unevenly, and the fold reads a partial per run
+// (7.5 bytes per ns, a tile takes 1.77 us at d = 128 and 1.19 at d = 64).  At d = 64 the walking form is itself 5 % slower.
+// Only from query tiles for a whole round on: below that shards side by side fill the chip (1500 x 32 heads x 2 x 5000 keys
+// 252 us, 253 to 283 walked; 1100 x 32 x 8 x 5000 714 and 960).  4096 x 64 rows of 128 x 8 x 8192 keys: 7.44 ms walked, 7.76 with
+// partials; 2048 x 32 x 8 x 2048 515 and 605 us, x 8 x 512 139 and 217, x (8000 + 500) 252 and 418; 4096 x 64 of 64 x 2 x 300 62
+// and 99.  Where the rounds come out uneven it is the other way: 1100 x 64 x 4 x 3000 549 and 454.
+static bool prefill_walks(const AttnProblem& p, const KeyRuns& runs, int Hq_k, int64_t tiles8, int64_t tiles4, int D, bool* four) {
+    const int64_t heads = (int64_t)p.B * Hq_k;
+    if (heads * tiles8 < attn_target_wgs()) return false;
+    int n = 0;
+    float total = 0.0f, longest = 0.0f;
+    for (int i = 0; i < p.n_shards; ++i) {
+        if (runs.s[i].L <= 0) continue;
+        const float tiles = (float)((runs.s[i].L + kPreK - 1) / kPreK);
+        total += tiles;
+        longest = tiles > longest ? tiles : longest;
+        ++n;
+    }
+    if (n < 2 || runs.n_runs != n) return false;
+    const float mean = total / (float)n;
+    const float rows = (float)p.B * (float)p.Hq * (float)p.Lq;
+    const float fold_us = 3.0f + (float)n * rows * (float)(D + 1) * 4.0f / 7.5e6f;
+    const float side_by_side = prefill_cost(heads * tiles8 * n, heads * tiles4 * n, mean, 4.0f, D, false).least() +
+                               0.5f * (longest - mean) + fold_us / (D == 64 ? 1.19f : 1.77f);
+    const PrefillCost walked = prefill_cost(heads * tiles8, heads * tiles4, total + (float)(n - 1), 4.0f, D, false);
+    *four = walked.four();
+    return walked.least() * (D == 64 ? 1.05f : 1.0f) < side_by_side;
 }
 
 // Order of a unit's workgroups when there are several runs.  The runs of a query tile side by side, unless one run's
@@ -591,7 +661,7 @@ static bool prefill_wants_4_waves(int64_t wgs8, int64_t wgs4, int64_t tiles, int
 constexpr int64_t kPreRunByRunBytes = 16 << 20;
 constexpr int64_t kPreTogetherBytes = 8 << 20;  // K and V of an XCD's units, whose L2 is 4 MiB
 
-template <class T, int D, bool CAUSAL, int QB, int NW>
+template <class T, int D, bool CAUSAL, int QB, int NW, bool WALK>
 static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, int Hq_k, int64_t Lq_k, int64_t q_tiles,
                                     float* Odst, float* Ldst, hipStream_t stream) {
     typedef typename T::elem elem;
@@ -611,7 +681,7 @@ static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, i
     // 8 x 4096 (16 MiB) 1524 and 1567.
     const int64_t units_per_xcd = (n_units + 7) / 8;
     const int together = CAUSAL && units_per_xcd * keys * (4 * D) <= kPreTogetherBytes ? 1 : 0;
-    hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB, NW>), dim3((unsigned)grid), dim3(NW * kWave), 0, stream,
+    hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB, NW, WALK>), dim3((unsigned)grid), dim3(NW * kWave), 0, stream,
                        (const elem*)p.Q, runs, p.K_params, p.V_params, Hq_k, FastDiv(p.Hkv), FastDiv(Hq_k / p.Hkv),
                        FastDiv(q_tiles), FastDiv(together ? units_per_xcd : per_unit), FastDiv(run_by_run ? tiles_of_unit : runs.n_runs),
                        run_by_run ? 1 : 0, Lq_k, p.kv_lens, p.q_lens, n_units, fold, together,
@@ -649,6 +719,19 @@ static hipError_t launch_prefill_t(const AttnProblem& p, hipStream_t stream) {
         Ldst = Odst + (size_t)splits * rows * D;
     }
     const int64_t tiles8 = (Lq_k + 8 * kPreQ - 1) / (8 * kPreQ), tiles4 = (Lq_k + 4 * kPreQ - 1) / (4 * kPreQ);
+    if constexpr (!CAUSAL && QB == 0) {
+        bool walk4 = false;
+        if (p.n_shards > 1 && prefill_walks(p, runs, Hq_k, tiles8, tiles4, D, &walk4)) {  // writes O, lse; no partials
+            KeyRuns all = runs;
+            all.n_shards = 0;
+            for (int i = 0; i < p.n_shards; ++i)
+                if (runs.s[i].L > 0) all.s[all.n_shards++] = runs.s[i];
+            all.n_runs = 1;
+            all.by_runs = FastDiv(1);
+            return walk4 ? launch_prefill_nw<T, D, false, 0, 4, true>(p, all, Hq_k, Lq_k, tiles4, p.O, p.lse, stream)
+                         : launch_prefill_nw<T, D, false, 0, 8, true>(p, all, Hq_k, Lq_k, tiles8, p.O, p.lse, stream);
+        }
+    }
     const int64_t heads = (int64_t)p.B * Hq_k * splits;
     int64_t key_tiles = 1;  // of the longest run
     for (int i = 0; i < runs.n_shards; ++i) {
@@ -658,8 +741,8 @@ static hipError_t launch_prefill_t(const AttnProblem& p, hipStream_t stream) {
     const bool four = CAUSAL || (p.q_lens && QB == 0 && p.B > 1) ||
                       prefill_wants_4_waves(heads * tiles8, heads * tiles4, key_tiles, D, QB != 0);
     hipError_t e = hipErrorInvalidValue;
-    if (four) e = launch_prefill_nw<T, D, CAUSAL, QB, 4>(p, runs, Hq_k, Lq_k, tiles4, Odst, Ldst, stream);
-    else if constexpr (!CAUSAL) e = launch_prefill_nw<T, D, false, QB, 8>(p, runs, Hq_k, Lq_k, tiles8, Odst, Ldst, stream);
+    if (four) e = launch_prefill_nw<T, D, CAUSAL, QB, 4, false>(p, runs, Hq_k, Lq_k, tiles4, Odst, Ldst, stream);
+    else if constexpr (!CAUSAL) e = launch_prefill_nw<T, D, false, QB, 8, false>(p, runs, Hq_k, Lq_k, tiles8, Odst, Ldst, stream);
     if (e != hipSuccess || splits == 1) return e;
     return launch_lse_merge(Odst, Ldst, splits, rows, D, p.O, p.lse, stream);
 }

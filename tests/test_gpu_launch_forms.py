@@ -45,6 +45,33 @@ def test_weights_between_shards_are_fp32(d, dt, Ls):
     assert torch.equal(O, Om) and torch.equal(lse, lm)
 
 
+# query tiles of a whole round and more: a workgroup visits the shards one after the other
+@pytest.mark.parametrize("B,Hq,d,dt,Lq,Ls", [(1, 32, 128, "bf16", 2048, [70, 64, 0, 1, 200]), (1, 32, 64, "f16", 2048, [128, 65, 500]),
+                                             (2, 32, 128, "f16", 1500, [64, 192]), (1, 64, 64, "bf16", 4096, [1, 1, 63, 129])])
+@pytest.mark.parametrize("spread", [0.0, 40.0])
+def test_shards_visited_in_turn(B, Hq, d, dt, Lq, Ls, spread):
+    """A shard's probabilities are rounded as in a launch of its own and the weight between shards is an fp32 number: the call
+    agrees with the shards one by one and the aggregation of their partials to fp32 sums.  Per shard these differ by a factor
+    (2^-21: two exponentials of 2^-22) and a rescale per tile (2^-24 each, below 2^-19 in all) of outputs of at most max |v| <= 6.
+    Also with shards whose scores are far apart, so far that a shard weighs nothing, in rising and in falling order."""
+    Q = rnd(B, Hq, Lq, d, dt, W.TID_Q).to(DEV)
+    Ks = [rnd(B, 8, L, d, dt, W.TID_K + 16 * (i + 1)) for i, L in enumerate(Ls)]
+    Vs = [rnd(B, 8, L, d, dt, W.TID_V + 16 * (i + 1)).to(DEV) for i, L in enumerate(Ls)]
+    Q[..., 0] = torch.where(torch.arange(Lq, device=DEV) % 2 == 0, 16.0, -16.0).to(Q.dtype)
+    for i, k in enumerate(Ks):
+        k[..., 0] = spread * i  # scores of +-16 * 40 * i / sqrt(d): hundreds apart
+    Ks = [k.to(DEV) for k in Ks]
+    print(f"shards in turn {B} {Hq} {d} {dt} {Lq} {Ls} {spread}", flush=True)
+    O, lse = fb.fedrag_partial_attn_shards(Q, Ks, Vs)
+    parts = [fb.fedrag_partial_attn(Q, k, v) for k, v in zip(Ks, Vs)]
+    Om, lm = fb.fedrag_lse_merge(torch.stack([p[0] for p in parts]), torch.stack([p[1] for p in parts]), n_kv_heads=8)
+    torch.cuda.synchronize()
+    # lse itself is held to 2^-23 of its size by either form, and the weights with it
+    tol = 2.0 ** -21 + 2.0 ** -19 + 2.0 ** -22 * float(lm.abs().max())
+    assert float((lse - lm).abs().max()) <= tol
+    assert float((O - Om).abs().max()) <= 6.0 * tol
+
+
 def test_every_shard_boundary_keeps_its_keys():
     """One key tile of one shard holds all the weight of a query row: a tile lost or read twice at a shard's end moves that
     row's log-sum-exp by ln 2 or more."""
