@@ -304,3 +304,37 @@ def test_masked_batches_reach_every_tile_of_every_unit(oracle, B, Hkv, G, Lq, L,
     heads = slice(0, min(Hkv, 16) * G)
     Or, lr = oracle.local_causal_attn(Q[-1:, heads], K[-1:, :min(Hkv, 16)], V[-1:, :min(Hkv, 16)])
     PT.check_attn(O[-1:, heads], lse[-1:, heads], Or, lr, torch.bfloat16, f"masked batch {B}x{Hkv}x{G} {Lq}/{L}", report=True)
+
+
+@pytest.mark.parametrize("L", [1, 2, 7, 16, 17])  # at most 16 rows a head have a kernel of their own
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("structured", [False, True])
+def test_few_rows(L, d, structured):
+    """A handful of rows per head, every storage type, gathered and scattered, several sequences: fp32 sums of d products, each
+    share of them in order (d + 2 roundings of 2^-24 of the sum of the terms' sizes at most), narrowed once."""
+    B, Hkv, G = 3, 2, 2
+    H = Hkv * G
+    g = torch.Generator().manual_seed(100 * L + d)
+    perm = torch.randperm(L, generator=g).to(torch.int32)
+    for dt in ("f32", "bf16", "f16"):
+        dtype = W.torch_dtype(dt)
+        x = torch.randn((B, H, L, d), generator=g).to(dtype)
+        if structured:
+            key = W.make_structured_keys(Hkv, d, L, 64, 1, seed=d + L, dtype=dtype).q
+            a, g1, g2, b = (t.double() if t.is_floating_point() else t.long() for t in key)
+            had = torch.from_numpy(W.sylvester_hadamard(d)).double()
+            had /= had[0, 0] * np.sqrt(d)
+            m = torch.stack([((torch.eye(d, dtype=torch.float64) * a[h])[:, g1[h]] @ had)[:, g2[h]] * b[h] for h in range(Hkv)])
+            key = tuple(t.to(DEV) for t in key)
+        else:
+            m = torch.randn((Hkv, d, d), generator=g).to(dtype)
+            key, m = m.to(DEV), m.double()
+        m = m.repeat_interleave(G, 0)
+        want, size = x.double() @ m, x.double().abs() @ m.abs()
+        tol = size * (d + 4) * 2.0 ** -24 + want.abs() * {"f32": 0.0, "bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dt] + 1e-7
+        print(f"few rows {L} {d} {structured} {dt}", flush=True)
+        got = (fb.fedrag_scramble_q_structured if structured else fb.fedrag_scramble_q)(x.to(DEV), key, perm.to(DEV)).cpu()
+        assert ((got.double() - want[:, :, perm.long()]).abs() <= tol[:, :, perm.long()]).all(), dt
+        if dt == "f32":  # Dec: the same rows scattered
+            got = (fb.fedrag_unscramble_structured if structured else fb.fedrag_unscramble)(x.to(DEV), key, perm.to(DEV)).cpu()
+            assert ((got.double()[:, :, perm.long()] - want).abs() <= tol).all()
