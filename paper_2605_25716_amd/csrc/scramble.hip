@@ -450,28 +450,30 @@ struct F32 {
     static __device__ __forceinline__ float to_float(elem x) { return x; }
 };
 
-// The Section 4.1 aggregation of two partials of a row, in the arithmetic and order of lse_merge_kernel.  *lse = its lse.
-__device__ __forceinline__ float merge_two(float mine, float la, float other, float lb, float* lse) {
+// The Section 4.1 aggregation of two partials of a row, in the arithmetic and order of lse_merge_kernel.
+struct RowWeights {
+    float a, b, inv;  // a, b < 0: weight zero, the partial takes no part
+};
+__device__ __forceinline__ RowWeights weights_of_two(float la, float lb, float* lse) {
     const float M = fmaxf(fmaxf(-INFINITY, la), lb);
-    float o = 0.f, den = 0.f;
+    RowWeights w{-1.f, -1.f, 0.f};
+    float den = 0.f;
     if (M != -INFINITY) {
-        if (la != -INFINITY) {
-            const float a = expf(la - M);
-            den += a;
-            o = __builtin_fmaf(a, mine, o);
-        }
-        if (lb != -INFINITY) {
-            const float a = expf(lb - M);
-            den += a;
-            o = __builtin_fmaf(a, other, o);
-        }
-        o *= 1.0f / den;
+        if (la != -INFINITY) den += w.a = expf(la - M);
+        if (lb != -INFINITY) den += w.b = expf(lb - M);
+        w.inv = 1.0f / den;
     }
     *lse = (M == -INFINITY) ? -INFINITY : M + logf(den);
-    return o;
+    return w;
+}
+__device__ __forceinline__ float merge_two(const RowWeights& w, float mine, float other) {
+    float o = 0.f;
+    if (w.a != -1.f) o = __builtin_fmaf(w.a, mine, o);
+    if (w.b != -1.f) o = __builtin_fmaf(w.b, other, o);
+    return w.a != -1.f || w.b != -1.f ? o * w.inv : 0.f;
 }
 
-template <class T, int D, bool SCATTER, bool ST>
+template <class T, int D, bool SCATTER, bool ST, bool WIDE>
 __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0, ScrambleJob job1,
                                                                const int32_t* __restrict__ perm,
                                                                int64_t perm_batch_stride, int H, int G, int L,
@@ -486,9 +488,10 @@ __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0,
     constexpr int XC = (kFewRows * D / EPC + kF32Threads - 1) / kF32Threads;  // such loads per thread, at most
     typedef elem chunk_t __attribute__((ext_vector_type(EPC)));
     typedef elem pair_t __attribute__((ext_vector_type(2)));
-    // fp32 storage: the rounding of the queries comes back multiplied by the scores, and there is time for sums in 64 bits (4 rows
-    // x 512 keys, outputs against 64 bits: 1.0e-6 with fp32 sums one after the other, 0.8e-6; log-sum-exps 1.0e-7 and 0.6e-7)
-    typedef typename std::conditional<kF32 && !SCATTER, double, float>::type acc_t;
+    // WIDE (fp32 storage): the rounding of the queries comes back multiplied by the scores, and there is time for sums in 64 bits
+    // (4 rows x 512 keys, outputs against 64 bits: 1.0e-6 with fp32 sums one after the other, 0.8e-6; log-sum-exps 1.0e-7, 0.6e-7)
+    static_assert(!WIDE || (kF32 && !SCATTER), "queries in fp32 storage");
+    typedef typename std::conditional<WIDE, double, float>::type acc_t;
     typedef acc_t acc4_t __attribute__((ext_vector_type(4)));
     typedef acc_t acc2_t __attribute__((ext_vector_type(2)));
     __shared__ __attribute__((aligned(16))) acc_t xs[kFewRows * D];
@@ -583,7 +586,7 @@ __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0,
             const int k = kg * KPG + i;
             phi[i][0] = structured_entry(s_in[k], p_in_inv[k], key_out0 & (D - 1));
             phi[i][1] = structured_entry(s_in[k], p_in_inv[k], key_out1 & (D - 1));
-            if (kF32) { phi[i][0] *= post0; phi[i][1] *= post1; }  // fp32: as the fp32 kernels below; 16 bits: after the sum
+            if (kF32) { phi[i][0] *= post0; phi[i][1] *= post1; }  // fp32: as the tiled fp32 kernel; 16 bits: after the sum
         } else {
             phi[i][0] = T::to_float(phi_in[i][0]);
             phi[i][1] = T::to_float(phi_in[i][1]);
@@ -618,101 +621,20 @@ __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0,
         if (ST && !kF32) v *= post0;
         if (SCATTER && mg.lse_in) {
             float l;
-            v = merge_two(v, o.la, o.other, o.lb, &l);
+            v = merge_two(weights_of_two(o.la, o.lb, &l), v, o.other);
             if (e % D == 0) mg.lse_out[(int64_t)bh * L + o.dst] = l;
         }
         Y[o.dst * D + e % D] = T::from_float(v);
     }
 }
 
-// fp32 rows times fp32 matrix with plain FMAs (fp32 storage path of Enc, and Dec for every storage type).
-// Thread (c, rg) owns output column c and holds column c of Phi in registers; rows are broadcast from LDS.
-//   SCATTER == false: Y[j]       = X[perm[j]] . Phi   (perm NULL = identity)
-//   SCATTER == true : Y[perm[i]] = X[i] . Phi
-constexpr int kF32Rows = 32;
-
-// mg.lse_in != NULL (scatter form only): the transformed row is one of two partials of Section 4.1 and is
-// aggregated with the other one, which is already in destination order, before it is stored - the same arithmetic,
-// in the same order, as lse_merge_kernel over (this row, the other partial).
-template <int D, bool SCATTER, bool ST>
-__global__ __launch_bounds__(kF32Threads) void rows_times_matrix_f32_kernel(ScrambleJob job0, ScrambleJob job1,
-                                                                            const int32_t* __restrict__ perm,
-                                                                            int64_t perm_batch_stride, int H, int G,
-                                                                            int64_t L, int chunks, int tiles_per_wg,
-                                                                            RowsMerge mg) {
-    constexpr int RG = kF32Threads / D;  // row groups
-    __shared__ __attribute__((aligned(16))) float xs[kF32Rows * D];
-    const ScrambleJob job = blockIdx.y == 0 ? job0 : job1;
-    const int tid = threadIdx.x;
-    const int c = tid % D;
-    const int rg = tid / D;
-    const int bh = blockIdx.x / chunks;
-    const int chunk = blockIdx.x % chunks;
-    const int b = bh / H;
-    const int h = bh % H;
-    float phi[D];
-    __shared__ int32_t p_in_inv[ST ? D : 1];
-    __shared__ float s_in[ST ? D : 1];
-    if (ST) {  // column c of S1 P1 H P2 S2, generated from the key
-        const int32_t* g1 = job.p_in + (int64_t)(h / G) * D;
-        for (int k = tid; k < D; k += kF32Threads) {
-            p_in_inv[g1[k] & (D - 1)] = k;
-            s_in[k] = job.s_in[(int64_t)(h / G) * D + k];
-        }
-        __syncthreads();
-        const int m = job.p_out[(int64_t)(h / G) * D + c] & (D - 1);
-        const float post = job.s_out[(int64_t)(h / G) * D + c] * (D == 128 ? 0.08838834764831845f : 0.125f);
-#pragma unroll
-        for (int k = 0; k < D; ++k) phi[k] = structured_entry(s_in[k], p_in_inv[k], m) * post;
-    } else {
-        const float* P = (const float*)job.Phi + (int64_t)(h / G) * D * D;
-#pragma unroll
-        for (int k = 0; k < D; ++k) phi[k] = P[k * D + c];
-    }
-
-    const float* X = (const float*)job.X + (int64_t)bh * L * D;
-    float* Y = (float*)job.Y + (int64_t)bh * L * D;
-    const int32_t* pm = perm ? perm + (int64_t)b * perm_batch_stride : nullptr;
-
-    int64_t row0 = (int64_t)chunk * tiles_per_wg * kF32Rows;
-    for (int t = 0; t < tiles_per_wg && row0 < L; ++t, row0 += kF32Rows) {
-        __syncthreads();
-        for (int e = tid; e < kF32Rows * (D / 4); e += kF32Threads) {
-            const int r = e / (D / 4);
-            const int c4 = (e % (D / 4)) * 4;
-            int64_t j = row0 + r;
-            if (j >= L) j = L - 1;
-            const int64_t src = (!SCATTER && pm) ? (int64_t)pm[j] : j;
-            *(f32x4_t*)(&xs[r * D + c4]) = *(const f32x4_t*)(X + src * D + c4);
-        }
-        __syncthreads();
-        for (int r = rg; r < kF32Rows; r += RG) {
-            const int64_t j = row0 + r;
-            if (j >= L) break;
-            float acc = 0.f;
-#pragma unroll
-            for (int k4 = 0; k4 < D; k4 += 4) {
-                const f32x4_t x = *(const f32x4_t*)(&xs[r * D + k4]);
-                acc = __builtin_fmaf(x[0], phi[k4 + 0], acc);
-                acc = __builtin_fmaf(x[1], phi[k4 + 1], acc);
-                acc = __builtin_fmaf(x[2], phi[k4 + 2], acc);
-                acc = __builtin_fmaf(x[3], phi[k4 + 3], acc);
-            }
-            const int64_t dst = (SCATTER && pm) ? (int64_t)pm[j] : j;
-            if (SCATTER && mg.lse_in) {
-                const float la = mg.lse_in[(int64_t)bh * L + j];
-                const float lb = mg.lse_other[(int64_t)bh * L + dst];
-                float l;
-                acc = merge_two(acc, la, mg.O_other[((int64_t)bh * L + dst) * D + c], lb, &l);
-                if (c == 0) mg.lse_out[(int64_t)bh * L + dst] = l;
-            }
-            Y[dst * D + c] = acc;
-        }
-    }
-}
-
-// The same product on the fp32 matrix cores, for slabs of at least kMfMinRows rows (the plain kernel above spends
-// its time on LDS broadcasts of the rows: 122 us for 65536 rows of 128, against 10 us of HBM time).
+// fp32 rows times fp32 matrix (fp32 storage path of Enc, and Dec for every storage type) on the fp32 matrix cores, for slabs
+// of more rows than the kernel above takes.  mg.lse_in != NULL (scatter form only): the transformed row is one of two partials
+// of Section 4.1 and is aggregated with the other one, which is already in destination order, before it is stored.
+// What bounds it below some hundred rows is the chain of trips to memory, so the rows, their destinations and what the
+// aggregation needs of them are asked for ahead of the matrix, or of the product of the step before, and a row's weights are
+// evaluated once, by one thread, not by each of its columns' (Dec of 117 rows of 32 heads of 128 7.4 -> 5.8 us, with the aggregation
+// 12.8 -> 6.9; 4096 rows 60 -> 48 and 132 -> 82; 40 rows, with plain FMAs and a column of the matrix a thread, 13.7, now 5.6).
 // v_mfma_f32_32x32x2_f32: A 32 x 2 (lane: row lane % 32, k = lane / 32), B 2 x 32 (lane: column lane % 32, k = lane / 32),
 // C 32 x 32 (lane: column lane % 32, register r: row 8 (r / 4) + 4 (lane / 32) + r % 4).  Wave w of the 4 owns the
 // 32-column slice w % (D / 32) of the output and keeps that slice of Phi in registers as B operands (D / 2 of them);
@@ -720,9 +642,7 @@ __global__ __launch_bounds__(kF32Threads) void rows_times_matrix_f32_kernel(Scra
 // reads its tile's rows from there 16 bytes at a time: the 4 floats are the A operands of 4 steps, contraction index
 // 8 j + 4 (lane / 32) + e for read j, element e.  The next step's rows are fetched into registers before the MFMAs
 // of the current one and go to the other LDS buffer after them: one barrier per step.
-constexpr int kMfMinRows = 64;
-
-template <int D, bool SCATTER, bool ST>
+template <int D, bool SCATTER, bool ST, bool MERGE>
 __global__ __launch_bounds__(kF32Threads) void rows_times_matrix_mfma_f32_kernel(ScrambleJob job0, ScrambleJob job1,
                                                                                  const int32_t* __restrict__ perm,
                                                                                  int64_t perm_batch_stride, int H,
@@ -739,6 +659,10 @@ __global__ __launch_bounds__(kF32Threads) void rows_times_matrix_mfma_f32_kernel
     __shared__ __attribute__((aligned(16))) float xs[2][TR * LDP];
     __shared__ int32_t p_in_inv[ST ? D : 1];
     __shared__ float s_in[ST ? D : 1];
+    // scatter form: where the rows of a step go and their weights, looked up and evaluated once a row
+    __shared__ int32_t row_dst[SCATTER ? 2 : 1][SCATTER ? TR : 1];
+    __shared__ RowWeights row_w[MERGE ? 2 : 1][MERGE ? TR : 1];
+    static_assert(SCATTER || !MERGE, "the aggregation is part of Dec");
 
     const ScrambleJob job = blockIdx.y == 0 ? job0 : job1;
     const int tid = threadIdx.x;
@@ -756,6 +680,37 @@ __global__ __launch_bounds__(kF32Threads) void rows_times_matrix_mfma_f32_kernel
     if (first_row >= L) return;  // workgroup-uniform, before any barrier
     int n_steps = (int)((L - first_row + TR - 1) / TR);
     if (n_steps > steps_per_wg) n_steps = steps_per_wg;
+
+    const float* X = (const float*)job.X + (int64_t)bh * L * D;
+    float* Y = (float*)job.Y + (int64_t)bh * L * D;
+    const int32_t* pm = perm ? perm + (int64_t)b * perm_batch_stride : nullptr;
+
+    auto fetch = [&](int64_t row0, f32x4_t (&buf)[CPT]) {
+#pragma unroll
+        for (int q = 0; q < CPT; ++q) {
+            const int e = tid + q * kF32Threads;
+            int64_t j = row0 + e / CPR;
+            if (j >= L) j = L - 1;  // rows past the end: computed on a real row, never stored
+            const int64_t src = (!SCATTER && pm) ? (int64_t)pm[j] : j;
+            buf[q] = *(const f32x4_t*)(X + src * D + (e % CPR) * 4);
+        }
+    };
+    // thread t < TR: row t of a step
+    int32_t next_dst = 0;
+    float next_la = 0.f, next_lb = 0.f;
+    auto fetch_row = [&](int64_t row0) {
+        if (!SCATTER || tid >= TR) return;
+        const int64_t j = row0 + tid < L ? row0 + tid : L - 1;
+        next_dst = pm ? pm[j] : (int32_t)j;
+        if constexpr (MERGE) {
+            next_la = mg.lse_in[(int64_t)bh * L + j];
+            next_lb = mg.lse_other[(int64_t)bh * L + next_dst];
+        }
+    };
+    // asked for ahead of the matrix
+    f32x4_t buf[CPT];
+    fetch(first_row, buf);
+    fetch_row(first_row);
 
     const int col = 32 * slice + n;  // this lane's output column
     float phi[NJ][4];
@@ -783,20 +738,6 @@ __global__ __launch_bounds__(kF32Threads) void rows_times_matrix_mfma_f32_kernel
             for (int e = 0; e < 4; ++e) phi[j][e] = P[(8 * j + 4 * kk + e) * D + col];
     }
 
-    const float* X = (const float*)job.X + (int64_t)bh * L * D;
-    float* Y = (float*)job.Y + (int64_t)bh * L * D;
-    const int32_t* pm = perm ? perm + (int64_t)b * perm_batch_stride : nullptr;
-
-    auto fetch = [&](int64_t row0, f32x4_t (&buf)[CPT]) {
-#pragma unroll
-        for (int q = 0; q < CPT; ++q) {
-            const int e = tid + q * kF32Threads;
-            int64_t j = row0 + e / CPR;
-            if (j >= L) j = L - 1;  // rows past the end: computed on a real row, never stored
-            const int64_t src = (!SCATTER && pm) ? (int64_t)pm[j] : j;
-            buf[q] = *(const f32x4_t*)(X + src * D + (e % CPR) * 4);
-        }
-    };
     auto stash = [&](int slot, const f32x4_t (&buf)[CPT]) {
 #pragma unroll
         for (int q = 0; q < CPT; ++q) {
@@ -805,38 +746,58 @@ __global__ __launch_bounds__(kF32Threads) void rows_times_matrix_mfma_f32_kernel
         }
     };
 
-    f32x4_t buf[CPT];
-    fetch(first_row, buf);
+    auto stash_row = [&](int slot, int64_t row0) {
+        if (!SCATTER || tid >= TR) return;
+        row_dst[slot][tid] = next_dst;
+        if constexpr (MERGE) {
+            float l;
+            row_w[slot][tid] = weights_of_two(next_la, next_lb, &l);
+            if (row0 + tid < L) mg.lse_out[(int64_t)bh * L + next_dst] = l;
+        }
+    };
+
     stash(0, buf);
+    stash_row(0, first_row);
     __syncthreads();
     for (int s_ = 0; s_ < n_steps; ++s_) {
         const int64_t row0 = first_row + (int64_t)s_ * TR;
         const bool more = s_ + 1 < n_steps;
-        if (more) fetch(row0 + TR, buf);
-        const float* xr = &xs[s_ & 1][(32 * rt + n) * LDP + 4 * kk];
-        f32x16_t acc = zero_vec<f32x16_t>();
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const f32x4_t a = *(const f32x4_t*)(xr + 8 * j);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], phi[j][e], acc, 0, 0, 0);
+        if (more) {
+            fetch(row0 + TR, buf);
+            fetch_row(row0 + TR);
         }
+        auto row_of = [&](int r) { return 32 * rt + 8 * (r / 4) + 4 * kk + (r % 4); };  // of the step, accumulator register r
+        if (row0 + 32 * rt < L) {  // (d = 64: the second tile of a step may be past the end)
+            float other[MERGE ? 16 : 1];
+            if constexpr (MERGE) {  // the other partial's elements are on their way behind the product
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t j = row0 + 32 * rt + 8 * (r / 4) + 4 * kk + (r % 4);
-            if (j >= L) continue;
-            const int64_t dst = (SCATTER && pm) ? (int64_t)pm[j] : j;
-            float v = acc[r];
-            if (SCATTER && mg.lse_in) {
-                const float la = mg.lse_in[(int64_t)bh * L + j];
-                const float lb = mg.lse_other[(int64_t)bh * L + dst];
-                float l;
-                v = merge_two(v, la, mg.O_other[((int64_t)bh * L + dst) * D + col], lb, &l);
-                if (col == 0) mg.lse_out[(int64_t)bh * L + dst] = l;
+                for (int r = 0; r < 16; ++r) other[r] = mg.O_other[((int64_t)bh * L + row_dst[s_ & 1][row_of(r)]) * D + col];
             }
-            Y[dst * D + col] = v;
+            const float* xr = &xs[s_ & 1][(32 * rt + n) * LDP + 4 * kk];
+            f32x16_t acc = zero_vec<f32x16_t>();
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const f32x4_t a = *(const f32x4_t*)(xr + 8 * j);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], phi[j][e], acc, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int64_t j = row0 + row_of(r);
+                if (j >= L) continue;
+                float v = acc[r];
+                if constexpr (SCATTER) {
+                    if constexpr (MERGE) v = merge_two(row_w[s_ & 1][row_of(r)], v, other[r]);
+                    Y[(int64_t)row_dst[s_ & 1][row_of(r)] * D + col] = v;
+                } else {
+                    Y[j * D + col] = v;
+                }
+            }
         }
-        if (more) stash((s_ + 1) & 1, buf);
+        if (more) {
+            stash((s_ + 1) & 1, buf);
+            stash_row((s_ + 1) & 1, row0 + TR);
+        }
         __syncthreads();
     }
 }
@@ -871,11 +832,11 @@ static ScrambleJob device_job(const RowsJob& j, int i) {
     return ScrambleJob{j.X[i], j.Phi[i], j.Y[i], j.s_in[i], j.p_in[i], j.p_out[i], j.s_out[i], j.params[i]};
 }
 
-template <class T, int D, bool SCATTER>
+template <class T, int D, bool SCATTER, bool WIDE>
 static hipError_t launch_few_rows(const RowsJob& j, hipStream_t stream) {
     if (!grid_fits(j.BH, kF32Threads)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)j.BH, (unsigned)j.n_jobs);
-    const auto kernel = j.structured ? few_rows_kernel<T, D, SCATTER, true> : few_rows_kernel<T, D, SCATTER, false>;
+    const auto kernel = j.structured ? few_rows_kernel<T, D, SCATTER, true, WIDE> : few_rows_kernel<T, D, SCATTER, false, WIDE>;
     hipLaunchKernelGGL(kernel, grid, dim3(kF32Threads), 0, stream, device_job(j, 0), device_job(j, 1), j.perm, j.perm_batch_stride,
                        j.H, j.G, (int)j.L, j.merge);
     return hipGetLastError();
@@ -883,7 +844,7 @@ static hipError_t launch_few_rows(const RowsJob& j, hipStream_t stream) {
 
 template <class T, int D>
 static hipError_t launch_scramble16(const RowsJob& j, hipStream_t stream) {
-    if (j.L <= kFewRows && j.quant_bits == 0) return launch_few_rows<T, D, false>(j, stream);
+    if (j.L <= kFewRows && j.quant_bits == 0) return launch_few_rows<T, D, false, false>(j, stream);
     const int waves = scr_waves(j.quant_bits);
     const int64_t rows_per_pass = (int64_t)waves * kScrRows;  // rows one workgroup covers per ring step
     const int64_t passes = (j.L + rows_per_pass - 1) / rows_per_pass;  // per [L, d] slab
@@ -956,37 +917,25 @@ static hipError_t launch_rows_mfma_f32(const RowsJob& j, hipStream_t stream) {
     if (!grid_fits(j.BH * chunks, kF32Threads)) return hipErrorInvalidValue;
     dim3 grid((unsigned)(j.BH * chunks), (unsigned)j.n_jobs);
     const ScrambleJob a = device_job(j, 0), b = device_job(j, 1);
-    if (j.structured)
-        hipLaunchKernelGGL((rows_times_matrix_mfma_f32_kernel<D, SCATTER, true>), grid, dim3(kF32Threads), 0, stream, a,
-                           b, j.perm, j.perm_batch_stride, j.H, j.G, j.L, chunks, spw, j.merge);
-    else
-        hipLaunchKernelGGL((rows_times_matrix_mfma_f32_kernel<D, SCATTER, false>), grid, dim3(kF32Threads), 0, stream,
-                           a, b, j.perm, j.perm_batch_stride, j.H, j.G, j.L, chunks, spw, j.merge);
+#define FEDRAG_MF(MERGE_) \
+    (j.structured ? rows_times_matrix_mfma_f32_kernel<D, SCATTER, true, MERGE_> : rows_times_matrix_mfma_f32_kernel<D, SCATTER, false, MERGE_>)
+    auto kernel = FEDRAG_MF(false);
+    if constexpr (SCATTER) {
+        if (j.merge.lse_in) kernel = FEDRAG_MF(true);
+    }
+#undef FEDRAG_MF
+    hipLaunchKernelGGL(kernel, grid, dim3(kF32Threads), 0, stream, a, b, j.perm, j.perm_batch_stride, j.H, j.G, j.L, chunks, spw,
+                       j.merge);
     return hipGetLastError();
 }
 
 template <int D, bool SCATTER>
 static hipError_t launch_rows_f32(const RowsJob& j, hipStream_t stream) {
-    if (j.L >= kMfMinRows) return launch_rows_mfma_f32<D, SCATTER>(j, stream);
-    // (sums in 64 bits of 16 rows of 64: 4.4 us against 4.2 below)
-    if (j.L <= (!SCATTER && D == 64 ? kFewRows / 2 : kFewRows)) return launch_few_rows<F32, D, SCATTER>(j, stream);
-    const int64_t tiles = (j.L + kF32Rows - 1) / kF32Rows;
-    const int64_t want_wgs = 2048;
-    const int64_t total = tiles * j.BH * j.n_jobs;
-    int tpw = (int)((total + want_wgs - 1) / want_wgs);
-    if (tpw < 1) tpw = 1;
-    if (tpw > 64) tpw = 64;
-    const int chunks = ceil_div_i64(tiles, tpw);
-    if (!grid_fits(j.BH * chunks, kF32Threads)) return hipErrorInvalidValue;
-    dim3 grid((unsigned)(j.BH * chunks), (unsigned)j.n_jobs);
-    const ScrambleJob a = device_job(j, 0), b = device_job(j, 1);
-    if (j.structured)
-        hipLaunchKernelGGL((rows_times_matrix_f32_kernel<D, SCATTER, true>), grid, dim3(kF32Threads), 0, stream, a, b,
-                           j.perm, j.perm_batch_stride, j.H, j.G, j.L, chunks, tpw, j.merge);
-    else
-        hipLaunchKernelGGL((rows_times_matrix_f32_kernel<D, SCATTER, false>), grid, dim3(kF32Threads), 0, stream, a, b,
-                           j.perm, j.perm_batch_stride, j.H, j.G, j.L, chunks, tpw, j.merge);
-    return hipGetLastError();
+    if constexpr (!SCATTER) {  // (d = 64, 16 rows: 4.4 us summed in 64 bits, 4.2 in 32)
+        if (j.L <= (D == 64 ? kFewRows / 2 : kFewRows)) return launch_few_rows<F32, D, false, true>(j, stream);
+    }
+    if (j.L <= kFewRows) return launch_few_rows<F32, D, SCATTER, false>(j, stream);
+    return launch_rows_mfma_f32<D, SCATTER>(j, stream);
 }
 
 hipError_t launch_rows_transform(const RowsJob& j, hipStream_t stream) {

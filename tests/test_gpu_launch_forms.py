@@ -306,12 +306,12 @@ def test_masked_batches_reach_every_tile_of_every_unit(oracle, B, Hkv, G, Lq, L,
     PT.check_attn(O[-1:, heads], lse[-1:, heads], Or, lr, torch.bfloat16, f"masked batch {B}x{Hkv}x{G} {Lq}/{L}", report=True)
 
 
-@pytest.mark.parametrize("L", [1, 2, 7, 16, 17])  # at most 16 rows a head have a kernel of their own
+@pytest.mark.parametrize("L", [1, 2, 7, 8, 9, 16, 17, 32, 33, 65])  # at most 16 rows a head have a kernel of their own
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("structured", [False, True])
 def test_few_rows(L, d, structured):
-    """A handful of rows per head, every storage type, gathered and scattered, several sequences: fp32 sums of d products, each
-    share of them in order (d + 2 roundings of 2^-24 of the sum of the terms' sizes at most), narrowed once."""
+    """A handful of rows per head, every storage type, gathered and scattered, several sequences, and the few more that the tiled
+    kernels begin with: fp32 sums of d products (d + 2 roundings of 2^-24 of the sum of the terms' sizes at most), narrowed once."""
     B, Hkv, G = 3, 2, 2
     H = Hkv * G
     g = torch.Generator().manual_seed(100 * L + d)
