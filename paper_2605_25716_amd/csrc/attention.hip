@@ -57,7 +57,7 @@ static bool use_decode_kernel(int Hq, int Hkv, int64_t Lq) { return (int64_t)(Hq
 // Prefill kernel: one workgroup per (sequence, query head, 256 query rows) walks a run, about 2 us per 64-key tile.
 // When those workgroups cover less than half of the compute units, the keys are cut into runs of at least
 // kPreMinTilesPerSplit tiles (so that a workgroup's fixed cost stays small beside its tiles) for one round of
-// workgroups over the chip; otherwise every shard is one run.
+// workgroups over the chip; otherwise every shard is one run.  The launch may cut them anew into fewer (two key groups to a workgroup).
 KeyRuns attn_plan_runs(int B, int Hq, int Hkv, int dtype, int64_t Lq, int n, const int64_t* Ls, bool codes4) {
     KeyRuns r;
     for (int i = 0; i < kMaxShards; ++i) {
@@ -104,10 +104,16 @@ KeyRuns attn_plan_runs(int B, int Hq, int Hkv, int dtype, int64_t Lq, int n, con
             }
         }
     }
+    for (int i = 0; i < n; ++i) r.s[i].L = Ls[i] > 0 ? Ls[i] : 0;
+    attn_cut_runs(r, per, quantum);
+    return r;
+}
+
+void attn_cut_runs(KeyRuns& r, int64_t per, int64_t quantum) {
+    const int n = r.n_shards;
     int at = 0;
     for (int i = 0; i < n; ++i) {
-        const int64_t L = Ls[i] > 0 ? Ls[i] : 0;
-        r.s[i].L = L;
+        const int64_t L = r.s[i].L;
         r.first[i] = at;
         if (L == 0) continue;  // no runs: first[i] == first[i + 1]
         const int64_t runs = per == INT64_MAX ? 1 : (L + per - 1) / per;
@@ -119,7 +125,6 @@ KeyRuns attn_plan_runs(int B, int Hq, int Hkv, int dtype, int64_t Lq, int n, con
     for (int i = n; i <= kMaxShards; ++i) r.first[i] = i == n ? at : INT_MAX;
     r.n_runs = at;
     r.by_runs = FastDiv(at > 0 ? at : 1);
-    return r;
 }
 
 KeyRuns attn_runs_of(const AttnProblem& p) {

@@ -42,7 +42,10 @@ constexpr int kPrePD = FEDRAG_PRE_PD;         // MFMA operands are read from LDS
 // weight collected so far, and the output takes the fp32 factor between the two, which may be as large as that.  (What stays
 // below is nothing beside fp32 sums.  With the maximum carried along the weight between shards sat in the 16 bits of the
 // probabilities: an error of 3.6e-4 against 64 bits where this, like a partial per shard, has 3.3e-4.)
-template <class T, int D, bool CAUSAL, int QB, int NW, bool WALK>
+// KG = 2: the waves form two groups that share the workgroup's query rows and halve its keys, each with tile slots of its own;
+// their outputs are aggregated through LDS.  For launches of few workgroups: the same rows and keys on as many waves with half
+// the query rows a workgroup, so half the runs, and half the fp32 partials to write and fold, or none.
+template <class T, int D, bool CAUSAL, int QB, int NW, bool WALK, int KG>
 __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefill_attn_kernel(const typename T::elem* __restrict__ Q,
                                                                       const KeyRuns runs,
                                                                       const float* __restrict__ Kprm,
@@ -57,8 +60,9 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
                                                                       float* __restrict__ O, float* __restrict__ lse) {
     typedef typename T::elem elem;
     typedef typename T::vec8 vec8;
-    constexpr int kThreads = NW * kWave;
-    constexpr int kQTile = NW * kPreQ;   // query rows per workgroup
+    constexpr int NWG = NW / KG;             // waves of a key group
+    constexpr int kThreads = NWG * kWave;
+    constexpr int kQTile = NWG * kPreQ;  // query rows per workgroup
     constexpr int ROWB = D * 2;             // bytes per tile row in LDS (no padding)
     constexpr int SLOT = kPreK * ROWB;      // bytes per tile slot
     constexpr int KS = D / 16;              // contraction steps of S^T
@@ -66,13 +70,14 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     constexpr int CH = D / 8;               // 16-byte chunks per row
     constexpr int LPT = (kPreK * CH) / kThreads;  // LDS-direct loads (QB: 8-element chunks) per thread per tile
     static_assert(!WALK || (!CAUSAL && QB == 0), "several shards: the plain form");
+    static_assert(KG == 1 || (KG == 2 && NW == 8 && QB == 0 && !CAUSAL && !WALK), "two groups of four waves: the plain form");
     static_assert(QB == 0 || QB == 8 || QB == 4, "16-bit values, or 8- / 4-bit codes");
     static_assert(QB == 0 || !CAUSAL, "codes are what travels to the Compute Node; the Inquirer's own K, V are plain");
     constexpr int CROWB = QB ? D * QB / 8 : ROWB;  // bytes per row of K' / V' as stored (values, or codes)
 
     // One array per tile slot: distinct objects let the compiler see that the LDS-direct load filling one slot
     // does not alias the LDS reads of another, so it does not make those reads wait for the load.
-    __shared__ __attribute__((aligned(16))) char ks0[SLOT], ks1[SLOT], vs0[SLOT], vs1[SLOT];
+    __shared__ __attribute__((aligned(16))) char ks0_all[KG * SLOT], ks1_all[KG * SLOT], vs0_all[KG * SLOT], vs1_all[KG * SLOT];
 
     // XCD-aware placement: consecutive workgroup ids are dealt round-robin to the 8 XCDs (one L2 each);
     // give every XCD whole (sequence, KV head) units so that the workgroups sharing K'/V' share an L2.
@@ -114,7 +119,13 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     const int h = g * G + hg;
 
     const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // wave-uniform
+    const int wave_all = __builtin_amdgcn_readfirstlane(tid / kWave);  // wave-uniform
+    const int grp = KG == 1 ? 0 : wave_all / NWG;
+    const int wave = KG == 1 ? wave_all : wave_all % NWG;  // in its group
+    char* const ks0 = ks0_all + grp * SLOT;
+    char* const ks1 = ks1_all + grp * SLOT;
+    char* const vs0 = vs0_all + grp * SLOT;
+    char* const vs1 = vs1_all + grp * SLOT;
     const int lane = tid % kWave;
     const int li = lane % 32;
     const int lh = lane / 32;
@@ -164,8 +175,8 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
 #pragma unroll
     for (int i = 0; i < MT; ++i) acc_o[i] = zero_vec<f32x16_t>();
     // CAUSAL: the running maximum starts at the lowest finite value: a row may see no key of the first tiles that its
-    // workgroup visits, and -inf - m_run has to be -inf then.
-    float m_run = CAUSAL ? -__FLT_MAX__ : -INFINITY, l_run = 0.f;
+    // workgroup visits, and -inf - m_run has to be -inf then.  KG = 2: so may the second group's.
+    float m_run = CAUSAL || KG == 2 ? -__FLT_MAX__ : -INFINITY, l_run = 0.f;
 
     // ---- global -> LDS (direct buffer loads).  One wave-wide load fills 64 consecutive 16-byte slots = 64 / CH
     // tile rows.  LDS slot p of row r holds global chunk p ^ swz(r): K' swz(r) = r % CH, V' swz(r) = (4 (r % 4)) % CH;
@@ -173,11 +184,11 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     // starts at the tile and covers the rest of the shard, so rows past the end of the shard arrive as zeros; tile -1 and
     // tiles past the end, which the loops ask for behind their last one, read nothing.
     constexpr int RPW = kWave / CH;  // rows per wave-wide load
-    const int ld_r = wave * RPW + lane / CH;  // row within a group of NW * RPW rows
+    const int ld_r = wave * RPW + lane / CH;  // row within a set of NWG * RPW rows
     const int ld_p = lane % CH;               // slot within the row
     const int ld_voff_k = ld_r * ROWB + ((ld_p ^ (ld_r % CH)) << 4);
     const int ld_voff_v = ld_r * ROWB + ((ld_p ^ ((4 * (ld_r % 4)) % CH)) << 4);
-    static_assert((NW * RPW) % 16 == 0, "swizzle must not depend on the load index");
+    static_assert((NWG * RPW) % 16 == 0, "swizzle must not depend on the load index");
     auto load_tile = [&](const char* G_, char* slot_base, int tile, bool is_k) {
         const int64_t byte0 = (int64_t)tile * SLOT;
         const int64_t left = L * ROWB - byte0;
@@ -186,9 +197,9 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(G_ + byte0), 0, n_rec, 0x00020000);
 #pragma unroll
         for (int j = 0; j < LPT; ++j) {
-            char* lp = slot_base + (j * NW + wave) * (RPW * ROWB);  // wave-uniform LDS base
+            char* lp = slot_base + (j * NWG + wave) * (RPW * ROWB);  // wave-uniform LDS base
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (void __attribute__((address_space(3)))*)lp, 16,
-                                                     is_k ? ld_voff_k : ld_voff_v, j * (NW * RPW * ROWB), 0, 0);
+                                                     is_k ? ld_voff_k : ld_voff_v, j * (NWG * RPW * ROWB), 0, 0);
         }
     };
 
@@ -267,6 +278,18 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     const int64_t wg_keys = CAUSAL ? (q_last + off + 1 < L ? q_last + off + 1 : L) : L;
     int n_tiles = (int)((wg_keys + kPreK - 1) / kPreK);
     int t_mask0 = (int)((CAUSAL ? (q_first + off + 1 < L ? q_first + off + 1 : L) : L) / kPreK);
+    int key_lim = (int)(CAUSAL ? (q_row + off + 1 < L ? q_row + off + 1 : L) : L);  // this lane's row sees keys < key_lim
+    if constexpr (KG == 2) {
+        // The second group begins half-way.  Both take the same number of tiles and of masked ones (barriers are common): where the
+        // count is odd the second group's last tile lies behind its keys and is masked as a whole.
+        const int half = (n_tiles + 1) / 2, first = grp * half;
+        n_tiles = half;
+        t_mask0 = t_mask0 > half ? t_mask0 - half : 0;
+        Kg += (int64_t)first * SLOT;
+        Vg += (int64_t)first * SLOT;
+        L -= (int64_t)first * kPreK;
+        key_lim -= first * kPreK;
+    }
     // prologue: K' of the first tile to visit is fetched first, Q' behind it
     int tile = CAUSAL ? n_tiles - 1 : 0;
     if constexpr (QB == 0) load_tile(Kg, ks0, tile, true);
@@ -276,7 +299,6 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qop[ks] = *(const vec8*)(Qh + q_ld * D + ks * 16 + lh * 8);
 
-    int key_lim = (int)(CAUSAL ? (q_row + off + 1 < L ? q_row + off + 1 : L) : L);  // this lane's row sees keys < key_lim
     f32x16_t S0;      // S^T of the current tile, keys 0..31
     f32x16_t S1[2];   // S1[t & 1]: S^T of tile t, keys 32..63 (kept one iteration longer, see below)
     vec8 P[2][4];     // P[t & 1]: P^T operands of tile t, one per 16-key step
@@ -561,25 +583,76 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
     // (the tiles are dead; every wave has its share of them), so that a store covers whole 128-byte lines: straight from
     // the accumulators it would cover 32 bytes of each of 32 rows, 4 us for a 256-row workgroup.  The 16-byte chunk
     // index is XORed with the row against bank conflicts.
-    const float l_tot = xor32_sum(l_run);
-    const float inv = (l_tot > 0.f) ? 1.0f / l_tot : 0.f;
+    float l_tot = xor32_sum(l_run);
     __syncthreads();
-    constexpr int WB = 4 * SLOT / NW;          // bytes per wave
-    constexpr int PC = WB / (kPreQ * 4);       // columns per pass
+    constexpr int WB = 4 * SLOT / NWG;         // bytes per wave
+    constexpr int OC = D / KG;                 // output columns that are this wave's to store
+    constexpr int PC = WB / (kPreQ * 4) < OC ? WB / (kPreQ * 4) : OC;  // columns per pass
     constexpr int PCH = PC / 4;                // 16-byte chunks per row and pass
-    static_assert(PC % 32 == 0 && D % PC == 0, "a pass is whole 32-column tiles");
-    const int slot_w = wave * 4 / NW;
-    char* mine = (slot_w == 0 ? ks0 : slot_w == 1 ? ks1 : slot_w == 2 ? vs0 : vs1) + (wave % (NW / 4)) * WB;
-    const int64_t row0 = (int64_t)qt * kQTile + wave * kPreQ;
+    static_assert(PC % 32 == 0 && OC % PC == 0, "a pass is whole 32-column tiles");
+    const int slot_w = wave_all * 4 / NW;
+    char* mine = (slot_w == 0 ? ks0_all : slot_w == 1 ? ks1_all : slot_w == 2 ? vs0_all : vs1_all) + (wave_all % (NW / 4)) * WB;
+    f32x16_t out[OC / 32];
+    if constexpr (KG == 1) {
 #pragma unroll
-    for (int c0 = 0; c0 < D; c0 += PC) {
+        for (int i = 0; i < MT; ++i) out[i] = acc_o[i];
+    } else {
+        // The other group's wave holds the same rows over the other keys: each gives away half of the columns, with its maximum and
+        // sum, and finishes the other half (Section 4.1 aggregation, in base 2).
+        constexpr int HT = MT / 2;
+        auto give = [&](int i0) {
+#pragma unroll
+            for (int i = 0; i < HT; ++i)
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    f32x4_t o;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) o[r] = acc_o[i0 + i][4 * r4 + r];
+                    *(f32x4_t*)(mine + (i * 4 + r4) * (kWave * 16) + lane * 16) = o;
+                }
+        };
+        if (grp == 0) give(HT);
+        else give(0);
+        f32x2_t ml;
+        ml[0] = m_run; ml[1] = l_tot;
+        *(f32x2_t*)(mine + HT * 4 * (kWave * 16) + lane * 8) = ml;
+#pragma unroll
+        for (int i = 0; i < HT; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float lo = acc_o[i][r], hi = acc_o[HT + i][r];
+                out[i][r] = grp == 0 ? lo : hi;
+            }
+        __syncthreads();
+        const int peer = wave_all < NWG ? wave_all + NWG : wave_all - NWG, slot_p = peer * 4 / NW;
+        const char* theirs = (slot_p == 0 ? ks0_all : slot_p == 1 ? ks1_all : slot_p == 2 ? vs0_all : vs1_all) + (peer % (NW / 4)) * WB;
+        ml = *(const f32x2_t*)(theirs + HT * 4 * (kWave * 16) + lane * 8);
+        const float m_all = fmaxf(m_run, ml[0]);
+        const float a = fast_exp2(m_run - m_all), b = fast_exp2(ml[0] - m_all);
+        l_tot = l_tot * a + ml[1] * b;
+        m_run = m_all;
+#pragma unroll
+        for (int i = 0; i < HT; ++i)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const f32x4_t o = *(const f32x4_t*)(theirs + (i * 4 + r4) * (kWave * 16) + lane * 16);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) out[i][4 * r4 + r] = out[i][4 * r4 + r] * a + o[r] * b;
+            }
+        __syncthreads();
+    }
+    const float inv = (l_tot > 0.f) ? 1.0f / l_tot : 0.f;
+    const int64_t row0 = (int64_t)qt * kQTile + wave * kPreQ;
+    const int col0 = grp * OC;
+#pragma unroll
+    for (int c0 = 0; c0 < OC; c0 += PC) {
 #pragma unroll
         for (int i = c0 / 32; i < (c0 + PC) / 32; ++i)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
                 f32x4_t o;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) o[r] = acc_o[i][4 * r4 + r] * inv;
+                for (int r = 0; r < 4; ++r) o[r] = out[i][4 * r4 + r] * inv;
                 const int chunk = 8 * (i - c0 / 32) + 2 * r4 + lh;
                 *(f32x4_t*)(mine + li * (PC * 4) + ((chunk ^ (li % PCH)) << 4)) = o;
             }
@@ -589,11 +662,11 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
             const int e = u * kWave + lane;
             const int row = e / PCH, chunk = e % PCH;
             const f32x4_t o = *(const f32x4_t*)(mine + row * (PC * 4) + ((chunk ^ (row % PCH)) << 4));
-            if (row0 + row < Lq_rows) *(f32x4_t*)(Oh + (row0 + row) * D + c0 + chunk * 4) = o;
+            if (row0 + row < Lq_rows) *(f32x4_t*)(Oh + (row0 + row) * D + col0 + c0 + chunk * 4) = o;
         }
         wave_lds_fence();
     }
-    if (lh == 0 && q_row < Lq_rows) Lh[q_row] = (l_tot > 0.f) ? (m_run + fast_log2(l_tot)) * kLn2 : -INFINITY;
+    if (grp == 0 && lh == 0 && q_row < Lq_rows) Lh[q_row] = (l_tot > 0.f) ? (m_run + fast_log2(l_tot)) * kLn2 : -INFINITY;
 }
 
 // Waves per workgroup.  Eight share a K'/V' tile between 256 query rows, one workgroup per compute unit: the best rate
@@ -654,6 +727,50 @@ static bool prefill_walks(const AttnProblem& p, const KeyRuns& runs, int Hq_k, i
     return walked.least() * (D == 64 ? 1.05f : 1.0f) < side_by_side;
 }
 
+// Few workgroups and runs at will: whether two groups of four waves share 128 query rows and halve their keys (KG = 2), with the
+// runs re-cut for that, twice as long, by cost as above.  Half the runs are half the partials to write and fold, or none (500 x
+// 32 x 1000 keys of 128 31.6 us against 27.8, 2 x 958 x 16 x 933 35.6 and 25.2, 487 x 64 x 2255 of 64 39.1 and 28.5), and shards
+// whose runs fitted no round fit one (123 x 32 x (6278 + 971 + 4650) 49.6 and 40.6).  Each group stages tiles of its own, which
+// at d = 128, where LDS is the busier side, costs a tenth (1024 x 16 x 8192 76.7 and 78.2: stays as it was), and a launch that
+// does not half fill the chip gains nothing (11 x 16 x 385 of 64 8.5 and 9.1).
+// Not where a workgroup takes all keys by rule (a mask, counts per sequence): up to 1.5 workgroups a compute unit two groups are
+// 7 to 15 % faster (2048 x 16 heads with a mask 51.2 us and 46.5), but from two on 10 % slower, and a sequence's outputs would
+// then depend on how many others are in its batch.
+static bool prefill_two_groups(KeyRuns* runs, int64_t wgs8, int64_t wgs4, int64_t rows, int D) {
+    const int64_t cus = attn_target_wgs();
+    int64_t total = 0, longest = 0, tiles1 = 0;
+    for (int i = 0; i < runs->n_shards; ++i) {
+        const int64_t L = runs->s[i].L, run = L < runs->s[i].per ? L : runs->s[i].per;
+        total += L;
+        longest = L > longest ? L : longest;
+        tiles1 = (run + kPreK - 1) / kPreK > tiles1 ? (run + kPreK - 1) / kPreK : tiles1;
+    }
+    if (wgs4 < 1 || wgs8 * 2 > cus) return false;
+    constexpr int64_t kPair = 2 * kPreK;  // a tile for each group
+    const int64_t want = cus / wgs4 > 0 ? cus / wgs4 : 1;
+    int64_t pairs = ((total + kPair - 1) / kPair + want - 1) / want;
+    if (pairs < kPreMinTilesPerSplit) pairs = kPreMinTilesPerSplit;
+    KeyRuns two = *runs;
+    attn_cut_runs(two, pairs * kPair, kPair);
+    while (two.n_runs * wgs4 > cus && pairs * kPair < longest) attn_cut_runs(two, ++pairs * kPair, kPair);
+    const int64_t wgs = two.n_runs * wgs4;
+    if (two.n_runs > runs->n_runs || wgs > cus || wgs * 2 < cus) return false;
+    int64_t steps = 0;
+    for (int i = 0; i < two.n_shards; ++i) {
+        const int64_t run = two.s[i].L < two.s[i].per ? two.s[i].L : two.s[i].per;
+        steps = (run + kPair - 1) / kPair > steps ? (run + kPair - 1) / kPair : steps;
+    }
+    const float tile_us = D == 64 ? 1.19f : 1.77f;
+    auto fold_us = [&](int n) { return n > 1 ? 3.0f + (float)n * (float)rows * (float)(D + 1) * 4.0f / 7.5e6f : 0.0f; };
+    const float ends = wgs8 * runs->n_runs <= cus ? 0.0f : 4.0f;
+    const float one = prefill_cost(wgs8 * runs->n_runs, wgs4 * runs->n_runs, (float)tiles1, ends, D, false).least() * tile_us +
+                      fold_us(runs->n_runs);
+    const float both = ((float)steps * (D == 64 ? 1.0f : 1.1f) + 0.33f) * tile_us + fold_us(two.n_runs);
+    if (both >= one) return false;
+    *runs = two;
+    return true;
+}
+
 // Order of a unit's workgroups when there are several runs.  The runs of a query tile side by side, unless one run's
 // workgroups fill the chip by themselves and a unit's keys are several times an XCD's 4 MiB of L2: then run by run, so that
 // the workgroups at work share the keys of one shard (8 shards of 8192 keys, 4096 x 64 query rows: 7.97 ms, 8.24 side by
@@ -661,7 +778,7 @@ static bool prefill_walks(const AttnProblem& p, const KeyRuns& runs, int Hq_k, i
 constexpr int64_t kPreRunByRunBytes = 16 << 20;
 constexpr int64_t kPreTogetherBytes = 8 << 20;  // K and V of an XCD's units, whose L2 is 4 MiB
 
-template <class T, int D, bool CAUSAL, int QB, int NW, bool WALK>
+template <class T, int D, bool CAUSAL, int QB, int NW, bool WALK, int KG = 1>
 static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, int Hq_k, int64_t Lq_k, int64_t q_tiles,
                                     float* Odst, float* Ldst, hipStream_t stream) {
     typedef typename T::elem elem;
@@ -681,7 +798,7 @@ static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, i
     // 8 x 4096 (16 MiB) 1524 and 1567.
     const int64_t units_per_xcd = (n_units + 7) / 8;
     const int together = CAUSAL && units_per_xcd * keys * (4 * D) <= kPreTogetherBytes ? 1 : 0;
-    hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB, NW, WALK>), dim3((unsigned)grid), dim3(NW * kWave), 0, stream,
+    hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB, NW, WALK, KG>), dim3((unsigned)grid), dim3(NW * kWave), 0, stream,
                        (const elem*)p.Q, runs, p.K_params, p.V_params, Hq_k, FastDiv(p.Hkv), FastDiv(Hq_k / p.Hkv),
                        FastDiv(q_tiles), FastDiv(together ? units_per_xcd : per_unit), FastDiv(run_by_run ? tiles_of_unit : runs.n_runs),
                        run_by_run ? 1 : 0, Lq_k, p.kv_lens, p.q_lens, n_units, fold, together,
@@ -730,6 +847,17 @@ static hipError_t launch_prefill_t(const AttnProblem& p, hipStream_t stream) {
             all.by_runs = FastDiv(1);
             return walk4 ? launch_prefill_nw<T, D, false, 0, 4, true>(p, all, Hq_k, Lq_k, tiles4, p.O, p.lse, stream)
                          : launch_prefill_nw<T, D, false, 0, 8, true>(p, all, Hq_k, Lq_k, tiles8, p.O, p.lse, stream);
+        }
+    }
+    if constexpr (!CAUSAL && QB == 0) {
+        KeyRuns two = runs;
+        if (!one_run_only && prefill_two_groups(&two, (int64_t)p.B * Hq_k * tiles8, (int64_t)p.B * Hq_k * tiles4, rows, D)) {
+            const bool parts = two.n_runs > 1;  // no more of them than the plan that the workspace is sized for has
+            float* Lpart = Odst + (size_t)two.n_runs * rows * D;
+            const hipError_t e = launch_prefill_nw<T, D, false, 0, 8, false, 2>(p, two, Hq_k, Lq_k, tiles4, parts ? Odst : p.O,
+                                                                                 parts ? Lpart : p.lse, stream);
+            if (e != hipSuccess || !parts) return e;
+            return launch_lse_merge(Odst, Lpart, two.n_runs, rows, D, p.O, p.lse, stream);
         }
     }
     const int64_t heads = (int64_t)p.B * Hq_k * splits;

@@ -139,6 +139,8 @@ inline size_t attn_workspace_bytes(int B, int Hq, int Hkv, int D, int dtype, int
 }
 // The plan of problem p with its pointers filled in.
 KeyRuns attn_runs_of(const AttnProblem& p);
+// Cuts the shards of r (s[].L, n_shards) into runs of about `per` keys, a multiple of `quantum` and rebalanced inside a shard.
+void attn_cut_runs(KeyRuns& r, int64_t per, int64_t quantum);
 hipError_t launch_partial_attn(const AttnProblem& p, hipStream_t stream);
 // Device address, on the current device, of the library's static scratch array of FEDRAG_STATIC_SCRATCH_BYTES bytes.
 hipError_t attn_static_scratch(void** ptr_out);

@@ -338,3 +338,25 @@ def test_few_rows(L, d, structured):
         if dt == "f32":  # Dec: the same rows scattered
             got = (fb.fedrag_unscramble_structured if structured else fb.fedrag_unscramble)(x.to(DEV), key, perm.to(DEV)).cpu()
             assert ((got.double()[:, :, perm.long()] - want).abs() <= tol).all()
+
+
+# few workgroups: two groups of four waves share 128 query rows and halve their keys
+@pytest.mark.parametrize("B,Hq,d,dt,Lq,Ls", [(1, 32, 128, "bf16", 500, [960]), (1, 32, 128, "f16", 500, [1000]),
+                                             (1, 32, 64, "bf16", 109, [1732, 6100, 30]), (2, 16, 64, "f16", 958, [513]),
+                                             (2, 16, 128, "f16", 30, [569, 0, 718, 7521]), (2, 16, 128, "bf16", 958, [769])])
+def test_keys_halved_between_two_groups(oracle, B, Hq, d, dt, Lq, Ls):
+    """Runs of an odd number of tiles, ragged ones and, beside long shards, one so short that the second group has no key; with
+    and without partials."""
+    Q = rnd(B, Hq, Lq, d, dt, W.TID_Q)
+    Ks = [rnd(B, 8, L, d, dt, W.TID_K + 16 * (i + 1)) for i, L in enumerate(Ls)]
+    Vs = [rnd(B, 8, L, d, dt, W.TID_V + 16 * (i + 1)) for i, L in enumerate(Ls)]
+    Or, lr = oracle.partial_attn(Q, torch.cat(Ks, dim=2), torch.cat(Vs, dim=2))
+    print(f"two groups {B} {Hq} {d} {dt} {Lq} {Ls}", flush=True)
+    O = torch.full(Or.shape, float("nan"), dtype=torch.float32, device=DEV)
+    lse = torch.full(lr.shape, float("nan"), dtype=torch.float32, device=DEV)
+    if len(Ls) > 1:
+        O, lse = fb.fedrag_partial_attn_shards(Q.to(DEV), [k.to(DEV) for k in Ks], [v.to(DEV) for v in Vs], O=O, lse=lse)
+    else:
+        fb.fedrag_partial_attn(Q.to(DEV), Ks[0].to(DEV), Vs[0].to(DEV), O_part=O, lse=lse)
+    torch.cuda.synchronize()
+    PT.check_attn(O, lse, Or, lr, Q.dtype, f"{B} {Hq} {d} {dt} {Lq} {Ls}")
