@@ -55,7 +55,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
                                                                       FastDiv by_inner, int run_by_run, int64_t Lq,
                                                                       const int32_t* __restrict__ kv_lens,
                                                                       const int32_t* __restrict__ q_lens, int n_units, int fold,
-                                                                      int together,
+                                                                      int together, int past_l2,
                                                                       float scale_log2,
                                                                       float* __restrict__ O, float* __restrict__ lse) {
     typedef typename T::elem elem;
@@ -671,13 +671,25 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
                 *(f32x4_t*)(mine + li * (PC * 4) + ((chunk ^ (li % PCH)) << 4)) = o;
             }
         wave_lds_fence();
+        auto store = [&](auto nontemporal) {
 #pragma unroll
-        for (int u = 0; u < kPreQ * PCH / kWave; ++u) {
-            const int e = u * kWave + lane;
-            const int row = e / PCH, chunk = e % PCH;
-            const f32x4_t o = *(const f32x4_t*)(mine + row * (PC * 4) + ((chunk ^ (row % PCH)) << 4));
-            if (row0 + row < Lq_rows) *(f32x4_t*)(Oh + (row0 + row) * D + col0 + c0 + chunk * 4) = o;
-        }
+            for (int u = 0; u < kPreQ * PCH / kWave; ++u) {
+                const int e = u * kWave + lane;
+                const int row = e / PCH, chunk = e % PCH;
+                const f32x4_t o = *(const f32x4_t*)(mine + row * (PC * 4) + ((chunk ^ (row % PCH)) << 4));
+                f32x4_t* to = (f32x4_t*)(Oh + (row0 + row) * D + col0 + c0 + chunk * 4);
+                if (row0 + row < Lq_rows) {
+                    if constexpr (decltype(nontemporal)::value) {
+                        __builtin_nontemporal_store(o, to);
+                        asm volatile("");  // (two stores that differ in the hint alone would be merged into one without it)
+                    } else {
+                        *to = o;
+                    }
+                }
+            }
+        };
+        if (past_l2) store(std::true_type{});
+        else store(std::false_type{});
         wave_lds_fence();
     }
     if (grp == 0 && lh == 0 && q_row < Lq_rows) Lh[q_row] = (l_tot > 0.f) ? (m_run + fast_log2(l_tot)) * kLn2 : -INFINITY;
@@ -792,6 +804,13 @@ static bool prefill_two_groups(KeyRuns* runs, int64_t wgs8, int64_t wgs4, int64_
 constexpr int64_t kPreRunByRunBytes = 16 << 20;
 constexpr int64_t kPreTogetherBytes = 8 << 20;  // K and V of an XCD's units, whose L2 is 4 MiB
 
+// Outputs (with partials: all of them) from this size on are stored past the L2s, 4 MiB on each of the 8 XCDs.  All workgroups
+// store at about the same time, at their end, and lines left dirty there are written back before the next launch may start:
+// 4 x 777 tokens x 16 heads of 128 with a mask (24 MiB) 31.0 us and 28.1, 8 x 300 x 32 of 64 (19 MiB) 17.2 and 15.2, 2048 x 32 of
+// 128 (32 MiB) 61.2 and 58.8, 117 x 32 x (4001 + 3277) of 64 (17 MiB of partials) 22.5 and 20.6.  Below, what reads them next
+// finds them in L2: 117 x 32 x 300 of 64 (1 MiB) 9.0 and 9.3, 128 x 16 x 1024 (2 MiB) 10.1 and 10.3; from 4 to 8 MiB even.
+constexpr int64_t kPrePastL2Bytes = 8 << 20;
+
 template <class T, int D, bool CAUSAL, int QB, int NW, bool WALK, int KG = 1>
 static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, int Hq_k, int64_t Lq_k, int64_t q_tiles,
                                     float* Odst, float* Ldst, hipStream_t stream) {
@@ -812,10 +831,11 @@ static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, i
     // 8 x 4096 (16 MiB) 1524 and 1567.
     const int64_t units_per_xcd = (n_units + 7) / 8;
     const int together = CAUSAL && units_per_xcd * keys * (4 * D) <= kPreTogetherBytes ? 1 : 0;
+    const int past_l2 = (int64_t)p.B * p.Hq * p.Lq * runs.n_runs * (4 * D) >= kPrePastL2Bytes ? 1 : 0;
     hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB, NW, WALK, KG>), dim3((unsigned)grid), dim3(NW * kWave), 0, stream,
                        (const elem*)p.Q, runs, p.K_params, p.V_params, Hq_k, FastDiv(p.Hkv), FastDiv(Hq_k / p.Hkv),
                        FastDiv(q_tiles), FastDiv(together ? units_per_xcd : per_unit), FastDiv(run_by_run ? tiles_of_unit : runs.n_runs),
-                       run_by_run ? 1 : 0, Lq_k, p.kv_lens, p.q_lens, n_units, fold, together,
+                       run_by_run ? 1 : 0, Lq_k, p.kv_lens, p.q_lens, n_units, fold, together, past_l2,
                        p.scale * kLog2e, Odst, Ldst);
     return hipGetLastError();
 }
