@@ -635,9 +635,6 @@ __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0,
 // aggregation needs of them are asked for ahead of the matrix, or of the product of the step before, and a row's weights are
 // evaluated once, by one thread, not by each of its columns' (Dec of 117 rows of 32 heads of 128 7.4 -> 5.8 us, with the aggregation
 // 12.8 -> 6.9; 4096 rows 60 -> 48 and 132 -> 82; 40 rows, with plain FMAs and a column of the matrix a thread, 13.7, now 5.6).
-// Stores go past L2, whose dirty lines would be written back between this launch and the next: 16 x 64 rows of 32 heads of 128
-// 16.4 -> 14.1 us, 4096 rows 49.7 -> 48.0, 2048 of 64 11.3 -> 9.6, nothing slower - but for structured keys in row order (Enc in
-// fp32), 16 x 8 x 8192 rows of 128 900 -> 937, which store as before.
 // v_mfma_f32_32x32x2_f32: A 32 x 2 (lane: row lane % 32, k = lane / 32), B 2 x 32 (lane: column lane % 32, k = lane / 32),
 // C 32 x 32 (lane: column lane % 32, register r: row 8 (r / 4) + 4 (lane / 32) + r % 4).  Wave w of the 4 owns the
 // 32-column slice w % (D / 32) of the output and keeps that slice of Phi in registers as B operands (D / 2 of them);
@@ -791,9 +788,7 @@ __global__ __launch_bounds__(kF32Threads) void rows_times_matrix_mfma_f32_kernel
                 float v = acc[r];
                 if constexpr (SCATTER) {
                     if constexpr (MERGE) v = merge_two(row_w[s_ & 1][row_of(r)], v, other[r]);
-                    __builtin_nontemporal_store(v, &Y[(int64_t)row_dst[s_ & 1][row_of(r)] * D + col]);
-                } else if constexpr (!ST) {
-                    __builtin_nontemporal_store(v, &Y[j * D + col]);
+                    Y[(int64_t)row_dst[s_ & 1][row_of(r)] * D + col] = v;
                 } else {
                     Y[j * D + col] = v;
                 }
