@@ -804,13 +804,6 @@ static bool prefill_two_groups(KeyRuns* runs, int64_t wgs8, int64_t wgs4, int64_
 constexpr int64_t kPreRunByRunBytes = 16 << 20;
 constexpr int64_t kPreTogetherBytes = 8 << 20;  // K and V of an XCD's units, whose L2 is 4 MiB
 
-// Outputs (with partials: all of them) from this size on are stored past the L2s, 4 MiB on each of the 8 XCDs.  All workgroups
-// store at about the same time, at their end, and lines left dirty there are written back before the next launch may start:
-// 4 x 777 tokens x 16 heads of 128 with a mask (24 MiB) 31.0 us and 28.1, 8 x 300 x 32 of 64 (19 MiB) 17.2 and 15.2, 2048 x 32 of
-// 128 (32 MiB) 61.2 and 58.8, 117 x 32 x (4001 + 3277) of 64 (17 MiB of partials) 22.5 and 20.6.  Below, what reads them next
-// finds them in L2: 117 x 32 x 300 of 64 (1 MiB) 9.0 and 9.3, 128 x 16 x 1024 (2 MiB) 10.1 and 10.3; from 4 to 8 MiB even.
-constexpr int64_t kPrePastL2Bytes = 8 << 20;
-
 template <class T, int D, bool CAUSAL, int QB, int NW, bool WALK, int KG = 1>
 static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, int Hq_k, int64_t Lq_k, int64_t q_tiles,
                                     float* Odst, float* Ldst, hipStream_t stream) {
@@ -831,7 +824,8 @@ static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, i
     // 8 x 4096 (16 MiB) 1524 and 1567.
     const int64_t units_per_xcd = (n_units + 7) / 8;
     const int together = CAUSAL && units_per_xcd * keys * (4 * D) <= kPreTogetherBytes ? 1 : 0;
-    const int past_l2 = (int64_t)p.B * p.Hq * p.Lq * runs.n_runs * (4 * D) >= kPrePastL2Bytes ? 1 : 0;
+    // all outputs of the launch; with several runs, the partials
+    const int past_l2 = (int64_t)p.B * p.Hq * p.Lq * runs.n_runs * (4 * D) >= kPastL2Bytes ? 1 : 0;
     hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB, NW, WALK, KG>), dim3((unsigned)grid), dim3(NW * kWave), 0, stream,
                        (const elem*)p.Q, runs, p.K_params, p.V_params, Hq_k, FastDiv(p.Hkv), FastDiv(Hq_k / p.Hkv),
                        FastDiv(q_tiles), FastDiv(together ? units_per_xcd : per_unit), FastDiv(run_by_run ? tiles_of_unit : runs.n_runs),

@@ -92,6 +92,14 @@ struct FastDiv {
     __host__ __device__ uint32_t mod(uint32_t n) const { return n - div(n) * d; }
 };
 
+// 32-bit outputs (with several runs: partials) of a prefill launch from this size on are stored past the L2s, 4 MiB on each of the
+// 8 XCDs.  All workgroups store at about the same time, at their end, and lines left dirty there are
+// written back before the next launch may start: 4 x 777 tokens x 16 heads of 128 with a mask (24 MiB) 31.0 us and 28.1, 8 x 300 x
+// 32 of 64 (19 MiB) 17.2 and 15.2, 2048 x 32 of 128 (32 MiB) 61.2 and 58.8, 117 x 32 x (4001 + 3277) of 64 (17 MiB of partials)
+// 22.5 and 20.6.  Below, what reads them next finds them in L2: 117 x 32 x 300 of 64 (1 MiB) 9.0 and 9.3, 128 x 16 x 1024 (2 MiB)
+// 10.1 and 10.3; from 4 to 8 MiB even.
+constexpr int64_t kPastL2Bytes = 8 << 20;
+
 // How a launch cuts the keys into runs, one workgroup per (unit of queries, run): what both attention kernels
 // receive by value.  Shard i contributes runs first[i] .. first[i+1]-1 of s[i].per keys each (the last one shorter);
 // first[i] = INT_MAX past the last shard, so a kernel finds its shard with compares only.  With more than one run

@@ -12,7 +12,6 @@ namespace fedrag {
 // one log-sum-exp and evaluates one exponential, and a weight reaches the others by a lane shuffle - the first batch of
 // partials is in flight before the weights are known, and the workgroups are one wave while rows are few.  Sums are
 // formed in shard order whatever the batch.
-// The outputs are stored past L2 (nothing is slower for it; 16384 rows of 128 over 2 partials 4.1 us and 3.6, 30000 8.7 and 6.7).
 // 32 rows of 128 over 16 partials, calls back to back: 3.5 us (6.7 with one partial after the other); 3744 rows over 16: 5.0
 // (11.9).  In a chain of other launches add what a launch costs there.
 
@@ -82,7 +81,7 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const float* __restrict_
         const float inv = 1.0f / den;
         acc[0] *= inv; acc[1] *= inv; acc[2] *= inv; acc[3] *= inv;
     }
-    __builtin_nontemporal_store(acc, (f32x4_t*)(O + r * D + c4));
+    *(f32x4_t*)(O + r * D + c4) = acc;
     if (c == 0) lse[r] = (M == -INFINITY) ? -INFINITY : M + logf(den);
 }
 
@@ -126,7 +125,7 @@ __global__ __launch_bounds__(256) void lse_merge_few_kernel(const float* __restr
         const float inv = 1.0f / den;
         acc[0] *= inv; acc[1] *= inv; acc[2] *= inv; acc[3] *= inv;
     }
-    __builtin_nontemporal_store(acc, (f32x4_t*)(O + r * D + c4));
+    *(f32x4_t*)(O + r * D + c4) = acc;
     if (c4 == 0) lse[r] = (M == -INFINITY) ? -INFINITY : M + logf(den);
 }
 
