@@ -136,7 +136,8 @@ fedrag_status fedrag_partial_attn_static(const fedrag_shape* shape, int64_t L_q,
  * aggregation launch, instead of one of each per shard (what counts when a shard is a few thousand tokens and a
  * launch costs as much as its work); at decode shapes, when a single shard's sequences already cover the chip, the
  * attention is launched shard by shard and aggregated once; at prefill shapes whose query tiles cover the chip, a
- * workgroup may visit the shards in turn and use no workspace.  The weight between shards is an fp32 number in every form.
+ * workgroup may visit the shards in turn and write no partials.  The weight between shards is an fp32 number in every form (of
+ * a shard below the others, where bf16 outputs are beyond 2^112, one of 16 bits).
  * The result equals attention over the concatenation of the shards' keys (eq. (1)).
  * n_shards : 1 .. FEDRAG_MAX_SHARDS.  L_kv, Ks, Vs : HOST arrays of n_shards entries - shard lengths (>= 0; an empty
  * shard contributes nothing and its pointers may be NULL) and DEVICE pointers to [B,Hkv,L_kv[i],d] tensors in

@@ -38,8 +38,9 @@ constexpr int kPrePD = FEDRAG_PRE_PD;         // MFMA operands are read from LDS
 // significant bits), at the price of twice the MFMAs of that product.
 // WALK: several shards whose query tiles alone cover the chip.  A workgroup visits the shards one after the other and carries
 // its maximum, sum and output along: no partials and no aggregation.  The probabilities of a shard are rounded against the
-// shard's own running maximum, as they are in a launch of its own: its first tile starts the maximum anew, 2^63 below the
-// weight collected so far, and the output takes the fp32 factor between the two, which may be as large as that.  (What stays
+// shard's own running maximum, as they are in a launch of its own: its first tile starts the maximum anew, 2^32 below the
+// weight collected so far, and the output takes the fp32 factor between the two, which may be as large as that, or less where it
+// would carry outputs beyond 2^120, so that values are as free as in a launch per shard.  (What stays
 // below is nothing beside fp32 sums.  With the maximum carried along the weight between shards sat in the 16 bits of the
 // probabilities: an error of 3.6e-4 against 64 bits where this, like a partial per shard, has 3.3e-4.)
 // KG = 2: the waves form two groups that share the workgroup's query rows and halve its keys, each with tile slots of its own;
@@ -322,7 +323,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
         }
     };
     float alph[2];    // alph[t & 1]: rescale factor of the running output that goes with P(t)
-    float drop = 0.f;  // WALK: what the first tile of a shard takes off the maximum it finds
+    int drop = 0;      // WALK: what the first tile of a shard takes off the maximum it finds
 
     auto read_vop = [&](const char* vt, int kk, int i) -> vec8 {
         const char* p = vt + kk * 16 * ROWB + v_off[i];
@@ -465,8 +466,11 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
                     if (j == FIRST) {
                         mx = xor32_max(mx);
                         // scale > 0: max commutes with the scaling
-                        m_new = fmaxf(WALK && kind == kFirst ? m_run - drop : m_run, mx * scale_log2);
+                        const float low = WALK && kind == kFirst ? m_run - (float)drop : m_run;
+                        m_new = fmaxf(low, mx * scale_log2);
                         alph[p] = exp2_diff(m_run, m_new);
+                        // what rounding took off `low` is far more than a rounding of m_run: 2^drop, and the rest exactly
+                        if (WALK && kind == kFirst && m_new == low) alph[p] = ldexpf(exp2_diff(m_run, low + (float)drop), drop);
                     }
                     if (j >= FIRST) {
                         constexpr int NS = NM - FIRST;
@@ -559,7 +563,7 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
         // pipeline's last iteration has put the next one.
         const int n_pipe = t_mask0 <= 2 ? 1 : t_mask0 - 1 + (t_mask0 & 1);
         iteration(0, 1, even, first, true);
-        drop = 0.f;
+        drop = 0;
         tile_barrier();
         for (tile = 1; tile < n_pipe; tile += 2) {
             iteration(tile, tile + 1, odd, steady, true);
@@ -589,7 +593,13 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
         n_tiles = (int)((L + kPreK - 1) / kPreK);
         t_mask0 = (int)(L / kPreK);
         key_lim = (int)L;
-        drop = 64.0f - (float)__builtin_amdgcn_frexp_expf(xor32_sum(l_run));
+        float top = 0.f;
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) top = fmaxf(top, fabsf(acc_o[i][r]));
+        const int down = 32 - __builtin_amdgcn_frexp_expf(xor32_sum(l_run)), room = 120 - __builtin_amdgcn_frexp_expf(xor32_max(top));
+        drop = down < room ? down : room;
         tile_barrier();
     }
 
@@ -691,6 +701,11 @@ __global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefil
         if (past_l2) store(std::true_type{});
         else store(std::false_type{});
         wave_lds_fence();
+    }
+    if constexpr (WALK) {  // a sum of up to 2^32 against a maximum as far down: its exponent goes to the maximum, where it is exact
+        const int e = __builtin_amdgcn_frexp_expf(l_tot);
+        m_run += (float)e;
+        l_tot = ldexpf(l_tot, -e);
     }
     if (grp == 0 && lh == 0 && q_row < Lq_rows) Lh[q_row] = (l_tot > 0.f) ? (m_run + fast_log2(l_tot)) * kLn2 : -INFINITY;
 }

@@ -72,6 +72,55 @@ def test_shards_visited_in_turn(B, Hq, d, dt, Lq, Ls, spread):
     assert float((O - Om).abs().max()) <= 6.0 * tol
 
 
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("size", [1.0, 2.0 ** 40, 2.0 ** 80, 2.0 ** 100, 2.0 ** 118])
+def test_shards_visited_in_turn_take_values_of_any_size(d, size):
+    """bf16 values far beyond any activation's: where the call with a partial per shard is finite, so is the visiting form, and
+    agrees with it as above, whatever the order of the shards' scores.  (Above 2^112 the weight of a shard that lies below another
+    rests in the 16 bits of its probabilities, 2^-9 of a weight of at most 2^-1.)"""
+    Ls = [70, 64, 130, 1, 200]
+    Q = rnd(1, 32, 2048, d, "bf16", W.TID_Q).to(DEV)
+    Q[..., 0] = torch.where(torch.arange(2048, device=DEV) % 2 == 0, 16.0, -16.0).to(Q.dtype)
+    Q[..., 1] = torch.where(torch.arange(2048, device=DEV) % 4 < 2, 16.0, 0.0).to(Q.dtype)
+    Ks = [rnd(1, 8, L, d, "bf16", W.TID_K + 16 * (i + 1)) for i, L in enumerate(Ls)]
+    Vs = [(rnd(1, 8, L, d, "f32", W.TID_V + 16 * (i + 1)) * size).to(torch.bfloat16).to(DEV) for i, L in enumerate(Ls)]
+    for i, k in enumerate(Ks):
+        k[..., 0] = 20.0 * i         # rising, falling
+        k[..., 1] = 60.0 * (i % 2)   # and up and down for every other pair of rows
+    Ks = [k.to(DEV) for k in Ks]
+    print(f"values of any size {d} {size}", flush=True)
+    O, lse = fb.fedrag_partial_attn_shards(Q, Ks, Vs)
+    parts = [fb.fedrag_partial_attn(Q, k, v) for k, v in zip(Ks, Vs)]
+    Om, lm = fb.fedrag_lse_merge(torch.stack([p[0] for p in parts]), torch.stack([p[1] for p in parts]), n_kv_heads=8)
+    torch.cuda.synchronize()
+    assert torch.isfinite(Om).all() and torch.isfinite(O).all()
+    tol = 2.0 ** -21 + 2.0 ** -19 + 2.0 ** -22 * float(lm.abs().max())
+    assert float((lse - lm).abs().max()) <= tol
+    assert float((O / size - Om / size).abs().max()) <= 6.0 * (tol if size < 2.0 ** 112 else 2.0 ** -9)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_a_shard_far_below_leaves_the_log_sum_exp_exact(d):
+    """A first shard with a log-sum-exp of order one and others far below it: their weight is nothing, and what the visit does to
+    the running maximum must not be seen either.  Maximum and logarithm of the sum are below 2^5 in base 2, so either form rounds
+    their sum by 2^-20 and what it makes of it by 2^-22 a step."""
+    Ls = [70, 64, 130]
+    Q = (rnd(1, 32, 2048, d, "f32", W.TID_Q) * 0.25).to(torch.bfloat16).to(DEV)
+    Q[..., 0] = 16.0
+    Ks = [rnd(1, 8, L, d, "bf16", W.TID_K + 16 * (i + 1)) for i, L in enumerate(Ls)]
+    Vs = [rnd(1, 8, L, d, "bf16", W.TID_V + 16 * (i + 1)).to(DEV) for i, L in enumerate(Ls)]
+    for i, k in enumerate(Ks):
+        k[..., 0] = -60.0 * (i > 0)
+    Ks = [k.to(DEV) for k in Ks]
+    print(f"shards far below {d}", flush=True)
+    O, lse = fb.fedrag_partial_attn_shards(Q, Ks, Vs)
+    parts = [fb.fedrag_partial_attn(Q, k, v) for k, v in zip(Ks, Vs)]
+    Om, lm = fb.fedrag_lse_merge(torch.stack([p[0] for p in parts]), torch.stack([p[1] for p in parts]), n_kv_heads=8)
+    torch.cuda.synchronize()
+    assert float(lm.abs().max()) < 16.0
+    assert float((lse - lm).abs().max()) <= 3 * 2.0 ** -20
+
+
 def test_every_shard_boundary_keeps_its_keys():
     """One key tile of one shard holds all the weight of a query row: a tile lost or read twice at a shard's end moves that
     row's log-sum-exp by ln 2 or more."""
