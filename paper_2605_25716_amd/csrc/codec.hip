@@ -85,13 +85,13 @@ __global__ __launch_bounds__(kCodecThreads) void quantize_rows_kernel(const char
             group_min_max<LPR>(lo, hi);
             const float range = hi - lo;
             const float scale = range / (float)LEVELS;
-            // x - lo >= 0, so the sum is >= 1/2: converting to unsigned truncates = floors, and only the upper clamp
-            // can act; a constant row (range 0) gets steps 0, hence code 0
+            // x - lo >= 0, so the sum is >= 1/2: converting to unsigned truncates = floors, and the lower clamp takes only NaN,
+            // the minimum of a range too small for LEVELS / range; a constant row (range 0) gets steps 0, hence code 0
             const float steps = range > 0.0f ? (float)LEVELS / range : 0.0f;
             uint32_t q[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e)
-                q[e] = (uint32_t)fminf(__builtin_fmaf(x[u][e] - lo, steps, 0.5f), (float)LEVELS);
+                q[e] = (uint32_t)clamp_code(__builtin_fmaf(x[u][e] - lo, steps, 0.5f), (float)LEVELS);
             if (row[u] < n_rows) {
                 uint8_t* out = codes + row[u] * CODE_ROWB;
                 if (BITS == 8) {

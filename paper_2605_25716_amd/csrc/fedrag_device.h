@@ -139,6 +139,10 @@ __device__ __forceinline__ void group_min_max(float& lo, float& hi) {
 #undef FEDRAG_MIN_MAX_OF_8
 #undef FEDRAG_MIN_MAX_STEP
 
+// A code of the transport codec before its truncation: t clamped to [0, levels], NaN to 0 (the median of three with a NaN among
+// them is the least of the others).
+__device__ __forceinline__ float clamp_code(float t, float levels) { return __builtin_amdgcn_fmed3f(t, 0.0f, levels); }
+
 // Sixteen values in [0, 256) truncated to bytes, value e in byte e % 4 of word e / 4, each conversion writing its byte.  The
 // words take turns because a partly written register must not be written again by the next instruction.
 __device__ __forceinline__ void bytes_of(const float (&t)[16], uint32_t (&w)[4]) {

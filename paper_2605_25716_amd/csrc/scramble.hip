@@ -266,8 +266,8 @@ __global__ __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_kernel
         hi = T::to_float(T::from_float(hi));
         const float range = hi - lo;
         const float scale = range / (float)LEVELS;
-        // x - lo >= 0, so the sum is >= 1/2: converting to unsigned truncates = floors, and only the upper
-        // clamp can act; a constant row (range 0) gets steps 0, hence code 0
+        // x - lo >= 0, so the sum is >= 1/2: converting to unsigned truncates = floors, and the lower clamp takes only NaN;
+        // a constant row (range 0) gets steps 0, hence code 0
         const float steps = range > 0.0f ? (float)LEVELS / range : 0.0f;
         // 8 bits: the sum is below 256 (x - lo <= range, and range * steps rounds to 255 or one unit above it), so
         // the truncated byte is the code; an infinite sum (a range too small for 255 / range) truncates to 255,
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_kernel
         auto code = [&](int c) {  // c-th of this lane's columns
             const typename T::elem x = T::from_float(y[c / 4][c % 4]);
             const float t = __builtin_fmaf(__builtin_fmaf(T::to_float(x), one, -lo), steps, 0.5f);
-            return QB == 8 ? t : fminf(t, (float)LEVELS);
+            return QB == 8 ? t : clamp_code(t, (float)LEVELS);
         };
         uint32_t w[D * QB / 128 ? D * QB / 128 : 1];
 #pragma unroll

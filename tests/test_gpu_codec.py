@@ -139,8 +139,8 @@ def test_scramble_with_codec_epilogue(oracle, bits, dt, d, structured):
 @pytest.mark.parametrize("dt,d", [("bf16", 128), ("f16", 128), ("bf16", 64), ("f16", 64)])
 def test_codec_epilogue_at_the_edges_of_its_tiles(bits, structured, dt, d):
     """Rows coded from the sums are the codes and parameters of the rows as stored, whatever the number of rows
-    left for the last 32-row tile, with and without a permutation, rows of zeros among them, and nothing is written behind the
-    last row.  Of a row with infinities only the parameters are defined."""
+    left for the last 32-row tile, with and without a permutation, rows of zeros, infinities and NaN among them, and nothing is
+    written behind the last row."""
     dtype = W.torch_dtype(dt)
     for B, H, L in ((1, 1, 1), (2, 3, 31), (1, 2, 32), (1, 2, 33), (2, 2, 257), (3, 1, 4100), (1, 1, 20001)):
         g = torch.Generator().manual_seed(1000 * L + d)
@@ -149,6 +149,8 @@ def test_codec_epilogue_at_the_edges_of_its_tiles(bits, structured, dt, d):
         V[:, :, L // 3, d // 2:] = 0.0
         if L > 1:
             V[:, :, L - 1] = 65000.0 if dt == "f16" else 3e38  # sums beyond the storage type
+            V[0, 0, 0] = float("inf")                          # infinite sums and NaN
+            K[0, 0, 0, d // 2] = float("nan")
         K, V = K.to(dtype).to(DEV), V.to(dtype).to(DEV)
         perms = W.make_keys(H, d, 1, L, 1, seed=L, dtype=dtype).perm_kv[0].to(DEV), None
         if structured:
@@ -173,14 +175,35 @@ def test_codec_epilogue_at_the_edges_of_its_tiles(bits, structured, dt, d):
             f = fb.fedrag_scramble_kv_structured if structured else fb.fedrag_scramble_kv
             ref = sum((fb.fedrag_quantize_rows(x, bits) for x in f(K, V, kk, kv, perm)), ())
             torch.cuda.synchronize()
-            defined = torch.isfinite(ref[3]).all(-1)
             for i, (a, b) in enumerate(zip(out, ref)):
-                if i == 2:
-                    a, b = a[defined], b[defined]
                 # (the sign of a zero minimum is that of either zero)
                 assert torch.equal(a, b) if i % 2 == 0 else torch.allclose(a, b, 0, 0, equal_nan=True), (i, L, perm is None)
             for end, begin in zip(ends, cut[1:] + [room.numel()]):
                 assert (room[end:begin] == 0xA5).all()
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+def test_rows_of_a_range_too_small_for_its_steps(oracle, bits, d, dt):
+    """levels / range is infinite for a range below levels / 2^128: the row's minimum, 0 times that, has code 0 and everything
+    above it the highest; by itself and through Enc."""
+    dtype = W.torch_dtype(dt)
+    g = torch.Generator().manual_seed(d + bits)
+    X = torch.randint(0, 8, (1, 2, 70, d), generator=g).float() * 2.0 ** -126
+    X[:, :, ::2] *= 2.0 ** 4     # a finite number of steps from some rows on
+    X[:, :, ::3] += 2.0 ** -120  # a minimum other than zero
+    X[:, :, 5] = 2.0 ** -126
+    X = X.to(dtype)
+    codes, params = fb.fedrag_quantize_rows(X.to(DEV), bits)
+    want, pw = oracle.quantize_rows(X, bits)
+    assert np.array_equal(params.cpu().numpy(), pw) and np.array_equal(codes.cpu().numpy(), want)
+    if dt == "bf16":
+        one = torch.eye(d, dtype=dtype).expand(2, d, d).contiguous().to(DEV)
+        out = fb.fedrag_scramble_kv_quantized(X.to(DEV), X.to(DEV), one, one, None, bits)
+        Ks, Vs = fb.fedrag_scramble_kv(X.to(DEV), X.to(DEV), one, one, None)
+        for a, b in zip(out, fb.fedrag_quantize_rows(Ks, bits) + fb.fedrag_quantize_rows(Vs, bits)):
+            assert torch.equal(a, b)
 
 
 ATTN_Q_CASES = [
