@@ -618,7 +618,10 @@ __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0,
 #pragma unroll
         for (int g = 1; g < KG; ++g) sum += part[g][e];
         float v = (float)sum;
-        if (ST && !kF32) v *= post0;
+        if (ST && !kF32) {
+            v *= post0;
+            pin_here(v);  // narrowed afterwards, as in the tiled kernel: in one operation a zero would lose its sign
+        }
         if (SCATTER && mg.lse_in) {
             float l;
             v = merge_two(weights_of_two(o.la, o.lb, &l), v, o.other);
