@@ -733,20 +733,26 @@ static PrefillCost prefill_cost(int64_t wgs8, int64_t wgs4, float tiles, float e
     const float b = D == 64 ? (codes ? 0.465f : 0.445f) : codes ? 0.55f : 0.51f;
     return PrefillCost{(float)q8 * (tiles + ends), (a + b * (float)q4) * (tiles + 0.5f * ends)};
 }
+// What the choice between the forms needs in microseconds: a key tile of the larger form, and the fold of n partials of `rows`
+// rows, at 7.5 bytes per ns.
+static float prefill_tile_us(int D) { return D == 64 ? 1.19f : 1.77f; }
+static float prefill_fold_us(int n, int64_t rows, int D) {
+    return n > 1 ? 3.0f + (float)n * (float)rows * (float)(D + 1) * 4.0f / 7.5e6f : 0.0f;
+}
 static bool prefill_wants_4_waves(int64_t wgs8, int64_t wgs4, int64_t tiles, int D, bool codes) {
     const float ends = wgs8 <= attn_target_wgs() ? 0.0f : codes ? 2.0f : 4.0f;
     return prefill_cost(wgs8, wgs4, (float)tiles, ends, D, codes).four();
 }
 
 // Several shards: whether a workgroup visits them all (WALK), by the same cost.  Either way a workgroup's start and end take
-// four tiles; a shard's end inside a walk takes one, runs of unequal length end unevenly, and the fold reads a partial per run
-// (7.5 bytes per ns, a tile takes 1.77 us at d = 128 and 1.19 at d = 64).  At d = 64 the walking form is itself 5 % slower.
+// four tiles; a shard's end inside a walk takes one, runs of unequal length end unevenly, and the fold reads a partial per run.
+// At d = 64 the walking form is itself 5 % slower.
 // Only from query tiles for a whole round on: below that shards side by side fill the chip (1500 x 32 heads x 2 x 5000 keys
 // 252 us, 253 to 283 walked; 1100 x 32 x 8 x 5000 714 and 960).  4096 x 64 rows of 128 x 8 x 8192 keys: 7.44 ms walked, 7.76 with
 // partials; 2048 x 32 x 8 x 2048 515 and 605 us, x 8 x 512 139 and 217, x (8000 + 500) 252 and 418; 4096 x 64 of 64 x 2 x 300 62
 // and 99.  Where the rounds come out uneven it is the other way: 1100 x 64 x 4 x 3000 549 and 454.
-static bool prefill_walks(const AttnProblem& p, const KeyRuns& runs, int Hq_k, int64_t tiles8, int64_t tiles4, int D, bool* four) {
-    const int64_t heads = (int64_t)p.B * Hq_k;
+static bool prefill_walks(const AttnProblem& p, const KeyRuns& runs, int64_t heads, int64_t tiles8, int64_t tiles4, bool* four) {
+    const int D = p.D;
     if (heads * tiles8 < attn_target_wgs()) return false;
     int n = 0;
     float total = 0.0f, longest = 0.0f;
@@ -759,10 +765,8 @@ static bool prefill_walks(const AttnProblem& p, const KeyRuns& runs, int Hq_k, i
     }
     if (n < 2 || runs.n_runs != n) return false;
     const float mean = total / (float)n;
-    const float rows = (float)p.B * (float)p.Hq * (float)p.Lq;
-    const float fold_us = 3.0f + (float)n * rows * (float)(D + 1) * 4.0f / 7.5e6f;
     const float side_by_side = prefill_cost(heads * tiles8 * n, heads * tiles4 * n, mean, 4.0f, D, false).least() +
-                               0.5f * (longest - mean) + fold_us / (D == 64 ? 1.19f : 1.77f);
+                               0.5f * (longest - mean) + prefill_fold_us(n, (int64_t)p.B * p.Hq * p.Lq, D) / prefill_tile_us(D);
     const PrefillCost walked = prefill_cost(heads * tiles8, heads * tiles4, total + (float)(n - 1), 4.0f, D, false);
     *four = walked.four();
     return walked.least() * (D == 64 ? 1.05f : 1.0f) < side_by_side;
@@ -779,37 +783,108 @@ static bool prefill_walks(const AttnProblem& p, const KeyRuns& runs, int Hq_k, i
 // then depend on how many others are in its batch.
 static bool prefill_two_groups(KeyRuns* runs, int64_t wgs8, int64_t wgs4, int64_t rows, int D) {
     const int64_t cus = attn_target_wgs();
-    int64_t total = 0, longest = 0, tiles1 = 0;
+    int64_t total = 0, tiles1 = 0;
+    int shards = 0;
     for (int i = 0; i < runs->n_shards; ++i) {
         const int64_t L = runs->s[i].L, run = L < runs->s[i].per ? L : runs->s[i].per;
         total += L;
-        longest = L > longest ? L : longest;
+        shards += L > 0 ? 1 : 0;
         tiles1 = (run + kPreK - 1) / kPreK > tiles1 ? (run + kPreK - 1) / kPreK : tiles1;
     }
-    if (wgs4 < 1 || wgs8 * 2 > cus) return false;
-    constexpr int64_t kPair = 2 * kPreK;  // a tile for each group
-    const int64_t want = cus / wgs4 > 0 ? cus / wgs4 : 1;
-    int64_t pairs = ((total + kPair - 1) / kPair + want - 1) / want;
+    if (wgs4 < 1 || wgs8 * 2 > cus || shards * wgs4 > cus) return false;
+    const int64_t want = cus / wgs4;
+    int64_t pairs = ((total + kPrePair - 1) / kPrePair + want - 1) / want;
     if (pairs < kPreMinTilesPerSplit) pairs = kPreMinTilesPerSplit;
     KeyRuns two = *runs;
-    attn_cut_runs(two, pairs * kPair, kPair);
-    while (two.n_runs * wgs4 > cus && pairs * kPair < longest) attn_cut_runs(two, ++pairs * kPair, kPair);
+    attn_cut_runs(two, prefill_least_run(two, pairs * kPrePair, want), kPrePair);
     const int64_t wgs = two.n_runs * wgs4;
     if (two.n_runs > runs->n_runs || wgs > cus || wgs * 2 < cus) return false;
     int64_t steps = 0;
     for (int i = 0; i < two.n_shards; ++i) {
         const int64_t run = two.s[i].L < two.s[i].per ? two.s[i].L : two.s[i].per;
-        steps = (run + kPair - 1) / kPair > steps ? (run + kPair - 1) / kPair : steps;
+        steps = (run + kPrePair - 1) / kPrePair > steps ? (run + kPrePair - 1) / kPrePair : steps;
     }
-    const float tile_us = D == 64 ? 1.19f : 1.77f;
-    auto fold_us = [&](int n) { return n > 1 ? 3.0f + (float)n * (float)rows * (float)(D + 1) * 4.0f / 7.5e6f : 0.0f; };
+    const float tile_us = prefill_tile_us(D);
     const float ends = wgs8 * runs->n_runs <= cus ? 0.0f : 4.0f;
     const float one = prefill_cost(wgs8 * runs->n_runs, wgs4 * runs->n_runs, (float)tiles1, ends, D, false).least() * tile_us +
-                      fold_us(runs->n_runs);
-    const float both = ((float)steps * (D == 64 ? 1.0f : 1.1f) + 0.33f) * tile_us + fold_us(two.n_runs);
+                      prefill_fold_us(runs->n_runs, rows, D);
+    const float both = ((float)steps * (D == 64 ? 1.0f : 1.1f) + 0.33f) * tile_us + prefill_fold_us(two.n_runs, rows, D);
     if (both >= one) return false;
     *runs = two;
     return true;
+}
+
+// The least run, in whole pairs of key tiles and of at least `from` keys, that leaves at most `most` runs.  A longer run never
+// leaves more of them, so it is found by halving; no less than one run a shard is asked for.  (Tried one pair after the other, 16
+// shards, the longest of 131072 keys, took 156 us of a call's host time.)
+int64_t prefill_least_run(const KeyRuns& shards, int64_t from, int64_t most) {
+    int64_t longest = 0;
+    for (int i = 0; i < shards.n_shards; ++i) longest = shards.s[i].L > longest ? shards.s[i].L : longest;
+    int64_t lo = from / kPrePair, hi = (longest + kPrePair - 1) / kPrePair;
+    if (hi < lo) hi = lo;  // a run a shard already
+    KeyRuns cut = shards;
+    attn_cut_runs(cut, lo * kPrePair, kPrePair);
+    if (cut.n_runs <= most) return lo * kPrePair;
+    while (hi - lo > 1) {  // lo leaves too many
+        const int64_t mid = lo + (hi - lo) / 2;
+        attn_cut_runs(cut, mid * kPrePair, kPrePair);
+        if (cut.n_runs <= most) hi = mid;
+        else lo = mid;
+    }
+    return hi * kPrePair;
+}
+
+// What a launch does, decided from the sizes alone.
+PrefillForm prefill_form(const AttnProblem& p) {
+    PrefillForm f;
+    // Without a mask or per-sequence query counts a row's position in its head means nothing, and the query heads of
+    // a KV head are contiguous in Q, O and lse: the kernel then sees one head of G * Lq rows per KV head, so that
+    // short segments fill their 256-row tiles (128 queries x 4 heads: 2 full tiles instead of 4 half-empty ones).
+    const bool pack_group = !p.causal && !p.q_lens;
+    f.Hq = pack_group ? p.Hkv : p.Hq;
+    f.Lq = pack_group ? (int64_t)(p.Hq / p.Hkv) * p.Lq : p.Lq;
+    f.kind = PrefillForm::kPlain;
+    f.four = false;
+    f.runs = attn_runs_of(p);
+    // several runs: only the plain call (every key of every sequence, every query row, no mask) takes them
+    const bool one_run_only = p.causal || p.kv_lens || p.q_lens;
+    if (one_run_only) {
+        if (p.n_shards > 1) f.runs.n_runs = 0;  // refused
+        else {
+            f.runs.s[0].per = f.runs.s[0].L > 0 ? ((f.runs.s[0].L + kPreK - 1) / kPreK) * kPreK : kPreK;
+            f.runs.first[1] = 1;
+            f.runs.n_runs = 1;
+            f.runs.by_runs = FastDiv(1);
+        }
+    }
+    if (f.runs.n_runs < 1) return f;
+    const int64_t tiles8 = (f.Lq + 8 * kPreQ - 1) / (8 * kPreQ), tiles4 = (f.Lq + 4 * kPreQ - 1) / (4 * kPreQ);
+    const int64_t heads = (int64_t)p.B * f.Hq;
+    if (!p.causal && p.quant_bits == 0) {
+        if (p.n_shards > 1 && prefill_walks(p, f.runs, heads, tiles8, tiles4, &f.four)) {  // writes O, lse; no partials
+            const KeyRuns runs = f.runs;
+            f.runs.n_shards = 0;
+            for (int i = 0; i < p.n_shards; ++i)
+                if (runs.s[i].L > 0) f.runs.s[f.runs.n_shards++] = runs.s[i];
+            f.runs.n_runs = 1;
+            f.runs.by_runs = FastDiv(1);
+            f.kind = PrefillForm::kWalk;
+            return f;
+        }
+        // (no more partials than the plan that the workspace is sized for has)
+        if (!one_run_only && prefill_two_groups(&f.runs, heads * tiles8, heads * tiles4, (int64_t)p.B * p.Hq * p.Lq, p.D)) {
+            f.kind = PrefillForm::kTwoGroups;
+            return f;
+        }
+    }
+    int64_t key_tiles = 1;  // of the longest run
+    for (int i = 0; i < f.runs.n_shards; ++i) {
+        const int64_t keys = f.runs.s[i].L < f.runs.s[i].per ? f.runs.s[i].L : f.runs.s[i].per;
+        if ((keys + kPreK - 1) / kPreK > key_tiles) key_tiles = (keys + kPreK - 1) / kPreK;
+    }
+    f.four = p.causal || (p.q_lens && p.quant_bits == 0 && p.B > 1) ||
+             prefill_wants_4_waves(heads * f.runs.n_runs * tiles8, heads * f.runs.n_runs * tiles4, key_tiles, p.D, p.quant_bits != 0);
+    return f;
 }
 
 // Order of a unit's workgroups when there are several runs.  The runs of a query tile side by side, unless one run's
@@ -820,11 +895,13 @@ constexpr int64_t kPreRunByRunBytes = 16 << 20;
 constexpr int64_t kPreTogetherBytes = 8 << 20;  // K and V of an XCD's units, whose L2 is 4 MiB
 
 template <class T, int D, bool CAUSAL, int QB, int NW, bool WALK, int KG = 1>
-static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, int Hq_k, int64_t Lq_k, int64_t q_tiles,
-                                    float* Odst, float* Ldst, hipStream_t stream) {
+static hipError_t launch_prefill_nw(const AttnProblem& p, const PrefillForm& f, float* Odst, float* Ldst, hipStream_t stream) {
     typedef typename T::elem elem;
+    const KeyRuns& runs = f.runs;
     const int n_units = p.B * p.Hkv;
-    const int64_t tiles_of_unit = (int64_t)(Hq_k / p.Hkv) * q_tiles;
+    constexpr int kRows = NW / KG * kPreQ;
+    const int64_t q_tiles = (f.Lq + kRows - 1) / kRows;
+    const int64_t tiles_of_unit = (int64_t)(f.Hq / p.Hkv) * q_tiles;
     const int64_t per_unit = tiles_of_unit * runs.n_runs;
     const int64_t grid = (int64_t)8 * ((n_units + 7) / 8) * per_unit;
     if (!grid_fits(grid, NW * kWave)) return hipErrorInvalidValue;
@@ -842,93 +919,56 @@ static hipError_t launch_prefill_nw(const AttnProblem& p, const KeyRuns& runs, i
     // all outputs of the launch; with several runs, the partials
     const int past_l2 = (int64_t)p.B * p.Hq * p.Lq * runs.n_runs * (4 * D) >= kPastL2Bytes ? 1 : 0;
     hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB, NW, WALK, KG>), dim3((unsigned)grid), dim3(NW * kWave), 0, stream,
-                       (const elem*)p.Q, runs, p.K_params, p.V_params, Hq_k, FastDiv(p.Hkv), FastDiv(Hq_k / p.Hkv),
+                       (const elem*)p.Q, runs, p.K_params, p.V_params, f.Hq, FastDiv(p.Hkv), FastDiv(f.Hq / p.Hkv),
                        FastDiv(q_tiles), FastDiv(together ? units_per_xcd : per_unit), FastDiv(run_by_run ? tiles_of_unit : runs.n_runs),
-                       run_by_run ? 1 : 0, Lq_k, p.kv_lens, p.q_lens, n_units, fold, together, past_l2,
+                       run_by_run ? 1 : 0, f.Lq, p.kv_lens, p.q_lens, n_units, fold, together, past_l2,
                        p.scale * kLog2e, Odst, Ldst);
     return hipGetLastError();
 }
 
 template <class T, int D, bool CAUSAL, int QB = 0>
-static hipError_t launch_prefill_t(const AttnProblem& p, hipStream_t stream) {
-    // Without a mask or per-sequence query counts a row's position in its head means nothing, and the query heads of
-    // a KV head are contiguous in Q, O and lse: the kernel then sees one head of G * Lq rows per KV head, so that
-    // short segments fill their 256-row tiles (128 queries x 4 heads: 2 full tiles instead of 4 half-empty ones).
-    const bool pack_group = !CAUSAL && !p.q_lens;
-    const int Hq_k = pack_group ? p.Hkv : p.Hq;
-    const int64_t Lq_k = pack_group ? (int64_t)(p.Hq / p.Hkv) * p.Lq : p.Lq;
-    // several runs: only the plain call (every key of every sequence, every query row, no mask) takes them
-    KeyRuns runs = attn_runs_of(p);
-    const bool one_run_only = CAUSAL || p.kv_lens || p.q_lens;
-    if (one_run_only) {
-        if (p.n_shards > 1) return hipErrorInvalidValue;
-        runs.s[0].per = runs.s[0].L > 0 ? ((runs.s[0].L + kPreK - 1) / kPreK) * kPreK : kPreK;
-        runs.first[1] = 1;
-        runs.n_runs = 1;
-        runs.by_runs = FastDiv(1);
-    }
-    if (runs.n_runs < 1) return hipErrorInvalidValue;
-    const int splits = runs.n_runs;
+static hipError_t launch_prefill_t(const AttnProblem& p, const PrefillForm& f, hipStream_t stream) {
     if (QB != 0 && (p.n_shards > 1 || !p.K_params || !p.V_params)) return hipErrorInvalidValue;
     const int64_t rows = (int64_t)p.B * p.Hq * p.Lq;
+    const int n = f.runs.n_runs;
     float* Odst = p.O;
     float* Ldst = p.lse;
-    if (splits > 1) {
-        if (!p.workspace || p.workspace_bytes < (size_t)splits * rows * (D + 1) * sizeof(float)) return hipErrorInvalidValue;
+    if (n > 1) {  // partials
+        if (!p.workspace || p.workspace_bytes < (size_t)n * rows * (D + 1) * sizeof(float)) return hipErrorInvalidValue;
         Odst = (float*)p.workspace;
-        Ldst = Odst + (size_t)splits * rows * D;
+        Ldst = Odst + (size_t)n * rows * D;
     }
-    const int64_t tiles8 = (Lq_k + 8 * kPreQ - 1) / (8 * kPreQ), tiles4 = (Lq_k + 4 * kPreQ - 1) / (4 * kPreQ);
-    if constexpr (!CAUSAL && QB == 0) {
-        bool walk4 = false;
-        if (p.n_shards > 1 && prefill_walks(p, runs, Hq_k, tiles8, tiles4, D, &walk4)) {  // writes O, lse; no partials
-            KeyRuns all = runs;
-            all.n_shards = 0;
-            for (int i = 0; i < p.n_shards; ++i)
-                if (runs.s[i].L > 0) all.s[all.n_shards++] = runs.s[i];
-            all.n_runs = 1;
-            all.by_runs = FastDiv(1);
-            return walk4 ? launch_prefill_nw<T, D, false, 0, 4, true>(p, all, Hq_k, Lq_k, tiles4, p.O, p.lse, stream)
-                         : launch_prefill_nw<T, D, false, 0, 8, true>(p, all, Hq_k, Lq_k, tiles8, p.O, p.lse, stream);
-        }
-    }
-    if constexpr (!CAUSAL && QB == 0) {
-        KeyRuns two = runs;
-        if (!one_run_only && prefill_two_groups(&two, (int64_t)p.B * Hq_k * tiles8, (int64_t)p.B * Hq_k * tiles4, rows, D)) {
-            const bool parts = two.n_runs > 1;  // no more of them than the plan that the workspace is sized for has
-            float* Lpart = Odst + (size_t)two.n_runs * rows * D;
-            const hipError_t e = launch_prefill_nw<T, D, false, 0, 8, false, 2>(p, two, Hq_k, Lq_k, tiles4, parts ? Odst : p.O,
-                                                                                 parts ? Lpart : p.lse, stream);
-            if (e != hipSuccess || !parts) return e;
-            return launch_lse_merge(Odst, Lpart, two.n_runs, rows, D, p.O, p.lse, stream);
-        }
-    }
-    const int64_t heads = (int64_t)p.B * Hq_k * splits;
-    int64_t key_tiles = 1;  // of the longest run
-    for (int i = 0; i < runs.n_shards; ++i) {
-        const int64_t keys = runs.s[i].L < runs.s[i].per ? runs.s[i].L : runs.s[i].per;
-        if ((keys + kPreK - 1) / kPreK > key_tiles) key_tiles = (keys + kPreK - 1) / kPreK;
-    }
-    const bool four = CAUSAL || (p.q_lens && QB == 0 && p.B > 1) ||
-                      prefill_wants_4_waves(heads * tiles8, heads * tiles4, key_tiles, D, QB != 0);
     hipError_t e = hipErrorInvalidValue;
-    if (four) e = launch_prefill_nw<T, D, CAUSAL, QB, 4, false>(p, runs, Hq_k, Lq_k, tiles4, Odst, Ldst, stream);
-    else if constexpr (!CAUSAL) e = launch_prefill_nw<T, D, false, QB, 8, false>(p, runs, Hq_k, Lq_k, tiles8, Odst, Ldst, stream);
-    if (e != hipSuccess || splits == 1) return e;
-    return launch_lse_merge(Odst, Ldst, splits, rows, D, p.O, p.lse, stream);
+    if constexpr (CAUSAL) {
+        e = launch_prefill_nw<T, D, true, 0, 4, false>(p, f, Odst, Ldst, stream);
+    } else {
+        if (f.kind == PrefillForm::kPlain)
+            e = f.four ? launch_prefill_nw<T, D, false, QB, 4, false>(p, f, Odst, Ldst, stream)
+                       : launch_prefill_nw<T, D, false, QB, 8, false>(p, f, Odst, Ldst, stream);
+        if constexpr (QB == 0) {
+            if (f.kind == PrefillForm::kWalk)
+                e = f.four ? launch_prefill_nw<T, D, false, 0, 4, true>(p, f, Odst, Ldst, stream)
+                           : launch_prefill_nw<T, D, false, 0, 8, true>(p, f, Odst, Ldst, stream);
+            if (f.kind == PrefillForm::kTwoGroups) e = launch_prefill_nw<T, D, false, 0, 8, false, 2>(p, f, Odst, Ldst, stream);
+        }
+    }
+    if (e != hipSuccess || n == 1) return e;
+    return launch_lse_merge(Odst, Ldst, n, rows, D, p.O, p.lse, stream);
 }
 
 template <class T>
 static hipError_t launch_prefill_d(const AttnProblem& p, hipStream_t stream) {
+    const PrefillForm f = prefill_form(p);
+    if (f.runs.n_runs < 1) return hipErrorInvalidValue;
     if (p.quant_bits != 0) {  // K', V' as transport codes (never with the mask: the Inquirer's own K, V are plain)
         if (p.causal || (p.quant_bits != 8 && p.quant_bits != 4)) return hipErrorInvalidValue;
         if (p.quant_bits == 8)
-            return p.D == 128 ? launch_prefill_t<T, 128, false, 8>(p, stream) : launch_prefill_t<T, 64, false, 8>(p, stream);
-        return p.D == 128 ? launch_prefill_t<T, 128, false, 4>(p, stream) : launch_prefill_t<T, 64, false, 4>(p, stream);
+            return p.D == 128 ? launch_prefill_t<T, 128, false, 8>(p, f, stream) : launch_prefill_t<T, 64, false, 8>(p, f, stream);
+        return p.D == 128 ? launch_prefill_t<T, 128, false, 4>(p, f, stream) : launch_prefill_t<T, 64, false, 4>(p, f, stream);
     }
     if (p.causal)
-        return p.D == 128 ? launch_prefill_t<T, 128, true>(p, stream) : launch_prefill_t<T, 64, true>(p, stream);
-    return p.D == 128 ? launch_prefill_t<T, 128, false>(p, stream) : launch_prefill_t<T, 64, false>(p, stream);
+        return p.D == 128 ? launch_prefill_t<T, 128, true>(p, f, stream) : launch_prefill_t<T, 64, true>(p, f, stream);
+    return p.D == 128 ? launch_prefill_t<T, 128, false>(p, f, stream) : launch_prefill_t<T, 64, false>(p, f, stream);
 }
 
 hipError_t launch_prefill_attn(const AttnProblem& p, hipStream_t stream) {

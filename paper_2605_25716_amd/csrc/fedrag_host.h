@@ -167,6 +167,17 @@ constexpr int kPreQ = 32;                     // query rows per wave (one 32-wid
 constexpr int kPrePlanRows = 8 * kPreQ;       // query rows the planner counts per workgroup (the larger of the two forms)
 constexpr int kPreK = 64;                     // keys per LDS tile
 constexpr int kPreMinTilesPerSplit = 4;       // a KV split is at least this many tiles
+constexpr int64_t kPrePair = 2 * kPreK;       // a tile for each of two key groups
+// The form a prefill launch takes (attn_prefill.hip), a host decision from sizes alone.
+struct PrefillForm {
+    enum Kind { kPlain, kWalk, kTwoGroups } kind;  // a run a workgroup; all shards in turn; a run's keys halved between two groups
+    bool four;      // plain, walk: four waves of 32 query rows per workgroup instead of eight
+    int Hq;         // heads and query rows per head as the kernel sees them
+    int64_t Lq;
+    KeyRuns runs;   // n_runs < 1: refused; more than one: partials
+};
+PrefillForm prefill_form(const AttnProblem& p);
+int64_t prefill_least_run(const KeyRuns& shards, int64_t from, int64_t most);
 hipError_t launch_attn_f32(const AttnProblem& p, hipStream_t stream);      // fp32 storage, any L_q
 hipError_t launch_decode_attn(const AttnProblem& p, hipStream_t stream);   // 16-bit storage, G * L_q <= 16
 hipError_t launch_prefill_attn(const AttnProblem& p, hipStream_t stream);  // 16-bit storage, any L_q

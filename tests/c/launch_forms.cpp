@@ -1,0 +1,78 @@
+// The host's choice of a prefill launch's form, looked at without a device (no call here enqueues anything).  Commands on stdin,
+// one answer a line:
+//   form B Hq Hkv d dtype Lq n L...   ->  kind four n_runs        (kind: 0 plain, 1 shards in turn, 2 two key groups)
+//   runs from most n L...             ->  keys a run by halving, by trying every length in turn
+//   time B Hq Hkv d dtype Lq n L...   ->  microseconds a choice takes, the least of many
+#include <algorithm>
+#include <chrono>
+#include <cstdio>
+#include <cstring>
+#include <vector>
+
+#include "fedrag_host.h"
+
+using namespace fedrag;
+
+static bool read_problem(AttnProblem& p, std::vector<int64_t>& L) {
+    std::memset(&p, 0, sizeof p);
+    long lq;
+    int n;
+    if (std::scanf("%d %d %d %d %d %ld %d", &p.B, &p.Hq, &p.Hkv, &p.D, &p.dtype, &lq, &n) != 7 || n < 1 || n > kMaxShards) return false;
+    p.Lq = lq;
+    p.scale = 1.0f;
+    p.n_shards = n;
+    L.resize(n);
+    for (int i = 0; i < n; ++i) {
+        long x;
+        if (std::scanf("%ld", &x) != 1) return false;
+        p.Ls[i] = L[i] = x;
+    }
+    p.Lkv = L[0];
+    return true;
+}
+
+static int64_t one_after_the_other(KeyRuns cut, int64_t from, int64_t most) {
+    int64_t longest = 0, per = from;
+    for (int i = 0; i < cut.n_shards; ++i) longest = std::max(longest, cut.s[i].L);
+    attn_cut_runs(cut, per, kPrePair);
+    while (cut.n_runs > most && per < longest) attn_cut_runs(cut, per += kPrePair, kPrePair);
+    return per;
+}
+
+int main() {
+    char what[16];
+    while (std::scanf("%15s", what) == 1) {
+        AttnProblem p;
+        std::vector<int64_t> L;
+        if (!std::strcmp(what, "form")) {
+            if (!read_problem(p, L)) return 2;
+            const PrefillForm f = prefill_form(p);
+            std::printf("%d %d %d\n", (int)f.kind, f.four ? 1 : 0, f.runs.n_runs);
+        } else if (!std::strcmp(what, "runs")) {
+            long from, most;
+            int n;
+            if (std::scanf("%ld %ld %d", &from, &most, &n) != 3 || n < 1 || n > kMaxShards) return 2;
+            KeyRuns r;
+            r.n_shards = n;
+            for (int i = 0; i < n; ++i) {
+                long x;
+                if (std::scanf("%ld", &x) != 1) return 2;
+                r.s[i] = KeyShard{nullptr, nullptr, x, 1};
+            }
+            std::printf("%ld %ld\n", (long)prefill_least_run(r, from, most), (long)one_after_the_other(r, from, most));
+        } else if (!std::strcmp(what, "time")) {
+            if (!read_problem(p, L)) return 2;
+            double least = 1e30;
+            int sum = 0;
+            for (int i = 0; i < 200; ++i) {
+                const auto t0 = std::chrono::steady_clock::now();
+                sum += prefill_form(p).runs.n_runs;
+                least = std::min(least, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count());
+            }
+            std::printf("%.3f %d\n", least, sum);
+        } else {
+            return 2;
+        }
+    }
+    return 0;
+}

@@ -455,6 +455,40 @@ def test_host_paths_under_address_and_undefined_behaviour_sanitizers():
     assert "host paths ok" in res.stdout
 
 
+@pytest.fixture(scope="module")
+def launch_forms(lib, tmp_path_factory):
+    """The host's choice of launch forms, asked through a small program linked with the library."""
+    exe = str(tmp_path_factory.mktemp("forms") / "launch_forms")
+    pkg = os.path.join(ROOT, "paper_2605_25716_amd")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(pkg, "csrc"),
+                    os.path.join(ROOT, "tests", "c", "launch_forms.cpp"), "-o", exe, fbuild.LIB_PATH, "-L/opt/rocm/lib", "-lamdhip64",
+                    "-Wl,-rpath," + pkg + ":/opt/rocm/lib"], check=True, capture_output=True, timeout=300)
+
+    def ask(lines):
+        r = subprocess.run([exe], input="\n".join(lines), capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stderr
+        out = [tuple(float(x) for x in line.split()) for line in r.stdout.splitlines()]
+        assert len(out) == len(lines)
+        return out
+    return ask
+
+
+def test_two_group_runs_by_halving(launch_forms):
+    """The run length found by halving is the one that trying every length in turn finds, and the choice stays a matter of
+    microseconds where one long shard stands beside many short ones (156 us with 131072 keys, 1.3 ms with a million, in turn)."""
+    import random
+    r = random.Random(3)
+    lines = []
+    while len(lines) < 2000:
+        Ls = [r.choice([0, 1, r.randint(1, 300), int(2 ** r.uniform(0, 17))]) for _ in range(r.randint(1, 16))]
+        if any(Ls):
+            lines.append(f"runs {128 * r.randint(4, 60)} {r.randint(1, 64)} {len(Ls)} " + " ".join(map(str, Ls)))
+    assert all(a == b for a, b in launch_forms(lines))
+    times = launch_forms([f"time 1 32 8 128 {fb.BF16} {Lq} 16 {L} " + " ".join(["256"] * 15)
+                          for Lq in (17, 64, 117) for L in (32768, 131072, 1 << 20)])
+    assert max(t for t, _ in times) < 40.0
+
+
 def test_missing_library_fails_loudly(tmp_path):
     """There is no fallback path: with no built library the binding raises instead of computing something else."""
     import subprocess
