@@ -145,7 +145,8 @@ fedrag_status fedrag_partial_attn_static(const fedrag_shape* shape, int64_t L_q,
  * Qs as in fedrag_partial_attn.  O : fp32 [B,Hq,L_q,d], lse : fp32 [B,Hq,L_q], aggregated over all shards; all
  * shards empty gives O = 0, lse = -inf.
  * workspace : at least fedrag_partial_attn_shards_workspace_bytes(shape, L_q, n_shards, L_kv) bytes of device
- * scratch (that function returns 0 for arguments this call would reject); may be NULL only when that is 0.
+ * scratch (that function returns 0 for arguments this call would reject); may be NULL only when that is 0.  The size is
+ * a partial per run and is asked for whether or not the form that the call takes writes any.
  * Errors as fedrag_partial_attn; n_shards out of range is FEDRAG_ERR_SHAPE.
  */
 #define FEDRAG_MAX_SHARDS 16

@@ -473,6 +473,23 @@ def launch_forms(lib, tmp_path_factory):
     return ask
 
 
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the choice is pinned for the 256 compute units it falls back to")
+def test_form_of_the_prefill_launches(launch_forms):
+    """The calls whose launch forms the GPU tests hold do take those forms."""
+    import test_gpu_launch_forms as LF
+    num = {"bf16": fb.BF16, "f16": fb.F16}
+    line = lambda B, Hq, d, dt, Lq, Ls: f"form {B} {Hq} 8 {d} {num[dt]} {Lq} {len(Ls)} " + " ".join(map(str, Ls))  # noqa: E731
+    in_turn = LF.IN_TURN + [(1, 32, d, "bf16", 2048, Ls) for d in (64, 128) for Ls in (LF.IN_TURN_ANY_SIZE, LF.IN_TURN_FAR_BELOW)]
+    assert all(kind == 1 and n == 1 for kind, _, n in launch_forms([line(*c) for c in in_turn]))
+    for d in (64, 128):  # with four waves and with eight
+        assert {four for _, four, _ in launch_forms([line(*c) for c in in_turn if c[2] == d])} == {0.0, 1.0}
+    two = launch_forms([line(*c) for c in LF.TWO_GROUPS])
+    assert all(kind == 2 for kind, _, _ in two) and min(n for _, _, n in two) == 1 and max(n for _, _, n in two) > 1
+    # a partial per shard: 8 units of 4132 rows are more than half a round and less than one
+    one_each = launch_forms([line(1, 32, d, "bf16", 1033, [192, 63, 0, 300]) for d in (64, 128)])
+    assert all(kind == 0 and n == 3 for kind, _, n in one_each)
+
+
 def test_two_group_runs_by_halving(launch_forms):
     """The run length found by halving is the one that trying every length in turn finds, and the choice stays a matter of
     microseconds where one long shard stands beside many short ones (156 us with 131072 keys, 1.3 ms with a million, in turn)."""
