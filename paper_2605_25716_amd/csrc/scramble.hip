@@ -441,6 +441,9 @@ __global__ __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_kernel
 // 4.4 and 10.4, 23.1, 22.7; what stays is mostly the launch (2.2 us).  (16 rows of 32 heads 6.1 against 8.7, Dec 7.5 against 8.6.)
 //   SCATTER == false: Y[j] = X[perm[j]] . Phi ; SCATTER == true (fp32): Y[perm[i]] = X[i] . Phi
 constexpr int kFewRows = 16;
+// Of the form that sums in 64 bits, whose LDS is twice as much a row: at d = 64 eight rows of it leave room for four workgroups
+// a compute unit, where 16 left two (64 x 32 slabs of 1, 5, 8 rows 4.8, 6.9, 8.6 us against 6.4, 9.7, 11.5).
+constexpr int wide_rows(int d) { return d == 64 ? kFewRows / 2 : kFewRows; }
 constexpr int kF32Threads = 256;  // workgroup size of the plain-FMA kernels
 
 // fp32 storage in the terms of the 16-bit types
@@ -484,8 +487,9 @@ __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0,
     constexpr int LPK = D / 2;              // lanes per row of the matrix, two columns each
     constexpr int KG = kF32Threads / LPK;   // shares of the contraction
     constexpr int KPG = D / KG;             // steps of a share
+    constexpr int kRows = WIDE ? wide_rows(D) : kFewRows;    // at most
     constexpr int EPC = 16 / (int)sizeof(elem);              // row elements per 16-byte load
-    constexpr int XC = (kFewRows * D / EPC + kF32Threads - 1) / kF32Threads;  // such loads per thread, at most
+    constexpr int XC = (kRows * D / EPC + kF32Threads - 1) / kF32Threads;  // such loads per thread, at most
     typedef elem chunk_t __attribute__((ext_vector_type(EPC)));
     typedef elem pair_t __attribute__((ext_vector_type(2)));
     // WIDE (fp32 storage): the rounding of the queries comes back multiplied by the scores, and there is time for sums in 64 bits
@@ -494,8 +498,8 @@ __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0,
     typedef typename std::conditional<WIDE, double, float>::type acc_t;
     typedef acc_t acc4_t __attribute__((ext_vector_type(4)));
     typedef acc_t acc2_t __attribute__((ext_vector_type(2)));
-    __shared__ __attribute__((aligned(16))) acc_t xs[kFewRows * D];
-    __shared__ __attribute__((aligned(16))) acc_t part[KG][kFewRows * D];
+    __shared__ __attribute__((aligned(16))) acc_t xs[kRows * D];
+    __shared__ __attribute__((aligned(16))) acc_t part[KG][kRows * D];
     __shared__ int32_t p_in_inv[ST ? D : 1];
     __shared__ float s_in[ST ? D : 1];
     const ScrambleJob job = blockIdx.y == 0 ? job0 : job1;
@@ -568,7 +572,7 @@ __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0,
     for (int u = 0; u < XC; ++u)
 #pragma unroll
         for (int q = 0; q < EPC; ++q)
-            if (XC > 1 || tid < kFewRows * D / EPC) xs[(tid + u * kF32Threads) * EPC + q] = T::to_float(x_in[u][q]);
+            if (XC > 1 || tid < kRows * D / EPC) xs[(tid + u * kF32Threads) * EPC + q] = T::to_float(x_in[u][q]);
     if constexpr (ST) {
         if (tid < D) {
             p_in_inv[key_inv & (D - 1)] = tid;
@@ -935,7 +939,7 @@ static hipError_t launch_rows_mfma_f32(const RowsJob& j, hipStream_t stream) {
 template <int D, bool SCATTER>
 static hipError_t launch_rows_f32(const RowsJob& j, hipStream_t stream) {
     if constexpr (!SCATTER) {  // (d = 64, 16 rows: 4.4 us summed in 64 bits, 4.2 in 32)
-        if (j.L <= (D == 64 ? kFewRows / 2 : kFewRows)) return launch_few_rows<F32, D, false, true>(j, stream);
+        if (j.L <= wide_rows(D)) return launch_few_rows<F32, D, false, true>(j, stream);
     }
     if (j.L <= kFewRows) return launch_few_rows<F32, D, SCATTER, false>(j, stream);
     return launch_rows_mfma_f32<D, SCATTER>(j, stream);
