@@ -51,3 +51,32 @@ def test_unscramble_merge(oracle, B, Hq, Hkv, d, Lq, permute):
     Or, lr = oracle.lse_merge(np.stack([Ou, Ol.double().numpy()]), np.stack([lu, l_loc.double().numpy()]))
     assert PT.rel_normwise(O, Or) <= PT.TOL_F32_REL
     assert PT.rel_normwise(lse, lr) <= PT.TOL_F32_REL
+
+
+@pytest.mark.parametrize("Lq", [2, 3, 4, 8, 15, 16, 17, 31, 32, 33, 64, 65, 129])
+@pytest.mark.parametrize("d", [64, 128])
+def test_unscramble_merge_at_the_edges_of_its_kernels(d, Lq):
+    """At most 16 rows, at most 32 of 64 columns, one and several row tiles: the values of the three calls bit for bit, with rows
+    that lack the first partial, the second and both throughout (what they hold is never read: poisoned)."""
+    B, Hq, Hkv = 3, 4, 2
+    keys = W.make_keys(Hkv, d, Lq, 64, 1, seed=17 + Lq, dtype=torch.float32)
+    g = torch.Generator().manual_seed(100 * Lq + d)
+    O_scr, O_loc = (torch.randn((B, Hq, Lq, d), generator=g) for _ in range(2))
+    l_scr, l_loc = (3.0 * torch.randn((B, Hq, Lq), generator=g) for _ in range(2))
+    perm = torch.randperm(Lq, generator=g).to(torch.int32)
+    row = torch.arange(Lq) + torch.arange(B * Hq).view(B, Hq, 1)  # another phase in every slab
+    no_loc = (row % 4 == 1) | (row % 4 == 2)
+    no_scr = ((row % 4 == 0) | (row % 4 == 2))[:, :, perm.long()]
+    l_loc[no_loc], O_loc[no_loc] = -np.inf, float("nan")
+    l_scr[no_scr], O_scr[no_scr] = -np.inf, float("nan")
+    dv = lambda t: t.to(DEV)  # noqa: E731
+    print(f"unscramble_merge {d} {Lq}", flush=True)
+    for p in (perm, None):
+        pd = None if p is None else dv(p)
+        O, lse = fb.fedrag_unscramble_merge(dv(O_scr), dv(l_scr), dv(keys.phi_v_inv), pd, dv(O_loc), dv(l_loc))
+        O1 = fb.fedrag_unscramble(dv(O_scr), dv(keys.phi_v_inv), pd)
+        l1 = fb.fedrag_unpermute_lse(dv(l_scr), pd)
+        O3, l3 = fb.fedrag_lse_merge(torch.stack([O1, dv(O_loc)]), torch.stack([l1, dv(l_loc)]), n_kv_heads=Hkv)
+        torch.cuda.synchronize()
+        assert torch.isfinite(O3).all()
+        assert torch.equal(O.view(torch.int32), O3.view(torch.int32)) and torch.equal(lse, l3)
