@@ -649,20 +649,24 @@ __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0,
 // reads its tile's rows from there 16 bytes at a time: the 4 floats are the A operands of 4 steps, contraction index
 // 8 j + 4 (lane / 32) + e for read j, element e.  The next step's rows are fetched into registers before the MFMAs
 // of the current one and go to the other LDS buffer after them: one barrier per step.
-template <int D, bool SCATTER, bool ST, bool MERGE>
-__global__ __launch_bounds__(kF32Threads) void rows_times_matrix_mfma_f32_kernel(ScrambleJob job0, ScrambleJob job1,
+// RT: 32-row tiles per step.  One at d = 128; two at d = 64, but one, with half the waves, for slabs of at most 32 rows, where the
+// second tile's waves had nothing to do and held their place: 64 x 32 slabs of 17, 24, 32 rows 11.5, 12.2, 12.7 us against 15.0, 15.3,
+// 15.6 (a plain-FMA kernel 11.9, 13.7, 15.8), structured 10.0, 10.8, 11.6 against 15.1, 15.5, 16.2.
+constexpr int mf_threads(int d, int rt) { return d / 32 * rt * kWave; }
+template <int D, bool SCATTER, bool ST, bool MERGE, int RT>
+__global__ __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f32_kernel(ScrambleJob job0, ScrambleJob job1,
                                                                                  const int32_t* __restrict__ perm,
                                                                                  int64_t perm_batch_stride, int H,
                                                                                  int G, int64_t L, int chunks,
                                                                                  int steps_per_wg, RowsMerge mg) {
     constexpr int SL = D / 32;         // 32-column slices of the output
-    constexpr int RT = 4 / SL;         // 32-row tiles per step
+    constexpr int kThreads = mf_threads(D, RT);
     constexpr int TR = 32 * RT;        // rows per step
     constexpr int LDP = D + 4;         // padded LDS row, floats: 16-byte reads of 8 rows cover all banks once
     constexpr int NJ = D / 8;          // 16-byte operand reads per row
     constexpr int CPR = D / 4;         // 16-byte chunks per row
-    constexpr int CPT = TR * CPR / kF32Threads;  // chunks per thread per step
-    static_assert(CPT * kF32Threads == TR * CPR, "a step's rows divide evenly over the threads");
+    constexpr int CPT = TR * CPR / kThreads;  // chunks per thread per step
+    static_assert(CPT * kThreads == TR * CPR, "a step's rows divide evenly over the threads");
     __shared__ __attribute__((aligned(16))) float xs[2][TR * LDP];
     __shared__ int32_t p_in_inv[ST ? D : 1];
     __shared__ float s_in[ST ? D : 1];
@@ -695,7 +699,7 @@ __global__ __launch_bounds__(kF32Threads) void rows_times_matrix_mfma_f32_kernel
     auto fetch = [&](int64_t row0, f32x4_t (&buf)[CPT]) {
 #pragma unroll
         for (int q = 0; q < CPT; ++q) {
-            const int e = tid + q * kF32Threads;
+            const int e = tid + q * kThreads;
             int64_t j = row0 + e / CPR;
             if (j >= L) j = L - 1;  // rows past the end: computed on a real row, never stored
             const int64_t src = (!SCATTER && pm) ? (int64_t)pm[j] : j;
@@ -723,7 +727,7 @@ __global__ __launch_bounds__(kF32Threads) void rows_times_matrix_mfma_f32_kernel
     float phi[NJ][4];
     if (ST) {  // column `col` of S1 P1 H P2 S2, generated from the key
         const int32_t* g1 = job.p_in + (int64_t)(h / G) * D;
-        for (int k = tid; k < D; k += kF32Threads) {
+        for (int k = tid; k < D; k += kThreads) {
             p_in_inv[g1[k] & (D - 1)] = k;
             s_in[k] = job.s_in[(int64_t)(h / G) * D + k];
         }
@@ -748,7 +752,7 @@ __global__ __launch_bounds__(kF32Threads) void rows_times_matrix_mfma_f32_kernel
     auto stash = [&](int slot, const f32x4_t (&buf)[CPT]) {
 #pragma unroll
         for (int q = 0; q < CPT; ++q) {
-            const int e = tid + q * kF32Threads;
+            const int e = tid + q * kThreads;
             *(f32x4_t*)(&xs[slot][(e / CPR) * LDP + (e % CPR) * 4]) = buf[q];
         }
     };
@@ -915,23 +919,25 @@ static int mf_steps_per_wg(int64_t steps, int64_t slabs, int D, bool structured,
     return best;
 }
 
-template <int D, bool SCATTER>
+template <int D, bool SCATTER, int RT>
 static hipError_t launch_rows_mfma_f32(const RowsJob& j, hipStream_t stream) {
-    constexpr int TR = 32 * (4 / (D / 32));  // rows per workgroup step
+    constexpr int TR = 32 * RT;  // rows per workgroup step
+    constexpr int kThreads = mf_threads(D, RT);
     const int64_t steps = (j.L + TR - 1) / TR;
     const int spw = mf_steps_per_wg(steps, j.BH * j.n_jobs, D, j.structured, j.merge.lse_in != nullptr);
     const int chunks = ceil_div_i64(steps, spw);
-    if (!grid_fits(j.BH * chunks, kF32Threads)) return hipErrorInvalidValue;
+    if (!grid_fits(j.BH * chunks, kThreads)) return hipErrorInvalidValue;
     dim3 grid((unsigned)(j.BH * chunks), (unsigned)j.n_jobs);
     const ScrambleJob a = device_job(j, 0), b = device_job(j, 1);
 #define FEDRAG_MF(MERGE_) \
-    (j.structured ? rows_times_matrix_mfma_f32_kernel<D, SCATTER, true, MERGE_> : rows_times_matrix_mfma_f32_kernel<D, SCATTER, false, MERGE_>)
+    (j.structured ? rows_times_matrix_mfma_f32_kernel<D, SCATTER, true, MERGE_, RT> \
+                  : rows_times_matrix_mfma_f32_kernel<D, SCATTER, false, MERGE_, RT>)
     auto kernel = FEDRAG_MF(false);
     if constexpr (SCATTER) {
         if (j.merge.lse_in) kernel = FEDRAG_MF(true);
     }
 #undef FEDRAG_MF
-    hipLaunchKernelGGL(kernel, grid, dim3(kF32Threads), 0, stream, a, b, j.perm, j.perm_batch_stride, j.H, j.G, j.L, chunks, spw,
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, a, b, j.perm, j.perm_batch_stride, j.H, j.G, j.L, chunks, spw,
                        j.merge);
     return hipGetLastError();
 }
@@ -942,7 +948,8 @@ static hipError_t launch_rows_f32(const RowsJob& j, hipStream_t stream) {
         if (j.L <= wide_rows(D)) return launch_few_rows<F32, D, false, true>(j, stream);
     }
     if (j.L <= kFewRows) return launch_few_rows<F32, D, SCATTER, false>(j, stream);
-    return launch_rows_mfma_f32<D, SCATTER>(j, stream);
+    if (D == 64 && j.L <= 32) return launch_rows_mfma_f32<D, SCATTER, 1>(j, stream);
+    return launch_rows_mfma_f32<D, SCATTER, 4 / (D / 32)>(j, stream);
 }
 
 hipError_t launch_rows_transform(const RowsJob& j, hipStream_t stream) {

@@ -68,3 +68,11 @@ def test_few_rows_in_64_bits(kernels):
     unit (two of them took 9.7 us for 64 x 32 slabs of 5 rows, four 6.9)."""
     for st in ("false", "true"):
         assert workgroups_per_unit(kernels[f"few_rows_kernel<F32, 64, false, {st}, true>"]) >= 4
+
+
+def test_rows_that_fill_half_a_step(kernels):
+    """fp32 rows of 64 columns, 32 at most: workgroups of one row tile's two waves, eight of them to a compute unit (they were
+    four of four waves, half of them idle)."""
+    for scatter in ("false", "true"):
+        k = kernels[f"rows_times_matrix_mfma_f32_kernel<64, {scatter}, false, false, 1>"]
+        assert k[".max_flat_workgroup_size"] == 128 and workgroups_per_unit(k) >= 8
