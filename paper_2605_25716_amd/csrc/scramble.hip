@@ -484,6 +484,7 @@ __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0,
     typedef typename T::elem elem;
     constexpr bool kF32 = sizeof(elem) == 4;
     static_assert(!SCATTER || kF32, "Dec is fp32");
+    constexpr bool kMerge = SCATTER && !ST;  // may be asked for the aggregation as well
     constexpr int LPK = D / 2;              // lanes per row of the matrix, two columns each
     constexpr int KG = kF32Threads / LPK;   // shares of the contraction
     constexpr int KPG = D / KG;             // steps of a share
@@ -559,7 +560,7 @@ __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0,
         Out o{0, 0.f, 0.f, 0.f};
         const int j = e < n_out ? e / D : L - 1;
         o.dst = SCATTER && pm ? (int64_t)pm[j] : j;
-        if (SCATTER && mg.lse_in) {
+        if (kMerge && mg.lse_in) {
             o.la = mg.lse_in[(int64_t)bh * L + j];
             o.lb = mg.lse_other[(int64_t)bh * L + o.dst];
             o.other = mg.O_other[((int64_t)bh * L + o.dst) * D + e % D];
@@ -626,7 +627,7 @@ __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0,
             v *= post0;
             pin_here(v);  // narrowed afterwards, as in the tiled kernel: in one operation a zero would lose its sign
         }
-        if (SCATTER && mg.lse_in) {
+        if (kMerge && mg.lse_in) {
             float l;
             v = merge_two(weights_of_two(o.la, o.lb, &l), v, o.other);
             if (e % D == 0) mg.lse_out[(int64_t)bh * L + o.dst] = l;
@@ -673,7 +674,7 @@ __global__ __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f32_
     // scatter form: where the rows of a step go and their weights, looked up and evaluated once a row
     __shared__ int32_t row_dst[SCATTER ? 2 : 1][SCATTER ? TR : 1];
     __shared__ RowWeights row_w[MERGE ? 2 : 1][MERGE ? TR : 1];
-    static_assert(SCATTER || !MERGE, "the aggregation is part of Dec");
+    static_assert(!MERGE || (SCATTER && !ST), "the aggregation is part of Dec by a matrix");
 
     const ScrambleJob job = blockIdx.y == 0 ? job0 : job1;
     const int tid = threadIdx.x;
@@ -929,14 +930,11 @@ static hipError_t launch_rows_mfma_f32(const RowsJob& j, hipStream_t stream) {
     if (!grid_fits(j.BH * chunks, kThreads)) return hipErrorInvalidValue;
     dim3 grid((unsigned)(j.BH * chunks), (unsigned)j.n_jobs);
     const ScrambleJob a = device_job(j, 0), b = device_job(j, 1);
-#define FEDRAG_MF(MERGE_) \
-    (j.structured ? rows_times_matrix_mfma_f32_kernel<D, SCATTER, true, MERGE_, RT> \
-                  : rows_times_matrix_mfma_f32_kernel<D, SCATTER, false, MERGE_, RT>)
-    auto kernel = FEDRAG_MF(false);
+    auto kernel = j.structured ? rows_times_matrix_mfma_f32_kernel<D, SCATTER, true, false, RT>
+                               : rows_times_matrix_mfma_f32_kernel<D, SCATTER, false, false, RT>;
     if constexpr (SCATTER) {
-        if (j.merge.lse_in) kernel = FEDRAG_MF(true);
+        if (j.merge.lse_in) kernel = rows_times_matrix_mfma_f32_kernel<D, true, false, true, RT>;
     }
-#undef FEDRAG_MF
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, a, b, j.perm, j.perm_batch_stride, j.H, j.G, j.L, chunks, spw,
                        j.merge);
     return hipGetLastError();
@@ -955,6 +953,7 @@ static hipError_t launch_rows_f32(const RowsJob& j, hipStream_t stream) {
 hipError_t launch_rows_transform(const RowsJob& j, hipStream_t stream) {
     if (j.L == 0 || j.BH == 0) return hipSuccess;
     if (j.scatter) {  // Dec: always fp32
+        if (j.structured && j.merge.lse_in) return hipErrorInvalidValue;  // (not aggregated by a key's factors)
         return j.D == 128 ? launch_rows_f32<128, true>(j, stream) : launch_rows_f32<64, true>(j, stream);
     }
     switch (j.dtype) {

@@ -76,3 +76,9 @@ def test_rows_that_fill_half_a_step(kernels):
     for scatter in ("false", "true"):
         k = kernels[f"rows_times_matrix_mfma_f32_kernel<64, {scatter}, false, false, 1>"]
         assert k[".max_flat_workgroup_size"] == 128 and workgroups_per_unit(k) >= 8
+
+
+def test_nothing_is_built_that_no_call_reaches(kernels):
+    """Dec with the aggregation takes a matrix, never a key's factors."""
+    merging = [n for n in kernels if re.match(r"rows_times_matrix_mfma_f32_kernel<\d+, \w+, \w+, true, ", n)]
+    assert len(merging) == 3 and not any(re.match(r"rows_times_matrix_mfma_f32_kernel<\d+, \w+, true, true, ", n) for n in merging)
