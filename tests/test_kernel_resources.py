@@ -82,3 +82,13 @@ def test_nothing_is_built_that_no_call_reaches(kernels):
     """Dec with the aggregation takes a matrix, never a key's factors."""
     merging = [n for n in kernels if re.match(r"rows_times_matrix_mfma_f32_kernel<\d+, \w+, \w+, true, ", n)]
     assert len(merging) == 3 and not any(re.match(r"rows_times_matrix_mfma_f32_kernel<\d+, \w+, true, true, ", n) for n in merging)
+
+
+def test_residency_that_the_row_products_are_cut_for(kernels):
+    """Workgroups a compute unit holds of the fp32 row products, as the choice of row steps per workgroup counts them."""
+    name = "rows_times_matrix_mfma_f32_kernel<%d, %s, %s, %s, %d>"
+    for scatter in ("false", "true"):
+        assert workgroups_per_unit(kernels[name % (128, scatter, "false", "false", 1)]) == 3
+        assert workgroups_per_unit(kernels[name % (128, scatter, "true", "false", 1)]) == 2
+        for st in ("false", "true"):
+            assert workgroups_per_unit(kernels[name % (64, scatter, st, "false", 2)]) == 4
