@@ -911,19 +911,26 @@ static hipError_t launch_scramble16(const RowsJob& j, hipStream_t stream) {
 }
 
 // Row steps per workgroup.  What a launch takes is the load of the compute unit that gets the most workgroups, in steps of a
-// unit whose matrix pipe is busy: `resident` workgroups of a unit (by registers: 120, 152, 184 a lane) take a step each in as
+// unit whose matrix pipe is busy: `resident` workgroups of a unit (by registers: up to 128, 168, 256 a lane) take a step each in as
 // many of those; one, two or three of them, which wait for their rows, take `part`, more with a second partial to read; every
 // workgroup costs `setup` (its slice of Phi, or the multiplying out of the key), and where they come in several rounds the last
-// one ends unevenly (`tail` of a workgroup).  Fitted to 16 splits of 172 launches; over those the choice is 0.5 % from the
-// best split on average, 14 % at most from 10 us on.  d = 128: Dec of 2048 rows x 32 heads 32 us (36 with 3072 workgroups for
-// every launch, as before; structured 33 and 40), Enc of 16 x 500 rows x 8 heads 51 (56; structured 51 and 68), of 16 x 8192
-// 851 (879; 903 and 993).
+// one ends unevenly (`tail` of a workgroup).  Fitted to up to 19 splits of each of 554 launches; over those the choice is 1 % from the
+// best split on average, 6 to 16 % at most by the form (of others, 12 x 75 rows x 64 heads with the aggregation 24 %).  The aggregating form, with 16 elements of the other partial in registers,
+// has one workgroup less to a unit: cut as the plain one it took 10 % longer than its best split on average at d = 128, 59 % at
+// most (4096 rows x 32 heads 60 us and 83, 8 x 500 60 and 80, 300 x 10 of 64 22.6 and 26.6).
+struct RowStepCost {
+    int resident;
+    float setup, tail, part[4];
+};
+static constexpr RowStepCost row_step_cost(int D, bool structured, bool merge) {
+    return D == 64 ? merge ? RowStepCost{3, 0.4f, 0.0f, {0.0f, 1.7f, 2.7f, 0.0f}} : RowStepCost{4, 0.4f, 0.4f, {0.0f, 1.5f, 2.5f, 3.1f}}
+           : merge ? RowStepCost{2, 0.05f, 0.1f, {0.0f, 1.8f, 0.0f, 0.0f}}
+           : structured ? RowStepCost{2, 0.4f, 0.0f, {0.0f, 1.2f, 0.0f, 0.0f}}
+                        : RowStepCost{3, 0.2f, 0.8f, {0.0f, 1.2f, 2.0f, 0.0f}};
+}
+int row_steps_resident(int D, bool structured, bool merge) { return row_step_cost(D, structured, merge).resident; }
 static int mf_steps_per_wg(int64_t steps, int64_t slabs, int D, bool structured, bool merge) {
-    const int resident = D == 64 ? 4 : structured ? 2 : 3;
-    const float setup = D == 64 ? 0.4f : structured ? 0.3f : 0.5f;
-    const float tail = structured && D != 64 ? 0.0f : 0.4f;
-    const float part[4] = {0.0f, merge ? 1.7f : resident == 2 ? 1.3f : 1.5f, merge ? 2.6f : D == 64 ? 2.5f : 2.3f,
-                           merge ? 3.3f : 3.1f};
+    const RowStepCost c = row_step_cost(D, structured, merge);
     const int64_t cus = attn_target_wgs();
     int best = 1;
     float least = 0.0f;
@@ -931,9 +938,9 @@ static int mf_steps_per_wg(int64_t steps, int64_t slabs, int D, bool structured,
         const int64_t chunks = (steps + most - 1) / most;
         const int64_t spw = (steps + chunks - 1) / chunks;
         const int64_t wgs = (slabs * chunks + cus - 1) / cus;  // of the fullest unit
-        const float load = (float)(wgs / resident * resident) + part[wgs % resident];
-        const float per = wgs <= resident ? (float)spw : (float)steps / (float)chunks;
-        const float cost = load * per + (float)wgs * setup + (wgs > resident ? tail * (float)spw : 0.0f);
+        const float load = (float)(wgs / c.resident * c.resident) + c.part[wgs % c.resident];
+        const float per = wgs <= c.resident ? (float)spw : (float)steps / (float)chunks;
+        const float cost = load * per + (float)wgs * c.setup + (wgs > c.resident ? c.tail * (float)spw : 0.0f);
         if (most == 1 || cost < least) {
             least = cost;
             best = (int)spw;
