@@ -480,14 +480,25 @@ def test_form_of_the_prefill_launches(launch_forms):
     num = {"bf16": fb.BF16, "f16": fb.F16}
     line = lambda B, Hq, d, dt, Lq, Ls: f"form {B} {Hq} 8 {d} {num[dt]} {Lq} {len(Ls)} " + " ".join(map(str, Ls))  # noqa: E731
     in_turn = LF.IN_TURN + [(1, 32, d, "bf16", 2048, Ls) for d in (64, 128) for Ls in (LF.IN_TURN_ANY_SIZE, LF.IN_TURN_FAR_BELOW)]
-    assert all(kind == 1 and n == 1 for kind, _, n in launch_forms([line(*c) for c in in_turn]))
+    assert all(kind == 1 and n == 1 for kind, _, n, _ in launch_forms([line(*c) for c in in_turn]))
     for d in (64, 128):  # with four waves and with eight
-        assert {four for _, four, _ in launch_forms([line(*c) for c in in_turn if c[2] == d])} == {0.0, 1.0}
+        assert {four for _, four, _, _ in launch_forms([line(*c) for c in in_turn if c[2] == d])} == {0.0, 1.0}
     two = launch_forms([line(*c) for c in LF.TWO_GROUPS])
-    assert all(kind == 2 for kind, _, _ in two) and min(n for _, _, n in two) == 1 and max(n for _, _, n in two) > 1
+    assert all(kind == 2 for kind, _, _, _ in two) and min(n for _, _, n, _ in two) == 1 and max(n for _, _, n, _ in two) > 1
     # a partial per shard: 8 units of 4132 rows are more than half a round and less than one
     one_each = launch_forms([line(1, 32, d, "bf16", 1033, [192, 63, 0, 300]) for d in (64, 128)])
-    assert all(kind == 0 and n == 3 for kind, _, n in one_each)
+    assert all(kind == 0 and n == 3 for kind, _, n, _ in one_each)
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="pinned for the 256 compute units that the plan falls back to")
+def test_which_prefill_outputs_are_stored_past_l2(launch_forms):
+    """Outputs from 8 MiB on; partials, which the fold reads at once, between that and the 32 MiB that all L2s hold."""
+    for Hq, d, Lq, Ls, want in ((32, 128, 500, [9000], True), (32, 128, 2048, [4096], True), (64, 128, 4096, [8192], True),
+                                (32, 64, 700, [300], False), (32, 128, 117, [4001, 3277], True), (16, 128, 1277, [307, 330], False),
+                                (16, 64, 1277, [307, 330], True), (16, 128, 2000, [600] * 4, False), (16, 128, 74, [900], False)):
+        (kind, _, n, past), = launch_forms([f"form 1 {Hq} 8 {d} {fb.BF16} {Lq} {len(Ls)} " + " ".join(map(str, Ls))])
+        mib = n * Hq * Lq * d * 4 / 2 ** 20
+        assert (past == 1) == want == (mib >= 8 and (n == 1 or mib <= 32)), (Hq, d, Lq, Ls, kind, n, mib)
 
 
 def test_two_group_runs_by_halving(launch_forms):
