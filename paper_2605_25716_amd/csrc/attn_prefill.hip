@@ -837,9 +837,9 @@ int64_t prefill_least_run(const KeyRuns& shards, int64_t from, int64_t most) {
     return hi * kPrePair;
 }
 
-bool prefill_stores_past_l2(const AttnProblem& p, int n_runs) {
-    const int64_t bytes = (int64_t)p.B * p.Hq * p.Lq * n_runs * (4 * p.D);
-    return bytes >= kPastL2Bytes && (n_runs == 1 || bytes <= kPastL2PartialBytes);
+bool prefill_stores_past_l2(const AttnProblem& p, const PrefillForm& f) {
+    const int64_t bytes = (int64_t)p.B * p.Hq * p.Lq * f.runs.n_runs * (4 * p.D);
+    return bytes >= kPastL2Bytes && (f.runs.n_runs == 1 || bytes < (p.D == 64 ? kPastL2Partials64 : kPastL2Partials128));
 }
 
 // What a launch does, decided from the sizes alone.
@@ -924,7 +924,7 @@ static hipError_t launch_prefill_nw(const AttnProblem& p, const PrefillForm& f, 
     // 8 x 4096 (16 MiB) 1524 and 1567.
     const int64_t units_per_xcd = (n_units + 7) / 8;
     const int together = CAUSAL && units_per_xcd * keys * (4 * D) <= kPreTogetherBytes ? 1 : 0;
-    const int past_l2 = prefill_stores_past_l2(p, runs.n_runs) ? 1 : 0;
+    const int past_l2 = prefill_stores_past_l2(p, f) ? 1 : 0;
     hipLaunchKernelGGL((prefill_attn_kernel<T, D, CAUSAL, QB, NW, WALK, KG>), dim3((unsigned)grid), dim3(NW * kWave), 0, stream,
                        (const elem*)p.Q, runs, p.K_params, p.V_params, f.Hq, FastDiv(p.Hkv), FastDiv(f.Hq / p.Hkv),
                        FastDiv(q_tiles), FastDiv(together ? units_per_xcd : per_unit), FastDiv(run_by_run ? tiles_of_unit : runs.n_runs),

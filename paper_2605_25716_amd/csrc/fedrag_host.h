@@ -100,11 +100,14 @@ struct FastDiv {
 // 32 of 64 (19 MiB) 17.2 and 15.2, 2048 x 32 of 128 (32 MiB) 61.2 and 58.8, 117 x 32 x (4001 + 3277) of 64 (17 MiB of partials)
 // 22.5 and 20.6.  Below, what reads them next finds them in L2: 117 x 32 x 300 of 64 (1 MiB) 9.0 and 9.3, 128 x 16 x 1024 (2 MiB)
 // 10.1 and 10.3; from 4 to 8 MiB even.
-// Partials are read again at once, by the fold: beyond what all L2s hold, from where they are on their way out before the launch
-// ends either way, being sent past them costs up to 6 % (1277 x 16 x (307 + 330) of 128, 40 MiB, 33.9 us and 36.0; 2000 x 16 x
-// 4 x 600, 63 MiB, 64.7 and 66.5; over 106 launches of more than 32 MiB 0.8 % on average, over 57 of less it gains 4 %).
+// Partials are read again at once, by the fold: towards and beyond the 32 MiB that all L2s hold, from where they are on their way
+// out before the launch ends either way, being sent past them costs up to 6 % (1277 x 16 x (307 + 330) of 128, 40 MiB, 33.9 us and
+// 36.0; 2048 x 16 x 600 on codes, 32 MiB, 33.7 and 35.5; 1500 x 16 x 1500 on codes, 23 MiB, 46.0 and 46.9; over 106 launches of
+// more than 32 MiB 0.8 % on average).  At d = 64, whose rows leave in half the time, they gain up to there (600 x 64 x 3 x 300, 28 MiB,
+// 31.9 and 29.8).
 constexpr int64_t kPastL2Bytes = 8 << 20;
-constexpr int64_t kPastL2PartialBytes = 32 << 20;
+constexpr int64_t kPastL2Partials128 = 20 << 20;
+constexpr int64_t kPastL2Partials64 = 32 << 20;
 
 // How a launch cuts the keys into runs, one workgroup per (unit of queries, run): what both attention kernels
 // receive by value.  Shard i contributes runs first[i] .. first[i+1]-1 of s[i].per keys each (the last one shorter);
@@ -183,7 +186,7 @@ struct PrefillForm {
     KeyRuns runs;   // n_runs < 1: refused; more than one: partials
 };
 PrefillForm prefill_form(const AttnProblem& p);
-bool prefill_stores_past_l2(const AttnProblem& p, int n_runs);  // see kPastL2Bytes
+bool prefill_stores_past_l2(const AttnProblem& p, const PrefillForm& f);  // see kPastL2Bytes
 int64_t prefill_least_run(const KeyRuns& shards, int64_t from, int64_t most);
 hipError_t launch_attn_f32(const AttnProblem& p, hipStream_t stream);      // fp32 storage, any L_q
 hipError_t launch_decode_attn(const AttnProblem& p, hipStream_t stream);   // 16-bit storage, G * L_q <= 16

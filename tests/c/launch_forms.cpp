@@ -1,6 +1,6 @@
 // The host's choice of a prefill launch's form, looked at without a device (no call here enqueues anything).  Commands on stdin,
 // one answer a line:
-//   form B Hq Hkv d dtype Lq n L...   ->  kind four n_runs past_l2   (kind: 0 plain, 1 shards in turn, 2 two key groups)
+//   form B Hq Hkv d dtype Lq n L... / codes B Hq Hkv d dtype Lq 1 L (4 bits)   ->  kind four n_runs past_l2   (kind: 0 plain, 1 shards in turn, 2 two key groups)
 //   runs from most n L...             ->  keys a run by halving, by trying every length in turn
 //   time B Hq Hkv d dtype Lq n L...   ->  microseconds a choice takes, the least of many
 #include <algorithm>
@@ -44,10 +44,11 @@ int main() {
     while (std::scanf("%15s", what) == 1) {
         AttnProblem p;
         std::vector<int64_t> L;
-        if (!std::strcmp(what, "form")) {
+        if (!std::strcmp(what, "form") || !std::strcmp(what, "codes")) {
             if (!read_problem(p, L)) return 2;
+            if (what[0] == 'c') p.quant_bits = 4;
             const PrefillForm f = prefill_form(p);
-            std::printf("%d %d %d %d\n", (int)f.kind, f.four ? 1 : 0, f.runs.n_runs, prefill_stores_past_l2(p, f.runs.n_runs) ? 1 : 0);
+            std::printf("%d %d %d %d\n", (int)f.kind, f.four ? 1 : 0, f.runs.n_runs, prefill_stores_past_l2(p, f) ? 1 : 0);
         } else if (!std::strcmp(what, "runs")) {
             long from, most;
             int n;
