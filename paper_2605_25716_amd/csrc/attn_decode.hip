@@ -155,7 +155,7 @@ constexpr int64_t kDecShortRun = 1024;
 #endif
 
 template <class T, int D, int QB, bool SHORT>
-__global__ __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OCC) void decode_attn_kernel(const typename T::elem* __restrict__ Q,
+FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OCC) void decode_attn_kernel(const typename T::elem* __restrict__ Q,
                                                                      const KeyRuns runs,
                                                                      const float* __restrict__ Kprm,
                                                                      const float* __restrict__ Vprm, int R,

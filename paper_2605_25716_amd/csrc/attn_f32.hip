@@ -31,7 +31,7 @@ __device__ __forceinline__ f32x4_t mfma_f32(float a, float b, f32x4_t c) {
 __device__ __forceinline__ float exp_diff(float a, float b) { return (a == -INFINITY) ? 0.0f : expf(a - b); }
 
 template <int D, int NQ, int W>
-__global__ __launch_bounds__(W * kWave, W == 1 && NQ == 1 ? (D == 64 ? 4 : 2) : 1) void attn_f32_kernel(const float* __restrict__ Q, const KeyRuns runs,
+FEDRAG_KERNEL __launch_bounds__(W * kWave, W == 1 && NQ == 1 ? (D == 64 ? 4 : 2) : 1) void attn_f32_kernel(const float* __restrict__ Q, const KeyRuns runs,
                                                                       FastDiv by_tiles, FastDiv by_lq, int Hkv, int R,
                                                                       int64_t Lq, int64_t causal_off, int causal,
                                                                       float scale, float* __restrict__ O,

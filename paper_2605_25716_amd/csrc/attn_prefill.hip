@@ -47,7 +47,7 @@ constexpr int kPrePD = FEDRAG_PRE_PD;         // MFMA operands are read from LDS
 // their outputs are aggregated through LDS.  For launches of few workgroups: the same rows and keys on as many waves with half
 // the query rows a workgroup, so half the runs, and half the fp32 partials to write and fold, or none.
 template <class T, int D, bool CAUSAL, int QB, int NW, bool WALK, int KG>
-__global__ __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefill_attn_kernel(const typename T::elem* __restrict__ Q,
+FEDRAG_KERNEL __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void prefill_attn_kernel(const typename T::elem* __restrict__ Q,
                                                                       const KeyRuns runs,
                                                                       const float* __restrict__ Kprm,
                                                                       const float* __restrict__ Vprm, int Hq,
@@ -949,15 +949,15 @@ static hipError_t launch_prefill_t(const AttnProblem& p, const PrefillForm& f, h
     if constexpr (CAUSAL) {
         e = launch_prefill_nw<T, D, true, 0, 4, false>(p, f, Odst, Ldst, stream);
     } else {
-        if (f.kind == PrefillForm::kPlain)
-            e = f.four ? launch_prefill_nw<T, D, false, QB, 4, false>(p, f, Odst, Ldst, stream)
-                       : launch_prefill_nw<T, D, false, QB, 8, false>(p, f, Odst, Ldst, stream);
         if constexpr (QB == 0) {
             if (f.kind == PrefillForm::kWalk)
                 e = f.four ? launch_prefill_nw<T, D, false, 0, 4, true>(p, f, Odst, Ldst, stream)
                            : launch_prefill_nw<T, D, false, 0, 8, true>(p, f, Odst, Ldst, stream);
             if (f.kind == PrefillForm::kTwoGroups) e = launch_prefill_nw<T, D, false, 0, 8, false, 2>(p, f, Odst, Ldst, stream);
         }
+        if (f.kind == PrefillForm::kPlain)
+            e = f.four ? launch_prefill_nw<T, D, false, QB, 4, false>(p, f, Odst, Ldst, stream)
+                       : launch_prefill_nw<T, D, false, QB, 8, false>(p, f, Odst, Ldst, stream);
     }
     if (e != hipSuccess || n == 1) return e;
     return launch_lse_merge(Odst, Ldst, n, rows, D, p.O, p.lse, stream);

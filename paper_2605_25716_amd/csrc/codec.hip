@@ -54,7 +54,7 @@ template <> struct CodecIO<BF16> : CodecIO16<BF16> {};
 template <> struct CodecIO<F16> : CodecIO16<F16> {};
 
 template <class T, int D, int BITS>
-__global__ __launch_bounds__(kCodecThreads) void quantize_rows_kernel(const char* __restrict__ X, int64_t n_rows,
+FEDRAG_KERNEL __launch_bounds__(kCodecThreads) void quantize_rows_kernel(const char* __restrict__ X, int64_t n_rows,
                                                                       uint8_t* __restrict__ codes,
                                                                       float* __restrict__ params) {
     typedef CodecIO<T> IO;
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kCodecThreads) void quantize_rows_kernel(const char
 }
 
 template <class T, int D, int BITS>
-__global__ __launch_bounds__(kCodecThreads) void dequantize_rows_kernel(const uint8_t* __restrict__ codes,
+FEDRAG_KERNEL __launch_bounds__(kCodecThreads) void dequantize_rows_kernel(const uint8_t* __restrict__ codes,
                                                                         const float* __restrict__ params,
                                                                         int64_t n_rows, char* __restrict__ X) {
     typedef CodecIO<T> IO;

@@ -3,6 +3,12 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+// A kernel starts on a page.  What a short launch waits for first is its own instructions, which many megabytes of keys between two
+// launches have pushed out of every cache, and where it lies in the code object decides how many such waits there are: each is
+// 0.6 us, and with kernels packed closely a change in the size of any other kernel moved one or two of them into or out of a layer
+// of seven launches (117 query rows over two contexts, 32 layers: 1.95 to 2.01 ms between builds of the same kernels).
+#define FEDRAG_KERNEL __global__ __attribute__((aligned(4096)))
+
 namespace fedrag {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));

@@ -27,7 +27,7 @@ __device__ __forceinline__ float row_max(float x) {
 // 5.2 us, 6.5 with two); beyond that memory is the bound and the waves that fewer registers leave room for are worth more than
 // loads in flight: two (16384 rows of 128 over 8: 13.1 us, 15.2 with eight, 14.2 one after the other).
 template <int D, int NB>
-__global__ __launch_bounds__(256) void lse_merge_kernel(const float* __restrict__ O_parts,
+FEDRAG_KERNEL __launch_bounds__(256) void lse_merge_kernel(const float* __restrict__ O_parts,
                                                         const float* __restrict__ lses, int S, int64_t rows,
                                                         float* __restrict__ O, float* __restrict__ lse,
                                                         const int32_t* __restrict__ q_lens, int64_t Lq,
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const float* __restrict_
 // at once.  65536 rows of 128 over 2: 16.6 us (18.7 one after the other, 18.2 in the form above, whose batch reads the last
 // partial again); 32 rows: 2.3 (2.5, 2.9).
 template <int D, int S>
-__global__ __launch_bounds__(256) void lse_merge_few_kernel(const float* __restrict__ O_parts,
+FEDRAG_KERNEL __launch_bounds__(256) void lse_merge_few_kernel(const float* __restrict__ O_parts,
                                                             const float* __restrict__ lses, int64_t rows,
                                                             float* __restrict__ O, float* __restrict__ lse,
                                                             const int32_t* __restrict__ q_lens, int64_t Lq,
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(256) void lse_merge_few_kernel(const float* __restr
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void fill_empty_kernel(float* __restrict__ O, float* __restrict__ lse,
+FEDRAG_KERNEL __launch_bounds__(256) void fill_empty_kernel(float* __restrict__ O, float* __restrict__ lse,
                                                          int64_t rows) {
     constexpr int TPR = D / 4;
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -180,7 +180,7 @@ hipError_t launch_fill_empty(float* O, float* lse, int64_t rows, int D, hipStrea
 // token-permutation part of Dec, Section 4.2, for the per-row scalar that travels with the output).
 // One thread per value over the whole tensor, whatever its rows: decoding steps have rows of one value by the thousand (262144
 // of them take 2.3 us; 59 with a workgroup of its own for every row).  Below 2^31 values the row is found without a division.
-__global__ __launch_bounds__(256) void scatter_rows_f32_kernel(const float* __restrict__ in,
+FEDRAG_KERNEL __launch_bounds__(256) void scatter_rows_f32_kernel(const float* __restrict__ in,
                                                                const int32_t* __restrict__ perm, int64_t L,
                                                                FastDiv by_l, int small, int64_t total,
                                                                float* __restrict__ out) {

@@ -73,7 +73,7 @@ __device__ __forceinline__ float structured_entry(float s_in_k, int p_in_inv_k, 
 // QB = 0: rows leave in the storage type.  QB = 8 or 4: each narrowed row goes through the transport codec instead
 // (same arithmetic as quantize_rows_kernel on the stored row) and leaves as codes plus (scale, lo).
 template <class T, int D, bool ST, int QB>
-__global__ __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_kernel(ScrambleJob job0, ScrambleJob job1,
+FEDRAG_KERNEL __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_kernel(ScrambleJob job0, ScrambleJob job1,
                                                                        const int32_t* __restrict__ perm,
                                                                        int64_t perm_batch_stride,  // 0 or L
                                                                        int B, int H, int G, int64_t L, int members,
@@ -477,7 +477,7 @@ __device__ __forceinline__ float merge_two(const RowWeights& w, float mine, floa
 }
 
 template <class T, int D, bool SCATTER, bool ST, bool WIDE>
-__global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0, ScrambleJob job1,
+FEDRAG_KERNEL __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0, ScrambleJob job1,
                                                                const int32_t* __restrict__ perm,
                                                                int64_t perm_batch_stride, int H, int G, int L,
                                                                RowsMerge mg) {
@@ -655,7 +655,7 @@ __global__ __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0,
 // 15.6 (a plain-FMA kernel 11.9, 13.7, 15.8), structured 10.0, 10.8, 11.6 against 15.1, 15.5, 16.2.
 constexpr int mf_threads(int d, int rt) { return d / 32 * rt * kWave; }
 template <int D, bool SCATTER, bool ST, bool MERGE, int RT>
-__global__ __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f32_kernel(ScrambleJob job0, ScrambleJob job1,
+FEDRAG_KERNEL __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f32_kernel(ScrambleJob job0, ScrambleJob job1,
                                                                                  const int32_t* __restrict__ perm,
                                                                                  int64_t perm_batch_stride, int H,
                                                                                  int G, int64_t L, int chunks,
@@ -836,7 +836,7 @@ __global__ __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f32_
     }
 }
 
-__global__ void invert_perm_kernel(const int32_t* __restrict__ perm, int64_t L, int32_t* __restrict__ inv) {
+FEDRAG_KERNEL void invert_perm_kernel(const int32_t* __restrict__ perm, int64_t L, int32_t* __restrict__ inv) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j < L) inv[perm[j]] = (int32_t)j;
 }
@@ -844,12 +844,12 @@ __global__ void invert_perm_kernel(const int32_t* __restrict__ perm, int64_t L, 
 // Debug aid: is every row of perm [n_perm, L] a permutation of 0..L-1?  marks [n_perm, L] counts the hits of every
 // index; flag receives bit 0 for an index outside [0, L) and bit 1 for an index that occurs more than once (every
 // index in range and none twice means all L occur).
-__global__ void validate_perm_clear_kernel(int32_t* __restrict__ marks, int64_t total, int32_t* __restrict__ flag) {
+FEDRAG_KERNEL void validate_perm_clear_kernel(int32_t* __restrict__ marks, int64_t total, int32_t* __restrict__ flag) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e < total) marks[e] = 0;
     if (e == 0) flag[0] = 0;
 }
-__global__ void validate_perm_kernel(const int32_t* __restrict__ perm, int64_t L, int64_t total,
+FEDRAG_KERNEL void validate_perm_kernel(const int32_t* __restrict__ perm, int64_t L, int64_t total,
                                      int32_t* __restrict__ marks, int32_t* __restrict__ flag) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= total) return;

@@ -38,6 +38,18 @@ def _kernels(elf):
             p += (size + 3) // 4 * 4
 
 
+def _functions(elf):
+    """(address, name) of the dynamic symbols that are functions"""
+    table, (entry, count) = struct.unpack_from("<Q", elf, 0x28)[0], struct.unpack_from("<HH", elf, 0x3A)
+    heads = [struct.unpack_from("<IIQQQQIIQQ", elf, table + k * entry) for k in range(count)]
+    for head in heads:
+        for at in range(head[4], head[4] + head[5], 24) if head[1] == 11 else ():
+            name, info, _, _, value, _ = struct.unpack_from("<IBBHQQ", elf, at)
+            if info & 15 == 2:
+                start = heads[head[6]][4] + name
+                yield value, elf[start:elf.index(b"\0", start)].decode()
+
+
 @pytest.fixture(scope="module")
 def kernels():
     """name<template arguments> -> metadata"""
@@ -62,6 +74,13 @@ def test_scratch_memory(kernels):
     for name, k in kernels.items():
         spills = re.match(r"prefill_attn_kernel<\w+, 64, false, 8, 4, false, 1>", name)
         assert k[".private_segment_fixed_size"] <= (16 if spills else 0), name
+
+
+def test_kernels_start_on_pages():
+    """So that the time of one does not hang on the sizes of the others in its code object."""
+    fbuild.build_library(force=False)
+    at = [f for elf in _code_objects(fbuild.LIB_PATH) for f in _functions(elf)]
+    assert len(at) > 50 and not [f for f in at if f[0] % 4096]
 
 
 def test_few_rows_in_64_bits(kernels):
