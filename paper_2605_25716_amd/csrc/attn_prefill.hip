@@ -773,8 +773,8 @@ static bool prefill_walks(const AttnProblem& p, const KeyRuns& runs, int64_t hea
 }
 
 // Few workgroups and runs at will: whether two groups of four waves share 128 query rows and halve their keys (KG = 2), with the
-// runs re-cut for that, twice as long, by cost as above.  Half the runs are half the partials to write and fold, or none (500 x
-// 32 x 1000 keys of 128 31.6 us against 27.8, 2 x 958 x 16 x 933 35.6 and 25.2, 487 x 64 x 2255 of 64 39.1 and 28.5), and shards
+// runs re-cut for that, twice as long, by cost as above.  Half the runs are half the partials to write and fold (500 x
+// 32 x 1000 keys of 128 31.6 us against 27.8), or none (2 x 958 x 16 x 933 35.6 and 25.2, 487 x 64 x 2255 of 64 39.1 and 28.5), and shards
 // whose runs fitted no round fit one (123 x 32 x (6278 + 971 + 4650) 49.6 and 40.6).  Each group stages tiles of its own, which
 // at d = 128, where LDS is the busier side, costs a tenth (1024 x 16 x 8192 76.7 and 78.2: stays as it was), and a launch that
 // does not half fill the chip gains nothing (11 x 16 x 385 of 64 8.5 and 9.1).

@@ -642,7 +642,7 @@ FEDRAG_KERNEL __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob jo
 // What bounds it below some hundred rows is the chain of trips to memory, so the rows, their destinations and what the
 // aggregation needs of them are asked for ahead of the matrix, or of the product of the step before, and a row's weights are
 // evaluated once, by one thread, not by each of its columns' (Dec of 117 rows of 32 heads of 128 7.4 -> 5.8 us, with the aggregation
-// 12.8 -> 6.9; 4096 rows 60 -> 48 and 132 -> 82; 40 rows, with plain FMAs and a column of the matrix a thread, 13.7, now 5.6).
+// 12.8 -> 6.7; 4096 rows 60 -> 48 and 132 -> 60; 40 rows, with plain FMAs and a column of the matrix a thread, 13.7, now 5.6).
 // v_mfma_f32_32x32x2_f32: A 32 x 2 (lane: row lane % 32, k = lane / 32), B 2 x 32 (lane: column lane % 32, k = lane / 32),
 // C 32 x 32 (lane: column lane % 32, register r: row 8 (r / 4) + 4 (lane / 32) + r % 4).  Wave w of the 4 owns the
 // 32-column slice w % (D / 32) of the output and keeps that slice of Phi in registers as B operands (D / 2 of them);
