@@ -469,8 +469,12 @@ FEDRAG_KERNEL __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void pre
                         const float low = WALK && kind == kFirst ? m_run - (float)drop : m_run;
                         m_new = fmaxf(low, mx * scale_log2);
                         alph[p] = exp2_diff(m_run, m_new);
-                        // what rounding took off `low` is far more than a rounding of m_run: 2^drop, and the rest exactly
-                        if (WALK && kind == kFirst && m_new == low) alph[p] = ldexpf(exp2_diff(m_run, low + (float)drop), drop);
+                        // m_run - drop is low and what rounding took off it, far more than a rounding of a small m_run and, of a
+                        // very large one, all of drop: the two are exact (Knuth's sum of two numbers), their factors one by one
+                        if (WALK && kind == kFirst && m_new == low && drop != 0) {
+                            const float d = (float)drop, back = low - m_run, err = (m_run - (low - back)) - (d + back);
+                            alph[p] = ldexpf(fast_exp2(err), drop);
+                        }
                     }
                     if (j >= FIRST) {
                         constexpr int NS = NM - FIRST;

@@ -479,7 +479,7 @@ def test_form_of_the_prefill_launches(launch_forms):
     import test_gpu_launch_forms as LF
     num = {"bf16": fb.BF16, "f16": fb.F16}
     line = lambda B, Hq, d, dt, Lq, Ls: f"form {B} {Hq} 8 {d} {num[dt]} {Lq} {len(Ls)} " + " ".join(map(str, Ls))  # noqa: E731
-    in_turn = LF.IN_TURN + [(1, 32, d, "bf16", 2048, Ls) for d in (64, 128) for Ls in (LF.IN_TURN_ANY_SIZE, LF.IN_TURN_FAR_BELOW)]
+    in_turn = LF.IN_TURN + [(1, 32, d, "bf16", 2048, Ls) for d in (64, 128) for Ls in (LF.IN_TURN_ANY_SIZE, LF.IN_TURN_FAR_BELOW, [70] * 3)]
     assert all(kind == 1 and n == 1 for kind, _, n, _ in launch_forms([line(*c) for c in in_turn]))
     for d in (64, 128):  # with four waves and with eight
         assert {four for _, four, _, _ in launch_forms([line(*c) for c in in_turn if c[2] == d])} == {0.0, 1.0}

@@ -128,6 +128,27 @@ def test_a_shard_far_below_leaves_the_log_sum_exp_exact(d):
     assert float((lse - lm).abs().max()) <= 3 * 2.0 ** -20
 
 
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("height", [64.0, 1024.0, 8192.0, 16384.0, 2.0 ** 20])
+def test_a_shard_far_below_leaves_the_weights_of_the_others(d, height):
+    """Two shards of the same keys and, between them, one far below: each of the two has half the weight, also where scores are so
+    large (height squared, 10^5 to 10^11 after scaling) that fp32 cannot hold a step of the maximum down and back."""
+    L = 70
+    Q = torch.zeros((1, 32, 2048, d), dtype=torch.bfloat16, device=DEV)
+    Q[..., 0] = height
+    K = torch.zeros((1, 8, L, d), dtype=torch.bfloat16, device=DEV)
+    K[..., 0] = height
+    Ks = [K, K * (1 - 2.0 ** -7), K] if height > 100.0 else [K, K * 0.5, K]
+    Vs = [rnd(1, 8, L, d, "bf16", W.TID_V + 16 * (i + 1)).to(DEV) for i in range(3)]
+    print(f"between two equal shards {d} {height}", flush=True)
+    O, lse = fb.fedrag_partial_attn_shards(Q, Ks, Vs)
+    parts = [fb.fedrag_partial_attn(Q, k, v) for k, v in zip(Ks, Vs)]
+    torch.cuda.synchronize()
+    # 3 tiles: outputs of at most 6, a rescale and a sum of 2^-24 each, 2^-22 an exponential
+    assert float((O - 0.5 * (parts[0][0] + parts[2][0])).abs().max()) <= 6.0 * 2.0 ** -19
+    assert float((lse - parts[0][1] - np.log(2.0)).abs().max()) <= 2.0 ** -19 + 2.0 ** -22 * float(parts[0][1].abs().max())
+
+
 def test_every_shard_boundary_keeps_its_keys():
     """One key tile of one shard holds all the weight of a query row: a tile lost or read twice at a shard's end moves that
     row's log-sum-exp by ln 2 or more."""
