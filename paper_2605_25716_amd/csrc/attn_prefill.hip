@@ -782,19 +782,19 @@ static bool prefill_walks(const AttnProblem& p, const KeyRuns& runs, int64_t hea
 // whose runs fitted no round fit one (123 x 32 x (6278 + 971 + 4650) 49.6 and 40.6).  Each group stages tiles of its own, which
 // at d = 128, where LDS is the busier side, costs a tenth (1024 x 16 x 8192 76.7 and 78.2: stays as it was), and a launch that
 // does not half fill the chip gains nothing (11 x 16 x 385 of 64 8.5 and 9.1).
-// Where the other form has more workgroups than one round, its cost is that of its longest run and so up to an eighth too high when
-// runs are unequal: two groups have to be that much cheaper (2 x 86 x 32 x (449 + 6900 + 2725 + 550) of 64, at 0.90 by cost, 34.3
-// us and 41.6; of 40 such launches the 33 below 0.88 gain 14 %, the 7 above lost 4 %).
+// Where the other form has more workgroups than one round they even out, and its cost is that of its mean run, not of its longest
+// (2 x 86 x 32 x (449 + 6900 + 2725 + 550) of 64, 0.90 by the longest, 1.04 by the mean: 34.3 us and 41.6 with two groups).
 // Not where a workgroup takes all keys by rule (a mask, counts per sequence): up to 1.5 workgroups a compute unit two groups are
 // 7 to 15 % faster (2048 x 16 heads with a mask 51.2 us and 46.5), but from two on 10 % slower, and a sequence's outputs would
 // then depend on how many others are in its batch.
 static bool prefill_two_groups(KeyRuns* runs, int64_t wgs8, int64_t wgs4, int64_t rows, int D) {
     const int64_t cus = attn_target_wgs();
-    int64_t total = 0, tiles1 = 0;
+    int64_t total = 0, tiles = 0, tiles1 = 0;  // tiles1: of the longest run
     int shards = 0;
     for (int i = 0; i < runs->n_shards; ++i) {
         const int64_t L = runs->s[i].L, run = L < runs->s[i].per ? L : runs->s[i].per;
         total += L;
+        tiles += (L + kPreK - 1) / kPreK;
         shards += L > 0 ? 1 : 0;
         tiles1 = (run + kPreK - 1) / kPreK > tiles1 ? (run + kPreK - 1) / kPreK : tiles1;
     }
@@ -812,11 +812,11 @@ static bool prefill_two_groups(KeyRuns* runs, int64_t wgs8, int64_t wgs4, int64_
         steps = (run + kPrePair - 1) / kPrePair > steps ? (run + kPrePair - 1) / kPrePair : steps;
     }
     const float tile_us = prefill_tile_us(D);
-    const float ends = wgs8 * runs->n_runs <= cus ? 0.0f : 4.0f;
-    const float one = prefill_cost(wgs8 * runs->n_runs, wgs4 * runs->n_runs, (float)tiles1, ends, D, false).least() * tile_us +
-                      prefill_fold_us(runs->n_runs, rows, D);
+    const bool one_round = wgs8 * runs->n_runs <= cus;
+    const float one = prefill_cost(wgs8 * runs->n_runs, wgs4 * runs->n_runs, one_round ? (float)tiles1 : (float)tiles / (float)runs->n_runs,
+                                   one_round ? 0.0f : 4.0f, D, false).least() * tile_us + prefill_fold_us(runs->n_runs, rows, D);
     const float both = ((float)steps * (D == 64 ? 1.0f : 1.1f) + 0.33f) * tile_us + prefill_fold_us(two.n_runs, rows, D);
-    if (both >= one * (ends > 0.0f ? 0.88f : 1.0f)) return false;
+    if (both >= one) return false;
     *runs = two;
     return true;
 }

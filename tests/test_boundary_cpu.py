@@ -486,7 +486,7 @@ def test_form_of_the_prefill_launches(launch_forms):
     two = launch_forms([line(*c) for c in LF.TWO_GROUPS])
     assert all(kind == 2 for kind, _, _, _ in two) and min(n for _, _, n, _ in two) == 1 and max(n for _, _, n, _ in two) > 1
     # the other form's unequal runs, in more than one round, are cheaper than its longest one says
-    uneven = [(2, 32, 64, 86, [449, 6900, 2725, 550]), (2, 16, 64, 189, [330, 2508, 2941, 4137]), (2, 64, 64, 73, [4555, 2182, 2982])]
+    uneven = [(2, 32, 64, 86, [449, 6900, 2725, 550]), (2, 16, 64, 189, [330, 2508, 2941, 4137])]
     assert all(kind == 0 for kind, _, _, _ in launch_forms([line(B, Hq, d, "bf16", Lq, Ls) for B, Hq, d, Lq, Ls in uneven]))
     # a partial per shard: 8 units of 4132 rows are more than half a round and less than one
     one_each = launch_forms([line(1, 32, d, "bf16", 1033, [192, 63, 0, 300]) for d in (64, 128)])
