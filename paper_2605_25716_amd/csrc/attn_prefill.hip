@@ -843,7 +843,8 @@ int64_t prefill_least_run(const KeyRuns& shards, int64_t from, int64_t most) {
 
 bool prefill_stores_past_l2(const AttnProblem& p, const PrefillForm& f) {
     const int64_t bytes = (int64_t)p.B * p.Hq * p.Lq * f.runs.n_runs * (4 * p.D);
-    return bytes >= kPastL2Bytes && (f.runs.n_runs == 1 || bytes < (p.D == 64 ? kPastL2Partials64 : kPastL2Partials128));
+    const int64_t most = p.D == 64 ? kPastL2Partials64 : f.runs.n_runs == 2 ? kPastL2TwoPartials : kPastL2Partials;
+    return bytes >= kPastL2Bytes && (f.runs.n_runs == 1 || bytes < most);
 }
 
 // What a launch does, decided from the sizes alone.

@@ -100,14 +100,16 @@ struct FastDiv {
 // 32 of 64 (19 MiB) 17.2 and 15.2, 2048 x 32 of 128 (32 MiB) 61.2 and 58.8, 117 x 32 x (4001 + 3277) of 64 (17 MiB of partials)
 // 22.5 and 20.6.  Below, what reads them next finds them in L2: 117 x 32 x 300 of 64 (1 MiB) 9.0 and 9.3, 128 x 16 x 1024 (2 MiB)
 // 10.1 and 10.3; from 4 to 8 MiB even.
-// Partials are read again at once, by the fold: towards and beyond the 32 MiB that all L2s hold, from where they are on their way
-// out before the launch ends either way, being sent past them costs up to 6 % (1277 x 16 x (307 + 330) of 128, 40 MiB, 33.9 us and
-// 36.0; 2048 x 16 x 600 on codes, 32 MiB, 33.7 and 35.5; 1500 x 16 x 1500 on codes, 23 MiB, 46.0 and 46.9; over 106 launches of
-// more than 32 MiB 0.8 % on average).  At d = 64, whose rows leave in half the time, they gain up to there (600 x 64 x 3 x 300, 28 MiB,
-// 31.9 and 29.8).
+// Partials are read again at once, by the fold: beyond the 32 MiB that all L2s hold, from where they are on their way out before the
+// launch ends either way, being sent past them costs up to 6 % (1277 x 16 x (307 + 330) of 128, 40 MiB, 33.9 us and 36.0; 2048 x 16 x
+// 600 on codes, 32 MiB, 33.7 and 35.5; over 106 launches 0.8 % on average); below it gains up to 10 % (266 x 32 x (638 + 638), 25 MiB,
+// 29.5 and 27.5).  Two partials of rows of 128 are so many rows that it is over sooner (800 x 32 x (500 + 400), 25 MiB, 34.0 and
+// 34.9; 1500 x 16 x 1500 on codes, 23 MiB, 46.0 and 46.9), rows of 64 go on a little longer (1300 x 32 x 4 x 200, 41 MiB, 35.2 and 33.9;
+// from 42 MiB on even, then 1 % slower).
 constexpr int64_t kPastL2Bytes = 8 << 20;
-constexpr int64_t kPastL2Partials128 = 20 << 20;
-constexpr int64_t kPastL2Partials64 = 32 << 20;
+constexpr int64_t kPastL2Partials = 32 << 20;
+constexpr int64_t kPastL2TwoPartials = 20 << 20;
+constexpr int64_t kPastL2Partials64 = 42 << 20;
 
 // How a launch cuts the keys into runs, one workgroup per (unit of queries, run): what both attention kernels
 // receive by value.  Shard i contributes runs first[i] .. first[i+1]-1 of s[i].per keys each (the last one shorter);

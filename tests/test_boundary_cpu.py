@@ -495,15 +495,16 @@ def test_form_of_the_prefill_launches(launch_forms):
 
 @pytest.mark.skipif(torch.cuda.is_available(), reason="pinned for the 256 compute units that the plan falls back to")
 def test_which_prefill_outputs_are_stored_past_l2(launch_forms):
-    """Outputs from 8 MiB on; partials, which the fold reads at once, between that and 20 of the 32 MiB that
-    all L2s hold, at 64 columns all of them."""
-    for Hq, d, Lq, Ls, want in ((32, 128, 500, [9000], False), (32, 128, 2048, [4096], True), (64, 128, 4096, [8192], True),
+    """Outputs from 8 MiB on; partials, which the fold reads at once, between that and the 32 MiB that all L2s hold, two of 128
+    columns up to 20 MiB, of 64 columns up to 42."""
+    for Hq, d, Lq, Ls, want in ((32, 128, 500, [9000], True), (32, 128, 2048, [4096], True), (64, 128, 4096, [8192], True),
                                 (32, 64, 700, [300], False), (16, 128, 153, [2000, 443, 580], True), (32, 128, 800, [500, 400], False),
                                 (16, 128, 1277, [307, 330], False), (16, 64, 1277, [307, 330], True), (64, 64, 600, [300] * 3, True),
-                                (16, 64, 2100, [600] * 4, False), (16, 128, 2000, [600] * 4, False), (16, 128, 74, [900], False)):
+                                (32, 128, 266, [638, 638], True), (32, 64, 1300, [200] * 4, True), (16, 64, 2900, [600] * 4, False), (16, 128, 2000, [600] * 4, False),
+                                (16, 128, 74, [900], False)):
         (kind, _, n, past), = launch_forms([f"form 1 {Hq} 8 {d} {fb.BF16} {Lq} {len(Ls)} " + " ".join(map(str, Ls))])
         mib = n * Hq * Lq * d * 4 / 2 ** 20
-        assert (past == 1) == want == (mib >= 8 and (n == 1 or mib < (32 if d == 64 else 20))), (Hq, d, Lq, Ls, kind, n, mib)
+        assert (past == 1) == want == (mib >= 8 and (n == 1 or mib < (42 if d == 64 else 20 if n == 2 else 32))), (Hq, d, Lq, Ls, kind, n, mib)
     codes = launch_forms([f"codes 1 16 8 128 {fb.BF16} {Lq} 1 600" for Lq in (1300, 2048, 2200)])
     assert [(n, past) for _, _, n, past in codes] == [(2, 0), (2, 0), (1, 1)]
 
