@@ -1,15 +1,21 @@
 // Decode-shaped partial attention (Section 4.1, per-node local computation) for 16-bit storage:
 // at most 16 query rows per (sequence, KV head) unit, i.e. the GQA group packed into one MFMA column tile.
-// HBM-bound: every K'/V' byte of the shard is read exactly once, nothing is reused, so the kernel is built
-// around keeping many full-row loads in flight per wave and no LDS traffic on the streaming path.
+// HBM-bound: every K'/V' byte of the shard is read exactly once and nothing is reused, so the kernel is built around keeping
+// whole rows in flight.
 //
 // One workgroup = one unit x one split of the shard's keys; its four waves take 32-key tiles round-robin.
 // Lane l of a wave: lr = l % 16, lq = l / 16.
 //   S^T tile (32 keys x 16 queries) = K'(32 x d) . Q'^T(d x 16): two 16-key MFMA tiles; this lane ends up with
 //   query lr and keys {16 mt + 4 lq + r}.  Those eight keys are also this lane's contraction slice of
-//   O^T(d x 16) += V'^T(d x 32) . P^T(32 x 16), whose d-rows are assigned d = DCH * i + j (tile j, row i) so
-//   that lane (i = lr) needs exactly the DCH contiguous elements [DCH*lr, DCH*lr + DCH) of each of its eight
-//   keys: full-row coalesced loads and an in-register 8 x DCH transpose.
+//   O^T(d x 16) += V'^T(d x 32) . P^T(32 x 16).
+// 16-bit values reach their operands through LDS, in tiles that belong to one wave and need no barrier.  A K' operand straight
+// from memory takes 64 bytes of each of 16 rows a load, 16 of them from each of 16 consecutive lanes, and a compute unit takes
+// 256 KB of such loads in twice the time of whole rows (9.7 us and 5.0 on 32 workgroups), which was what a launch that does not
+// fill the chip waited for: one sequence of 8192 keys x 8 heads of 128 16.8 us and 13.4 now (call with its aggregation), 512 keys
+// 9.9 and 7.8, of 64 10.9 and 9.3, 5.9 and 4.8; launches at the rate of memory gain 0 to 4 %.  What is in flight holds no registers.
+// On transport codes, whose rebuilding is the bound, operands are loaded straight into registers, and the d-rows of O^T are
+// assigned d = DCH * i + j (tile j, row i) so that lane (i = lr) needs exactly the DCH contiguous elements [DCH*lr, DCH*lr + DCH)
+// of each of its eight keys: an in-register 8 x DCH transpose.
 // P is split into two storage-type terms (hi + lo) so that the probabilities enter the second product with
 // ~16 significant bits; the matrix pipe is idle most of the time anyway.
 // Splits are normalised partials (O, lse) in the caller's workspace and are folded by the Section 4.1
@@ -139,23 +145,27 @@ __device__ __forceinline__ typename T::vec8 dequant8(uint32_t w, const RowScale&
 #ifndef FEDRAG_DEC_NBUF_Q4
 #define FEDRAG_DEC_NBUF_Q4 1
 #endif
-#ifndef FEDRAG_DEC_NBUF
-#define FEDRAG_DEC_NBUF 2   // register tile sets per wave
-#endif
-// SHORT: no run is longer than this, so a wave has at most 8 tiles.  A ring of two then spends its time in the code
-// around its steady state (every copy of a step fetched cold): with one tile set 768-key runs take 20.6 us instead of
-// 21.1 (4 sequences of 6000 keys) and a decoded token's layer 30.4 instead of 31.2; runs of 32768 keys are 1.8 % slower
-// with one.
-constexpr int64_t kDecShortRun = 1024;
-#ifndef FEDRAG_DEC_OCC
-#define FEDRAG_DEC_OCC 1    // workgroups per CU the register budget is sized for
-#endif
 #ifndef FEDRAG_DEC_AUX
 #define FEDRAG_DEC_AUX 2    // cache-policy bits of the streaming loads: non-temporal (K'/V' are read once)
 #endif
 
-template <class T, int D, int QB, bool SHORT>
-FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC_OCC) void decode_attn_kernel(const typename T::elem* __restrict__ Q,
+// 16-bit values: NS tiles of K' and V' per wave in LDS.  Two, 128 KiB of LDS at d = 128 and half of that at d = 64, so one or two
+// workgroups to a compute unit.  One, and twice the workgroups, where there are more of them than compute units and their runs are so
+// short that start and end are what they spend their time on, which a neighbour then hides: 64 sequences x 8 heads of 128 x 100
+// keys 7.3 us against 10.4 (8.5 before), 400 keys 20.0 and 22.4, 1000 44.6 and 45.4; beyond that two tiles are 0 to 1 % ahead.  At
+// d = 64 100 keys 5.4 and 5.9, 256 8.1 either way, 400 11.5 and 11.3.  Also where a wave has one tile: 128 keys x 8 heads 3.7 and 4.3.
+// (2048 units of at most 64 keys of 64 are 1 to 5 % behind the registers used before, with more of them to a compute unit.)
+constexpr int64_t dec_single_tile_run(int d) { return d == 128 ? 1024 : 256; }  // keys of the longest run up to which it is one
+
+// 16-bit values of 128 columns in whole rounds of long runs stay in registers: at the rate of memory the LDS form is 1 to 4 % behind
+// where the units lie powers of two apart (64 sequences x 8 heads x 32768 keys 1189 us and 1217, x 8192 301 and 310, 16 x 8192 75.4
+// and 78.4), for whatever reason - not the order in which a tile's rows or a run's tiles are asked for - and within 1.5 % of it
+// elsewhere (64 x 3000 122 and 120, 32 x 4000 80.5 and 82).  At d = 64 both take the same time.  Where the last round is partly empty
+// what counts is again what a compute unit takes by itself (33 x 4096 131 us and 116).
+constexpr int64_t kDecLongRun = 2048;
+
+template <class T, int D, int QB, int NS>
+FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : NS * D > 0 && NS * D <= 128 ? 2 : 1) void decode_attn_kernel(const typename T::elem* __restrict__ Q,
                                                                      const KeyRuns runs,
                                                                      const float* __restrict__ Kprm,
                                                                      const float* __restrict__ Vprm, int R,
@@ -167,18 +177,26 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC
     typedef typename T::elem elem;
     typedef typename T::vec8 vec8;
     typedef DecTile<T, D, QB> Tile;
-    static_assert(QB == 0 || D == 128, "the quantised path is laid out for d = 128");
+    static_assert(QB == 0 || (D == 128 && NS == 0), "the quantised path is laid out for d = 128, in registers");
     constexpr int KS = D / 32;   // contraction steps of the first product
     constexpr int DCH = D / 16;  // elements per lane per key of V' (= number of 16-row tiles of O^T)
     constexpr int NW = DCH / 2;  // 32-bit words of that
     constexpr int ROWB = QB ? D * QB / 8 : D * 2;  // bytes per row of K' / V' as stored (values, or codes)
     constexpr int TILEB = kDecTile * ROWB;
-    constexpr int NBUF = SHORT ? 1 : QB == 0 ? FEDRAG_DEC_NBUF : (QB == 8 ? FEDRAG_DEC_NBUF_Q8 : FEDRAG_DEC_NBUF_Q4);
+    constexpr bool LDS = NS > 0;  // tiles go to LDS; otherwise to registers
+    constexpr int NBUF = QB == 0 ? 2 : QB == 8 ? FEDRAG_DEC_NBUF_Q8 : FEDRAG_DEC_NBUF_Q4;
     constexpr int AUX = FEDRAG_DEC_AUX;
 
+    // LDS: NS slots per wave for the tiles, an array each, so that the compiler sees that the fill of one does not alias the
+    // reads of another.  At the end the waves' outputs take their place: 8 rows in the first slot of K', 8 in that of V'.
+    constexpr int OROW = (D + 4) * 4;  // bytes
+    constexpr int SLOT = LDS ? TILEB : 8 * OROW;
+    static_assert(SLOT >= 8 * OROW, "eight rows of outputs fit a slot");
+    __shared__ __attribute__((aligned(16))) char ks0[kDecWaves][SLOT], vs0[kDecWaves][SLOT];
+    __shared__ __attribute__((aligned(16))) char ks1[kDecWaves][NS == 2 ? SLOT : 16], vs1[kDecWaves][NS == 2 ? SLOT : 16];
     __shared__ float sm_m[kDecWaves][16];
     __shared__ float sm_l[kDecWaves][16];
-    __shared__ __attribute__((aligned(16))) float sm_o[kDecWaves][16][D + 4];
+    auto out_row = [&](int w, int n) { return (float*)((n < 8 ? ks0[w] : vs0[w]) + n % 8 * OROW); };
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // wave-uniform: keeps the tile loop scalar
@@ -211,8 +229,7 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC
 
     // Q'^T operands: column lr (query), contraction slice 32 ks + 8 lq; padding queries lie past the end of the
     // buffer and arrive as zeros
-    // Which 8 channels lane group lq contracts in step ks is free as long as Q' and K' agree.  16-bit K': 32 ks + 8 lq
-    // (a step's 32 channels are contiguous: 64 bytes per row and load).  Codes: every lane fetches 16 bytes of its
+    // Which 8 channels lane group lq contracts in step ks is free as long as Q' and K' agree.  16-bit K': 32 ks + 8 lq.  Codes: every lane fetches 16 bytes of its
     // row at once - 16 codes = steps 2h, 2h+1 (8 bits) or 32 codes = all four steps (4 bits) - so that a load still
     // covers 64 contiguous bytes per row; with 8- or 4-byte loads the kernel was bound by the number of rows a load
     // instruction touches, not by bytes.
@@ -230,15 +247,13 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC
     for (int i = 0; i < DCH; ++i) acc_o[i] = zero_vec<f32x4_t>();
     float m_run = -INFINITY, l_run = 0.f;
 
-    // per-lane byte offsets inside a 32-key tile (the tile base is wave-uniform)
+    const int64_t split_bytes = (k_end - k_begin) * ROWB;  // < 2^31, guaranteed by the split planner
+    // Registers: per-lane byte offsets inside a 32-key tile, and buffer resources based at the split's first key: the address is
+    // (scalar resource base) + (scalar tile offset) + (per-lane 32-bit offset), one VGPR per lane in total.
     constexpr int EB = QB ? QB : 16;  // bits per stored element
     const uint32_t koff = (uint32_t)(lr * ROWB + lq * EB);          // 8 elements per lane and contraction step
     const uint32_t kqoff = (uint32_t)(lr * ROWB + lq * 16);         // codes: 16 bytes per lane
     const uint32_t voff = (uint32_t)(lq * 4 * ROWB + lr * DCH * EB / 8);
-
-    // Streaming loads go through buffer resources based at the split's first key: the address is
-    // (scalar resource base) + (scalar tile offset) + (per-lane 32-bit offset), one VGPR per lane in total.
-    const int64_t split_bytes = (k_end - k_begin) * ROWB;  // < 2^31, guaranteed by the split planner
     const __amdgpu_buffer_rsrc_t rk =
         __builtin_amdgcn_make_buffer_rsrc((void*)(Kb + k_begin * ROWB), 0, (int)split_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rv =
@@ -249,6 +264,27 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC
         (void*)(QB ? Kprm + (unit * L + k_begin) * 2 : nullptr), 0, QB ? (int)(n_split_keys * 8) : 0, 0x00020000);
     const __amdgpu_buffer_rsrc_t rvp = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(QB ? Vprm + (unit * L + k_begin) * 2 : nullptr), 0, QB ? (int)(n_split_keys * 8) : 0, 0x00020000);
+    // LDS: a tile arrives in whole rows, 1 KiB of them a load.  Slot p of row r holds chunk p ^ swz(r), so that the 16 rows
+    // of a K' operand, and the 16 of a transposing read of V', fall on different banks.  The resource starts at the tile and ends
+    // with the run: rows past the end (with per-sequence key counts they are padding that may hold anything), and tiles behind it,
+    // are not read and arrive as zeros.
+    constexpr int CH = D / 8;               // 16-byte chunks per row
+    constexpr int RPW = kWave / CH;         // rows per load
+    constexpr int KL = kDecTile / RPW;      // loads per tile of K' or V'
+    auto swz_k = [&](int r) { return D == 128 ? r % 16 : r / 2 % 8; };
+    auto swz_v = [&](int r) { return D == 128 ? r % 4 * 4 + r / 4 % 2 * 2 : r / 2 % 4 * 2; };
+    auto fill = [&](int tile, char* slot, bool is_k) {
+        const int left = (int)split_bytes - tile * TILEB;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)((is_k ? Kb : Vb) + k_begin * ROWB + (int64_t)tile * TILEB), 0, left > 0 ? left : 0, 0x00020000);
+#pragma unroll
+        for (int j = 0; j < KL; ++j) {
+            const int r = lane / CH + j * RPW;
+            const int off = r * ROWB + (((lane % CH) ^ (is_k ? swz_k(r) : swz_v(r))) << 4);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (void __attribute__((address_space(3)))*)(slot + j * (kWave * 16)), 16, off,
+                                                     0, 0, AUX);
+        }
+    };
     auto load_k = [&](int tile, Tile& t) {  // tile index inside the split; all 32 keys exist
         const int soff = tile * TILEB;
 #pragma unroll
@@ -324,28 +360,17 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC
         }
     };
 
-    // d = 64: without fences the steps of both tile sets are scheduled into one another, the refills go to other registers than
-    // the loop expects them in, and it waits at its top for every load in flight to copy them: 8 shards of 25479 keys, 32
-    // units, 279 us; 252 with a fence behind each step, 251 with one around every refill as well, which 512 units of 9000
-    // keys, two workgroups to a compute unit, need (227, 185 and 175 us).
-    auto fence = [&]() {
-        if (D == 64) __builtin_amdgcn_sched_barrier(0);
+    // all loads done but the N asked for last (LDS-direct loads are waited for by hand)
+    auto wait_loads = [&](auto n) {
+        constexpr int N = decltype(n)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
+        __builtin_amdgcn_sched_barrier(0);
     };
-    auto refill_k = [&](int tile, Tile& t) {
-        fence();
-        load_k(tile, t);
-        fence();
-    };
-    auto refill_v = [&](int tile, Tile& t) {
-        fence();
-        load_v(tile, t);
-        fence();
-    };
-
-    // One 32-key tile.  `reload` refills the tile's registers for key `next0` as soon as each half has been
-    // consumed (K' after the first product, V' after the in-register transpose), so the loads fly behind the
-    // softmax, the second product and the other tile set's step.
-    auto step = [&](Tile& t, int64_t key0, bool masked, bool reload, int next_tile) {
+    // One 32-key tile.  `reload` refills its slots or registers with tile `next_tile` as soon as each half has been consumed (K'
+    // after the first product, V' after the second, or after the in-register transpose), so that the loads fly behind the
+    // softmax, the second product and the other set's step.  younger: loads asked for after this tile's V' when it is used.
+    auto step = [&](Tile& t, int64_t key0, bool masked, bool reload, int next_tile, char* kslot, char* vslot, auto younger) {
         f32x4_t s[2];
         auto score = [&](auto plain) {
             RowScale krow[2];
@@ -359,7 +384,9 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
                     vec8 kop;
-                    if constexpr (QB == 0) kop = t.k[mt][ks];
+                    if constexpr (LDS)
+                        kop = *(const vec8*)(kslot + (mt * 16 + lr) * ROWB + (((4 * ks + lq) ^ swz_k(lr)) << 4));
+                    else if constexpr (QB == 0) kop = t.k[mt][ks];
                     else if constexpr (QB == 8) {
                         const u32x4_t w = t.kc[mt][ks / 2];
                         u32x2_t c;  // (vector elements are copied out one by one before use)
@@ -381,28 +408,42 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC
         } else {
             score(std::true_type{});
         }
-        if (reload) refill_k(next_tile, t);
+        if (reload) {
+            if constexpr (LDS) {
+                __builtin_amdgcn_sched_barrier(0);
+                fill(next_tile, kslot, true);
+                __builtin_amdgcn_sched_barrier(0);
+            } else {
+                load_k(next_tile, t);
+            }
+        }
         float p[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[e] = s[e / 4][e % 4] * scale_log2;
+        if (masked) {  // the ragged end of the run
+            const int left = (int)(k_end - key0) - lq * 4;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if ((e / 4) * 16 + e % 4 >= left) p[e] = -INFINITY;
+        }
         float mx = -INFINITY;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float v = s[e / 4][e % 4] * scale_log2;
-            if (masked) {
-                const int64_t key = key0 + (e / 4) * 16 + lq * 4 + (e % 4);
-                if (key >= k_end) v = -INFINITY;
-            }
-            p[e] = v;
-            mx = fmaxf(mx, v);
-        }
+        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, p[e]);
         mx = xor32_max(xor16_max(mx));
         const float m_new = fmaxf(m_run, mx);  // finite: the tile's first key exists
         const float alpha = exp2_diff(m_run, m_new);
+        if (masked) {  // a key alone has the probability 1
+#pragma unroll
+            for (int e = 0; e < 8; ++e) p[e] -= m_new;
+        } else {  // one rounding of the exponent's argument: scores of some hundreds leave 2^-15 in a product rounded first
+#pragma unroll
+            for (int e = 0; e < 8; ++e) p[e] = __builtin_fmaf(s[e / 4][e % 4], scale_log2, -m_new);
+        }
         float psum = 0.f;
         vec8 ph, pl;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            // one rounding of the exponent's argument: scores of some hundreds leave 2^-15 in a product rounded first
-            const float pe = fast_exp2(masked ? p[e] - m_new : __builtin_fmaf(s[e / 4][e % 4], scale_log2, -m_new));
+            const float pe = fast_exp2(p[e]);
             psum += pe;
             ph[e] = T::from_float(pe);
             pl[e] = T::from_float(pe - T::to_float(ph[e]));
@@ -411,7 +452,18 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC
         m_run = m_new;
         // second product in two halves of the d-rows to keep the transposed operands short-lived
         u32x4_t vt[DCH];
-        if constexpr (QB == 0) {
+        if constexpr (LDS) {
+            wait_loads(younger);
+#pragma unroll
+            for (int i = 0; i < DCH; ++i)
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    const int r = mt * 16 + lq * 4 + lr / 4;
+                    const u32x2_t w = lds_read_tr16(vslot + r * ROWB + (((2 * i + lr % 4 / 2) ^ swz_v(r)) << 4) + lr % 2 * 8);
+                    vt[i][2 * mt] = w[0];
+                    vt[i][2 * mt + 1] = w[1];
+                }
+        } else if constexpr (QB == 0) {
             transpose_keys_b16<DCH>(t.v, vt);
         } else {
             uint32_t v16[8][DCH / 2];  // the eight keys' rows in the storage type, as the unquantised path loads them
@@ -431,7 +483,9 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC
             }
             transpose_keys_b16<DCH>(v16, vt);
         }
-        if (reload) refill_v(next_tile, t);
+        if constexpr (!LDS) {
+            if (reload) load_v(next_tile, t);
+        }
 #pragma unroll
         for (int i = 0; i < DCH; ++i) {
             acc_o[i] *= alpha;
@@ -439,12 +493,73 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC
             acc_o[i] = T::mfma16(vop, ph, acc_o[i]);
             acc_o[i] = T::mfma16(vop, pl, acc_o[i]);
         }
+        if constexpr (LDS) {
+            if (reload) {
+                __builtin_amdgcn_sched_barrier(0);
+                fill(next_tile, vslot, false);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
     };
 
-    // Wave w owns tiles w, w+4, ... of the split.  NBUF register tile sets form a ring: a set is refilled with
+    // Wave w owns tiles w, w+4, ... of the split.  NS sets of slots (codes: NBUF register tile sets) form a ring: a set is refilled with
     // the tile NBUF steps ahead as soon as it has been consumed.  In the steady-state loop every refill is
     // unconditional, so the in-order load counter can be waited on precisely (oldest tile only).
-    {
+    if constexpr (LDS) {
+        const int64_t n_keys = k_end - k_begin;
+        const int n_tiles = (int)((n_keys + kDecTile - 1) / kDecTile);  // the ragged one among them
+        const int n_mine = n_tiles > wave ? (n_tiles - wave + kDecWaves - 1) / kDecWaves : 0;
+        const int ragged = n_keys % kDecTile ? n_tiles - 1 : -1;  // rows past its end arrive as zeros and are masked
+        char *k0 = ks0[wave], *v0 = vs0[wave], *k1 = ks1[wave], *v1 = vs1[wave];
+        // i-th tile of this wave out of a set of slots, with `others` sets asked for after it
+        auto turn = [&](int i, auto set, auto others, auto reload) {
+            constexpr int N = 2 * KL * decltype(others)::value;
+            constexpr bool more = decltype(reload)::value;
+            const int tile = wave + i * kDecWaves;
+            Tile none;
+            wait_loads(std::integral_constant<int, N + KL>{});
+            step(none, k_begin + (int64_t)tile * kDecTile, tile == ragged, more, tile + NS * kDecWaves,
+                 decltype(set)::value ? k1 : k0, decltype(set)::value ? v1 : v0, std::integral_constant<int, N + (more ? KL : 0)>{});
+        };
+        std::integral_constant<int, 0> c0;
+        std::integral_constant<int, 1> c1;
+        std::true_type refill;
+        std::false_type done;
+        if (n_mine > 0) {
+            fill(wave, k0, true);
+            fill(wave, v0, false);
+            if constexpr (NS == 2) {
+                fill(wave + kDecWaves, k1, true);  // (nothing if there is none)
+                fill(wave + kDecWaves, v1, false);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {  // waited for here: ahead of a loop the compiler waits for all in flight
+                u32x4_t w = __builtin_bit_cast(u32x4_t, qop[ks]);
+                pin_here(w);
+                qop[ks] = __builtin_bit_cast(vec8, w);
+            }
+            if constexpr (NS == 1) {
+                for (int i = 0; i + 1 < n_mine; ++i) turn(i, c0, c0, refill);
+                turn(n_mine - 1, c0, c0, done);
+            } else {
+                int i = 0;
+                for (; i + 4 <= n_mine; i += 2) {
+                    turn(i, c0, c1, refill);
+                    turn(i + 1, c1, c1, refill);
+                }
+                if (n_mine - i == 3) {
+                    turn(i, c0, c1, refill);
+                    turn(i + 1, c1, c1, done);
+                    turn(i + 2, c0, c0, done);
+                } else {
+                    turn(i, c0, c1, done);
+                    if (n_mine - i == 2) turn(i + 1, c1, c0, done);
+                }
+            }
+            wait_loads(c0);  // (a second tile that is not there)
+        }
+    } else {
         const int64_t n_keys = k_end - k_begin;
         const int n_full_all = (int)(n_keys / kDecTile);  // full tiles in the split
         const int n_mine = (n_full_all > wave) ? (n_full_all - wave + kDecWaves - 1) / kDecWaves : 0;
@@ -458,27 +573,26 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC
         for (; i + 2 * NBUF <= n_mine; i += NBUF) {
 #pragma unroll
             for (int j = 0; j < NBUF; ++j) {
-                step(t[j], tile_key(i + j), false, true, tile_of(i + j + NBUF));
-                fence();
+                step(t[j], tile_key(i + j), false, true, tile_of(i + j + NBUF), nullptr, nullptr, 0);
             }
         }
         // fewer than 2*NBUF tiles left: refills become conditional, then the ring drains
 #pragma unroll
         for (int j = 0; j < NBUF; ++j) {
             if (i + j < n_mine) {
-                if (i + j + NBUF < n_mine) step(t[j], tile_key(i + j), false, true, tile_of(i + j + NBUF));
-                else step(t[j], tile_key(i + j), false, false, 0);
+                if (i + j + NBUF < n_mine) step(t[j], tile_key(i + j), false, true, tile_of(i + j + NBUF), nullptr, nullptr, 0);
+                else step(t[j], tile_key(i + j), false, false, 0, nullptr, nullptr, 0);
             }
         }
 #pragma unroll
         for (int j = 0; j < NBUF; ++j)
-            if (i + NBUF + j < n_mine) step(t[j], tile_key(i + NBUF + j), false, false, 0);
+            if (i + NBUF + j < n_mine) step(t[j], tile_key(i + NBUF + j), false, false, 0, nullptr, nullptr, 0);
         // ragged tail of the split (fewer than 32 keys): the wave whose turn it is takes it
         const int rem = (int)(n_keys % kDecTile);
         if (rem > 0 && (n_full_all % kDecWaves) == wave) {
             const int64_t key0 = k_begin + (int64_t)n_full_all * kDecTile;
             load_clamped(key0, t[0]);
-            step(t[0], key0, true, false, 0);
+            step(t[0], key0, true, false, 0, nullptr, nullptr, 0);
         }
     }
 
@@ -490,15 +604,20 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC
         sm_l[wave][lr] = l_tot;
     }
     if (lr < R) {
+        if constexpr (LDS) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+            for (int i = 0; i < DCH; ++i) *(f32x4_t*)(out_row(wave, lr) + 16 * i + 4 * lq) = acc_o[i];
+        } else {
 #pragma unroll
-            for (int i = 0; i < DCH; i += 4) {
-                f32x4_t o;
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = acc_o[i + e][r];
-                *(f32x4_t*)&sm_o[wave][lr][DCH * (4 * lq + r) + i] = o;
-            }
+                for (int i = 0; i < DCH; i += 4) {
+                    f32x4_t o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = acc_o[i + e][r];
+                    *(f32x4_t*)(out_row(wave, lr) + DCH * (4 * lq + r) + i) = o;
+                }
+        }
     }
     __syncthreads();
     float* Oout = O + ((int64_t)run * total_rows + unit * R) * D;
@@ -522,7 +641,7 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : FEDRAG_DEC
 #pragma unroll
         for (int w = 0; w < kDecWaves; ++w) {
             const float a = exp2_diff(sm_m[w][n], M);
-            const f32x4_t o = *(const f32x4_t*)&sm_o[w][n][d];
+            const f32x4_t o = *(const f32x4_t*)(out_row(w, n) + d);
 #pragma unroll
             for (int e = 0; e < 4; ++e) num[e] = __builtin_fmaf(a, o[e], num[e]);
             den = __builtin_fmaf(a, sm_l[w][n], den);
@@ -556,10 +675,22 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
         Ldst = Odst + (size_t)splits * rows * D;
     }
     if (!grid_fits(units * splits, kDecThreads)) return hipErrorInvalidValue;
-    bool is_short = QB == 0;  // on codes the rings above serve every run
-    for (int i = 0; i < runs.n_shards; ++i)
-        if (runs.s[i].L > kDecShortRun && runs.s[i].per > kDecShortRun) is_short = false;
-    const auto kernel = is_short ? decode_attn_kernel<T, D, QB, QB == 0> : decode_attn_kernel<T, D, QB, false>;
+    int64_t longest = 0;
+    for (int i = 0; i < runs.n_shards; ++i) {
+        const int64_t keys = runs.s[i].L < runs.s[i].per ? runs.s[i].L : runs.s[i].per;
+        longest = keys > longest ? keys : longest;
+    }
+    int tiles = 0;  // per wave in LDS
+    if (QB == 0) {
+        const int64_t wgs = units * splits, cus = attn_target_wgs(), rounds = (wgs + cus - 1) / cus;
+        tiles = longest <= kDecStride || (wgs > cus && longest <= dec_single_tile_run(D)) ? 1 : 2;
+        if (D == 128 && longest >= kDecLongRun && wgs * 10 >= rounds * cus * 9) tiles = 0;
+    }
+    auto kernel = decode_attn_kernel<T, D, QB, QB == 0 && D == 64 ? 2 : 0>;
+    if constexpr (QB == 0) {
+        if (tiles == 1) kernel = decode_attn_kernel<T, D, 0, 1>;
+        if (tiles == 2) kernel = decode_attn_kernel<T, D, 0, 2>;
+    }
     hipLaunchKernelGGL(kernel, dim3((unsigned)(units * splits)), dim3(kDecThreads), 0, stream, (const elem*)p.Q, runs,
                        p.K_params, p.V_params, R, scale_log2, Odst, Ldst, rows, p.kv_lens, p.q_lens, (int)p.Lq, p.Hkv);
     hipError_t e = hipGetLastError();

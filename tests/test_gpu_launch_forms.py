@@ -304,6 +304,27 @@ def test_decode_key_runs(oracle, Ls, d):
     PT.check_attn(O, lse, Or, lr, Q.dtype, str(Ls))
 
 
+# 8 B workgroups: one tile of LDS per wave (runs of up to 128 keys; up to 1024, of 64 columns 256, with more workgroups than compute
+# units), two, and registers (whole rounds of runs from 2048 keys on); a wave's one to nine tiles, whole and ragged
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("B,L,d", [(1, 1, 128), (2, 128, 64), (1, 129, 128), (3, 353, 64), (3, 511, 128), (33, 200, 128), (33, 1000, 128),
+                                   (40, 256, 64), (40, 257, 64), (33, 1100, 128), (32, 2113, 128), (33, 2050, 128), (32, 2100, 64)])
+def test_decode_tile_forms(oracle, B, L, d, dt):
+    Q, K, V = rnd(B, 16, 1, d, dt, W.TID_Q), rnd(B, 8, L, d, dt, W.TID_K), rnd(B, 8, L, d, dt, W.TID_V)
+    lens = torch.tensor([(L * (b + 1) // B) if b else 0 for b in range(B)], dtype=torch.int32)
+    for kv_lens in (None, lens):
+        if kv_lens is None:
+            Or, lr = oracle.partial_attn(Q, K, V)
+            O, lse = fb.fedrag_partial_attn(Q.to(DEV), K.to(DEV), V.to(DEV))
+        else:
+            Or, lr = oracle.partial_attn_varlen(Q, K, V, kv_lens)
+            for b in range(B):  # what lies past a sequence's keys is not looked at
+                K[b, :, int(lens[b]):], V[b, :, int(lens[b]):] = float("nan"), float("inf")
+            O, lse = fb.fedrag_partial_attn_varlen(Q.to(DEV), K.to(DEV), V.to(DEV), kv_lens.to(DEV))
+        torch.cuda.synchronize()
+        PT.check_attn(O, lse, Or, lr, Q.dtype, f"{B} {L} {d}")
+
+
 @pytest.mark.parametrize("dt", ["bf16", "f16"])
 def test_decode_on_4bit_codes_of_every_scale(dt):
     """Rows of every magnitude, tiny, ordinary and (bf16) beyond 2^100, rebuild to what fedrag_dequantize_rows gives: with one
