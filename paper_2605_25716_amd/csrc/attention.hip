@@ -127,14 +127,50 @@ void attn_cut_runs(KeyRuns& r, int64_t per, int64_t quantum) {
     r.by_runs = FastDiv(at > 0 ? at : 1);
 }
 
+// One round of workgroups where the streaming kernel would have one and a bit.  The plan above rounds the runs of a unit up, as the
+// workspace is sized, and a few workgroups over a round take as long as the round did; their number is rounded down here.  What
+// is left idle costs less, as a compute unit takes more of the memory's rate when others rest (8192 keys x 8 heads of 128: 3
+// sequences, 264 workgroups and 240, 27.7 us and 22.2; 9, 288 and 216, 67.6 and 52.8; 17, 272 and 136, 122 and 103; 31, 496 and
+// 248, 164 and 160; of 64, 9 and 17 sequences 35.0 and 28.6, 64.1 and 53.1; on 8-bit codes 3 and 9 28.5 and 21.4, 58.1 and 45.1,
+// 20 103 either way; 5 x (4001 + 3277 + 300) keys of 128 39.7 and 31.4).  Never more runs than the plan
+// has.  Where the shards alone are more than a round the rounds even out (20 x (4001 + 3277 + 300): 135 us, 139 with a run a shard),
+// and a shard much longer than the others would be a run too long (9 of them: 55.6 us, 57.0).
+static void decode_one_round(KeyRuns& r, int64_t units, int64_t cus) {
+    auto longest = [](const KeyRuns& k) {
+        int64_t most = 0;
+        for (int i = 0; i < k.n_shards; ++i) {
+            const int64_t run = k.s[i].L < k.s[i].per ? k.s[i].L : k.s[i].per;
+            most = run > most ? run : most;
+        }
+        return most;
+    };
+    int64_t shards = 0, per = kDecStride;
+    for (int i = 0; i < r.n_shards; ++i) {
+        shards += r.s[i].L > 0 ? 1 : 0;
+        if (r.s[i].L > 0 && r.s[i].per > per) per = r.s[i].per;
+    }
+    if (units < 1 || units * r.n_runs <= cus || units * shards > cus) return;
+    static_assert(kPrePair == kDecStride, "runs of whole steps");
+    const int64_t least = prefill_least_run(r, per, cus / units);
+    KeyRuns one = r;
+    attn_cut_runs(one, least, kDecStride);
+    const int64_t rounds = (units * r.n_runs + cus - 1) / cus;
+    if (least <= (int64_t)1 << 22 && longest(one) <= rounds * longest(r)) r = one;  // (a run is addressed in 32 bits)
+}
+
 KeyRuns attn_runs_of(const AttnProblem& p) {
+    const bool streaming = use_decode_kernel(p.Hq, p.Hkv, p.Lq) && p.dtype != FEDRAG_F32 && !p.causal && (p.quant_bits == 0 || p.D == 128);
+    const int64_t units = (int64_t)p.B * p.Hkv;
     if (p.n_shards <= 1) {
-        KeyRuns r = attn_plan_runs(p.B, p.Hq, p.Hkv, p.dtype, p.Lq, 1, &p.Lkv, p.quant_bits == 4 && p.D == 128);
+        const bool codes4 = p.quant_bits == 4 && p.D == 128;
+        KeyRuns r = attn_plan_runs(p.B, p.Hq, p.Hkv, p.dtype, p.Lq, 1, &p.Lkv, codes4);
+        if (streaming) decode_one_round(r, units, (int64_t)attn_target_wgs() * (codes4 ? kDecCodesOcc : 1));
         r.s[0].K = p.K;
         r.s[0].V = p.V;
         return r;
     }
     KeyRuns r = attn_plan_runs(p.B, p.Hq, p.Hkv, p.dtype, p.Lq, p.n_shards, p.Ls);
+    if (streaming) decode_one_round(r, units, attn_target_wgs());
     for (int i = 0; i < p.n_shards && i < kMaxShards; ++i) {
         r.s[i].K = p.Ks[i];
         r.s[i].V = p.Vs[i];

@@ -160,8 +160,8 @@ constexpr int64_t dec_single_tile_run(int d) { return d == 128 ? 1024 : 256; }  
 // 16-bit values of 128 columns in whole rounds of long runs stay in registers: at the rate of memory the LDS form is 1 to 4 % behind
 // where the units lie powers of two apart (64 sequences x 8 heads x 32768 keys 1189 us and 1217, x 8192 301 and 310, 16 x 8192 75.4
 // and 78.4), for whatever reason - not the order in which a tile's rows or a run's tiles are asked for - and within 1.5 % of it
-// elsewhere (64 x 3000 122 and 120, 32 x 4000 80.5 and 82).  At d = 64 both take the same time.  Where the last round is partly empty
-// what counts is again what a compute unit takes by itself (33 x 4096 131 us and 116).
+// elsewhere (64 x 3000 122 and 120, 32 x 4000 80.5 and 82).  At d = 64 both take the same time.  Where a round is partly empty,
+// for its number of workgroups or for shorter ones, what counts is again what a compute unit takes by itself (33 x 4096 131 us and 116).
 constexpr int64_t kDecLongRun = 2048;
 
 template <class T, int D, int QB, int NS>
@@ -675,8 +675,9 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
         Ldst = Odst + (size_t)splits * rows * D;
     }
     if (!grid_fits(units * splits, kDecThreads)) return hipErrorInvalidValue;
-    int64_t longest = 0;
+    int64_t longest = 0, total = 0;
     for (int i = 0; i < runs.n_shards; ++i) {
+        total += runs.s[i].L;
         const int64_t keys = runs.s[i].L < runs.s[i].per ? runs.s[i].L : runs.s[i].per;
         longest = keys > longest ? keys : longest;
     }
@@ -684,7 +685,7 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
     if (QB == 0) {
         const int64_t wgs = units * splits, cus = attn_target_wgs(), rounds = (wgs + cus - 1) / cus;
         tiles = longest <= kDecStride || (wgs > cus && longest <= dec_single_tile_run(D)) ? 1 : 2;
-        if (D == 128 && longest >= kDecLongRun && wgs * 10 >= rounds * cus * 9) tiles = 0;
+        if (D == 128 && longest >= kDecLongRun && units * total * 10 >= rounds * cus * longest * 9) tiles = 0;
     }
     auto kernel = decode_attn_kernel<T, D, QB, QB == 0 && D == 64 ? 2 : 0>;
     if constexpr (QB == 0) {

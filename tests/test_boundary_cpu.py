@@ -525,6 +525,28 @@ def test_two_group_runs_by_halving(launch_forms):
     assert max(t for t, _ in times) < 40.0
 
 
+@pytest.mark.skipif(torch.cuda.is_available(), reason="pinned for the 256 compute units that the plan falls back to")
+def test_decode_launches_make_one_round(launch_forms):
+    """The streaming kernel's launches cover every key once with at most the runs that the workspace holds, and are one round of
+    workgroups where a shard is alone and its units are not more."""
+    import random
+    r = random.Random(5)
+    shapes = [(3, 128, [8192]), (9, 128, [8192]), (20, 64, [8192]), (5, 128, [4001, 3277, 300]), (9, 128, [4096, 4096]), (31, 128, [513])]
+    while len(shapes) < 1500:
+        Ls = [r.choice([0, r.randint(1, 600), int(2 ** r.uniform(0, 16))]) for _ in range(r.choice([1, 1, 2, 3, 8, 16]))]
+        if any(Ls):
+            shapes.append((int(2 ** r.uniform(0, 6.5)), r.choice([64, 128]), Ls))
+    for what, round_ in (("decode", 256), ("decode4", 512)):
+        cases = [(B, d, Ls) for B, d, Ls in shapes if what == "decode" or (len(Ls) == 1 and d == 128)]
+        got = launch_forms([f"{what} {B} 32 8 {d} {fb.BF16} 1 {len(Ls)} " + " ".join(map(str, Ls)) for B, d, Ls in cases])
+        for (B, d, Ls), (runs, covered, longest, held) in zip(cases, got):
+            assert covered == sum(Ls) and runs <= max(held, 1), (what, B, d, Ls, runs, held)
+            assert 8 * B * runs <= round_ or 8 * B > round_ or len(Ls) > 1, (what, B, d, Ls, runs)
+    assert [g[0] for g in launch_forms([f"decode {B} 32 8 128 {fb.BF16} 1 1 8192" for B in (1, 3, 9, 16, 17, 33)])] == [16, 10, 3, 2, 1, 1]
+    several = [(5, [4001, 3277, 300]), (9, [4096, 4096]), (9, [4001, 3277, 300]), (20, [4001, 3277, 300])]
+    assert [g[0] for g in launch_forms([f"decode {B} 32 8 128 {fb.BF16} 1 {len(Ls)} " + " ".join(map(str, Ls)) for B, Ls in several])] == [6, 2, 6, 4]
+
+
 def test_missing_library_fails_loudly(tmp_path):
     """There is no fallback path: with no built library the binding raises instead of computing something else."""
     import subprocess
