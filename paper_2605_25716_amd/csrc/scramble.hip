@@ -436,9 +436,9 @@ FEDRAG_KERNEL __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_ker
 // thread asks for its share of the matrix, the rows, and what the aggregation needs of the first outputs, before it waits for
 // anything: two columns of every 32 (d = 128) or 8 contraction steps, whole rows of the matrix to a wave.  Sums of a share are
 // formed in its wave, the shares are added through LDS in order, the fp32 sum is narrowed once.
-// d = 128, calls back to back: a decoded token's queries 2.7 us, by structured keys 3.1, Dec of its result with the aggregation
-// 3.6; 64 sequences 5.4, 8.6, 10.2 (Dec alone).  With a whole column of the matrix a thread, 128 loads behind the rows', 3.5, 4.0,
-// 4.4 and 10.4, 23.1, 22.7; what stays is mostly the launch (2.2 us).  (16 rows of 32 heads 6.1 against 8.7, Dec 7.5 against 8.6.)
+// d = 128, calls back to back: a decoded token's queries 2.7 us, Dec of its result with the aggregation 3.6; 64 sequences 5.4, 10.2
+// (Dec alone).  With a whole column of the matrix a thread, 128 loads behind the rows', 3.5, 4.4 and 10.4, 22.7.  (16 rows of 32
+// heads 6.1 against 8.7, Dec 7.5 against 8.6.)
 //   SCATTER == false: Y[j] = X[perm[j]] . Phi ; SCATTER == true (fp32): Y[perm[i]] = X[i] . Phi
 constexpr int kFewRows = 16;
 // Of the form that sums in 64 bits, whose LDS is twice as much a row: at d = 64 eight rows of it leave room for four workgroups
@@ -836,6 +836,155 @@ FEDRAG_KERNEL __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f
     }
 }
 
+// Rows times a structured key, factor by factor: the scales and the channel gathers are what they are, and the Hadamard matrix is
+// seven (d = 64: six) steps of additions and subtractions, in place of a product with a matrix that every workgroup multiplies out.
+// 16 lanes hold a row, D / 16 values each: a lane's own values are combined in registers, those of different lanes by
+// data-parallel moves; the two gathers go through LDS, within a wave.  Every load but those of rows that wait for their indices is
+// asked for at once.
+// Dec, always: the fp32 product was bound by the fp32 matrix pipe or, for few rows, by its chain of waits; this is bound by memory
+// or by the launch (32 heads of 128: 1 row 3.3 -> 2.9 us, 16 7.1 -> 2.9, 117 6.4 -> 3.2, 1000 17.2 -> 7.5, 4096 47 -> 23; of 64 2.5 -> 2.4,
+// 4.4 -> 2.6, 5.0 -> 2.7, 7.8 -> 4.9, 20.3 -> 12.0).  Its sums of 128 are seven roundings deep.
+// Queries in 16 bits: heads of at most kHadSlab rows, where a tile of the product is mostly padding or its matrix is all it does
+// (32 heads of 128: 4 rows 3.8 -> 3.0 us, 16 6.3 -> 3.0, 256 x 32 69.6 -> 26.1, x 64 75 -> 49; of 64 3.0 -> 2.5, 4.2 -> 2.6, 30.4 -> 16.6,
+// 33 -> 27), or at most kHadTotal rows in all (117 6.0 -> 3.2, 1000 7.4 -> 6.3, 1500 10.3 -> 9.0; of 64 4.2 -> 2.7, 4.6 -> 4.3, 6.0 -> 5.1).
+// Beyond that the product is hidden by memory and this is not (2 x 1000 rows of 128 10.4 and 11.0, 32 x 117 14.0 and 16.9; of 64 6.2
+// and 6.1, 8.9 and 10.0).  Enc of K and V, which its coded form equals bit for bit, keeps the product at every size.
+//   SCATTER == false: Y[j] = X[perm[j]] . Phi ; SCATTER == true (fp32): Y[perm[i]] = X[i] . Phi
+constexpr int64_t kHadSlab = 64, kHadTotal = 48 << 10;
+constexpr int64_t kHadWgs = 2048;   // workgroups, eight to a compute unit, from where on one takes several steps
+constexpr int kHadRows = 16;        // rows per workgroup step
+constexpr int kHadThreads = 16 * kHadRows;
+template <class T, int D, bool SCATTER>
+FEDRAG_KERNEL __launch_bounds__(kHadThreads) void hadamard_rows_kernel(ScrambleJob job, const int32_t* __restrict__ perm,
+                                                                       int64_t perm_batch_stride, FastDiv by_chunks, FastDiv by_heads,
+                                                                       FastDiv by_group, int64_t L, int steps_per_wg) {
+    typedef typename T::elem elem;
+    static_assert(!SCATTER || sizeof(elem) == 4, "Dec is fp32");
+    constexpr int E = D / 16;                                            // values per lane
+    constexpr int EPC = E * (int)sizeof(elem) > 16 ? 16 / (int)sizeof(elem) : E;  // values per load, a lane's loads 16 lanes apart
+    constexpr int NC = E / EPC;
+    constexpr int LDP = D + 4;
+    typedef elem chunk_t __attribute__((ext_vector_type(EPC)));
+    typedef int32_t keys_t __attribute__((ext_vector_type(4), aligned(4)));  // key arrays are dword-aligned
+    __shared__ __attribute__((aligned(16))) float rows[kHadRows][LDP];
+    const int tid = threadIdx.x, rl = tid / 16, l = tid % 16;
+    const int bh = (int)by_chunks.div(blockIdx.x), chunk = (int)blockIdx.x - bh * (int)by_chunks.d;
+    const int b = (int)by_heads.div(bh), h = bh - b * (int)by_heads.d;
+    const int64_t at = (int64_t)by_group.div(h) * D;
+    const int32_t* pm = perm ? perm + (int64_t)b * perm_batch_stride : nullptr;
+    const elem* X = (const elem*)job.X + (int64_t)bh * L * D;
+    elem* Y = (elem*)job.Y + (int64_t)bh * L * D;
+    float* my = rows[rl];
+    const int64_t row0 = (int64_t)chunk * steps_per_wg * kHadRows + rl;
+    int n_steps = (int)((L - (int64_t)chunk * steps_per_wg * kHadRows + kHadRows - 1) / kHadRows);
+    if (n_steps > steps_per_wg) n_steps = steps_per_wg;
+
+    auto natural = [&](int c) { return (c * 16 + l) * EPC; };  // first channel of this lane's load c
+    auto row_of = [&](int s) { const int64_t j = row0 + (int64_t)s * kHadRows; return j < L ? j : L - 1; };
+    // Which block of E positions of the Hadamard product lane l holds: the moves flip bit 0, bit 1, bits 0 to 2 and bit 3 of a lane's
+    // number, and block a is where the set of these that leads there from lane 0 is a.
+    const int a = l ^ (l & 4 ? 3 : 0);
+
+    int32_t idx = pm ? pm[row_of(0)] : (int32_t)row_of(0);
+    auto load = [&](int64_t j, chunk_t (&x)[NC]) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) x[c] = *(const chunk_t*)(X + j * D + natural(c));
+    };
+    chunk_t x[NC];
+    if constexpr (SCATTER) load(row_of(0), x);
+    float s_in[E], post[E];
+    int g_in[E], g_out[E];  // the gathers, as channels
+    auto load_key = [&](const void* p, int (&v)[E], bool in_place) {
+#pragma unroll
+        for (int q = 0; q < E / 4; ++q) {
+            const int n = in_place ? E * a + 4 * q : EPC < 8 ? natural(q) : natural(0) + 4 * q;
+            const keys_t w = *(const keys_t*)((const int32_t*)p + at + n);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * q + e] = w[e];
+        }
+    };
+    load_key(job.p_in, g_in, true);
+    load_key(job.p_out, g_out, false);
+    int bits[E];
+    load_key(job.s_in, bits, false);
+#pragma unroll
+    for (int e = 0; e < E; ++e) s_in[e] = T::to_float(T::from_float(__builtin_bit_cast(float, bits[e])));  // as the products take it
+    load_key(job.s_out, bits, false);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        post[e] = __builtin_bit_cast(float, bits[e]) * (D == 128 ? 0.08838834764831845f : 0.125f);  // 1 / sqrt(D)
+        g_in[e] &= D - 1;
+        g_out[e] &= D - 1;
+    }
+    if constexpr (!SCATTER) load(idx, x);
+    const uint32_t sign[4] = {(a & 1) ? 0x80000000u : 0u, (a & 2) ? 0x80000000u : 0u, (a & 4) ? 0x80000000u : 0u,
+                              (a & 8) ? 0x80000000u : 0u};
+    for (int s = 0; s < n_steps; ++s) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int q = 0; q < EPC; q += 4) {
+                f32x4_t v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = T::to_float(x[c][q + e]) * s_in[c * EPC + q + e];
+                *(f32x4_t*)(my + natural(c) + q) = v;
+            }
+        const int64_t j = row0 + (int64_t)s * kHadRows;
+        const int64_t to = SCATTER ? idx : j;
+        if (s + 1 < n_steps) {  // the next row, on its way meanwhile
+            idx = pm ? pm[row_of(s + 1)] : (int32_t)row_of(s + 1);
+            load(SCATTER ? row_of(s + 1) : idx, x);
+        }
+        wave_lds_fence();
+        float z[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) z[e] = my[g_in[e]];
+#pragma unroll
+        for (int w = 1; w < E; w *= 2)
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (!(e & w)) {
+                    const float p = z[e], q = z[e + w];
+                    z[e] = p + q;
+                    z[e + w] = p - q;
+                }
+        auto across = [&](float v, float other, int bit) {
+            return other + __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) ^ sign[bit]);
+        };
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            z[e] = across(z[e], dpp_move<0xB1>(z[e]), 0);   // quad_perm [1,0,3,2]
+            z[e] = across(z[e], dpp_move<0x4E>(z[e]), 1);   // quad_perm [2,3,0,1]
+            z[e] = across(z[e], dpp_move<0x141>(z[e]), 2);  // row_half_mirror
+            z[e] = across(z[e], dpp_move<0x128>(z[e]), 3);  // row_ror:8
+        }
+        wave_lds_fence();  // all have gathered
+#pragma unroll
+        for (int q = 0; q < E; q += 4) {
+            f32x4_t v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = z[q + e];
+            *(f32x4_t*)(my + E * a + q) = v;
+        }
+        wave_lds_fence();
+        chunk_t y[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) {
+                // a sum of zeros is +0, as it is out of a product that starts there
+                float v = (my[g_out[c * EPC + e]] + 0.0f) * post[c * EPC + e];
+                pin_here(v);  // rounded before it is narrowed
+                y[c][e] = T::from_float(v);
+            }
+        if (j < L) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) *(chunk_t*)(Y + to * D + natural(c)) = y[c];
+        }
+        wave_lds_fence();
+    }
+}
+
 FEDRAG_KERNEL void invert_perm_kernel(const int32_t* __restrict__ perm, int64_t L, int32_t* __restrict__ inv) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j < L) inv[perm[j]] = (int32_t)j;
@@ -866,6 +1015,9 @@ static ScrambleJob device_job(const RowsJob& j, int i) {
     return ScrambleJob{j.X[i], j.Phi[i], j.Y[i], j.s_in[i], j.p_in[i], j.p_out[i], j.s_out[i], j.params[i]};
 }
 
+template <class T, int D, bool SCATTER>
+static hipError_t launch_hadamard(const RowsJob& j, hipStream_t stream);
+
 template <class T, int D, bool SCATTER, bool WIDE>
 static hipError_t launch_few_rows(const RowsJob& j, hipStream_t stream) {
     if (!grid_fits(j.BH, kF32Threads)) return hipErrorInvalidValue;
@@ -878,6 +1030,9 @@ static hipError_t launch_few_rows(const RowsJob& j, hipStream_t stream) {
 
 template <class T, int D>
 static hipError_t launch_scramble16(const RowsJob& j, hipStream_t stream) {
+    if (j.structured && j.n_jobs == 1 && j.quant_bits == 0 && (j.L <= kHadSlab || j.BH * j.L <= kHadTotal) &&
+        grid_fits(j.BH, kHadThreads))
+        return launch_hadamard<T, D, false>(j, stream);
     if (j.L <= kFewRows && j.quant_bits == 0) return launch_few_rows<T, D, false, false>(j, stream);
     const int waves = scr_waves(j.quant_bits);
     const int64_t rows_per_pass = (int64_t)waves * kScrRows;  // rows one workgroup covers per ring step
@@ -979,10 +1134,25 @@ static hipError_t launch_rows_f32(const RowsJob& j, hipStream_t stream) {
     return launch_rows_mfma_f32<D, SCATTER, 4 / (D / 32)>(j, stream);
 }
 
+template <class T, int D, bool SCATTER>
+static hipError_t launch_hadamard(const RowsJob& j, hipStream_t stream) {
+    const int64_t chunks16 = (j.L + kHadRows - 1) / kHadRows;
+    const int64_t steps = (j.BH * chunks16 + kHadWgs - 1) / kHadWgs;
+    const int per = (int)(steps < 1 ? 1 : steps < chunks16 ? steps : chunks16);
+    const int64_t chunks = (chunks16 + per - 1) / per;
+    if (!grid_fits(j.BH * chunks, kHadThreads)) return hipErrorInvalidValue;  // (at most kHadWgs, or BH)
+    hipLaunchKernelGGL((hadamard_rows_kernel<T, D, SCATTER>), dim3((unsigned)(j.BH * chunks)), dim3(kHadThreads), 0, stream,
+                       device_job(j, 0), j.perm, j.perm_batch_stride, FastDiv(chunks), FastDiv(j.H), FastDiv(j.G), j.L, per);
+    return hipGetLastError();
+}
+
 hipError_t launch_rows_transform(const RowsJob& j, hipStream_t stream) {
     if (j.L == 0 || j.BH == 0) return hipSuccess;
     if (j.scatter) {  // Dec: always fp32
         if (j.structured && j.merge.lse_in) return hipErrorInvalidValue;  // (not aggregated by a key's factors)
+        // (slabs by the ten million are more workgroups than a grid of the factors' form; of 17 to 32 rows of 64, not of the product's)
+        if (j.structured && grid_fits(j.BH, kHadThreads))
+            return j.D == 128 ? launch_hadamard<F32, 128, true>(j, stream) : launch_hadamard<F32, 64, true>(j, stream);
         return j.D == 128 ? launch_rows_f32<128, true>(j, stream) : launch_rows_f32<64, true>(j, stream);
     }
     switch (j.dtype) {

@@ -104,6 +104,46 @@ def chain_error(oracle, Q, Ks, Vs, enc_q, enc_kv, dec, perm_q, dtype):
     return float(np.linalg.norm(PT.f64(out) - ref) / np.linalg.norm(ref))
 
 
+# factor by factor: a step of 16 rows short and full, several steps a workgroup (more than 2048 x 16 rows), the slab and the total
+# from where on queries take the product
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("B,H,L,d", [(1, 2, 1, 128), (2, 4, 15, 64), (1, 2, 16, 128), (3, 2, 17, 128), (1, 4, 33, 64), (700, 2, 64, 64),
+                                     (400, 2, 65, 64), (1, 4, 4097, 128), (5, 2, 5000, 64)])
+def test_structured_rows_factor_by_factor(oracle, B, H, L, d, dt):
+    ks = W.make_structured_keys(H, d, L, 8, 1, seed=L + d, dtype=W.torch_dtype(dt), pow2=False)
+    perm = torch.randperm(L, generator=torch.Generator().manual_seed(L)).int()
+    X = W.activations(B, 2 * H, L, d, seed=9, tensor_id=W.TID_Q, outliers=True, dtype=W.torch_dtype(dt))
+    Q = fb.fedrag_scramble_q_structured(X.to(DEV), dev_key(ks.q), perm.to(DEV))
+    O = fb.fedrag_unscramble_structured(X.float().to(DEV), dev_key(ks.v_inv), perm.to(DEV))
+    torch.cuda.synchronize()
+    PT.check_scramble(Q, oracle.structured(X, ks.q, perm), X, abs_dense(ks.q, d), perm, 2, X.dtype, "Q'")
+    assert PT.rel_normwise(O, oracle.structured(X.float(), ks.v_inv, perm, scatter=True)) <= 1e-6  # 7 additions of 2^-24 each
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_structured_rows_of_special_values(d, dt):
+    """Infinities, NaN and zeros of either sign come out of the factors as they do out of the matrix (Enc of K, V)."""
+    ks = W.make_structured_keys(2, d, 40, 8, 1, seed=3, dtype=W.torch_dtype(dt), pow2=True)
+    X = W.activations(1, 2, 40, d, seed=4, tensor_id=W.TID_Q, outliers=False, dtype=W.torch_dtype(dt))
+    X[0, 0, 0], X[0, 0, 1], X[0, 1, 2] = 0.0, -0.0, 0.0
+    X[0, :, 3, 5], X[0, :, 4, 7], X[0, :, 5, 1] = float("inf"), float("-inf"), float("nan")
+    X[0, :, 6, 3], X[0, :, 6, 12] = float("inf"), float("inf")
+    X[0, :, 7, 3], X[0, :, 7, d - 1], X[0, :, 7, 9] = float("inf"), float("-inf"), float("inf")
+    a = fb.fedrag_scramble_q_structured(X.to(DEV), dev_key(ks.q), None)
+    b, _ = fb.fedrag_scramble_kv_structured(X.to(DEV), X.to(DEV), dev_key(ks.q), dev_key(ks.q), None)
+    torch.cuda.synchronize()
+    a, b = a.cpu(), b.cpu()
+    assert torch.equal(torch.isnan(a), torch.isnan(b)) and bool(torch.isnan(a[0, 0, 5]).all())
+    assert torch.equal(torch.isinf(a), torch.isinf(b)) and bool(torch.isinf(a[0, 0, 3]).all())
+    assert torch.equal(torch.signbit(a[:, :, :3]), torch.signbit(b[:, :, :3]))
+    fin = torch.isfinite(a)
+    diff = (a[fin].double() - b[fin].double()).abs()
+    assert float((diff / (a[fin].double().abs() + 1e-2)).max()) <= 2 ** (-7 if dt == "bf16" else -10)  # a unit in the last place
+    assert torch.equal(a[0, :, 3:5][torch.isinf(a[0, :, 3:5])], b[0, :, 3:5][torch.isinf(b[0, :, 3:5])])
+
+
+
 @pytest.mark.parametrize("outliers", [False, True], ids=["gaussian", "outlier_channels"])
 @pytest.mark.parametrize("L", [128, 512, 2048])
 def test_stability_structured_against_dense_random(oracle, L, outliers):
