@@ -85,6 +85,15 @@ FEDRAG_KERNEL __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void pre
     // With more than one run (several shards, or few query tiles and many keys; not CAUSAL) there is one workgroup
     // per (query tile, run) and O / lse are [n_runs][rows] partials that the Section 4.1 aggregation folds afterwards.
     // The launch chooses which of the two varies faster inside a unit (by_inner: the number of runs, or of query tiles).
+    // The arguments are one trip to memory, not one per branch and division that reads them: short causal calls 4..6 % (117 rows
+    // of 32 heads of 128: 8.9 -> 8.4 us), long ones 0..2 %.  The form on 8-bit codes with four waves has no register
+    // to spare for them.
+    if constexpr (!(QB != 0 && D == 64 && NW == 4)) {
+        FEDRAG_HAVE_HERE(FEDRAG_S3(by_unit), FEDRAG_S3(by_inner), FEDRAG_S3(by_tiles), FEDRAG_S3(by_group), FEDRAG_S3(by_heads),
+                         FEDRAG_S(run_by_run), FEDRAG_S(n_units), FEDRAG_S(Lq), FEDRAG_S(kv_lens), FEDRAG_S(q_lens), FEDRAG_S(Q),
+                         FEDRAG_S(O), FEDRAG_S(lse), FEDRAG_S(Hq), FEDRAG_S(fold), FEDRAG_S(together), FEDRAG_S(runs.n_shards),
+                         FEDRAG_S(runs.n_runs));
+    }
     const int G = (int)by_group.d;
     const int n_runs = runs.n_runs;
     const int xcd = blockIdx.x % 8;
@@ -101,6 +110,7 @@ FEDRAG_KERNEL __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void pre
     const int run = run_by_run ? outer : inner;
     int split = 0;
     const KeyShard shard = WALK ? runs.s[0] : runs.shard_of(run, &split);
+    FEDRAG_HAVE_HERE(FEDRAG_S(shard.K), FEDRAG_S(shard.V), FEDRAG_S(shard.L), FEDRAG_S(shard.per));
     const elem* K = (const elem*)shard.K;
     const elem* V = (const elem*)shard.V;
     const int64_t L_stride = shard.L;
@@ -138,15 +148,13 @@ FEDRAG_KERNEL __launch_bounds__(NW * kWave, D == 64 && NW == 4 ? 3 : 2) void pre
     const float* Vpg = QB ? Vprm + (int64_t)unit * L_stride * 2 : nullptr;
     // keys of this sequence: all L_stride rows, or the first kv_lens[b] of them (padded batch of unequal sequences)
     int64_t L = L_stride;
-    if (kv_lens) {
-        const int64_t v = kv_lens[b];
-        L = v < 0 ? 0 : (v < L_stride ? v : L_stride);
-    }
     // query rows of this sequence that exist (padded batch): rows past them are neither computed nor written
     int64_t Lq_rows = Lq;
-    if (q_lens) {
-        const int64_t v = q_lens[b];
-        Lq_rows = v < 0 ? 0 : (v < Lq ? v : Lq);
+    if (kv_lens || q_lens) {  // both asked for at once
+        const int nk = (kv_lens ? kv_lens : q_lens)[b], nq = (q_lens ? q_lens : kv_lens)[b];
+        asm volatile("" ::"v"(nk), "v"(nq));
+        if (kv_lens) L = nk < 0 ? 0 : (nk < L_stride ? nk : L_stride);
+        if (q_lens) Lq_rows = nq < 0 ? 0 : (nq < Lq ? nq : Lq);
     }
     if ((int64_t)qt * kQTile >= Lq_rows) return;  // workgroup-uniform, before any barrier
     const int64_t part_row0 = (int64_t)run * n_units * G * Lq;  // n_units * G * Lq = rows of one partial

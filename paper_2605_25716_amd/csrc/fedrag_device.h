@@ -181,6 +181,13 @@ __device__ __forceinline__ void pin_here(V& v) {
     asm volatile("" : "+v"(v));
 }
 
+// Scalars (a kernel's arguments) that are all in registers from here on: asked for where the code happens to need them they are as
+// many trips to memory, one after the other, as there are branches and address computations between, 0.2 us each in a launch
+// whose caches are cold.
+#define FEDRAG_S(x) "s"(x)
+#define FEDRAG_S3(f) "s"((f).m), "s"((f).s), "s"((f).d)  // a FastDiv
+#define FEDRAG_HAVE_HERE(...) asm volatile("" ::__VA_ARGS__)
+
 // Transposing LDS read: within each group of 16 lanes, lane j receives element (j % 4) of the 8 bytes addressed
 // by lane 4 e + j / 4, for e = 0..3.  With lane s of the group pointing at row (s / 4), columns 4 (s % 4)..+4 of
 // a row-major 4 x 16 block, lane j gets column j of the block, rows 0..3.
