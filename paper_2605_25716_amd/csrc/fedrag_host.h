@@ -86,9 +86,8 @@ struct FastDiv {
     uint32_t m, s, d;
     FastDiv() = default;
     explicit FastDiv(int64_t div) : d((uint32_t)div) {
-        s = 31;
-        while (((int64_t)1 << (s - 31)) < div) ++s;
-        m = (uint32_t)((((unsigned __int128)1 << s) + (uint64_t)div - 1) / (uint64_t)div);
+        s = 31 + (div > 1 ? 64 - (uint32_t)__builtin_clzll((uint64_t)div - 1) : 0);  // + ceil(log2(div))
+        m = (uint32_t)((((uint64_t)1 << s) + (uint64_t)div - 1) / (uint64_t)div);
     }
     __host__ __device__ uint32_t div(uint32_t n) const { return (uint32_t)(((uint64_t)n * m) >> s); }
     __host__ __device__ uint32_t mod(uint32_t n) const { return n - div(n) * d; }

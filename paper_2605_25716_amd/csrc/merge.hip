@@ -215,8 +215,9 @@ hipError_t launch_scatter_rows_f32(const float* in, const int32_t* perm, int64_t
     const int64_t total = n_bh * L;
     if (total == 0) return hipSuccess;
     if (!grid_fits((total + 255) / 256, 256)) return hipErrorInvalidValue;
+    const int small = total <= 0x7fffffffLL ? 1 : 0;
     hipLaunchKernelGGL(scatter_rows_f32_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, in, perm,
-                       L, FastDiv(L), total <= 0x7fffffffLL ? 1 : 0, total, out);
+                       L, FastDiv(small ? L : 1), small, total, out);
     return hipGetLastError();
 }
 

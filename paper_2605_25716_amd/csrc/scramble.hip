@@ -436,11 +436,20 @@ FEDRAG_KERNEL __launch_bounds__(scr_waves(QB) * kWave, 1) void scramble_rows_ker
 // thread asks for its share of the matrix, the rows, and what the aggregation needs of the first outputs, before it waits for
 // anything: two columns of every 32 (d = 128) or 8 contraction steps, whole rows of the matrix to a wave.  Sums of a share are
 // formed in its wave, the shares are added through LDS in order, the fp32 sum is narrowed once.
-// d = 128, calls back to back: a decoded token's queries 2.7 us, Dec of its result with the aggregation 3.6; 64 sequences 5.4, 10.2
-// (Dec alone).  With a whole column of the matrix a thread, 128 loads behind the rows', 3.5, 4.4 and 10.4, 22.7.  (16 rows of 32
-// heads 6.1 against 8.7, Dec 7.5 against 8.6.)
+// With a whole column of the matrix a thread, 128 loads behind the rows', 64 sequences of 32 heads took 10.4 us and Dec 22.7, now
+// 4.8 and 10.2.
+// CS: workgroups that a slab's columns are split over, of 256 / CS threads; sums are formed as without, in the same order.  What one
+// compute unit can fetch is then no longer the bound of a launch with few slabs, nor its LDS that of several rows.  d = 128, 32
+// slabs, calls back to back, CS = 1 and 4: a decoded token's queries 2.65 and 2.41 us (fp32 3.33, 2.54), Dec of its result 3.20, 2.56, with
+// the aggregation 3.57, 2.90; 4 rows 3.37, 3.08 (4.27, 3.21), 3.99, 3.24 and 4.53, 3.64; 16 rows 6.0, 5.3 (7.4, 5.9), 7.3, 6.3 and 9.4, 8.6.
+// With up to kSplitRows rows, whose staging needs an eighth of the loads and registers, it is worth it for any number of slabs:
+// 2048 x 4 rows of 128 7.7, 7.2 (16.3, 13.4), Dec 11.9, 11.9; at d = 64, whose workgroups of four columns' share are small, CS = 2
+// from kSplitSlabs on (2048 x 1: 3.5, CS = 4 4.0, CS = 2 3.2; 512 x 4: 2.8, 2.85, 2.75).  More rows: from kSplitSlabs on CS = 1 (512 x 8
+// of 128: 5.0, 5.1; fp32 7.9, 11.1; 128 x 8: 4.35, 4.23; 5.6, 4.7).
 //   SCATTER == false: Y[j] = X[perm[j]] . Phi ; SCATTER == true (fp32): Y[perm[i]] = X[i] . Phi
 constexpr int kFewRows = 16;
+constexpr int kSplitRows = 4;
+constexpr int64_t kSplitSlabs = 128;
 // Of the form that sums in 64 bits, whose LDS is twice as much a row: at d = 64 eight rows of it leave room for four workgroups
 // a compute unit, where 16 left two (64 x 32 slabs of 1, 5, 8 rows 4.8, 6.9, 8.6 us against 6.4, 9.7, 11.5).
 constexpr int wide_rows(int d) { return d == 64 ? kFewRows / 2 : kFewRows; }
@@ -476,21 +485,22 @@ __device__ __forceinline__ float merge_two(const RowWeights& w, float mine, floa
     return w.a != -1.f || w.b != -1.f ? o * w.inv : 0.f;
 }
 
-template <class T, int D, bool SCATTER, bool ST, bool WIDE>
-FEDRAG_KERNEL __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0, ScrambleJob job1,
-                                                               const int32_t* __restrict__ perm,
-                                                               int64_t perm_batch_stride, int H, int G, int L,
-                                                               RowsMerge mg) {
+template <class T, int D, bool SCATTER, bool ST, bool WIDE, int CS, int ROWS>
+__device__ __forceinline__ void few_rows(const ScrambleJob& job0, const ScrambleJob& job1, const int32_t* __restrict__ perm,
+                                         int64_t perm_batch_stride, FastDiv by_h, FastDiv by_g, int L, const RowsMerge& mg) {
     typedef typename T::elem elem;
     constexpr bool kF32 = sizeof(elem) == 4;
     static_assert(!SCATTER || kF32, "Dec is fp32");
     constexpr bool kMerge = SCATTER && !ST;  // may be asked for the aggregation as well
-    constexpr int LPK = D / 2;              // lanes per row of the matrix, two columns each
-    constexpr int KG = kF32Threads / LPK;   // shares of the contraction
+    static_assert(CS == 1 || !ST, "the key's factors are for all columns");
+    constexpr int kThreads = kF32Threads / CS;
+    constexpr int COLS = D / CS;            // columns of this workgroup
+    constexpr int LPK = COLS / 2;           // lanes per row of the matrix, two columns each
+    constexpr int KG = kThreads / LPK;      // shares of the contraction, as many whatever CS
     constexpr int KPG = D / KG;             // steps of a share
-    constexpr int kRows = WIDE ? wide_rows(D) : kFewRows;    // at most
+    constexpr int kRows = WIDE && ROWS > wide_rows(D) ? wide_rows(D) : ROWS;  // at most
     constexpr int EPC = 16 / (int)sizeof(elem);              // row elements per 16-byte load
-    constexpr int XC = (kRows * D / EPC + kF32Threads - 1) / kF32Threads;  // such loads per thread, at most
+    constexpr int XC = (kRows * D / EPC + kThreads - 1) / kThreads;  // such loads per thread, at most
     typedef elem chunk_t __attribute__((ext_vector_type(EPC)));
     typedef elem pair_t __attribute__((ext_vector_type(2)));
     // WIDE (fp32 storage): the rounding of the queries comes back multiplied by the scores, and there is time for sums in 64 bits
@@ -500,43 +510,54 @@ FEDRAG_KERNEL __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob jo
     typedef acc_t acc4_t __attribute__((ext_vector_type(4)));
     typedef acc_t acc2_t __attribute__((ext_vector_type(2)));
     __shared__ __attribute__((aligned(16))) acc_t xs[kRows * D];
-    __shared__ __attribute__((aligned(16))) acc_t part[KG][kRows * D];
+    __shared__ __attribute__((aligned(16))) acc_t part[KG][kRows * COLS];
     __shared__ int32_t p_in_inv[ST ? D : 1];
     __shared__ float s_in[ST ? D : 1];
     const ScrambleJob job = blockIdx.y == 0 ? job0 : job1;
+    FEDRAG_HAVE_HERE(FEDRAG_S(job.X), FEDRAG_S(job.Y), FEDRAG_S(perm), FEDRAG_S(perm_batch_stride), FEDRAG_S3(by_h), FEDRAG_S3(by_g),
+                     FEDRAG_S(L));
+    if constexpr (ST) FEDRAG_HAVE_HERE(FEDRAG_S(job.s_in), FEDRAG_S(job.p_in), FEDRAG_S(job.p_out), FEDRAG_S(job.s_out));
+    else FEDRAG_HAVE_HERE(FEDRAG_S(job.Phi));
+    if constexpr (kMerge)
+        FEDRAG_HAVE_HERE(FEDRAG_S(mg.lse_in), FEDRAG_S(mg.O_other), FEDRAG_S(mg.lse_other), FEDRAG_S(mg.lse_out));
     const int tid = threadIdx.x;
     const int cl = 2 * (tid % LPK);  // first of this thread's two columns
     const int kg = tid / LPK;
     const int bh = blockIdx.x;
-    const int b = bh / H;
-    const int h = bh % H;
+    const int b = (int)by_h.div((uint32_t)bh);
+    const int hk = (int)by_g.div(by_h.mod((uint32_t)bh));  // the head's matrix
+    const int c0 = CS > 1 ? (int)blockIdx.z * COLS : 0;
     const elem* X = (const elem*)job.X + (int64_t)bh * L * D;
     elem* Y = (elem*)job.Y + (int64_t)bh * L * D;
     const int32_t* pm = perm ? perm + (int64_t)b * perm_batch_stride : nullptr;
-    const int n_out = L * D;
+    const int n_out = L * COLS;
 
     // where the rows come from (those past the end re-read the last one and are left out)
     int src[XC];
 #pragma unroll
     for (int u = 0; u < XC; ++u) {
-        const int j = (tid + u * kF32Threads) / (D / EPC);
+        const int j = (tid + u * kThreads) / (D / EPC);
         src[u] = j < L ? j : L - 1;
     }
     if (!SCATTER && pm) {
 #pragma unroll
         for (int u = 0; u < XC; ++u) src[u] = pm[src[u]];
     }
+    // and where this thread's first output goes: asked for ahead of the matrix, which a wait for it would be a wait for otherwise
+    auto row_of = [&](int e) { return e < n_out ? e / COLS : L - 1; };
+    int first_dst = row_of(tid);
+    if (SCATTER && pm) first_dst = pm[first_dst];
     // the matrix
     pair_t phi_in[ST ? 1 : KPG];
     if constexpr (!ST) {
-        const elem* P = (const elem*)job.Phi + (int64_t)(h / G) * D * D + (int64_t)kg * KPG * D + cl;
+        const elem* P = (const elem*)job.Phi + (int64_t)hk * D * D + (int64_t)kg * KPG * D + c0 + cl;
 #pragma unroll
         for (int i = 0; i < KPG; ++i) phi_in[i] = *(const pair_t*)(P + i * D);
     }
     int32_t key_inv = 0, key_out0 = 0, key_out1 = 0;
     float key_in = 0.f, post0 = 1.f, post1 = 1.f;  // post: fp32 of columns cl, cl + 1; 16 bits (post0) of column tid % D
     if constexpr (ST) {
-        const int64_t at = (int64_t)(h / G) * D;
+        const int64_t at = (int64_t)hk * D;
         if (tid < D) {
             key_inv = job.p_in[at + tid];
             key_in = job.s_in[at + tid];
@@ -550,30 +571,28 @@ FEDRAG_KERNEL __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob jo
     chunk_t x_in[XC];
 #pragma unroll
     for (int u = 0; u < XC; ++u)
-        x_in[u] = *(const chunk_t*)(X + (int64_t)src[u] * D + (tid + u * kF32Threads) % (D / EPC) * EPC);
+        x_in[u] = *(const chunk_t*)(X + (int64_t)src[u] * D + (tid + u * kThreads) % (D / EPC) * EPC);
     // outputs e = tid, tid + 256, ... : row and what the aggregation reads of it
     struct Out {
         int64_t dst;
         float la, lb, other;
     };
-    auto out_of = [&](int e) {
-        Out o{0, 0.f, 0.f, 0.f};
-        const int j = e < n_out ? e / D : L - 1;
-        o.dst = SCATTER && pm ? (int64_t)pm[j] : j;
+    auto out_of = [&](int e, int dst) {
+        Out o{dst, 0.f, 0.f, 0.f};
         if (kMerge && mg.lse_in) {
-            o.la = mg.lse_in[(int64_t)bh * L + j];
-            o.lb = mg.lse_other[(int64_t)bh * L + o.dst];
-            o.other = mg.O_other[((int64_t)bh * L + o.dst) * D + e % D];
+            o.la = mg.lse_in[(int64_t)bh * L + row_of(e)];
+            o.lb = mg.lse_other[(int64_t)bh * L + dst];
+            o.other = mg.O_other[((int64_t)bh * L + dst) * D + c0 + e % COLS];
         }
         return o;
     };
-    Out next = out_of(tid);
+    Out next = out_of(tid, first_dst);
 
 #pragma unroll
     for (int u = 0; u < XC; ++u)
 #pragma unroll
         for (int q = 0; q < EPC; ++q)
-            if (XC > 1 || tid < kRows * D / EPC) xs[(tid + u * kF32Threads) * EPC + q] = T::to_float(x_in[u][q]);
+            if (XC > 1 || tid < kRows * D / EPC) xs[(tid + u * kThreads) * EPC + q] = T::to_float(x_in[u][q]);
     if constexpr (ST) {
         if (tid < D) {
             p_in_inv[key_inv & (D - 1)] = tid;
@@ -612,13 +631,16 @@ FEDRAG_KERNEL __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob jo
                     else a[c] = __builtin_fmaf(x[e], phi[i4 + e][c], a[c]);
                 }
         }
-        *(acc2_t*)(&part[kg][r * D + cl]) = a;
+        *(acc2_t*)(&part[kg][r * COLS + cl]) = a;
     }
     __syncthreads();
 #pragma unroll 1
-    for (int e = tid; e < n_out; e += kF32Threads) {
+    for (int e = tid; e < n_out; e += kThreads) {
         const Out o = next;
-        if (e + kF32Threads < n_out) next = out_of(e + kF32Threads);
+        if (e + kThreads < n_out) {
+            const int row = row_of(e + kThreads);
+            next = out_of(e + kThreads, SCATTER && pm ? pm[row] : row);
+        }
         acc_t sum = part[0][e];
 #pragma unroll
         for (int g = 1; g < KG; ++g) sum += part[g][e];
@@ -630,10 +652,26 @@ FEDRAG_KERNEL __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob jo
         if (kMerge && mg.lse_in) {
             float l;
             v = merge_two(weights_of_two(o.la, o.lb, &l), v, o.other);
-            if (e % D == 0) mg.lse_out[(int64_t)bh * L + o.dst] = l;
+            if (c0 + e % COLS == 0) mg.lse_out[(int64_t)bh * L + o.dst] = l;
         }
-        Y[o.dst * D + e % D] = T::from_float(v);
+        Y[o.dst * D + c0 + e % COLS] = T::from_float(v);
     }
+}
+
+template <class T, int D, bool SCATTER, bool ST, bool WIDE>
+FEDRAG_KERNEL __launch_bounds__(kF32Threads) void few_rows_kernel(ScrambleJob job0, ScrambleJob job1,
+                                                               const int32_t* __restrict__ perm,
+                                                               int64_t perm_batch_stride, FastDiv by_h, FastDiv by_g, int L,
+                                                               RowsMerge mg) {
+    few_rows<T, D, SCATTER, ST, WIDE, 1, kFewRows>(job0, job1, perm, perm_batch_stride, by_h, by_g, L, mg);
+}
+
+template <class T, int D, bool SCATTER, bool WIDE, int CS, int ROWS>
+FEDRAG_KERNEL __launch_bounds__(kF32Threads / CS) void few_rows_of_few_columns_kernel(ScrambleJob job0, ScrambleJob job1,
+                                                                                   const int32_t* __restrict__ perm,
+                                                                                   int64_t perm_batch_stride, FastDiv by_h,
+                                                                                   FastDiv by_g, int L, RowsMerge mg) {
+    few_rows<T, D, SCATTER, false, WIDE, CS, ROWS>(job0, job1, perm, perm_batch_stride, by_h, by_g, L, mg);
 }
 
 // fp32 rows times fp32 matrix (fp32 storage path of Enc, and Dec for every storage type) on the fp32 matrix cores, for slabs
@@ -1020,11 +1058,18 @@ static hipError_t launch_hadamard(const RowsJob& j, hipStream_t stream);
 
 template <class T, int D, bool SCATTER, bool WIDE>
 static hipError_t launch_few_rows(const RowsJob& j, hipStream_t stream) {
+    const bool few_slabs = j.BH * j.n_jobs <= kSplitSlabs, handful = j.L <= kSplitRows;
+    const int cs = j.structured ? 1 : few_slabs || (handful && D == 128) ? 4 : handful ? 2 : 1;
     if (!grid_fits(j.BH, kF32Threads)) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)j.BH, (unsigned)j.n_jobs);
-    const auto kernel = j.structured ? few_rows_kernel<T, D, SCATTER, true, WIDE> : few_rows_kernel<T, D, SCATTER, false, WIDE>;
-    hipLaunchKernelGGL(kernel, grid, dim3(kF32Threads), 0, stream, device_job(j, 0), device_job(j, 1), j.perm, j.perm_batch_stride,
-                       j.H, j.G, (int)j.L, j.merge);
+    const dim3 grid((unsigned)j.BH, (unsigned)j.n_jobs, (unsigned)cs);
+#define FEDRAG_SPLIT(CS_, ROWS_) few_rows_of_few_columns_kernel<T, D, SCATTER, WIDE, CS_, ROWS_>
+    auto kernel = j.structured ? few_rows_kernel<T, D, SCATTER, true, WIDE> : few_rows_kernel<T, D, SCATTER, false, WIDE>;
+    if (cs == 4) kernel = handful ? FEDRAG_SPLIT(4, kSplitRows) : FEDRAG_SPLIT(4, kFewRows);
+    if constexpr (D == 64)
+        if (cs == 2) kernel = FEDRAG_SPLIT(2, kSplitRows);
+#undef FEDRAG_SPLIT
+    hipLaunchKernelGGL(kernel, grid, dim3(kF32Threads / cs), 0, stream, device_job(j, 0), device_job(j, 1), j.perm, j.perm_batch_stride,
+                       FastDiv(j.H), FastDiv(j.G), (int)j.L, j.merge);
     return hipGetLastError();
 }
 

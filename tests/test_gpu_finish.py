@@ -80,3 +80,37 @@ def test_unscramble_merge_at_the_edges_of_its_kernels(d, Lq):
         torch.cuda.synchronize()
         assert torch.isfinite(O3).all()
         assert torch.equal(O.view(torch.int32), O3.view(torch.int32)) and torch.equal(lse, l3)
+
+
+@pytest.mark.parametrize("rows", [1, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dt", ["bf16", "f16", "f32"])
+def test_few_rows_of_few_and_of_many_slabs(oracle, dt, d, rows):
+    """Columns split over two or four workgroups, or not, by the rows and by the slabs (up to 128 and more): sums in the same
+    order, so the values of a sequence bit for bit in a batch of 33, and those of the oracle."""
+    B, Hq, Hkv = 33, 4, 2
+    dtype = W.torch_dtype(dt)
+    keys = W.make_keys(Hkv, d, rows, 64, 1, seed=rows + d, dtype=dtype)
+    X = W.activations(B, Hq, rows, d, seed=5, tensor_id=W.TID_Q, outliers=False, dtype=dtype)
+    O, other = X.float() * 0.5, X.float().flip(0).contiguous()
+    la, lb = O[..., 0].contiguous(), other[..., 1].contiguous()
+    perm = torch.randperm(rows, generator=torch.Generator().manual_seed(rows)).to(torch.int32)
+    print(f"few rows {dt} {d} {rows}", flush=True)
+    dv = lambda t: t.to(DEV)  # noqa: E731
+
+    def calls(b):
+        s = slice(0, b)
+        out = [fb.fedrag_scramble_q(dv(X[s]), dv(keys.phi_q), dv(perm)), fb.fedrag_unscramble(dv(O[s]), dv(keys.phi_v_inv), dv(perm))]
+        return out + list(fb.fedrag_unscramble_merge(dv(O[s]), dv(la[s]), dv(keys.phi_v_inv), dv(perm), dv(other[s]), dv(lb[s])))
+
+    one, many = calls(1), calls(B)
+    torch.cuda.synchronize()
+    for a, b in zip(one, many):
+        assert torch.equal(a, b[:1])
+    PT.check_scramble(many[0], oracle.scramble(X, keys.phi_q, perm), X, keys.phi_q, perm, Hq // Hkv, dtype, "Q'")
+    dec = oracle.unscramble(O, keys.phi_v_inv, perm)
+    assert PT.rel_normwise(many[1], dec) <= PT.TOL_F32_REL
+    moved = torch.empty_like(la)
+    moved[:, :, perm.long()] = la
+    Or, lr = oracle.lse_merge(np.stack([dec, other.double().numpy()]), np.stack([moved.double().numpy(), lb.double().numpy()]))
+    assert PT.rel_normwise(many[2], Or) <= PT.TOL_F32_REL and PT.rel_normwise(many[3], lr) <= PT.TOL_F32_REL
