@@ -32,7 +32,7 @@ __device__ __forceinline__ float exp_diff(float a, float b) { return (a == -INFI
 
 template <int D, int NQ, int W>
 FEDRAG_KERNEL __launch_bounds__(W * kWave, W == 1 && NQ == 1 ? (D == 64 ? 4 : 2) : 1) void attn_f32_kernel(const float* __restrict__ Q, const KeyRuns runs,
-                                                                      FastDiv by_tiles, FastDiv by_lq, int Hkv, int R,
+                                                                      FastDiv by_tiles, FastDiv by_lq, FastDiv by_hkv, int R,
                                                                       int64_t Lq, int64_t causal_off, int causal,
                                                                       float scale, float* __restrict__ O,
                                                                       float* __restrict__ lse, int64_t total_rows,
@@ -50,17 +50,24 @@ FEDRAG_KERNEL __launch_bounds__(W * kWave, W == 1 && NQ == 1 ? (D == 64 ? 4 : 2)
     const int lane = tid % kWave;
     const int lr = lane % 16;
     const int lq = lane / 16;
+    // The arguments, then the shard: two trips to memory where branches and addresses made five (4 rows x 512 keys of 64 0.6 %, on
+    // average over 80 launches 0.7 %; with two row tiles a wave, 256 rows x 32 heads of 64, 2 % slower: not there).
+    if constexpr (NQ == 1)
+        FEDRAG_HAVE_HERE(FEDRAG_S(Q), FEDRAG_S3(runs.by_runs), FEDRAG_S(runs.n_shards), FEDRAG_S3(by_tiles), FEDRAG_S3(by_lq), FEDRAG_S(R),
+                         FEDRAG_S(Lq), FEDRAG_S(causal_off), FEDRAG_S(causal), FEDRAG_S(scale), FEDRAG_S(O), FEDRAG_S(lse),
+                         FEDRAG_S(total_rows), FEDRAG_S(kv_lens), FEDRAG_S(q_lens));
     const uint32_t group = runs.by_runs.div(blockIdx.x);  // (unit, row tile); the runs of one are neighbours
     const int run = (int)(blockIdx.x - group * runs.by_runs.d);
     const uint32_t unit = by_tiles.div(group);
     const int row0 = (int)(group - unit * by_tiles.d) * (NQ * 16);
     int split;
     const KeyShard shard = runs.shard_of(run, &split);  // one run per shard: split == 0
+    if constexpr (NQ == 1) FEDRAG_HAVE_HERE(FEDRAG_S(shard.K), FEDRAG_S(shard.V), FEDRAG_S(shard.L));
     int64_t L = shard.L;
     const float* K = (const float*)shard.K + (int64_t)unit * L * D;
     const float* V = (const float*)shard.V + (int64_t)unit * L * D;
     if (kv_lens) {  // padded batch of unequal sequences: only the first kv_lens[b] keys exist
-        const int64_t v = kv_lens[(int)unit / Hkv];
+        const int64_t v = __builtin_amdgcn_readfirstlane(kv_lens[by_hkv.div(unit)]);
         L = v < 0 ? 0 : (v < L ? v : L);
     }
 
@@ -68,7 +75,7 @@ FEDRAG_KERNEL __launch_bounds__(W * kWave, W == 1 && NQ == 1 ? (D == 64 ? 4 : 2)
     // sequence's count, or the sequence has none
     int q_rows = 0;
     if (q_lens) {
-        q_rows = q_lens[(int)unit / Hkv];
+        q_rows = __builtin_amdgcn_readfirstlane(q_lens[by_hkv.div(unit)]);
         const int first = (int)by_lq.mod((uint32_t)row0);
         if (q_rows <= 0 || (first >= q_rows && first + NQ * 16 <= Lq)) return;
     }
@@ -296,7 +303,7 @@ static hipError_t launch_f32_t(const AttnProblem& p, const KeyRuns& runs, hipStr
         Ldst = Odst + (size_t)runs.n_runs * rows * D;
     }
     hipLaunchKernelGGL((attn_f32_kernel<D, NQ, W>), dim3((unsigned)grid), dim3(W * kWave), 0, stream,
-                       (const float*)p.Q, runs, FastDiv(tiles), FastDiv(p.Lq), p.Hkv, (int)R, p.Lq, p.Lkv - p.Lq,
+                       (const float*)p.Q, runs, FastDiv(tiles), FastDiv(p.Lq), FastDiv(p.Hkv), (int)R, p.Lq, p.Lkv - p.Lq,
                        p.causal ? 1 : 0, p.scale, Odst, Ldst, rows, p.kv_lens, p.q_lens);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || runs.n_runs == 1) return e;

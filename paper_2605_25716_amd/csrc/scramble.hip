@@ -695,8 +695,8 @@ constexpr int mf_threads(int d, int rt) { return d / 32 * rt * kWave; }
 template <int D, bool SCATTER, bool ST, bool MERGE, int RT>
 FEDRAG_KERNEL __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f32_kernel(ScrambleJob job0, ScrambleJob job1,
                                                                                  const int32_t* __restrict__ perm,
-                                                                                 int64_t perm_batch_stride, int H,
-                                                                                 int G, int64_t L, int chunks,
+                                                                                 int64_t perm_batch_stride, FastDiv by_h,
+                                                                                 FastDiv by_g, int64_t L, FastDiv by_chunks,
                                                                                  int steps_per_wg, RowsMerge mg) {
     constexpr int SL = D / 32;         // 32-column slices of the output
     constexpr int kThreads = mf_threads(D, RT);
@@ -715,6 +715,13 @@ FEDRAG_KERNEL __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f
     static_assert(!MERGE || (SCATTER && !ST), "the aggregation is part of Dec by a matrix");
 
     const ScrambleJob job = blockIdx.y == 0 ? job0 : job1;
+    // one trip to memory, and heads without divisions: 1 to 7 % of launches of up to some 30 us, 2.5 % on average over 114
+    FEDRAG_HAVE_HERE(FEDRAG_S(job.X), FEDRAG_S(job.Y), FEDRAG_S(perm), FEDRAG_S(perm_batch_stride), FEDRAG_S3(by_h), FEDRAG_S3(by_g),
+                     FEDRAG_S(L), FEDRAG_S3(by_chunks), FEDRAG_S(steps_per_wg));
+    if constexpr (ST) FEDRAG_HAVE_HERE(FEDRAG_S(job.s_in), FEDRAG_S(job.p_in), FEDRAG_S(job.p_out), FEDRAG_S(job.s_out));
+    else FEDRAG_HAVE_HERE(FEDRAG_S(job.Phi));
+    if constexpr (MERGE)
+        FEDRAG_HAVE_HERE(FEDRAG_S(mg.lse_in), FEDRAG_S(mg.O_other), FEDRAG_S(mg.lse_other), FEDRAG_S(mg.lse_out));
     const int tid = threadIdx.x;
     const int wave = tid / kWave;
     const int lane = tid % kWave;
@@ -722,10 +729,10 @@ FEDRAG_KERNEL __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f
     const int kk = lane / 32;
     const int slice = wave % SL;
     const int rt = wave / SL;
-    const int bh = blockIdx.x / chunks;
-    const int chunk = blockIdx.x % chunks;
-    const int b = bh / H;
-    const int h = bh % H;
+    const int bh = (int)by_chunks.div(blockIdx.x);
+    const int chunk = (int)by_chunks.mod(blockIdx.x);
+    const int b = (int)by_h.div((uint32_t)bh);
+    const int hk = (int)by_g.div(by_h.mod((uint32_t)bh));  // the head's matrix
     const int64_t first_row = (int64_t)chunk * steps_per_wg * TR;
     if (first_row >= L) return;  // workgroup-uniform, before any barrier
     int n_steps = (int)((L - first_row + TR - 1) / TR);
@@ -782,14 +789,14 @@ FEDRAG_KERNEL __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f
     const int col = 32 * slice + n;  // this lane's output column
     float phi[NJ][4];
     if (ST) {  // column `col` of S1 P1 H P2 S2, generated from the key
-        const int32_t* g1 = job.p_in + (int64_t)(h / G) * D;
+        const int32_t* g1 = job.p_in + (int64_t)hk * D;
         for (int k = tid; k < D; k += kThreads) {
             p_in_inv[g1[k] & (D - 1)] = k;
-            s_in[k] = job.s_in[(int64_t)(h / G) * D + k];
+            s_in[k] = job.s_in[(int64_t)hk * D + k];
         }
         __syncthreads();
-        const int m = job.p_out[(int64_t)(h / G) * D + col] & (D - 1);
-        const float post = job.s_out[(int64_t)(h / G) * D + col] * (D == 128 ? 0.08838834764831845f : 0.125f);
+        const int m = job.p_out[(int64_t)hk * D + col] & (D - 1);
+        const float post = job.s_out[(int64_t)hk * D + col] * (D == 128 ? 0.08838834764831845f : 0.125f);
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -798,7 +805,7 @@ FEDRAG_KERNEL __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f
                 phi[j][e] = structured_entry(s_in[k], p_in_inv[k], m) * post;
             }
     } else {
-        const float* P = (const float*)job.Phi + (int64_t)(h / G) * D * D;
+        const float* P = (const float*)job.Phi + (int64_t)hk * D * D;
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -880,7 +887,7 @@ FEDRAG_KERNEL __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f
 // data-parallel moves; the two gathers go through LDS, within a wave.  Every load but those of rows that wait for their indices is
 // asked for at once.
 // Dec, always: the fp32 product was bound by the fp32 matrix pipe or, for few rows, by its chain of waits; this is bound by memory
-// or by the launch (32 heads of 128: 1 row 3.3 -> 2.9 us, 16 7.1 -> 2.9, 117 6.4 -> 3.2, 1000 17.2 -> 7.5, 4096 47 -> 23; of 64 2.5 -> 2.4,
+// or by the launch, whose arguments are one trip to memory (117 rows 3.2 -> 3.05) (32 heads of 128: 1 row 3.3 -> 2.9 us, 16 7.1 -> 2.9, 117 6.4 -> 3.2, 1000 17.2 -> 7.5, 4096 47 -> 23; of 64 2.5 -> 2.4,
 // 4.4 -> 2.6, 5.0 -> 2.7, 7.8 -> 4.9, 20.3 -> 12.0).  Its sums of 128 are seven roundings deep.
 // Queries in 16 bits: heads of at most kHadSlab rows, where a tile of the product is mostly padding or its matrix is all it does
 // (32 heads of 128: 4 rows 3.8 -> 3.0 us, 16 6.3 -> 3.0, 256 x 32 69.6 -> 26.1, x 64 75 -> 49; of 64 3.0 -> 2.5, 4.2 -> 2.6, 30.4 -> 16.6,
@@ -905,6 +912,9 @@ FEDRAG_KERNEL __launch_bounds__(kHadThreads) void hadamard_rows_kernel(ScrambleJ
     typedef elem chunk_t __attribute__((ext_vector_type(EPC)));
     typedef int32_t keys_t __attribute__((ext_vector_type(4), aligned(4)));  // key arrays are dword-aligned
     __shared__ __attribute__((aligned(16))) float rows[kHadRows][LDP];
+    FEDRAG_HAVE_HERE(FEDRAG_S(job.X), FEDRAG_S(job.Y), FEDRAG_S(job.s_in), FEDRAG_S(job.p_in), FEDRAG_S(job.p_out), FEDRAG_S(job.s_out),
+                     FEDRAG_S(perm), FEDRAG_S(perm_batch_stride), FEDRAG_S3(by_chunks), FEDRAG_S3(by_heads), FEDRAG_S3(by_group), FEDRAG_S(L),
+                     FEDRAG_S(steps_per_wg));
     const int tid = threadIdx.x, rl = tid / 16, l = tid % 16;
     const int bh = (int)by_chunks.div(blockIdx.x), chunk = (int)blockIdx.x - bh * (int)by_chunks.d;
     const int b = (int)by_heads.div(bh), h = bh - b * (int)by_heads.d;
@@ -1164,8 +1174,8 @@ static hipError_t launch_rows_mfma_f32(const RowsJob& j, hipStream_t stream) {
     if constexpr (SCATTER) {
         if (j.merge.lse_in) kernel = rows_times_matrix_mfma_f32_kernel<D, true, false, true, RT>;
     }
-    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, a, b, j.perm, j.perm_batch_stride, j.H, j.G, j.L, chunks, spw,
-                       j.merge);
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, a, b, j.perm, j.perm_batch_stride, FastDiv(j.H), FastDiv(j.G), j.L,
+                       FastDiv(chunks), spw, j.merge);
     return hipGetLastError();
 }
 
