@@ -164,8 +164,8 @@ constexpr int64_t dec_single_tile_run(int d) { return d == 128 ? 1024 : 256; }  
 // for its number of workgroups or for shorter ones, what counts is again what a compute unit takes by itself (33 x 4096 131 us and 116).
 constexpr int64_t kDecLongRun = 2048;
 
-template <class T, int D, int QB, int NS>
-FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : NS * D > 0 && NS * D <= 128 ? 2 : 1) void decode_attn_kernel(const typename T::elem* __restrict__ Q,
+template <class T, int D, int QB, int NS, int WAVES>
+FEDRAG_KERNEL __launch_bounds__(WAVES * kWave, QB == 4 ? kDecCodesOcc : NS * D > 0 && NS * D <= 128 ? 2 : 1) void decode_attn_kernel(const typename T::elem* __restrict__ Q,
                                                                      const KeyRuns runs,
                                                                      const float* __restrict__ Kprm,
                                                                      const float* __restrict__ Vprm, int R,
@@ -192,10 +192,10 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : NS * D > 0
     constexpr int OROW = (D + 4) * 4;  // bytes
     constexpr int SLOT = LDS ? TILEB : 8 * OROW;
     static_assert(SLOT >= 8 * OROW, "eight rows of outputs fit a slot");
-    __shared__ __attribute__((aligned(16))) char ks0[kDecWaves][SLOT], vs0[kDecWaves][SLOT];
-    __shared__ __attribute__((aligned(16))) char ks1[kDecWaves][NS == 2 ? SLOT : 16], vs1[kDecWaves][NS == 2 ? SLOT : 16];
-    __shared__ float sm_m[kDecWaves][16];
-    __shared__ float sm_l[kDecWaves][16];
+    __shared__ __attribute__((aligned(16))) char ks0[WAVES][SLOT], vs0[WAVES][SLOT];
+    __shared__ __attribute__((aligned(16))) char ks1[WAVES][NS == 2 ? SLOT : 16], vs1[WAVES][NS == 2 ? SLOT : 16];
+    __shared__ float sm_m[WAVES][16];
+    __shared__ float sm_l[WAVES][16];
     auto out_row = [&](int w, int n) { return (float*)((n < 8 ? ks0[w] : vs0[w]) + n % 8 * OROW); };
 
     const int tid = threadIdx.x;
@@ -518,17 +518,17 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : NS * D > 0
     if constexpr (LDS) {
         const int64_t n_keys = k_end - k_begin;
         const int n_tiles = (int)((n_keys + kDecTile - 1) / kDecTile);  // the ragged one among them
-        const int n_mine = n_tiles > wave ? (n_tiles - wave + kDecWaves - 1) / kDecWaves : 0;
+        const int n_mine = n_tiles > wave ? (n_tiles - wave + WAVES - 1) / WAVES : 0;
         const int ragged = n_keys % kDecTile ? n_tiles - 1 : -1;  // rows past its end arrive as zeros and are masked
         char *k0 = ks0[wave], *v0 = vs0[wave], *k1 = ks1[wave], *v1 = vs1[wave];
         // i-th tile of this wave out of a set of slots, with `others` sets asked for after it
         auto turn = [&](int i, auto set, auto others, auto reload) {
             constexpr int N = 2 * KL * decltype(others)::value;
             constexpr bool more = decltype(reload)::value;
-            const int tile = wave + i * kDecWaves;
+            const int tile = wave + i * WAVES;
             Tile none;
             wait_loads(std::integral_constant<int, N + KL>{});
-            step(none, k_begin + (int64_t)tile * kDecTile, tile == ragged, more, tile + NS * kDecWaves,
+            step(none, k_begin + (int64_t)tile * kDecTile, tile == ragged, more, tile + NS * WAVES,
                  decltype(set)::value ? k1 : k0, decltype(set)::value ? v1 : v0, std::integral_constant<int, N + (more ? KL : 0)>{});
         };
         std::integral_constant<int, 0> c0;
@@ -539,8 +539,8 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : NS * D > 0
             fill(wave, k0, true);
             fill(wave, v0, false);
             if constexpr (NS == 2) {
-                fill(wave + kDecWaves, k1, true);  // (nothing if there is none)
-                fill(wave + kDecWaves, v1, false);
+                fill(wave + WAVES, k1, true);  // (nothing if there is none)
+                fill(wave + WAVES, v1, false);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -572,8 +572,8 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : NS * D > 0
     } else {
         const int64_t n_keys = k_end - k_begin;
         const int n_full_all = (int)(n_keys / kDecTile);  // full tiles in the split
-        const int n_mine = (n_full_all > wave) ? (n_full_all - wave + kDecWaves - 1) / kDecWaves : 0;
-        auto tile_of = [&](int i) { return wave + i * kDecWaves; };  // i-th tile of this wave
+        const int n_mine = (n_full_all > wave) ? (n_full_all - wave + WAVES - 1) / WAVES : 0;
+        auto tile_of = [&](int i) { return wave + i * WAVES; };  // i-th tile of this wave
         auto tile_key = [&](int i) { return k_begin + (int64_t)tile_of(i) * kDecTile; };
         Tile t[NBUF];
 #pragma unroll
@@ -599,7 +599,7 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : NS * D > 0
             if (i + NBUF + j < n_mine) step(t[j], tile_key(i + NBUF + j), false, false, 0, nullptr, nullptr, 0);
         // ragged tail of the split (fewer than 32 keys): the wave whose turn it is takes it
         const int rem = (int)(n_keys % kDecTile);
-        if (rem > 0 && (n_full_all % kDecWaves) == wave) {
+        if (rem > 0 && (n_full_all % WAVES) == wave) {
             const int64_t key0 = k_begin + (int64_t)n_full_all * kDecTile;
             load_clamped(key0, t[0]);
             step(t[0], key0, true, false, 0, nullptr, nullptr, 0);
@@ -639,17 +639,17 @@ FEDRAG_KERNEL __launch_bounds__(kDecThreads, QB == 4 ? kDecCodesOcc : NS * D > 0
         const int v = q_len;
         q_rows = v < 0 ? 0 : (v < Lq ? v : Lq);
     }
-    for (int idx = tid; idx < R * (D / 4); idx += kDecThreads) {
+    for (int idx = tid; idx < R * (D / 4); idx += WAVES * kWave) {
         const int n = idx / (D / 4);
         const int d = idx % (D / 4) * 4;
         if (q_lens && n % Lq >= q_rows) continue;
         float M = sm_m[0][n];
 #pragma unroll
-        for (int w = 1; w < kDecWaves; ++w) M = fmaxf(M, sm_m[w][n]);
+        for (int w = 1; w < WAVES; ++w) M = fmaxf(M, sm_m[w][n]);
         f32x4_t num = zero_vec<f32x4_t>();
         float den = 0.f;
 #pragma unroll
-        for (int w = 0; w < kDecWaves; ++w) {
+        for (int w = 0; w < WAVES; ++w) {
             const float a = exp2_diff(sm_m[w][n], M);
             const f32x4_t o = *(const f32x4_t*)(out_row(w, n) + d);
 #pragma unroll
@@ -684,7 +684,6 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
         Odst = (float*)p.workspace;
         Ldst = Odst + (size_t)splits * rows * D;
     }
-    if (!grid_fits(units * splits, kDecThreads)) return hipErrorInvalidValue;
     int64_t longest = 0, total = 0;
     for (int i = 0; i < runs.n_shards; ++i) {
         total += runs.s[i].L;
@@ -697,12 +696,22 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
         tiles = longest <= kDecStride || (wgs > cus && longest <= dec_single_tile_run(D)) ? 1 : 2;
         if (D == 128 && longest >= kDecLongRun && units * total * 10 >= rounds * cus * longest * 9) tiles = 0;
     }
-    auto kernel = decode_attn_kernel<T, D, QB, QB == 0 && D == 64 ? 2 : 0>;
+    auto kernel = decode_attn_kernel<T, D, QB, QB == 0 && D == 64 ? 2 : 0, kDecWaves>;
+    int threads = kDecThreads;
     if constexpr (QB == 0) {
-        if (tiles == 1) kernel = decode_attn_kernel<T, D, 0, 1>;
-        if (tiles == 2) kernel = decode_attn_kernel<T, D, 0, 2>;
+        if (tiles == 1) kernel = decode_attn_kernel<T, D, 0, 1, kDecWaves>;
+        if (tiles == 2) kernel = decode_attn_kernel<T, D, 0, 2, kDecWaves>;
+        // Two tiles a wave and no more, on compute units of their own: eight waves with one tile each instead, whose loads are out at
+        // once and whose chain of products is half as long (129 keys x 8 heads 4.8 -> 4.3 us, 192 4.9 -> 4.3, 256 5.5 -> 5.2, 1000 in
+        // four runs 7.9 -> 7.65).  From some 300 keys on the two are within 1 %, at d = 64, whose tiles are half the bytes, this loses 2 to 5 %.
+        if constexpr (D == 128)
+            if (tiles == 2 && longest <= 2 * kDecStride) {
+                kernel = decode_attn_kernel<T, D, 0, 1, 2 * kDecWaves>;
+                threads = 2 * kDecThreads;
+            }
     }
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(units * splits)), dim3(kDecThreads), 0, stream, (const elem*)p.Q, runs,
+    if (!grid_fits(units * splits, threads)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(units * splits)), dim3(threads), 0, stream, (const elem*)p.Q, runs,
                        p.K_params, p.V_params, R, scale_log2, Odst, Ldst, rows, p.kv_lens, p.q_lens, (int)p.Lq, FastDiv(p.Hkv));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
