@@ -3,7 +3,7 @@
 // HBM-bound: every K'/V' byte of the shard is read exactly once and nothing is reused, so the kernel is built around keeping
 // whole rows in flight.
 //
-// One workgroup = one unit x one split of the shard's keys; its four waves take 32-key tiles round-robin.
+// One workgroup = one unit x one split of the shard's keys; its four (or eight) waves take 32-key tiles round-robin.
 // Lane l of a wave: lr = l % 16, lq = l / 16.
 //   S^T tile (32 keys x 16 queries) = K'(32 x d) . Q'^T(d x 16): two 16-key MFMA tiles; this lane ends up with
 //   query lr and keys {16 mt + 4 lq + r}.  Those eight keys are also this lane's contraction slice of
@@ -512,7 +512,7 @@ FEDRAG_KERNEL __launch_bounds__(WAVES * kWave, QB == 4 ? kDecCodesOcc : NS * D >
         }
     };
 
-    // Wave w owns tiles w, w+4, ... of the split.  NS sets of slots (codes: NBUF register tile sets) form a ring: a set is refilled with
+    // Wave w owns tiles w, w + WAVES, ... of the split.  NS sets of slots (codes: NBUF register tile sets) form a ring: a set is refilled with
     // the tile NBUF steps ahead as soon as it has been consumed.  In the steady-state loop every refill is
     // unconditional, so the in-order load counter can be waited on precisely (oldest tile only).
     if constexpr (LDS) {

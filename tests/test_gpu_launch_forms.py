@@ -290,8 +290,7 @@ def test_aggregation_of_partials_without_a_number(S):
     assert bool((got[0, 0, ::2] == 1).all())
 
 
-# one run up to 512 keys, 256-key runs up to 2048 in all where those are one round, 512-key runs otherwise; one tile set up to
-# 1024 keys per run
+# one run up to 512 keys, 256-key runs up to 2048 in all where those are one round, 512-key runs otherwise
 @pytest.mark.parametrize("Ls", [[31], [512], [513], [2047], [2049], [400, 700], [300, 0, 213], [9000]])
 @pytest.mark.parametrize("d", [64, 128])
 def test_decode_key_runs(oracle, Ls, d):
