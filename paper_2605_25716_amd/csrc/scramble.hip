@@ -1020,8 +1020,9 @@ FEDRAG_KERNEL __launch_bounds__(kHadThreads) void hadamard_rows_kernel(ScrambleJ
         for (int c = 0; c < NC; ++c)
 #pragma unroll
             for (int e = 0; e < EPC; ++e) {
-                // a sum of zeros is +0, as it is out of a product that starts there
-                float v = (my[g_out[c * EPC + e]] + 0.0f) * post[c * EPC + e];
+                // Zeros have the sign that the products give them, whose sums start at +0: in 16 bits before the scale, in fp32 behind it.
+                const float sum = my[g_out[c * EPC + e]];
+                float v = SCATTER ? __builtin_fmaf(sum, post[c * EPC + e], 0.0f) : (sum + 0.0f) * post[c * EPC + e];
                 pin_here(v);  // rounded before it is narrowed
                 y[c][e] = T::from_float(v);
             }

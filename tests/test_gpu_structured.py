@@ -143,6 +143,30 @@ def test_structured_rows_of_special_values(d, dt):
     assert torch.equal(a[0, :, 3:5][torch.isinf(a[0, :, 3:5])], b[0, :, 3:5][torch.isinf(b[0, :, 3:5])])
 
 
+@pytest.mark.parametrize("L", [1, 33])
+@pytest.mark.parametrize("d", [64, 128])
+def test_structured_dec_of_special_values(d, L):
+    """Zeros of either sign give +0 in every column, whatever the sign of its scale, as a sum of products that starts at +0 does;
+    an infinity reaches every column, a NaN too, and two infinities are NaN where they meet with opposite signs."""
+    a, g1, g2, b = W.make_structured_keys(2, d, L, 8, 1, seed=8, dtype=torch.float32, pow2=True).v_inv
+    assert bool((b < 0).any())
+    X = torch.from_numpy(np.random.default_rng(d).standard_normal((1, 8, L, d))).float()
+    X[0, 0], X[0, 1], X[0, 2] = 0.0, -0.0, torch.tensor([0.0, -0.0]).repeat(d // 2)
+    X[0, 3, 0, 5], X[0, 4, 0, 9], X[0, 5, 0, 3] = float("inf"), float("-inf"), float("nan")
+    X[0, 6, 0, 3], X[0, 6, 0, 12] = float("inf"), float("inf")
+    Y = fb.fedrag_unscramble_structured(X.to(DEV), dev_key((a, g1, g2, b)), None)
+    torch.cuda.synchronize()
+    Y = Y.cpu()
+    assert bool((Y[0, :3] == 0).all()) and not bool(torch.signbit(Y[0, :3]).any())
+    H = torch.from_numpy(W.sylvester_hadamard(d)).double()
+    dense = torch.stack([a[h].double()[:, None] * H[torch.argsort(g1[h].long())][:, g2[h].long()] * b[h].double()
+                         for h in range(2)]).repeat_interleave(4, 0)
+    for h in (3, 4, 5, 6):
+        rows = X[0, h, 0].double()
+        ref = (rows[:, None] * dense[h]).sum(0)
+        assert torch.equal(torch.isnan(Y[0, h, 0]), torch.isnan(ref)), h
+        assert torch.equal(Y[0, h, 0][torch.isinf(ref)].double(), ref[torch.isinf(ref)]), h
+
 
 @pytest.mark.parametrize("outliers", [False, True], ids=["gaussian", "outlier_channels"])
 @pytest.mark.parametrize("L", [128, 512, 2048])
