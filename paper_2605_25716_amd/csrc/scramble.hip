@@ -899,6 +899,7 @@ constexpr int64_t kHadSlab = 64, kHadTotal = 48 << 10;
 constexpr int64_t kHadWgs = 2048;   // workgroups, eight to a compute unit, from where on one takes several steps
 constexpr int kHadRows = 16;        // rows per workgroup step
 constexpr int kHadThreads = 16 * kHadRows;
+constexpr float kHadLeast = 0x1p-100f;  // terms of sums above it have all their bits that count
 template <class T, int D, bool SCATTER>
 FEDRAG_KERNEL __launch_bounds__(kHadThreads) void hadamard_rows_kernel(ScrambleJob job, const int32_t* __restrict__ perm,
                                                                        int64_t perm_batch_stride, FastDiv by_chunks, FastDiv by_heads,
@@ -1015,6 +1016,16 @@ FEDRAG_KERNEL __launch_bounds__(kHadThreads) void hadamard_rows_kernel(ScrambleJ
             *(f32x4_t*)(my + E * a + q) = v;
         }
         wave_lds_fence();
+        float out_of_range = 0.f, most = 0.f;  // NaN where a sum is not finite; the largest sum
+        if constexpr (SCATTER) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                out_of_range = __builtin_fmaf(z[e], 0.f, out_of_range);
+                most = fmaxf(most, fabsf(z[e]));
+            }
+            out_of_range = most < kHadLeast ? 1.f : out_of_range;
+            pin_here(out_of_range);  // (the sums would be kept for it)
+        }
         chunk_t y[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c)
@@ -1031,6 +1042,36 @@ FEDRAG_KERNEL __launch_bounds__(kHadThreads) void hadamard_rows_kernel(ScrambleJ
             for (int c = 0; c < NC; ++c) *(chunk_t*)(Y + to * D + natural(c)) = y[c];
         }
         wave_lds_fence();
+        if constexpr (SCATTER) {
+            // The products have both of a key's scales in every term.  Here a sum may pass the range that its column's scale would bring it
+            // back into, or lose bits below it: rows with a sum that is not finite, or none above kHadLeast, are formed again, column by column
+            // in 64 bits, and stored over.  (A row that holds an infinity comes out the same; one of zeros is left.)
+            if (__builtin_expect(__any(out_of_range != 0.f), 0)) {
+                load(j < L ? j : L - 1, x);
+                float in = 0.f;
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int e = 0; e < EPC; ++e) in = fmaxf(in, fabsf(x[c][e]));
+                in = group_max<16>(in);
+                const bool again = group_max<16>(out_of_range == out_of_range ? 0.f : 1.f) > 0.f || group_max<16>(most) < kHadLeast;
+                if (again && in > 0.f && j < L) {
+#pragma unroll 1
+                    for (int e = 0; e < E; ++e) {  // what this lane has stored
+                        const int c = natural(e / EPC) + e % EPC, m = job.p_out[at + c] & (D - 1);
+                        double sum = 0.0;
+#pragma unroll 1
+                        for (int i = 0; i < D; ++i) {
+                            const int k = job.p_in[at + i] & (D - 1);
+                            const double t = (double)X[j * D + k] * (double)job.s_in[at + k];
+                            sum += __popc(i & m) & 1 ? -t : t;
+                        }
+                        Y[to * D + c] = (float)(sum * ((double)job.s_out[at + c] * (D == 128 ? 0.08838834764831845 : 0.125)) + 0.0);
+                    }
+                }
+                load(row_of(s + 1), x);  // as it was
+            }
+        }
     }
 }
 

@@ -168,6 +168,35 @@ def test_structured_dec_of_special_values(d, L):
         assert torch.equal(Y[0, h, 0][torch.isinf(ref)].double(), ref[torch.isinf(ref)]), h
 
 
+@pytest.mark.parametrize("L", [1, 33])
+@pytest.mark.parametrize("d", [64, 128])
+def test_structured_dec_keeps_the_range_of_its_outputs(oracle, d, L):
+    """What comes out below 3.4e38 is finite, and what comes out normal has all its bits, wherever the key's scales would take the
+    sums: each term of a column is formed with both scales in it.  Six additions of 2^-24 of all terms (seven at d = 128) and the scales."""
+    H = 4
+    _, g1, g2, _ = W.make_structured_keys(H, d, L, 8, 1, seed=12, dtype=torch.float32, pow2=True).v_inv
+    r = np.random.default_rng(d + L)
+    ones, rnd = torch.ones(H, d), torch.from_numpy(r.uniform(0.5, 1.0, (2, H, L, d))).float()
+    one = ones.clone()
+    one[torch.arange(H), (g2 == 0).long().argmax(1)] = 2.0 ** -12  # the column that takes the sum of all
+    const = torch.ones(2, H, L, d)
+    for name, a, b, X in (("by 1 / sqrt(d)", ones, ones, rnd * (2.0e38 / d ** 0.5)), ("eight and an eighth", 8 * ones, ones / 8, rnd * (2.0e38 / d ** 0.5)),
+                          ("far apart", ones * 2.0 ** 70, ones * 2.0 ** -70, rnd * (2.0e38 / d ** 0.5)),
+                          ("apart below", ones * 2.0 ** -100, ones * 2.0 ** 100, rnd * 2.0 ** -40),
+                          ("one small column", ones, one, const * 1e38), ("of one row", ones, one, const)):
+        if name == "of one row":
+            X = const.clone()
+            X[:, :, L // 2] = 1e38
+        key = tuple(t.contiguous() for t in (a, g1, g2, b))
+        ref = oracle.structured(X, key, None, scatter=True)
+        assert np.abs(ref).max() < 3.3e38, name
+        Y = fb.fedrag_unscramble_structured(X.to(DEV), dev_key(key), None)
+        torch.cuda.synchronize()
+        Y = PT.f64(Y)
+        assert np.isfinite(Y).all(), name
+        assert (np.abs(Y - ref) <= 1e-6 * np.matmul(np.abs(PT.f64(X)), abs_dense(key, d)[None])).all(), name
+
+
 @pytest.mark.parametrize("outliers", [False, True], ids=["gaussian", "outlier_channels"])
 @pytest.mark.parametrize("L", [128, 512, 2048])
 def test_stability_structured_against_dense_random(oracle, L, outliers):
