@@ -164,7 +164,9 @@ constexpr int64_t dec_single_tile_run(int d) { return d == 128 ? 1024 : 256; }  
 // for its number of workgroups or for shorter ones, what counts is again what a compute unit takes by itself (33 x 4096 131 us and 116).
 constexpr int64_t kDecLongRun = 2048;
 
-template <class T, int D, int QB, int NS, int WAVES>
+// PARTS: a run is summed part by part, `part` tiles of a wave at a time (KeyRuns::part).  A form of its own: the check in the loop and
+// the second set of accumulators take 0 to 4 % of a launch on codes.
+template <class T, int D, int QB, int NS, int WAVES, bool PARTS>
 FEDRAG_KERNEL __launch_bounds__(WAVES * kWave, QB == 4 ? kDecCodesOcc : NS * D > 0 && NS * D <= 128 ? 2 : 1) void decode_attn_kernel(const typename T::elem* __restrict__ Q,
                                                                      const KeyRuns runs,
                                                                      const float* __restrict__ Kprm,
@@ -173,7 +175,7 @@ FEDRAG_KERNEL __launch_bounds__(WAVES * kWave, QB == 4 ? kDecCodesOcc : NS * D >
                                                                      float* __restrict__ lse, int64_t total_rows,
                                                                      const int32_t* __restrict__ kv_lens,
                                                                      const int32_t* __restrict__ q_lens, int Lq,
-                                                                     FastDiv by_hkv) {
+                                                                     FastDiv by_hkv, int part) {
     typedef typename T::elem elem;
     typedef typename T::vec8 vec8;
     typedef DecTile<T, D, QB> Tile;
@@ -206,7 +208,7 @@ FEDRAG_KERNEL __launch_bounds__(WAVES * kWave, QB == 4 ? kDecCodesOcc : NS * D >
     // The arguments are one trip to memory and the shard a second one, where branches and addresses made five of them: a token's
     // attention in a request over 32 layers, 24.9 -> 24.4 us a layer; 128 keys 3.72 -> 3.66 us; long runs even.
     FEDRAG_HAVE_HERE(FEDRAG_S3(runs.by_runs), FEDRAG_S(runs.n_shards), FEDRAG_S(Q), FEDRAG_S(R), FEDRAG_S(scale_log2), FEDRAG_S(O),
-                     FEDRAG_S(lse), FEDRAG_S(total_rows), FEDRAG_S(kv_lens), FEDRAG_S(q_lens), FEDRAG_S(Lq), FEDRAG_S3(by_hkv));
+                     FEDRAG_S(lse), FEDRAG_S(total_rows), FEDRAG_S(kv_lens), FEDRAG_S(q_lens), FEDRAG_S(Lq), FEDRAG_S3(by_hkv), FEDRAG_S(part));
     const int64_t unit = runs.by_runs.div(blockIdx.x);
     const int run = (int)runs.by_runs.mod(blockIdx.x);  // index of this workgroup's partial
     int split;
@@ -256,6 +258,31 @@ FEDRAG_KERNEL __launch_bounds__(WAVES * kWave, QB == 4 ? kDecCodesOcc : NS * D >
 #pragma unroll
     for (int i = 0; i < DCH; ++i) acc_o[i] = zero_vec<f32x4_t>();
     float m_run = -INFINITY, l_run = 0.f;
+    // PARTS: what a wave has put aside, outputs, sums and their maximum.  Every addition to it halves what is there, by a maximum above
+    // both, so that the parts together pass fp32's range no sooner than one of them.
+    f32x4_t part_o[PARTS ? DCH : 1];
+    float m_part = -INFINITY, l_part = 0.f;
+    int part_end = part;
+#pragma unroll
+    for (int i = 0; i < (PARTS ? DCH : 1); ++i) part_o[i] = zero_vec<f32x4_t>();
+    auto put_aside = [&]() {
+        if constexpr (PARTS) {
+            const float M = fmaxf(m_part, m_run) + 1.0f;
+            const float a = exp2_diff(m_part, M), b = exp2_diff(m_run, M);
+#pragma unroll
+            for (int i = 0; i < DCH; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    part_o[i][e] = __builtin_fmaf(acc_o[i][e], b, part_o[i][e] * a);
+                    acc_o[i][e] = 0.f;
+                }
+            l_part = __builtin_fmaf(l_run, b, l_part * a);
+            m_part = M;
+            l_run = 0.f;
+            m_run = -INFINITY;
+            part_end += part;
+        }
+    };
 
     const int64_t split_bytes = (k_end - k_begin) * ROWB;  // < 2^31, guaranteed by the split planner
     // Registers: per-lane byte offsets inside a 32-key tile, and buffer resources based at the split's first key: the address is
@@ -557,6 +584,7 @@ FEDRAG_KERNEL __launch_bounds__(WAVES * kWave, QB == 4 ? kDecCodesOcc : NS * D >
                 for (; i + 4 <= n_mine; i += 2) {
                     turn(i, c0, c1, refill);
                     turn(i + 1, c1, c1, refill);
+                    if (PARTS && i + 2 >= part_end) put_aside();
                 }
                 if (n_mine - i == 3) {
                     turn(i, c0, c1, refill);
@@ -585,6 +613,7 @@ FEDRAG_KERNEL __launch_bounds__(WAVES * kWave, QB == 4 ? kDecCodesOcc : NS * D >
             for (int j = 0; j < NBUF; ++j) {
                 step(t[j], tile_key(i + j), false, true, tile_of(i + j + NBUF), nullptr, nullptr, 0);
             }
+            if (PARTS && i + NBUF >= part_end) put_aside();
         }
         // fewer than 2*NBUF tiles left: refills become conditional, then the ring drains
 #pragma unroll
@@ -606,6 +635,13 @@ FEDRAG_KERNEL __launch_bounds__(WAVES * kWave, QB == 4 ? kDecCodesOcc : NS * D >
         }
     }
 
+    if constexpr (PARTS) {
+        put_aside();
+#pragma unroll
+        for (int i = 0; i < DCH; ++i) acc_o[i] = part_o[i];
+        m_run = m_part;
+        l_run = l_part;
+    }
     // fold the four waves (Section 4.1 aggregation, in base 2); a thread finishes 4 columns of a row, so that the
     // fold of a short launch is one pass of 16-byte LDS reads
     const float l_tot = xor32_sum(xor16_sum(l_run));
@@ -696,23 +732,25 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
         tiles = longest <= kDecStride || (wgs > cus && longest <= dec_single_tile_run(D)) ? 1 : 2;
         if (D == 128 && longest >= kDecLongRun && units * total * 10 >= rounds * cus * longest * 9) tiles = 0;
     }
-    auto kernel = decode_attn_kernel<T, D, QB, QB == 0 && D == 64 ? 2 : 0, kDecWaves>;
+    constexpr int kRegisters = QB == 0 && D == 64 ? 2 : 0;  // (16 bits of 64 columns have no such form)
+    const int part = (int)((runs.part + kDecStride - 1) / kDecStride) & ~1;  // a wave's tiles of it, which are taken in pairs
+    auto kernel = runs.part ? decode_attn_kernel<T, D, QB, kRegisters, kDecWaves, true> : decode_attn_kernel<T, D, QB, kRegisters, kDecWaves, false>;
     int threads = kDecThreads;
     if constexpr (QB == 0) {
-        if (tiles == 1) kernel = decode_attn_kernel<T, D, 0, 1, kDecWaves>;
-        if (tiles == 2) kernel = decode_attn_kernel<T, D, 0, 2, kDecWaves>;
+        if (tiles == 1) kernel = decode_attn_kernel<T, D, 0, 1, kDecWaves, false>;  // (runs that were not cut anew)
+        if (tiles == 2) kernel = runs.part ? decode_attn_kernel<T, D, 0, 2, kDecWaves, true> : decode_attn_kernel<T, D, 0, 2, kDecWaves, false>;
         // Two tiles a wave and no more, on compute units of their own: eight waves with one tile each instead, whose loads are out at
         // once and whose chain of products is half as long (129 keys x 8 heads 4.8 -> 4.3 us, 192 4.9 -> 4.3, 256 5.5 -> 5.2, 1000 in
         // four runs 7.9 -> 7.65).  From some 300 keys on the two are within 1 %, at d = 64, whose tiles are half the bytes, this loses 2 to 5 %.
         if constexpr (D == 128)
             if (tiles == 2 && longest <= 2 * kDecStride) {
-                kernel = decode_attn_kernel<T, D, 0, 1, 2 * kDecWaves>;
+                kernel = decode_attn_kernel<T, D, 0, 1, 2 * kDecWaves, false>;
                 threads = 2 * kDecThreads;
             }
     }
     if (!grid_fits(units * splits, threads)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(units * splits)), dim3(threads), 0, stream, (const elem*)p.Q, runs,
-                       p.K_params, p.V_params, R, scale_log2, Odst, Ldst, rows, p.kv_lens, p.q_lens, (int)p.Lq, FastDiv(p.Hkv));
+                       p.K_params, p.V_params, R, scale_log2, Odst, Ldst, rows, p.kv_lens, p.q_lens, (int)p.Lq, FastDiv(p.Hkv), part > 2 ? part : 2);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
     return launch_lse_merge(Odst, Ldst, splits, rows, D, p.O, p.lse, stream, p.q_lens, p.Lq, (int64_t)p.Hq * p.Lq);

@@ -127,6 +127,7 @@ struct KeyRuns {
     FastDiv by_runs;  // n_runs (1 when there is none)
     int first[kMaxShards + 1];
     KeyShard s[kMaxShards];
+    int64_t part;  // streaming kernel: keys of a run that are summed by themselves, where the launch made runs longer than the plan's; else 0
     // The shard that run `run` (0 <= run < n_runs) belongs to; *split = index of the run inside it.  All of first[] is
     // read at once and counted (one compare after the other, each waiting for its own scalar load, kept a short
     // kernel from starting for 1.5 us); a single shard needs none of it.

@@ -1,7 +1,8 @@
 // The host's choice of a prefill launch's form, looked at without a device (no call here enqueues anything).  Commands on stdin,
 // one answer a line:
 //   form B Hq Hkv d dtype Lq n L... / codes B Hq Hkv d dtype Lq 1 L (4 bits)   ->  kind four n_runs past_l2   (kind: 0 plain, 1 shards in turn, 2 two key groups)
-//   decode B Hq Hkv d dtype Lq n L... / decode4 (4-bit codes)  ->  n_runs, keys that the runs cover, longest run, runs the workspace holds
+//   decode B Hq Hkv d dtype Lq n L... / decode4 (4-bit codes)  ->  n_runs, keys that the runs cover, longest run, runs the workspace
+//       holds, longest run of the plan, keys of a part (0: runs are summed in one go), runs of the plan
 //   runs from most n L...             ->  keys a run by halving, by trying every length in turn
 //   time B Hq Hkv d dtype Lq n L...   ->  microseconds a choice takes, the least of many
 #include <algorithm>
@@ -63,7 +64,10 @@ int main() {
                 longest = std::max<long>(longest, keys);
             }
             const size_t bytes = attn_workspace_bytes(p.B, p.Hq, p.Hkv, p.D, p.dtype, p.Lq, p.n_shards, p.Ls);
-            std::printf("%d %ld %ld %ld\n", r.n_runs, covered, longest, (long)(bytes / ((size_t)p.B * p.Hq * p.Lq * (p.D + 1) * 4)));
+            const KeyRuns plan = attn_plan_runs(p.B, p.Hq, p.Hkv, p.dtype, p.Lq, p.n_shards > 1 ? p.n_shards : 1, p.n_shards > 1 ? p.Ls : &p.Lkv, p.quant_bits == 4);
+            long planned = 0;
+            for (int i = 0; i < plan.n_shards; ++i) planned = std::max<long>(planned, std::min(plan.s[i].per, plan.s[i].L));
+            std::printf("%d %ld %ld %ld %ld %ld %d\n", r.n_runs, covered, longest, (long)(bytes / ((size_t)p.B * p.Hq * p.Lq * (p.D + 1) * 4)), planned, (long)r.part, plan.n_runs);
         } else if (!std::strcmp(what, "runs")) {
             long from, most;
             int n;

@@ -539,9 +539,17 @@ def test_decode_launches_make_one_round(launch_forms):
     for what, round_ in (("decode", 256), ("decode4", 512)):
         cases = [(B, d, Ls) for B, d, Ls in shapes if what == "decode" or (len(Ls) == 1 and d == 128)]
         got = launch_forms([f"{what} {B} 32 8 {d} {fb.BF16} 1 {len(Ls)} " + " ".join(map(str, Ls)) for B, d, Ls in cases])
-        for (B, d, Ls), (runs, covered, longest, held) in zip(cases, got):
+        for (B, d, Ls), (runs, covered, longest, held, planned, part, plan_runs) in zip(cases, got):
             assert covered == sum(Ls) and runs <= max(held, 1), (what, B, d, Ls, runs, held)
             assert 8 * B * runs <= round_ or 8 * B > round_ or len(Ls) > 1, (what, B, d, Ls, runs)
+            # a run is addressed in 32 bits, takes no longer than the rounds that the plan would make, and is summed in parts that
+            # are no longer than the plan's runs
+            rounds = -(-8 * B * plan_runs // round_)
+            assert longest <= min(2 ** 22, max(rounds, 1) * planned), (what, B, d, Ls, longest, planned)
+            assert (part == 0) == (longest <= planned) and part <= planned, (what, B, d, Ls, longest, planned, part)
+    from test_gpu_launch_forms import CUT_ANEW
+    cut = launch_forms([f"decode{4 if bits == 4 else ''} {B} 16 8 {d} {fb.BF16} 1 {len(Ls)} " + " ".join(map(str, Ls)) for B, d, bits, Ls in CUT_ANEW])
+    assert all(0 < part <= planned < longest for _, _, longest, _, planned, part, _ in cut), cut
     assert [g[0] for g in launch_forms([f"decode {B} 32 8 128 {fb.BF16} 1 1 8192" for B in (1, 3, 9, 16, 17, 33)])] == [16, 10, 3, 2, 1, 1]
     several = [(5, [4001, 3277, 300]), (9, [4096, 4096]), (9, [4001, 3277, 300]), (20, [4001, 3277, 300])]
     assert [g[0] for g in launch_forms([f"decode {B} 32 8 128 {fb.BF16} 1 {len(Ls)} " + " ".join(map(str, Ls)) for B, Ls in several])] == [6, 2, 6, 4]

@@ -325,6 +325,73 @@ def test_decode_tile_forms(oracle, B, L, d, dt):
         PT.check_attn(O, lse, Or, lr, Q.dtype, f"{B} {L} {d}")
 
 
+# launches cut into fewer, longer runs than planned, which are summed in parts (that they are cut is held on the host, by
+# test_boundary_cpu.py): two tiles of LDS per wave, registers, codes; several shards; one part, two, and a ragged end
+CUT_ANEW = [(9, 128, 0, [2001]), (9, 64, 0, [2300]), (31, 128, 0, [2100]), (5, 128, 0, [4001, 3277, 300]), (9, 64, 0, [700, 1300]),
+            (17, 128, 0, [1025]), (11, 128, 8, [2048]), (17, 128, 8, [600]), (17, 128, 4, [3000]), (20, 128, 4, [1023])]
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("B,d,bits,Ls", CUT_ANEW)
+def test_decode_launches_cut_anew(oracle, B, d, bits, Ls, dt):
+    print(f"cut anew {B} {d} {bits} {Ls} {dt}", flush=True)
+    Q = rnd(B, 16, 1, d, dt, W.TID_Q)
+    Ks = [rnd(B, 8, L, d, dt, W.TID_K + 16 * (i + 1)) for i, L in enumerate(Ls)]
+    Vs = [rnd(B, 8, L, d, dt, W.TID_V + 16 * (i + 1)) for i, L in enumerate(Ls)]
+    Qd, Kd, Vd = Q.to(DEV), [k.to(DEV) for k in Ks], [v.to(DEV) for v in Vs]
+    if bits:
+        codes = fb.fedrag_quantize_rows(Kd[0], bits) + fb.fedrag_quantize_rows(Vd[0], bits)
+        Ks, Vs = ([fb.fedrag_dequantize_rows(c, p, bits, Q.dtype).cpu()] for c, p in (codes[:2], codes[2:]))
+        O, lse = fb.fedrag_partial_attn_quantized(Qd, *codes, bits)
+    else:
+        O, lse = fb.fedrag_partial_attn_shards(Qd, Kd, Vd)
+    torch.cuda.synchronize()
+    Or, lr = oracle.partial_attn(Q, torch.cat(Ks, dim=2), torch.cat(Vs, dim=2))
+    PT.check_attn(O, lse, Or, lr, Q.dtype, f"{B} {Ls}")
+    if len(Ls) > 1:
+        return
+    lens = torch.tensor([(Ls[0] * (b + 1) // B) if b else 0 for b in range(B)], dtype=torch.int32)
+    Or, lr = oracle.partial_attn_varlen(Q, Ks[0], Vs[0], lens)
+    if bits:
+        O, lse = fb.fedrag_partial_attn_varlen_quantized(Qd, *codes, bits, lens.to(DEV))
+    else:
+        O, lse = fb.fedrag_partial_attn_varlen(Qd, Kd[0], Vd[0], lens.to(DEV))
+    torch.cuda.synchronize()
+    PT.check_attn(O, lse, Or, lr, Q.dtype, f"{B} {Ls} padded")
+
+
+def test_longer_runs_keep_the_error_of_the_plan():
+    """A batch of 16 takes two runs of 10000 keys a sequence, one of 17 a single run: it is summed in two parts, so the same
+    sequences come out with the same error against 64 bits (in one go it was 1.17 times that; the two differ by some 3 % in either
+    direction by where a part ends)."""
+    g = torch.Generator(device=DEV).manual_seed(4)
+    Q, K, V = (torch.randn((17, h, n, 128), generator=g, device=DEV).half() for h, n in ((32, 2), (8, 20000), (8, 20000)))
+    S = torch.matmul(Q[:3].double().view(3, 8, 8, 128), K[:3].double().transpose(2, 3).contiguous()) / np.sqrt(128)
+    ref, ref_l = torch.matmul(torch.softmax(S, -1), V[:3].double()).view(3, 32, 2, 128), torch.logsumexp(S, -1).view(3, 32, 2)
+    err = []
+    for B in (16, 17):
+        O, lse = fb.fedrag_partial_attn(Q[:B].contiguous(), K[:B].contiguous(), V[:B].contiguous())
+        err.append((float((O[:3] - ref).norm() / ref.norm()), float((lse[:3] - ref_l).norm() / ref_l.norm())))
+    torch.cuda.synchronize()
+    print(err, flush=True)
+    assert err[1][0] <= 1.06 * err[0][0] and err[1][1] <= 1.5 * err[0][1], err
+
+
+@pytest.mark.parametrize("bits", [0, 8])
+@pytest.mark.parametrize("B,L", [(17, 8192), (31, 8192)])
+def test_longer_runs_keep_the_range_of_the_plan(B, L, bits):
+    """8192 equal scores, values of 1.5 x 2^115: 4096 of them fit fp32, a sum of all would not."""
+    Q, K = torch.zeros((B, 8, 1, 128), dtype=torch.bfloat16, device=DEV), rnd(1, 8, L, 128, "bf16", W.TID_K).to(DEV).repeat(B, 1, 1, 1)
+    V = torch.full((B, 8, L, 128), 1.5 * 2.0 ** 115, dtype=torch.bfloat16, device=DEV)
+    if bits:
+        O, lse = fb.fedrag_partial_attn_quantized(Q, *fb.fedrag_quantize_rows(K, bits), *fb.fedrag_quantize_rows(V, bits), bits)
+    else:
+        O, lse = fb.fedrag_partial_attn(Q, K, V)
+    torch.cuda.synchronize()
+    assert float((O.double() / (1.5 * 2.0 ** 115) - 1).abs().max()) <= 1e-5  # 64 additions of a tile's sum and the fold
+    assert float((lse.double() - np.log(L)).abs().max()) <= 1e-5
+
+
 @pytest.mark.parametrize("dt", ["bf16", "f16"])
 def test_decode_on_4bit_codes_of_every_scale(dt):
     """Rows of every magnitude, tiny, ordinary and (bf16) beyond 2^100, rebuild to what fedrag_dequantize_rows gives: with one
