@@ -46,7 +46,7 @@ int attn_target_wgs() {
 // chip idle: 400 + 700 keys take 23.1 us a layer in 256-key runs against 24.9 - as long as those are one round of workgroups:
 // 9 sequences x 8 KV heads x 1024 keys take 15.0 us in 144 workgroups of 512 keys and 17.9 in 288 of 256 (8-bit codes; 16-bit
 // 16.2 and 17.5 for 12 sequences).  On 4-bit codes, two workgroups to a unit, a second round begun costs less than longer runs
-// (20 x 8 x 800 keys 13.2 us in 640 workgroups, 14.2 in 320).
+// (20 x 8 x 800 keys 13.2 us in 640 workgroups, 14.2 in 320; the launch makes 480 of them, 13.0).
 constexpr int kDecMinSteps = 4;
 constexpr int kDecMinStepsShort = 2;
 constexpr int64_t kDecShortContext = 2048;  // keys of all shards of a unit up to which the shorter run is taken
@@ -129,14 +129,21 @@ void attn_cut_runs(KeyRuns& r, int64_t per, int64_t quantum) {
 }
 
 // One round of workgroups where the streaming kernel would have one and a bit.  The plan above rounds the runs of a unit up, as the
-// workspace is sized, and a few workgroups over a round take as long as the round did; their number is rounded down here.  What
-// is left idle costs less, as a compute unit takes more of the memory's rate when others rest (8192 keys x 8 heads of 128: 3
-// sequences, 264 workgroups and 240, 27.7 us and 22.2; 9, 288 and 216, 67.6 and 52.8; 17, 272 and 136, 122 and 103; 31, 496 and
-// 248, 164 and 160; of 64, 9 and 17 sequences 35.0 and 28.6, 64.1 and 53.1; on 8-bit codes 3 and 9 28.5 and 21.4, 58.1 and 45.1,
-// 20 103 either way; 5 x (4001 + 3277 + 300) keys of 128 39.7 and 31.4).  Never more runs than the plan
-// has.  Where the shards alone are more than a round the rounds even out (20 x (4001 + 3277 + 300): 135 us, 139 with a run a shard),
-// and a shard much longer than the others would be a run too long (9 of them: 55.6 us, 57.0).
-static void decode_one_round(KeyRuns& r, int64_t units, int64_t cus) {
+// workspace is sized, and a few workgroups over a round take as long as the round did; their number is rounded down here.  Never
+// more runs than the plan has.  Where the shards alone are more than a round the rounds even out (20 x (4001 + 3277 + 300) keys:
+// 135 us, 139 with a run a shard), and a shard much longer than the others would be a run too long (9 of them: 55.6 us, 57.0).
+// 16-bit values, the plan's runs and one round, 8192 keys x 8 heads of 128: 3 sequences (264 workgroups and 240) 27.7 and 22.2 us,
+// 9 (288, 216) 67.6 and 52.8, 17 (272, 136) 122 and 103, 31 (496, 248) 164 and 160; of 64, 9 and 17 sequences 35.0 and 28.6, 64.1
+// and 53.1; 5 x (4001 + 3277 + 300) 39.7 and 31.4.  What is left idle costs little: a compute unit takes more of the memory's rate
+// when others rest.
+// Codes are bound by the instructions that rebuild them, so there what counts is the load of the compute unit that has the most
+// workgroups, in keys, each with its start and end (`start`), and one round has to be ahead by that: of 8-bit codes by 5 % (3 and 9
+// x 8192 27.6 and 21.9 us, 56.8 and 44.3, 30 x 600 22.3 and 15.7, 20 x 8192 even; 20 x 16384 188 and 194: as planned).  Of 4-bit codes,
+// two workgroups to a unit, by 15 %, and three quarters full (20 x 800 13.2 and 13.0, 60 x 600 19.8 and 15.1, 9 x 8192 31.9 and 29.6; 22 x
+// 1100, 352 workgroups, 16.3 and 17.6: as planned), because where two runs a sequence, three on some units, would be one run, two on
+// some units, it is a third more: 33 x 3000 42.5 and 50.4, 33 x 8192 101 and 127, 40 x 16384 199 and 254.
+static void decode_one_round(KeyRuns& r, int64_t units, int quant_bits) {
+    const int64_t cus = attn_target_wgs(), round = cus * (quant_bits == 4 ? kDecCodesOcc : 1);
     auto longest = [](const KeyRuns& k) {
         int64_t most = 0;
         for (int i = 0; i < k.n_shards; ++i) {
@@ -150,18 +157,21 @@ static void decode_one_round(KeyRuns& r, int64_t units, int64_t cus) {
         shards += r.s[i].L > 0 ? 1 : 0;
         if (r.s[i].L > 0 && r.s[i].per > per) per = r.s[i].per;
     }
-    if (units < 1 || units * r.n_runs <= cus || units * shards > cus) return;
+    if (units < 1 || units * r.n_runs <= round || units * shards > round) return;
     static_assert(kPrePair == kDecStride, "runs of whole steps");
-    const int64_t least = prefill_least_run(r, per, cus / units);
+    const int64_t least = prefill_least_run(r, per, round / units);
+    if (least > (int64_t)1 << 22) return;  // (a run is addressed in 32 bits)
     KeyRuns one = r;
     attn_cut_runs(one, least, kDecStride);
-    const int64_t rounds = (units * r.n_runs + cus - 1) / cus;
-    if (least > (int64_t)1 << 22 || longest(one) > rounds * longest(r)) return;  // (a run is addressed in 32 bits)
+    auto cost = [&](const KeyRuns& k, int64_t start) { return (units * k.n_runs + cus - 1) / cus * (longest(k) + start); };
+    if (quant_bits == 0 && cost(r, 0) < cost(one, 0)) return;
+    if (quant_bits == 8 && cost(r, 500) * 20 < cost(one, 500) * 21) return;
+    if (quant_bits == 4 && (cost(r, 400) * 20 < cost(one, 400) * 23 || units * one.n_runs * 4 < round * 3)) return;
     // Summed in parts no longer than the plan's runs, with a maximum of their own: in one go a run twice as long left up to 17 % more
     // error (fp16, 17 x 2 rows x 20000 keys 6.1e-7 and 7.1e-7; bf16 1 to 3 %), as fp32 sums are longer and half as many keys have the
     // probability 1 exactly.
     const int64_t parts = (longest(one) + longest(r) - 1) / longest(r);
-    one.part = (longest(one) + parts - 1) / parts;
+    one.part = parts > 1 ? (longest(one) + parts - 1) / parts : 0;
     r = one;
 }
 
@@ -171,13 +181,13 @@ KeyRuns attn_runs_of(const AttnProblem& p) {
     if (p.n_shards <= 1) {
         const bool codes4 = p.quant_bits == 4 && p.D == 128;
         KeyRuns r = attn_plan_runs(p.B, p.Hq, p.Hkv, p.dtype, p.Lq, 1, &p.Lkv, codes4);
-        if (streaming) decode_one_round(r, units, (int64_t)attn_target_wgs() * (codes4 ? kDecCodesOcc : 1));
+        if (streaming) decode_one_round(r, units, p.quant_bits);
         r.s[0].K = p.K;
         r.s[0].V = p.V;
         return r;
     }
     KeyRuns r = attn_plan_runs(p.B, p.Hq, p.Hkv, p.dtype, p.Lq, p.n_shards, p.Ls);
-    if (streaming) decode_one_round(r, units, attn_target_wgs());
+    if (streaming) decode_one_round(r, units, 0);
     for (int i = 0; i < p.n_shards && i < kMaxShards; ++i) {
         r.s[i].K = p.Ks[i];
         r.s[i].V = p.Vs[i];

@@ -1,13 +1,14 @@
 // The host's choice of a prefill launch's form, looked at without a device (no call here enqueues anything).  Commands on stdin,
 // one answer a line:
 //   form B Hq Hkv d dtype Lq n L... / codes B Hq Hkv d dtype Lq 1 L (4 bits)   ->  kind four n_runs past_l2   (kind: 0 plain, 1 shards in turn, 2 two key groups)
-//   decode B Hq Hkv d dtype Lq n L... / decode4 (4-bit codes)  ->  n_runs, keys that the runs cover, longest run, runs the workspace
+//   decode B Hq Hkv d dtype Lq n L... / decode4, decode8 (codes)  ->  n_runs, keys that the runs cover, longest run, runs the workspace
 //       holds, longest run of the plan, keys of a part (0: runs are summed in one go), runs of the plan
 //   runs from most n L...             ->  keys a run by halving, by trying every length in turn
 //   time B Hq Hkv d dtype Lq n L...   ->  microseconds a choice takes, the least of many
 #include <algorithm>
 #include <chrono>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <vector>
 
@@ -51,9 +52,9 @@ int main() {
             if (what[0] == 'c') p.quant_bits = 4;
             const PrefillForm f = prefill_form(p);
             std::printf("%d %d %d %d\n", (int)f.kind, f.four ? 1 : 0, f.runs.n_runs, prefill_stores_past_l2(p, f) ? 1 : 0);
-        } else if (!std::strcmp(what, "decode") || !std::strcmp(what, "decode4")) {
+        } else if (!std::strncmp(what, "decode", 6)) {
             if (!read_problem(p, L)) return 2;
-            if (what[6]) p.quant_bits = 4;
+            p.quant_bits = std::atoi(what + 6);
             const KeyRuns r = attn_runs_of(p);
             long covered = 0, longest = 0;
             for (int run = 0; run < r.n_runs; ++run) {  // as the kernel finds its keys

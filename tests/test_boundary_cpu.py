@@ -528,7 +528,7 @@ def test_two_group_runs_by_halving(launch_forms):
 @pytest.mark.skipif(torch.cuda.is_available(), reason="pinned for the 256 compute units that the plan falls back to")
 def test_decode_launches_make_one_round(launch_forms):
     """The streaming kernel's launches cover every key once with at most the runs that the workspace holds, and are one round of
-    workgroups where a shard is alone and its units are not more."""
+    workgroups where a shard of 16-bit values is alone and its units are not more; otherwise one round or what was planned."""
     import random
     r = random.Random(5)
     shapes = [(3, 128, [8192]), (9, 128, [8192]), (20, 64, [8192]), (5, 128, [4001, 3277, 300]), (9, 128, [4096, 4096]), (31, 128, [513])]
@@ -536,21 +536,26 @@ def test_decode_launches_make_one_round(launch_forms):
         Ls = [r.choice([0, r.randint(1, 600), int(2 ** r.uniform(0, 16))]) for _ in range(r.choice([1, 1, 2, 3, 8, 16]))]
         if any(Ls):
             shapes.append((int(2 ** r.uniform(0, 6.5)), r.choice([64, 128]), Ls))
-    for what, round_ in (("decode", 256), ("decode4", 512)):
+    for what, round_ in (("decode", 256), ("decode4", 512), ("decode8", 256)):
         cases = [(B, d, Ls) for B, d, Ls in shapes if what == "decode" or (len(Ls) == 1 and d == 128)]
         got = launch_forms([f"{what} {B} 32 8 {d} {fb.BF16} 1 {len(Ls)} " + " ".join(map(str, Ls)) for B, d, Ls in cases])
         for (B, d, Ls), (runs, covered, longest, held, planned, part, plan_runs) in zip(cases, got):
             assert covered == sum(Ls) and runs <= max(held, 1), (what, B, d, Ls, runs, held)
-            assert 8 * B * runs <= round_ or 8 * B > round_ or len(Ls) > 1, (what, B, d, Ls, runs)
+            left = runs == plan_runs and (8 * B > round_ or len(Ls) > 1 or what != "decode")  # cut whole, or as planned
+            assert 8 * B * runs <= round_ or left, (what, B, d, Ls, runs, plan_runs)
             # a run is addressed in 32 bits, takes no longer than the rounds that the plan would make, and is summed in parts that
             # are no longer than the plan's runs
             rounds = -(-8 * B * plan_runs // round_)
             assert longest <= min(2 ** 22, max(rounds, 1) * planned), (what, B, d, Ls, longest, planned)
             assert (part == 0) == (longest <= planned) and part <= planned, (what, B, d, Ls, longest, planned, part)
     from test_gpu_launch_forms import CUT_ANEW
-    cut = launch_forms([f"decode{4 if bits == 4 else ''} {B} 16 8 {d} {fb.BF16} 1 {len(Ls)} " + " ".join(map(str, Ls)) for B, d, bits, Ls in CUT_ANEW])
+    cut = launch_forms([f"decode{bits or ''} {B} 16 8 {d} {fb.BF16} 1 {len(Ls)} " + " ".join(map(str, Ls)) for B, d, bits, Ls in CUT_ANEW])
     assert all(0 < part <= planned < longest for _, _, longest, _, planned, part, _ in cut), cut
     assert [g[0] for g in launch_forms([f"decode {B} 32 8 128 {fb.BF16} 1 1 8192" for B in (1, 3, 9, 16, 17, 33)])] == [16, 10, 3, 2, 1, 1]
+    # codes: bound by instructions, so not where one round is more keys on the fullest compute unit
+    assert [g[0] for g in launch_forms([f"decode4 {B} 32 8 128 {fb.BF16} 1 1 {L}" for B, L in ((20, 800), (9, 2000), (20, 1023), (9, 8192), (50, 1024), (60, 600))])] == [3, 6, 3, 7, 1, 1]
+    assert [g[0] for g in launch_forms([f"decode4 {B} 32 8 128 {fb.BF16} 1 1 {L}" for B, L in ((33, 1500), (33, 3000), (40, 8192), (48, 16384), (22, 1100))])] == [2, 2, 2, 2, 3]
+    assert [g[0] for g in launch_forms([f"decode8 {B} 32 8 128 {fb.BF16} 1 1 {L}" for B, L in ((3, 8192), (30, 600), (20, 8192), (20, 16384), (9, 16384))])] == [10, 1, 1, 2, 3]
     several = [(5, [4001, 3277, 300]), (9, [4096, 4096]), (9, [4001, 3277, 300]), (20, [4001, 3277, 300])]
     assert [g[0] for g in launch_forms([f"decode {B} 32 8 128 {fb.BF16} 1 {len(Ls)} " + " ".join(map(str, Ls)) for B, Ls in several])] == [6, 2, 6, 4]
 
