@@ -3,7 +3,7 @@
 // HBM-bound: every K'/V' byte of the shard is read exactly once and nothing is reused, so the kernel is built around keeping
 // whole rows in flight.
 //
-// One workgroup = one unit x one split of the shard's keys; its four (or eight) waves take 32-key tiles round-robin.
+// One workgroup = one unit x one split of the shard's keys; its four (two, eight) waves take 32-key tiles round-robin.
 // Lane l of a wave: lr = l % 16, lq = l / 16.
 //   S^T tile (32 keys x 16 queries) = K'(32 x d) . Q'^T(d x 16): two 16-key MFMA tiles; this lane ends up with
 //   query lr and keys {16 mt + 4 lq + r}.  Those eight keys are also this lane's contraction slice of
@@ -154,7 +154,6 @@ __device__ __forceinline__ typename T::vec8 dequant8(uint32_t w, const RowScale&
 // short that start and end are what they spend their time on, which a neighbour then hides: 64 sequences x 8 heads of 128 x 100
 // keys 7.3 us against 10.4 (8.5 before), 400 keys 20.0 and 22.4, 1000 44.6 and 45.4; beyond that two tiles are 0 to 1 % ahead.  At
 // d = 64 100 keys 5.4 and 5.9, 256 8.1 either way, 400 11.5 and 11.3.  Also where a wave has one tile: 128 keys x 8 heads 3.7 and 4.3.
-// (2048 units of at most 64 keys of 64 are 1 to 5 % behind the registers used before, with more of them to a compute unit.)
 constexpr int64_t dec_single_tile_run(int d) { return d == 128 ? 1024 : 256; }  // keys of the longest run up to which it is one
 
 // 16-bit values of 128 columns in whole rounds of long runs stay in registers: at the rate of memory the LDS form is 1 to 4 % behind
@@ -739,6 +738,13 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
     if constexpr (QB == 0) {
         if (tiles == 1) kernel = decode_attn_kernel<T, D, 0, 1, kDecWaves, false>;  // (runs that were not cut anew)
         if (tiles == 2) kernel = runs.part ? decode_attn_kernel<T, D, 0, 2, kDecWaves, true> : decode_attn_kernel<T, D, 0, 2, kDecWaves, false>;
+        // Two tiles in all: two waves and half of the LDS, so twice the workgroups to a compute unit (2048 units of 5, 20, 33, 48, 64 keys of
+        // 64 4.9, 5.6, 6.7, 7.5, 8.6 us against 6.6, 7.3, 8.1, 8.8, 9.7, 8192 units 12.6 and 20.5, 26.3 and 28.9; of 128 2048 x 5 8.8 and 12.3;
+        // a handful 1 to 3 %).  The waves left out had nothing.
+        if (tiles == 1 && longest <= 2 * kDecTile) {
+            kernel = decode_attn_kernel<T, D, 0, 1, kDecWaves / 2, false>;
+            threads = kDecThreads / 2;
+        }
         // Two tiles a wave and no more, on compute units of their own: eight waves with one tile each instead, whose loads are out at
         // once and whose chain of products is half as long (129 keys x 8 heads 4.8 -> 4.3 us, 192 4.9 -> 4.3, 256 5.5 -> 5.2, 1000 in
         // four runs 7.9 -> 7.65).  From some 300 keys on the two are within 1 %, at d = 64, whose tiles are half the bytes, this loses 2 to 5 %.
@@ -748,7 +754,7 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
                 threads = 2 * kDecThreads;
             }
     }
-    if (!grid_fits(units * splits, threads)) return hipErrorInvalidValue;
+    if (!grid_fits(units * splits, kDecThreads)) return hipErrorInvalidValue;  // (eight waves are one round at most)
     hipLaunchKernelGGL(kernel, dim3((unsigned)(units * splits)), dim3(threads), 0, stream, (const elem*)p.Q, runs,
                        p.K_params, p.V_params, R, scale_log2, Odst, Ldst, rows, p.kv_lens, p.q_lens, (int)p.Lq, FastDiv(p.Hkv), part > 2 ? part : 2);
     hipError_t e = hipGetLastError();

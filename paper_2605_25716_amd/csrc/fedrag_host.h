@@ -165,7 +165,7 @@ hipError_t launch_partial_attn(const AttnProblem& p, hipStream_t stream);
 hipError_t attn_static_scratch(void** ptr_out);
 
 // decode kernel geometry (shared by the split planner and the kernel)
-constexpr int kDecWaves = 4;  // twice that for runs of two steps of 128 columns
+constexpr int kDecWaves = 4;  // twice that for runs of two steps of 128 columns, half for runs of half a step
 constexpr int kDecThreads = kDecWaves * 64;
 constexpr int kDecTile = 32;                      // keys per wave step
 constexpr int kDecStride = kDecWaves * kDecTile;  // keys per workgroup step
