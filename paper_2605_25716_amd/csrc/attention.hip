@@ -67,7 +67,6 @@ KeyRuns attn_plan_runs(int B, int Hq, int Hkv, int dtype, int64_t Lq, int n, con
     r.first[kMaxShards] = INT_MAX;
     r.n_runs = 0;
     r.n_shards = n;
-    r.part = 0;
     r.by_runs = FastDiv(1);
     if (n < 1 || n > kMaxShards) return r;
     int64_t total = 0;
@@ -142,7 +141,8 @@ void attn_cut_runs(KeyRuns& r, int64_t per, int64_t quantum) {
 // two workgroups to a unit, by 15 %, and three quarters full (20 x 800 13.2 and 13.0, 60 x 600 19.8 and 15.1, 9 x 8192 31.9 and 29.6; 22 x
 // 1100, 352 workgroups, 16.3 and 17.6: as planned), because where two runs a sequence, three on some units, would be one run, two on
 // some units, it is a third more: 33 x 3000 42.5 and 50.4, 33 x 8192 101 and 127, 40 x 16384 199 and 254.
-static void decode_one_round(KeyRuns& r, int64_t units, int quant_bits) {
+// Returns the keys of a part, as attn_runs_of does.
+static int64_t decode_one_round(KeyRuns& r, int64_t units, int quant_bits) {
     const int64_t cus = attn_target_wgs(), round = cus * (quant_bits == 4 ? kDecCodesOcc : 1);
     auto longest = [](const KeyRuns& k) {
         int64_t most = 0;
@@ -157,37 +157,40 @@ static void decode_one_round(KeyRuns& r, int64_t units, int quant_bits) {
         shards += r.s[i].L > 0 ? 1 : 0;
         if (r.s[i].L > 0 && r.s[i].per > per) per = r.s[i].per;
     }
-    if (units < 1 || units * r.n_runs <= round || units * shards > round) return;
+    if (units < 1 || units * r.n_runs <= round || units * shards > round) return 0;
     static_assert(kPrePair == kDecStride, "runs of whole steps");
     const int64_t least = prefill_least_run(r, per, round / units);
-    if (least > (int64_t)1 << 22) return;  // (a run is addressed in 32 bits)
+    if (least > (int64_t)1 << 22) return 0;  // (a run is addressed in 32 bits)
     KeyRuns one = r;
     attn_cut_runs(one, least, kDecStride);
     auto cost = [&](const KeyRuns& k, int64_t start) { return (units * k.n_runs + cus - 1) / cus * (longest(k) + start); };
-    if (quant_bits == 0 && cost(r, 0) < cost(one, 0)) return;
-    if (quant_bits == 8 && cost(r, 500) * 20 < cost(one, 500) * 21) return;
-    if (quant_bits == 4 && (cost(r, 400) * 20 < cost(one, 400) * 23 || units * one.n_runs * 4 < round * 3)) return;
+    if (quant_bits == 0 && cost(r, 0) < cost(one, 0)) return 0;
+    if (quant_bits == 8 && cost(r, 500) * 20 < cost(one, 500) * 21) return 0;
+    if (quant_bits == 4 && (cost(r, 400) * 20 < cost(one, 400) * 23 || units * one.n_runs * 4 < round * 3)) return 0;
     // Summed in parts no longer than the plan's runs, with a maximum of their own: in one go a run twice as long left up to 17 % more
     // error (fp16, 17 x 2 rows x 20000 keys 6.1e-7 and 7.1e-7; bf16 1 to 3 %), as fp32 sums are longer and half as many keys have the
     // probability 1 exactly.
     const int64_t parts = (longest(one) + longest(r) - 1) / longest(r);
-    one.part = parts > 1 ? (longest(one) + parts - 1) / parts : 0;
     r = one;
+    return parts > 1 ? (longest(one) + parts - 1) / parts : 0;
 }
 
-KeyRuns attn_runs_of(const AttnProblem& p) {
+KeyRuns attn_runs_of(const AttnProblem& p, int64_t* part) {
+    int64_t keys = 0;
+    if (!part) part = &keys;
+    *part = 0;
     const bool streaming = use_decode_kernel(p.Hq, p.Hkv, p.Lq) && p.dtype != FEDRAG_F32 && !p.causal && (p.quant_bits == 0 || p.D == 128);
     const int64_t units = (int64_t)p.B * p.Hkv;
     if (p.n_shards <= 1) {
         const bool codes4 = p.quant_bits == 4 && p.D == 128;
         KeyRuns r = attn_plan_runs(p.B, p.Hq, p.Hkv, p.dtype, p.Lq, 1, &p.Lkv, codes4);
-        if (streaming) decode_one_round(r, units, p.quant_bits);
+        if (streaming) *part = decode_one_round(r, units, p.quant_bits);
         r.s[0].K = p.K;
         r.s[0].V = p.V;
         return r;
     }
     KeyRuns r = attn_plan_runs(p.B, p.Hq, p.Hkv, p.dtype, p.Lq, p.n_shards, p.Ls);
-    if (streaming) decode_one_round(r, units, 0);
+    if (streaming) *part = decode_one_round(r, units, 0);
     for (int i = 0; i < p.n_shards && i < kMaxShards; ++i) {
         r.s[i].K = p.Ks[i];
         r.s[i].V = p.Vs[i];

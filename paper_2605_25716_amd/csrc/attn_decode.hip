@@ -163,7 +163,7 @@ constexpr int64_t dec_single_tile_run(int d) { return d == 128 ? 1024 : 256; }  
 // for its number of workgroups or for shorter ones, what counts is again what a compute unit takes by itself (33 x 4096 131 us and 116).
 constexpr int64_t kDecLongRun = 2048;
 
-// PARTS: a run is summed part by part, `part` tiles of a wave at a time (KeyRuns::part).  A form of its own: the check in the loop and
+// PARTS: a run is summed part by part, `part` tiles of a wave at a time (attn_runs_of).  A form of its own: the check in the loop and
 // the second set of accumulators take 0 to 4 % of a launch on codes.
 template <class T, int D, int QB, int NS, int WAVES, bool PARTS>
 FEDRAG_KERNEL __launch_bounds__(WAVES * kWave, QB == 4 ? kDecCodesOcc : NS * D > 0 && NS * D <= 128 ? 2 : 1) void decode_attn_kernel(const typename T::elem* __restrict__ Q,
@@ -207,7 +207,8 @@ FEDRAG_KERNEL __launch_bounds__(WAVES * kWave, QB == 4 ? kDecCodesOcc : NS * D >
     // The arguments are one trip to memory and the shard a second one, where branches and addresses made five of them: a token's
     // attention in a request over 32 layers, 24.9 -> 24.4 us a layer; 128 keys 3.72 -> 3.66 us; long runs even.
     FEDRAG_HAVE_HERE(FEDRAG_S3(runs.by_runs), FEDRAG_S(runs.n_shards), FEDRAG_S(Q), FEDRAG_S(R), FEDRAG_S(scale_log2), FEDRAG_S(O),
-                     FEDRAG_S(lse), FEDRAG_S(total_rows), FEDRAG_S(kv_lens), FEDRAG_S(q_lens), FEDRAG_S(Lq), FEDRAG_S3(by_hkv), FEDRAG_S(part));
+                     FEDRAG_S(lse), FEDRAG_S(total_rows), FEDRAG_S(kv_lens), FEDRAG_S(q_lens), FEDRAG_S(Lq), FEDRAG_S3(by_hkv));
+    if constexpr (PARTS) FEDRAG_HAVE_HERE(FEDRAG_S(part));
     const int64_t unit = runs.by_runs.div(blockIdx.x);
     const int run = (int)runs.by_runs.mod(blockIdx.x);  // index of this workgroup's partial
     int split;
@@ -704,7 +705,8 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
     typedef typename T::elem elem;
     const float scale_log2 = p.scale * kLog2e;
     const int64_t rows = (int64_t)p.B * p.Hq * p.Lq;
-    const KeyRuns runs = attn_runs_of(p);
+    int64_t part_keys;
+    const KeyRuns runs = attn_runs_of(p, &part_keys);
     const int splits = runs.n_runs;
     if (splits < 1) return hipErrorInvalidValue;
     if (QB != 0 && p.n_shards > 1) return hipErrorInvalidValue;
@@ -732,12 +734,12 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
         if (D == 128 && longest >= kDecLongRun && units * total * 10 >= rounds * cus * longest * 9) tiles = 0;
     }
     constexpr int kRegisters = QB == 0 && D == 64 ? 2 : 0;  // (16 bits of 64 columns have no such form)
-    const int part = (int)((runs.part + kDecStride - 1) / kDecStride) & ~1;  // a wave's tiles of it, which are taken in pairs
-    auto kernel = runs.part ? decode_attn_kernel<T, D, QB, kRegisters, kDecWaves, true> : decode_attn_kernel<T, D, QB, kRegisters, kDecWaves, false>;
+    const int part = (int)((part_keys + kDecStride - 1) / kDecStride) & ~1;  // a wave's tiles of it, which are taken in pairs
+    auto kernel = part_keys ? decode_attn_kernel<T, D, QB, kRegisters, kDecWaves, true> : decode_attn_kernel<T, D, QB, kRegisters, kDecWaves, false>;
     int threads = kDecThreads;
     if constexpr (QB == 0) {
         if (tiles == 1) kernel = decode_attn_kernel<T, D, 0, 1, kDecWaves, false>;  // (runs that were not cut anew)
-        if (tiles == 2) kernel = runs.part ? decode_attn_kernel<T, D, 0, 2, kDecWaves, true> : decode_attn_kernel<T, D, 0, 2, kDecWaves, false>;
+        if (tiles == 2) kernel = part_keys ? decode_attn_kernel<T, D, 0, 2, kDecWaves, true> : decode_attn_kernel<T, D, 0, 2, kDecWaves, false>;
         // Two tiles in all: two waves and half of the LDS, so twice the workgroups to a compute unit (2048 units of 5, 20, 33, 48, 64 keys of
         // 64 4.9, 5.6, 6.7, 7.5, 8.6 us against 6.6, 7.3, 8.1, 8.8, 9.7, 8192 units 12.6 and 20.5, 26.3 and 28.9; of 128 2048 x 5 8.8 and 12.3;
         // a handful 1 to 3 %).  The waves left out had nothing.

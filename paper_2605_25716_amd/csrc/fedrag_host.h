@@ -127,7 +127,6 @@ struct KeyRuns {
     FastDiv by_runs;  // n_runs (1 when there is none)
     int first[kMaxShards + 1];
     KeyShard s[kMaxShards];
-    int64_t part;  // streaming kernel: keys of a run that are summed by themselves, where the launch made runs longer than the plan's; else 0
     // The shard that run `run` (0 <= run < n_runs) belongs to; *split = index of the run inside it.  All of first[] is
     // read at once and counted (one compare after the other, each waiting for its own scalar load, kept a short
     // kernel from starting for 1.5 us); a single shard needs none of it.
@@ -156,8 +155,9 @@ size_t attn_workspace_bytes(int B, int Hq, int Hkv, int D, int dtype, int64_t Lq
 inline size_t attn_workspace_bytes(int B, int Hq, int Hkv, int D, int dtype, int64_t Lq, int64_t Lkv) {
     return attn_workspace_bytes(B, Hq, Hkv, D, dtype, Lq, 1, &Lkv);
 }
-// The plan of problem p with its pointers filled in.
-KeyRuns attn_runs_of(const AttnProblem& p);
+// The plan of problem p with its pointers filled in.  *part: keys of a run that the streaming kernel sums by themselves, where its
+// runs were made longer than the plan's; else 0.
+KeyRuns attn_runs_of(const AttnProblem& p, int64_t* part = nullptr);
 // Cuts the shards of r (s[].L, n_shards) into runs of about `per` keys, a multiple of `quantum` and rebalanced inside a shard.
 void attn_cut_runs(KeyRuns& r, int64_t per, int64_t quantum);
 hipError_t launch_partial_attn(const AttnProblem& p, hipStream_t stream);

@@ -55,7 +55,8 @@ int main() {
         } else if (!std::strncmp(what, "decode", 6)) {
             if (!read_problem(p, L)) return 2;
             p.quant_bits = std::atoi(what + 6);
-            const KeyRuns r = attn_runs_of(p);
+            int64_t part;
+            const KeyRuns r = attn_runs_of(p, &part);
             long covered = 0, longest = 0;
             for (int run = 0; run < r.n_runs; ++run) {  // as the kernel finds its keys
                 int i = 0;
@@ -68,7 +69,7 @@ int main() {
             const KeyRuns plan = attn_plan_runs(p.B, p.Hq, p.Hkv, p.dtype, p.Lq, p.n_shards > 1 ? p.n_shards : 1, p.n_shards > 1 ? p.Ls : &p.Lkv, p.quant_bits == 4);
             long planned = 0;
             for (int i = 0; i < plan.n_shards; ++i) planned = std::max<long>(planned, std::min(plan.s[i].per, plan.s[i].L));
-            std::printf("%d %ld %ld %ld %ld %ld %d\n", r.n_runs, covered, longest, (long)(bytes / ((size_t)p.B * p.Hq * p.Lq * (p.D + 1) * 4)), planned, (long)r.part, plan.n_runs);
+            std::printf("%d %ld %ld %ld %ld %ld %d\n", r.n_runs, covered, longest, (long)(bytes / ((size_t)p.B * p.Hq * p.Lq * (p.D + 1) * 4)), planned, (long)part, plan.n_runs);
         } else if (!std::strcmp(what, "runs")) {
             long from, most;
             int n;
