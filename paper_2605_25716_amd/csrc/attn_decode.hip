@@ -730,7 +730,10 @@ static hipError_t launch_decode_t(const AttnProblem& p, hipStream_t stream) {
     int tiles = 0;  // per wave in LDS
     if (QB == 0) {
         const int64_t wgs = units * splits, cus = attn_target_wgs(), rounds = (wgs + cus - 1) / cus;
-        tiles = longest <= kDecStride || (wgs > cus && longest <= dec_single_tile_run(D)) ? 1 : 2;
+        // One tile also where such runs fill one round, from some 300 keys of 128 on (32 x 8 x 400 keys 11.7 us and 12.2 with two, 777 19.6
+        // and 20.2, 1024 24.4 and 25.3 - 24.6 from registers -, 300 9.5 either way; of 64 two: 512 8.2 and 7.7).  (Parts need two.)
+        const bool whole = D == 128 && part_keys == 0 && wgs * 10 >= cus * 9 && longest > 3 * kDecStride;
+        tiles = longest <= kDecStride || ((wgs > cus || whole) && longest <= dec_single_tile_run(D)) ? 1 : 2;
         if (D == 128 && longest >= kDecLongRun && units * total * 10 >= rounds * cus * longest * 9) tiles = 0;
     }
     constexpr int kRegisters = QB == 0 && D == 64 ? 2 : 0;  // (16 bits of 64 columns have no such form)
