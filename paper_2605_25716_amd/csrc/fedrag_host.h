@@ -49,6 +49,12 @@ struct RowsJob {
 hipError_t launch_rows_transform(const RowsJob& job, hipStream_t stream);
 // Workgroups of the fp32 row products a compute unit holds, as their split over workgroups counts them.
 int row_steps_resident(int D, bool structured, bool merge);
+// Workgroups per slab of the product with a key's factors, and row steps of each.
+struct RowSteps {
+    int64_t chunks;
+    int per;
+};
+RowSteps hadamard_steps(int64_t slabs, int64_t L);
 hipError_t launch_invert_perm(const int32_t* perm, int64_t L, int32_t* inv, hipStream_t stream);
 // flag[0] = 0 if every row of perm [n_perm, L] is a permutation of 0..L-1, else bit 0 (index out of range) and / or
 // bit 1 (index repeated); marks [n_perm, L] is scratch.

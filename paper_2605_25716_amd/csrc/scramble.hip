@@ -898,7 +898,7 @@ FEDRAG_KERNEL __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f
 // and 6.1, 8.9 and 10.0).  Enc of K and V, which its coded form equals bit for bit, keeps the product at every size.
 //   SCATTER == false: Y[j] = X[perm[j]] . Phi ; SCATTER == true (fp32): Y[perm[i]] = X[i] . Phi
 constexpr int64_t kHadSlab = 64, kHadTotal = 48 << 10;
-constexpr int64_t kHadWgs = 2048;   // workgroups, eight to a compute unit, from where on one takes several steps
+constexpr int64_t kHadWgsPerUnit = 8;  // workgroups a compute unit has from where on one takes several steps
 constexpr int kHadRows = 16;        // rows per workgroup step
 constexpr int kHadThreads = 16 * kHadRows;
 constexpr float kHadLeast = 0x1p-100f;  // terms of sums above it have all their bits that count
@@ -1233,13 +1233,19 @@ static hipError_t launch_rows_f32(const RowsJob& j, hipStream_t stream) {
     return launch_rows_mfma_f32<D, SCATTER, 4 / (D / 32)>(j, stream);
 }
 
+// Fewer than `most` + slabs workgroups, and those of a slab within one step of each other: 2045 slabs of 1000 steps are two
+// workgroups of 500 each, where a workgroup of as many steps as fill 2048 of them had 999 and left one.
+RowSteps hadamard_steps(int64_t slabs, int64_t L) {
+    const int64_t steps = (L + kHadRows - 1) / kHadRows, most = kHadWgsPerUnit * attn_target_wgs();
+    const int64_t per = (slabs * steps + most - 1) / most;
+    const int64_t chunks = per < steps ? (steps + per - 1) / per : 1;
+    return {chunks, (int)((steps + chunks - 1) / chunks)};
+}
+
 template <class T, int D, bool SCATTER>
 static hipError_t launch_hadamard(const RowsJob& j, hipStream_t stream) {
-    const int64_t chunks16 = (j.L + kHadRows - 1) / kHadRows;
-    const int64_t steps = (j.BH * chunks16 + kHadWgs - 1) / kHadWgs;
-    const int per = (int)(steps < 1 ? 1 : steps < chunks16 ? steps : chunks16);
-    const int64_t chunks = (chunks16 + per - 1) / per;
-    if (!grid_fits(j.BH * chunks, kHadThreads)) return hipErrorInvalidValue;  // (at most kHadWgs, or BH)
+    const auto [chunks, per] = hadamard_steps(j.BH, j.L);
+    if (!grid_fits(j.BH * chunks, kHadThreads)) return hipErrorInvalidValue;
     hipLaunchKernelGGL((hadamard_rows_kernel<T, D, SCATTER>), dim3((unsigned)(j.BH * chunks)), dim3(kHadThreads), 0, stream,
                        device_job(j, 0), j.perm, j.perm_batch_stride, FastDiv(chunks), FastDiv(j.H), FastDiv(j.G), j.L, per);
     return hipGetLastError();

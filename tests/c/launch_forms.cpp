@@ -3,6 +3,7 @@
 //   form B Hq Hkv d dtype Lq n L... / codes B Hq Hkv d dtype Lq 1 L (4 bits)   ->  kind four n_runs past_l2   (kind: 0 plain, 1 shards in turn, 2 two key groups)
 //   decode B Hq Hkv d dtype Lq n L... / decode4, decode8 (codes)  ->  n_runs, keys that the runs cover, longest run, runs the workspace
 //       holds, longest run of the plan, keys of a part (0: runs are summed in one go), runs of the plan
+//   factors slabs L  ->  workgroups per slab of a product with a key's factors, row steps of each
 //   runs from most n L...             ->  keys a run by halving, by trying every length in turn
 //   time B Hq Hkv d dtype Lq n L...   ->  microseconds a choice takes, the least of many
 #include <algorithm>
@@ -70,6 +71,11 @@ int main() {
             long planned = 0;
             for (int i = 0; i < plan.n_shards; ++i) planned = std::max<long>(planned, std::min(plan.s[i].per, plan.s[i].L));
             std::printf("%d %ld %ld %ld %ld %ld %d\n", r.n_runs, covered, longest, (long)(bytes / ((size_t)p.B * p.Hq * p.Lq * (p.D + 1) * 4)), planned, (long)part, plan.n_runs);
+        } else if (!std::strcmp(what, "factors")) {
+            long slabs, rows;
+            if (std::scanf("%ld %ld", &slabs, &rows) != 2) return 2;
+            const RowSteps r = hadamard_steps(slabs, rows);
+            std::printf("%ld %d\n", (long)r.chunks, r.per);
         } else if (!std::strcmp(what, "runs")) {
             long from, most;
             int n;

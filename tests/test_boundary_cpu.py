@@ -560,6 +560,21 @@ def test_decode_launches_make_one_round(launch_forms):
     assert [g[0] for g in launch_forms([f"decode {B} 32 8 128 {fb.BF16} 1 {len(Ls)} " + " ".join(map(str, Ls)) for B, Ls in several])] == [6, 2, 6, 4]
 
 
+@pytest.mark.skipif(torch.cuda.is_available(), reason="pinned for the 256 compute units that the plan falls back to")
+def test_factors_split_slabs_evenly(launch_forms):
+    """Products with a key's factors: a slab's steps of 16 rows are covered by workgroups within one step of each other, fewer than
+    2048 of them and one a slab."""
+    import random
+    r = random.Random(6)
+    shapes = [(1, 1), (32, 16), (1025, 160), (2045, 16000), (2048, 5000), ((1 << 24) - 1, 17)]
+    shapes += [(int(2 ** r.uniform(0, 24)), int(2 ** r.uniform(0, 17))) for _ in range(2000)]
+    for (slabs, L), (chunks, per) in zip(shapes, launch_forms([f"factors {n} {L}" for n, L in shapes])):
+        steps = -(-L // 16)
+        assert chunks * per >= steps > (chunks - 1) * per and chunks * (per - 1) < steps, (slabs, L, chunks, per)
+        assert slabs * chunks < 2048 + slabs, (slabs, L, chunks, per)
+        assert chunks == steps or slabs * steps > 2048, (slabs, L, chunks, per)
+
+
 def test_missing_library_fails_loudly(tmp_path):
     """There is no fallback path: with no built library the binding raises instead of computing something else."""
     import subprocess
