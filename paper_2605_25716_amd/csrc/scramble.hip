@@ -490,8 +490,8 @@ __device__ __forceinline__ void few_rows(const ScrambleJob& job0, const Scramble
                                          int64_t perm_batch_stride, FastDiv by_h, FastDiv by_g, int L, const RowsMerge& mg) {
     typedef typename T::elem elem;
     constexpr bool kF32 = sizeof(elem) == 4;
-    static_assert(!SCATTER || kF32, "Dec is fp32");
-    constexpr bool kMerge = SCATTER && !ST;  // may be asked for the aggregation as well
+    static_assert(!SCATTER || (kF32 && !ST), "Dec is fp32, and by a matrix here");
+    constexpr bool kMerge = SCATTER;  // may be asked for the aggregation as well
     static_assert(CS == 1 || !ST, "the key's factors are for all columns");
     constexpr int kThreads = kF32Threads / CS;
     constexpr int COLS = D / CS;            // columns of this workgroup
@@ -714,7 +714,8 @@ FEDRAG_KERNEL __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f
     // scatter form: where the rows of a step go and their weights, looked up and evaluated once a row
     __shared__ int32_t row_dst[SCATTER ? 2 : 1][SCATTER ? TR : 1];
     __shared__ RowWeights row_w[MERGE ? 2 : 1][MERGE ? TR : 1];
-    static_assert(!MERGE || (SCATTER && !ST), "the aggregation is part of Dec by a matrix");
+    static_assert(!SCATTER || !ST, "Dec by a key's factors is not a product");
+    static_assert(!MERGE || SCATTER, "the aggregation is part of Dec");
 
     const ScrambleJob job = blockIdx.y == 0 ? job0 : job1;
     // one trip to memory, and heads without divisions: 1 to 7 % of launches of up to some 30 us, 2.5 % on average over 114
@@ -905,7 +906,7 @@ constexpr float kHadLeast = 0x1p-100f;  // terms of sums above it have all their
 template <class T, int D, bool SCATTER>
 FEDRAG_KERNEL __launch_bounds__(kHadThreads) void hadamard_rows_kernel(ScrambleJob job, const int32_t* __restrict__ perm,
                                                                        int64_t perm_batch_stride, FastDiv by_chunks, FastDiv by_heads,
-                                                                       FastDiv by_group, int64_t L, int steps_per_wg) {
+                                                                       FastDiv by_group, int64_t L, int steps_per_wg, int first_slab) {
     typedef typename T::elem elem;
     static_assert(!SCATTER || sizeof(elem) == 4, "Dec is fp32");
     constexpr int E = D / 16;                                            // values per lane
@@ -917,9 +918,10 @@ FEDRAG_KERNEL __launch_bounds__(kHadThreads) void hadamard_rows_kernel(ScrambleJ
     __shared__ __attribute__((aligned(16))) float rows[kHadRows][LDP];
     FEDRAG_HAVE_HERE(FEDRAG_S(job.X), FEDRAG_S(job.Y), FEDRAG_S(job.s_in), FEDRAG_S(job.p_in), FEDRAG_S(job.p_out), FEDRAG_S(job.s_out),
                      FEDRAG_S(perm), FEDRAG_S(perm_batch_stride), FEDRAG_S3(by_chunks), FEDRAG_S3(by_heads), FEDRAG_S3(by_group), FEDRAG_S(L),
-                     FEDRAG_S(steps_per_wg));
+                     FEDRAG_S(steps_per_wg), FEDRAG_S(first_slab));
     const int tid = threadIdx.x, rl = tid / 16, l = tid % 16;
-    const int bh = (int)by_chunks.div(blockIdx.x), chunk = (int)blockIdx.x - bh * (int)by_chunks.d;
+    const int slab = (int)by_chunks.div(blockIdx.x), chunk = (int)blockIdx.x - slab * (int)by_chunks.d;
+    const int bh = first_slab + slab;
     const int b = (int)by_heads.div(bh), h = bh - b * (int)by_heads.d;
     const int64_t at = (int64_t)by_group.div(h) * D;
     const int32_t* pm = perm ? perm + (int64_t)b * perm_batch_stride : nullptr;
@@ -1117,7 +1119,9 @@ static hipError_t launch_few_rows(const RowsJob& j, hipStream_t stream) {
     if (!grid_fits(j.BH, kF32Threads)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)j.BH, (unsigned)j.n_jobs, (unsigned)cs);
 #define FEDRAG_SPLIT(CS_, ROWS_) few_rows_of_few_columns_kernel<T, D, SCATTER, WIDE, CS_, ROWS_>
-    auto kernel = j.structured ? few_rows_kernel<T, D, SCATTER, true, WIDE> : few_rows_kernel<T, D, SCATTER, false, WIDE>;
+    auto kernel = few_rows_kernel<T, D, SCATTER, false, WIDE>;
+    if constexpr (!SCATTER)
+        if (j.structured) kernel = few_rows_kernel<T, D, false, true, WIDE>;
     if (cs == 4) kernel = handful ? FEDRAG_SPLIT(4, kSplitRows) : FEDRAG_SPLIT(4, kFewRows);
     if constexpr (D == 64)
         if (cs == 2) kernel = FEDRAG_SPLIT(2, kSplitRows);
@@ -1213,10 +1217,11 @@ static hipError_t launch_rows_mfma_f32(const RowsJob& j, hipStream_t stream) {
     if (!grid_fits(j.BH * chunks, kThreads)) return hipErrorInvalidValue;
     dim3 grid((unsigned)(j.BH * chunks), (unsigned)j.n_jobs);
     const ScrambleJob a = device_job(j, 0), b = device_job(j, 1);
-    auto kernel = j.structured ? rows_times_matrix_mfma_f32_kernel<D, SCATTER, true, false, RT>
-                               : rows_times_matrix_mfma_f32_kernel<D, SCATTER, false, false, RT>;
+    auto kernel = rows_times_matrix_mfma_f32_kernel<D, SCATTER, false, false, RT>;
     if constexpr (SCATTER) {
         if (j.merge.lse_in) kernel = rows_times_matrix_mfma_f32_kernel<D, true, false, true, RT>;
+    } else {
+        if (j.structured) kernel = rows_times_matrix_mfma_f32_kernel<D, false, true, false, RT>;
     }
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, a, b, j.perm, j.perm_batch_stride, FastDiv(j.H), FastDiv(j.G), j.L,
                        FastDiv(chunks), spw, j.merge);
@@ -1228,7 +1233,9 @@ static hipError_t launch_rows_f32(const RowsJob& j, hipStream_t stream) {
     if constexpr (!SCATTER) {  // (d = 64, 16 rows: 4.4 us summed in 64 bits, 4.2 in 32)
         if (j.L <= wide_rows(D)) return launch_few_rows<F32, D, false, true>(j, stream);
     }
-    if (j.L <= kFewRows) return launch_few_rows<F32, D, SCATTER, false>(j, stream);
+    if constexpr (SCATTER || wide_rows(D) < kFewRows) {
+        if (j.L <= kFewRows) return launch_few_rows<F32, D, SCATTER, false>(j, stream);
+    }
     if (D == 64 && j.L <= 32) return launch_rows_mfma_f32<D, SCATTER, 1>(j, stream);
     return launch_rows_mfma_f32<D, SCATTER, 4 / (D / 32)>(j, stream);
 }
@@ -1245,18 +1252,23 @@ RowSteps hadamard_steps(int64_t slabs, int64_t L) {
 template <class T, int D, bool SCATTER>
 static hipError_t launch_hadamard(const RowsJob& j, hipStream_t stream) {
     const auto [chunks, per] = hadamard_steps(j.BH, j.L);
-    if (!grid_fits(j.BH * chunks, kHadThreads)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((hadamard_rows_kernel<T, D, SCATTER>), dim3((unsigned)(j.BH * chunks)), dim3(kHadThreads), 0, stream,
-                       device_job(j, 0), j.perm, j.perm_batch_stride, FastDiv(chunks), FastDiv(j.H), FastDiv(j.G), j.L, per);
-    return hipGetLastError();
+    const int64_t most = 0xffffffffLL / kHadThreads / chunks;  // slabs of a launch: below 2^24 of them, all
+    if (j.BH > 0x7fffffffLL) return hipErrorInvalidValue;
+    for (int64_t first = 0; first < j.BH; first += most) {
+        const int64_t slabs = j.BH - first < most ? j.BH - first : most;
+        hipLaunchKernelGGL((hadamard_rows_kernel<T, D, SCATTER>), dim3((unsigned)(slabs * chunks)), dim3(kHadThreads), 0, stream,
+                           device_job(j, 0), j.perm, j.perm_batch_stride, FastDiv(chunks), FastDiv(j.H), FastDiv(j.G), j.L, per, (int)first);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_rows_transform(const RowsJob& j, hipStream_t stream) {
     if (j.L == 0 || j.BH == 0) return hipSuccess;
     if (j.scatter) {  // Dec: always fp32
         if (j.structured && j.merge.lse_in) return hipErrorInvalidValue;  // (not aggregated by a key's factors)
-        // (slabs by the ten million are more workgroups than a grid of the factors' form; of 17 to 32 rows of 64, not of the product's)
-        if (j.structured && grid_fits(j.BH, kHadThreads))
+        if (j.structured)
             return j.D == 128 ? launch_hadamard<F32, 128, true>(j, stream) : launch_hadamard<F32, 64, true>(j, stream);
         return j.D == 128 ? launch_rows_f32<128, true>(j, stream) : launch_rows_f32<64, true>(j, stream);
     }

@@ -168,6 +168,17 @@ def test_structured_dec_of_special_values(d, L):
         assert torch.equal(Y[0, h, 0][torch.isinf(ref)].double(), ref[torch.isinf(ref)]), h
 
 
+def test_structured_dec_of_more_slabs_than_a_grid():
+    """2^24 slabs and more are more workgroups than one launch names."""
+    B, H = (1 << 21) + 1, 8
+    ks = W.make_structured_keys(2, 64, 1, 8, 1, seed=2, dtype=torch.float32, pow2=True)
+    X = torch.randn((B, H, 1, 64), generator=torch.Generator(device=DEV).manual_seed(1), device=DEV)
+    key = dev_key(ks.v_inv)
+    Y = fb.fedrag_unscramble_structured(X, key, None)
+    for b in range(0, B, 1 << 20):  # the last one: the sequences of the second launch
+        assert torch.equal(Y[b:b + (1 << 20)], fb.fedrag_unscramble_structured(X[b:b + (1 << 20)], key, None)), b
+
+
 @pytest.mark.parametrize("L", [1, 33])
 @pytest.mark.parametrize("d", [64, 128])
 def test_structured_dec_keeps_the_range_of_its_outputs(oracle, d, L):

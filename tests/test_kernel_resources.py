@@ -99,9 +99,12 @@ def test_rows_that_fill_half_a_step(kernels):
 
 
 def test_nothing_is_built_that_no_call_reaches(kernels):
-    """Dec with the aggregation takes a matrix, never a key's factors."""
+    """Dec with the aggregation takes a matrix, never a key's factors; Dec by a key's factors is no product."""
     merging = [n for n in kernels if re.match(r"rows_times_matrix_mfma_f32_kernel<\d+, \w+, \w+, true, ", n)]
     assert len(merging) == 3 and not any(re.match(r"rows_times_matrix_mfma_f32_kernel<\d+, \w+, true, true, ", n) for n in merging)
+    assert not [n for n in kernels if re.match(r"rows_times_matrix_mfma_f32_kernel<\d+, true, true, ", n)]
+    few = [n for n in kernels if n.startswith("few_rows_kernel<")]
+    assert few and not [n for n in few if ", true, true, " in n]  # <type, d, Dec, key's factors, ...>
 
 
 def test_residency_that_the_row_products_are_cut_for(kernels):
@@ -114,4 +117,4 @@ def test_residency_that_the_row_products_are_cut_for(kernels):
         if m and (m[1], m[4]) != ("64", "1"):  # (that form has one step)
             assert workgroups_per_unit(k) == counted(int(m[1]), m[2] == "true", m[3] == "true"), name
             checked += 1
-    assert checked == 10
+    assert checked == 8
