@@ -890,15 +890,26 @@ FEDRAG_KERNEL __launch_bounds__(mf_threads(D, RT)) void rows_times_matrix_mfma_f
 // data-parallel moves; the two gathers go through LDS, within a wave.  Every load but those of rows that wait for their indices is
 // asked for at once.
 // Dec, always: the fp32 product was bound by the fp32 matrix pipe or, for few rows, by its chain of waits; this is bound by memory
-// or by the launch, whose arguments are one trip to memory (117 rows 3.2 -> 3.05) (32 heads of 128: 1 row 3.3 -> 2.9 us, 16 7.1 -> 2.9, 117 6.4 -> 3.2, 1000 17.2 -> 7.5, 4096 47 -> 23; of 64 2.5 -> 2.4,
-// 4.4 -> 2.6, 5.0 -> 2.7, 7.8 -> 4.9, 20.3 -> 12.0).  Its sums of 128 are seven roundings deep.
-// Queries in 16 bits: heads of at most kHadSlab rows, where a tile of the product is mostly padding or its matrix is all it does
-// (32 heads of 128: 4 rows 3.8 -> 3.0 us, 16 6.3 -> 3.0, 256 x 32 69.6 -> 26.1, x 64 75 -> 49; of 64 3.0 -> 2.5, 4.2 -> 2.6, 30.4 -> 16.6,
-// 33 -> 27), or at most kHadTotal rows in all (117 6.0 -> 3.2, 1000 7.4 -> 6.3, 1500 10.3 -> 9.0; of 64 4.2 -> 2.7, 4.6 -> 4.3, 6.0 -> 5.1).
-// Beyond that the product is hidden by memory and this is not (2 x 1000 rows of 128 10.4 and 11.0, 32 x 117 14.0 and 16.9; of 64 6.2
-// and 6.1, 8.9 and 10.0).  Enc of K and V, which its coded form equals bit for bit, keeps the product at every size.
+// or by the launch, whose arguments are one trip to memory (117 rows 3.2 -> 3.05 us).  Its sums of 128 are seven roundings deep.
+//   32 heads, us, product -> factors    1 row        16           117          1000         4096
+//   of 128                              3.3 -> 2.9   7.1 -> 2.9   6.4 -> 3.2   17.2 -> 7.5  47 -> 23
+//   of 64                               2.5 -> 2.4   4.4 -> 2.6   5.0 -> 2.7   7.8 -> 4.9   20.3 -> 12.0
+// Queries in 16 bits: heads of at most kHadSlab rows, where a tile of the product is mostly padding or its matrix is all it does,
+// or at most kHadTotal rows in all.  Beyond that the product is hidden by memory and this is not.  Only 129 to 160 rows a head
+// would gain again (256 x 32 x 129 rows of 128 151 and 124, 64 x 32 x 160 42.7 and 32.9; of 64 65.9 and 65.2, 21.4 and 19.3), as the
+// product begins a second pass of 128 rows there; it has no rule of its own.
+//   32 heads, us, product, factors      4 rows       16           117          1000         1500         2048         4096
+//   of 128                              3.8, 3.0     6.3, 3.0     6.0, 3.2     7.4, 6.3     10.3, 9.0    11.1, 11.0   15.5, 16.9
+//   of 64                               3.0, 2.5     4.2, 2.6     4.2, 2.7     4.6, 4.3     6.0, 5.1     6.9, 6.5     10.6, 10.5
+//   x 256 sequences                     32 rows      64           80           96           112          128          256
+//   of 128                              69.6, 26.1   72.9, 47.4   76.5, 69.8   82.4, 83.4   87.8, 97.5   92.2, 109    183, 223
+//   of 64                               30.4, 16.6   33.1, 27.9   35.5, 33.5   38.9, 39.4   42.0, 45.2   46.7, 52.0   91, 134
+//   x 32                                48           64           80           96           112          128          256
+//   of 128                              14.8, 10.8   14.8, 11.5   14.2, 13.9   14.2, 14.0   14.4, 16.5   15.3, 17.3   27.4, 27.5
+//   of 64                               7.8, 6.2     8.1, 6.5     8.7, 8.1     9.0, 8.6     9.5, 10.5    9.7, 10.4    15.7, 16.3
+// Enc of K and V, which its coded form equals bit for bit, keeps the product at every size.
 //   SCATTER == false: Y[j] = X[perm[j]] . Phi ; SCATTER == true (fp32): Y[perm[i]] = X[i] . Phi
-constexpr int64_t kHadSlab = 64, kHadTotal = 48 << 10;
+constexpr int64_t kHadSlab = 96, kHadTotal = 48 << 10;
 constexpr int64_t kHadWgsPerUnit = 8;  // workgroups a compute unit has from where on one takes several steps
 constexpr int kHadRows = 16;        // rows per workgroup step
 constexpr int kHadThreads = 16 * kHadRows;

@@ -108,7 +108,7 @@ def chain_error(oracle, Q, Ks, Vs, enc_q, enc_kv, dec, perm_q, dtype):
 # from where on queries take the product
 @pytest.mark.parametrize("dt", ["bf16", "f16"])
 @pytest.mark.parametrize("B,H,L,d", [(1, 2, 1, 128), (2, 4, 15, 64), (1, 2, 16, 128), (3, 2, 17, 128), (1, 4, 33, 64), (700, 2, 64, 64),
-                                     (400, 2, 65, 64), (1, 4, 4097, 128), (5, 2, 5000, 64)])
+                                     (400, 2, 65, 64), (300, 2, 96, 128), (300, 2, 97, 64), (1, 4, 4097, 128), (5, 2, 5000, 64)])
 def test_structured_rows_factor_by_factor(oracle, B, H, L, d, dt):
     ks = W.make_structured_keys(H, d, L, 8, 1, seed=L + d, dtype=W.torch_dtype(dt), pow2=False)
     perm = torch.randperm(L, generator=torch.Generator().manual_seed(L)).int()
