@@ -13,9 +13,10 @@
 // 256 KB of such loads in twice the time of whole rows (9.7 us and 5.0 on 32 workgroups), which was what a launch that does not
 // fill the chip waited for: one sequence of 8192 keys x 8 heads of 128 16.8 us and 13.4 now (call with its aggregation), 512 keys
 // 9.9 and 7.8, of 64 10.9 and 9.3, 5.9 and 4.8; launches at the rate of memory gain 0 to 4 %.  What is in flight holds no registers.
-// On transport codes, whose rebuilding is the bound, operands are loaded straight into registers, and the d-rows of O^T are
-// assigned d = DCH * i + j (tile j, row i) so that lane (i = lr) needs exactly the DCH contiguous elements [DCH*lr, DCH*lr + DCH)
-// of each of its eight keys: an in-register 8 x DCH transpose.
+// Transport codes, whose rebuilding is the bound, and 16-bit values of 128 columns in whole rounds of long runs (kDecLongRun) are
+// loaded straight into registers as operands, and the d-rows of O^T are assigned d = DCH * i + j (tile j, row i) so that lane
+// (i = lr) needs exactly the DCH contiguous elements [DCH*lr, DCH*lr + DCH) of each of its eight keys: an in-register 8 x DCH
+// transpose.  Past the end of a run the register form reads the last key again and the LDS form reads nothing; both mask it.
 // P is split into two storage-type terms (hi + lo) so that the probabilities enter the second product with
 // ~16 significant bits; the matrix pipe is idle most of the time anyway.
 // Splits are normalised partials (O, lse) in the caller's workspace and are folded by the Section 4.1
@@ -163,8 +164,10 @@ constexpr int64_t dec_single_tile_run(int d) { return d == 128 ? 1024 : 256; }  
 // for its number of workgroups or for shorter ones, what counts is again what a compute unit takes by itself (33 x 4096 131 us and 116).
 constexpr int64_t kDecLongRun = 2048;
 
-// PARTS: a run is summed part by part, `part` tiles of a wave at a time (attn_runs_of).  A form of its own: the check in the loop and
-// the second set of accumulators take 0 to 4 % of a launch on codes.
+// PARTS: a run is summed part by part, `part` tiles of a wave at a time (attn_runs_of).  A form of its own, as putting a part aside
+// takes some 0.3 us: 0 to 3 % of cut launches on 16-bit values and most on 8-bit codes (9 x 2000 keys 16.8 -> 17.7 us), on 4-bit
+// codes 2 to 8 % (9 x 8192 keys 26.7 -> 27.7 us, uncut 31.5; 11 x 1400 12.0 -> 12.9, uncut 13.3).  Put aside in LDS instead, codes
+// took another 2 to 6 %.
 template <class T, int D, int QB, int NS, int WAVES, bool PARTS>
 FEDRAG_KERNEL __launch_bounds__(WAVES * kWave, QB == 4 ? kDecCodesOcc : NS * D > 0 && NS * D <= 128 ? 2 : 1) void decode_attn_kernel(const typename T::elem* __restrict__ Q,
                                                                      const KeyRuns runs,
@@ -241,9 +244,9 @@ FEDRAG_KERNEL __launch_bounds__(WAVES * kWave, QB == 4 ? kDecCodesOcc : NS * D >
 
     // Q'^T operands: column lr (query), contraction slice 32 ks + 8 lq; padding queries lie past the end of the
     // buffer and arrive as zeros
-    // Which 8 channels lane group lq contracts in step ks is free as long as Q' and K' agree.  16-bit K': 32 ks + 8 lq.  Codes: every lane fetches 16 bytes of its
-    // row at once - 16 codes = steps 2h, 2h+1 (8 bits) or 32 codes = all four steps (4 bits) - so that a load still
-    // covers 64 contiguous bytes per row; with 8- or 4-byte loads the kernel was bound by the number of rows a load
+    // Which 8 channels lane group lq contracts in step ks is free as long as Q' and K' agree.  16-bit K': 32 ks + 8 lq.  Codes: every
+    // lane fetches 16 bytes of its row at once - 16 codes = steps 2h, 2h+1 (8 bits) or 32 codes = all four steps (4 bits) - so that a
+    // load still covers 64 contiguous bytes per row; with 8- or 4-byte loads the kernel was bound by the number of rows a load
     // instruction touches, not by bytes.
     auto chan0 = [&](int ks) -> int {
         return QB == 0 ? ks * 32 + lq * 8 : (QB == 8 ? 16 * lq + 64 * (ks / 2) + 8 * (ks % 2) : 32 * lq + 8 * ks);

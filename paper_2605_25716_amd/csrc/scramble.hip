@@ -1184,9 +1184,10 @@ static hipError_t launch_scramble16(const RowsJob& j, hipStream_t stream) {
 // many of those; one, two or three of them, which wait for their rows, take `part`, more with a second partial to read; every
 // workgroup costs `setup` (its slice of Phi, or the multiplying out of the key), and where they come in several rounds the last
 // one ends unevenly (`tail` of a workgroup).  Fitted to up to 19 splits of each of 554 launches; over those the choice is 1 % from the
-// best split on average, 6 to 16 % at most by the form (of others, 12 x 75 rows x 64 heads with the aggregation 24 %).  The aggregating form, with 16 elements of the other partial in registers,
-// has one workgroup less to a unit: cut as the plain one it took 10 % longer than its best split on average at d = 128, 59 % at
-// most (4096 rows x 32 heads 60 us and 83, 8 x 500 60 and 80, 300 x 10 of 64 22.6 and 26.6).
+// best split on average, 6 to 16 % at most by the form (of others, 12 x 75 rows x 64 heads with the aggregation 24 %).  The
+// aggregating form, with 16 elements of the other partial in registers, has one workgroup less to a unit: cut as the plain one it
+// took 10 % longer than its best split on average at d = 128, 59 % at most (4096 rows x 32 heads 60 us and 83, 8 x 500 60 and 80,
+// 300 x 10 of 64 22.6 and 26.6).
 struct RowStepCost {
     int resident;
     float setup, tail, part[4];

@@ -304,8 +304,8 @@ def test_decode_key_runs(oracle, Ls, d):
 
 
 # 8 B workgroups: one tile of LDS per wave (runs of up to 128 keys; up to 1024, of 64 columns 256, with more workgroups than compute
-# units, or of 128 columns from 385 on where they fill one round), also on eight waves (129 to 256 keys of 128) and on two (up to 64), two, and registers (whole rounds of runs from 2048
-# keys on); a wave's one to nine tiles, whole and ragged
+# units, or of 128 columns from 385 on where they fill one round), also on eight waves (129 to 256 keys of 128) and on two (up to
+# 64), two, and registers (whole rounds of runs from 2048 keys on); a wave's one to nine tiles, whole and ragged
 @pytest.mark.parametrize("dt", ["bf16", "f16"])
 @pytest.mark.parametrize("B,L,d", [(1, 1, 128), (2, 128, 64), (1, 129, 128), (2, 255, 128), (4, 256, 128), (1, 257, 128), (3, 353, 64), (3, 511, 128), (33, 200, 128), (33, 1000, 128),
                                    (40, 256, 64), (40, 257, 64), (1, 1, 64), (2, 32, 64), (3, 33, 64), (40, 64, 64), (300, 63, 64), (3, 65, 64), (3, 32, 128), (40, 63, 128), (300, 5, 128), (32, 385, 128), (30, 511, 128), (33, 1100, 128), (32, 2113, 128), (33, 2050, 128), (32, 2100, 64)])
