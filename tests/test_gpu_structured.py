@@ -208,6 +208,29 @@ def test_structured_dec_keeps_the_range_of_its_outputs(oracle, d, L):
         assert (np.abs(Y - ref) <= 1e-6 * np.matmul(np.abs(PT.f64(X)), abs_dense(key, d)[None])).all(), name
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_structured_dec_formed_again_between_steps(oracle, d):
+    """Rows that are formed again, among others, in workgroups of several steps and with a row order: a sequence of the batch comes out
+    as it does by itself, where a workgroup has one step, bit for bit, and as the oracle has it."""
+    B, H, L = 300, 8, 117  # 8 steps of 16 rows a slab, all in one workgroup
+    g = torch.Generator(device=DEV).manual_seed(d)
+    X = torch.rand((B, H, L, d), generator=g, device=DEV) + 0.5
+    X[:, :, 5::17] *= 2.0e38 / d ** 0.5
+    X[:, :, 7::23] *= 2.0 ** -110
+    X[:, :, 11::29] = 0.0
+    perm = torch.randperm(L, generator=torch.Generator().manual_seed(d)).int()
+    _, g1, g2, _ = W.make_structured_keys(2, d, L, 8, 1, seed=12, dtype=torch.float32, pow2=True).v_inv
+    key = (torch.ones(2, d), g1, g2, torch.ones(2, d))
+    Y = fb.fedrag_unscramble_structured(X, dev_key(key), perm.to(DEV))
+    for b in (0, 1, B - 1):
+        assert torch.equal(Y[b:b + 1], fb.fedrag_unscramble_structured(X[b:b + 1].contiguous(), dev_key(key), perm.to(DEV))), b
+    x, y = PT.f64(X[:1]), PT.f64(Y[:1])
+    ref = oracle.structured(X[:1].cpu(), key, perm, scatter=True)
+    bound = np.empty_like(ref)
+    bound[:, :, perm.long().numpy()] = 1e-6 * np.matmul(np.abs(x), np.repeat(abs_dense(key, d), H // 2, 0)[None])
+    assert np.isfinite(y).all() and (np.abs(y - ref) <= bound).all()
+
+
 @pytest.mark.parametrize("outliers", [False, True], ids=["gaussian", "outlier_channels"])
 @pytest.mark.parametrize("L", [128, 512, 2048])
 def test_stability_structured_against_dense_random(oracle, L, outliers):
